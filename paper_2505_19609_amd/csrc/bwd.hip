@@ -38,7 +38,8 @@ struct BwdParams {
     uint16_t *dq, *dk, *dv;
     const int4 *fwd_items, *dkv_items;
     const int32_t *cu_q, *cu_k, *q_begin, *q_len, *kv_len, *shares_kv;
-    int32_t Hq, Hkv, total_q, BM, BN;
+    RowMap rows;  // dQ: which row blocks a workgroup's waves take
+    int32_t Hq, Hkv, total_q, BN;
     float scale, scale_log2;
     // dK/dV head split: the query heads of a KV group are shared out over `head_split`
     // workgroups, which leave unrounded partial sums in dk_part / dv_part
@@ -85,8 +86,8 @@ __device__ __forceinline__ uint32_t ds_mul_pack(float t0, float t1, float g0, fl
     return pk;
 }
 
-// One workgroup = one forward work item (at most 256 query rows) x one query head;
-// each of the 8 waves owns 32 query rows, two waves per SIMD.  K and V stream in
+// One workgroup = part of a forward work item (at most 256 query rows) x one KV head (tiles.h:
+// row_blocks); each of the 8 waves owns 32 query rows of one head, two waves per SIMD.  K and V stream in
 // 64-row tiles through LDS rings (K: five slots, V: four), fetched two tiles ahead by
 // buffer loads that write LDS directly; fetches are issued, and the workgroup meets
 // at a barrier, every second tile.  Half-tile j (32 keys) goes through
@@ -98,8 +99,9 @@ __device__ __forceinline__ uint32_t ds_mul_pack(float t0, float t1, float g0, fl
 // which is why the K ring has one slot more than the V ring.  Steps at the start, the
 // end and the causal diagonal of a wave's range take a plain path with guards.
 template <int D, int NWQ>
-__device__ __forceinline__ void dq_work(const BwdParams &prm, const int bid)
+__device__ __forceinline__ void dq_work(const int bid)
 {
+    const kernarg_t<BwdParams> prm = kernarg<BwdParams>();
     constexpr bool SMALL = NWQ == NWQ_SMALL;
     constexpr int KSL = SMALL ? 3 : 5, VSL = SMALL ? 2 : 4;  // ring slots
     constexpr int KS = D / 16, TT = D / 32, KT = TILE_ROWS;
@@ -115,35 +117,26 @@ __device__ __forceinline__ void dq_work(const BwdParams &prm, const int bid)
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform, lives in an SGPR
     const int n = lane & 31, h = lane >> 5;
-    // an item of more rows than the workgroup covers is split over `subs` workgroups
-    const int subs = (prm.BM + 32 * NWQ - 1) / (32 * NWQ);
-    const int item_id = bid / (prm.Hq * subs), sub = (bid / prm.Hq) % subs;
-    const int hl = bid % prm.Hq;
-    const int g = prm.Hq / prm.Hkv;
-    const int c = hl % prm.Hkv;
-    const int head = c * g + hl / prm.Hkv;
+    const RowBlocks rb = row_blocks(prm, prm->fwd_items, bid);
+    const int c = rb.c;
+    if (!rb.has(0)) return;  // the item has no row block for this part (the whole workgroup leaves)
 
     FragAddr<D> fa;
     fa.init(lane);
     Loader ld;
-    ld.init(lane, wave, (uint32_t)prm.Hkv * D * 2);
+    ld.init(lane, wave, (uint32_t)prm->Hkv * D * 2);
     const uint32_t ring_k = lds_addr(&lds_k[0][0]), ring_v = lds_addr(&lds_v[0][0]);
 
-    const int4 it = prm.fwd_items[item_id];
-    const int seq = it.x;
-    const int qb = prm.q_begin[seq], ql = prm.q_len[seq], kvl = prm.kv_len[seq];
-    const int kbase = prm.cu_k[seq];
-    const int row0 = it.y * prm.BM + sub * 32 * NWQ;
-    const int qrow0 = it.z + sub * 32 * NWQ;
-    const int rows = min(32 * NWQ, min(prm.BM, ql - it.y * prm.BM) - sub * 32 * NWQ);
-    if (rows <= 0) return;  // the item ends before this part (the whole workgroup leaves)
-    const uint64_t trace_t0 = trace_begin(prm.trace_dq);
-    const int p0 = qb + row0;  // global position of the item's first query
-    const int n_tiles = (p0 + rows + KT - 1) / KT;
-    const float cs = prm.scale_log2;
+    const int kvl = rb.kvl, kbase = rb.kbase;
+    const uint64_t trace_t0 = trace_begin(prm->trace_dq);
+    const int p0 = rb.p0;  // global position of the item's first query
+    const int rows = rb.rows, qrow0 = rb.qrow0;
+    const int n_tiles = (p0 + min(rb.block(0) * 32 + 32, rows) + KT - 1) / KT;  // for the workgroup's last row block
+    const float cs = prm->scale_log2;
 
-    const int wrow0 = 32 * wave;
-    const bool wave_active = wrow0 < rows;
+    const bool wave_active = rb.has(wave);
+    const int wrow0 = wave_active ? rb.block(wave) * 32 : 0;  // first row of this wave's block inside the item
+    const int head = rb.head(wave);
     const int my_i = wrow0 + n;
     const int w_pmin = p0 + wrow0;
     const int w_pmax = p0 + min(wrow0 + 31, rows - 1);
@@ -151,8 +144,8 @@ __device__ __forceinline__ void dq_work(const BwdParams &prm, const int bid)
     const int L = wave_active ? w_pmax / 32 : -1;
     const int n_full = wave_active ? (w_pmin + 1) / 32 : 0;
 
-    const i32x4 rk = ld.rsrc(prm.k + ((size_t)kbase * prm.Hkv + c) * D, kvl);
-    const i32x4 rv = ld.rsrc(prm.v + ((size_t)kbase * prm.Hkv + c) * D, kvl);
+    const i32x4 rk = ld.rsrc(prm->k + ((size_t)kbase * prm->Hkv + c) * D, kvl);
+    const i32x4 rv = ld.rsrc(prm->v + ((size_t)kbase * prm->Hkv + c) * D, kvl);
 
     // Large shape: the fetch group issued at the start of an even period t is K and V tiles
     // t+2, t+3 (tiles past the end read as zero).  Small shape: every period t fetches K
@@ -192,14 +185,14 @@ __device__ __forceinline__ void dq_work(const BwdParams &prm, const int bid)
     {
         Stage st;
         st.init(lane);
-        const uint32_t pitch = (uint32_t)prm.Hq * D * 2;
-        const size_t hoff = ((size_t)qrow0 * prm.Hq + head) * D;
+        const uint32_t pitch = (uint32_t)prm->Hq * D * 2;
+        const size_t hoff = ((size_t)qrow0 * prm->Hq + head) * D;
         u32x4 vq[Stage::N], vg[Stage::N], vo[Stage::N];
-        st.load(vq, prm.q + hoff, pitch, wrow0, rows);
-        st.load(vg, prm.d_o + hoff, pitch, wrow0, rows);
-        st.load(vo, prm.o + hoff, pitch, wrow0, rows);
+        st.load(vq, prm->q + hoff, pitch, wrow0, rows);
+        st.load(vg, prm->d_o + hoff, pitch, wrow0, rows);
+        st.load(vo, prm->o + hoff, pitch, wrow0, rows);
         const int my_row = qrow0 + min(my_i, rows - 1);  // packed row, clamped for loads
-        lse2 = prm.lse[(size_t)head * prm.total_q + my_row] * kLog2e;
+        lse2 = prm->lse[(size_t)head * prm->total_q + my_row] * kLog2e;
         st.put(stage, vq);
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) qf[ks] = fa.rows_at(stage, ks);
@@ -396,6 +389,7 @@ __device__ __forceinline__ void dq_work(const BwdParams &prm, const int bid)
     for (; t <= n_tiles; ++t) plain_period(t);
 
     __syncthreads();  // nobody reads a tile any more: the staging regions are free
+    const kernarg_t<BwdParams> out = kernarg<BwdParams>();
     if (wave_active) {
         // derived after the loop from opaque copies, so that no part of the
         // output addresses is kept in registers during the loop
@@ -404,14 +398,14 @@ __device__ __forceinline__ void dq_work(const BwdParams &prm, const int bid)
         const int on = li & 31, oh = li >> 5, oi = wrow0 + on;
         Stage st;
         st.init(li);
-        st.put_acc(stage, acc, prm.scale, on, oh);
-        st.store(stage, prm.dq + ((size_t)qrow0 * prm.Hq + head) * D, (uint32_t)prm.Hq * D * 2, wrow0, rows);
+        st.put_acc(stage, acc, out->scale, on, oh);
+        st.store(stage, out->dq + ((size_t)qrow0 * out->Hq + head) * D, (uint32_t)out->Hq * D * 2, wrow0, rows);
         if (oh == 0 && oi < rows) {
-            prm.delta[(size_t)head * prm.total_q + qrow0 + oi] = nd;
-            prm.lse2[(size_t)head * prm.total_q + qrow0 + oi] = lse2;
+            out->delta[(size_t)head * out->total_q + qrow0 + oi] = nd;
+            out->lse2[(size_t)head * out->total_q + qrow0 + oi] = lse2;
         }
     }
-    trace_end(prm.trace_dq, trace_t0, bid);
+    trace_end(out->trace_dq, trace_t0, bid);
 }
 
 template <int D, int NWQ>
@@ -419,7 +413,7 @@ __global__ __launch_bounds__(64 * NWQ, 2) void dq_kernel(const BwdParams prm)
 {
     __shared__ int work_slot;
     work_loop(prm.queue_dq, prm.n_work_dq, &work_slot,
-              [&](int w) __attribute__((always_inline)) { dq_work<D, NWQ>(prm, w); });
+              [&](int w) __attribute__((always_inline)) { dq_work<D, NWQ>(w); });
 }
 
 // ---------------------------------------------------------------------------
@@ -958,7 +952,10 @@ hipError_t launch_pair(const skrull_attn_plan_t *p, BwdParams prm, int threads_q
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    if (!queued_q) prm.queue_dq = nullptr;
+    if (!queued_q) {
+        prm.queue_dq = nullptr;
+        spread_parts(prm.rows);
+    }
     if (!queued_kv) prm.queue_dkv = nullptr;
     hipError_t e = launch_work<KernelQ>(threads_q, prm.n_work_dq, queued_q, prm, st);
     if (e != hipSuccess) return e;
@@ -994,10 +991,14 @@ hipError_t launch_d(const skrull_attn_plan_t *p, const BwdParams &prm, hipStream
 
 }  // namespace
 
+static RowMap map_dq(const skrull_attn_plan_t *p)
+{
+    return row_map(p->BM, p->Hq, p->Hkv, small_dq_shape(p) ? NWQ_SMALL : NWQ_LARGE);
+}
+
 int grid_dq(const skrull_attn_plan_t *p)
 {
-    const int subs = small_dq_shape(p) ? (p->BM + 32 * NWQ_SMALL - 1) / (32 * NWQ_SMALL) : 1;
-    return p->n_fwd * p->Hq * subs;
+    return p->n_fwd * p->Hkv * map_dq(p).parts;
 }
 
 int grid_dkv(const skrull_attn_plan_t *p)
@@ -1020,7 +1021,8 @@ hipError_t launch_bwd(const skrull_attn_plan_t *p, const void *q, const void *k,
     prm.fwd_items = (const int4 *)p->fwd_items; prm.dkv_items = (const int4 *)p->dkv_items;
     prm.cu_q = p->cu_q; prm.cu_k = p->cu_k; prm.q_begin = p->q_begin; prm.q_len = p->q_len;
     prm.kv_len = p->kv_len; prm.shares_kv = p->shares_kv;
-    prm.Hq = p->Hq; prm.Hkv = p->Hkv; prm.total_q = p->total_q; prm.BM = p->BM; prm.BN = p->BN;
+    prm.Hq = p->Hq; prm.Hkv = p->Hkv; prm.total_q = p->total_q;
+    prm.rows = map_dq(p); prm.BN = p->BN;
     prm.scale = p->scale; prm.scale_log2 = p->scale * kLog2e;
     prm.head_split = p->head_split; prm.total_k = p->total_k;
     prm.n_work_dq = grid_dq(p);

@@ -3,9 +3,10 @@
 // the gathered KV prefix -- paper Sec. 4.1).  This is the O(n^2) term of the
 // paper's cost model (App. B.2), the thing its scheduler balances.
 //
-// One workgroup = one work item (a block of BM query rows of one sequence) x
-// one query head, or a 128-row part of it.  In its large shape it has 8 wavefronts
-// (two per SIMD), each owning 32 query rows, so it covers 256 rows; the key / value
+// One workgroup = a part of one work item (a block of BM query rows of one sequence) x
+// one KV head: some of its 32-row blocks, of all the query heads that read this KV head
+// (tiles.h: row_blocks).  In its large shape it has 8 wavefronts
+// (two per SIMD), each owning one such block of 32 query rows of one head; the key / value
 // prefix is streamed in tiles of 64 rows through two rings of four LDS slots: two
 // tiles are read while the next two are fetched, and the workgroup meets at a
 // barrier every second tile.  The small shape (4 wavefronts, two-slot rings, two
@@ -45,7 +46,8 @@ struct FwdParams {
     float *lse;
     const int4 *items;
     const int32_t *cu_k, *q_begin, *q_len, *kv_len;
-    int32_t Hq, Hkv, total_q, BM;
+    RowMap rows;               // which row blocks a workgroup's waves take
+    int32_t Hq, Hkv, total_q;
     int32_t variant;  // 0: 4 wavefronts, 128 rows per workgroup; 1: 8 wavefronts, 256 rows
     float scale_log2;  // softmax_scale * log2(e)
     WgTrace *trace;    // null, or one record per work item (measurement aid)
@@ -53,13 +55,13 @@ struct FwdParams {
     int32_t n_work;    // work items: what a plain grid would have as workgroups
 };
 
-// Two shapes of the one kernel.  Large: 8 wavefronts = 256 query rows per workgroup and
+// Two shapes of the one kernel.  Large: 8 wavefronts = 8 row blocks per workgroup and
 // 4 ring slots per operand (two tiles being read, two being fetched; a barrier every
 // second tile); its 139 KB of LDS leave room for one workgroup per compute unit.  Small:
-// 4 wavefronts = 128 rows (a larger item is split over two workgroups) and 2 ring slots
-// (fetch one tile ahead, a barrier every tile), 70 KB, so that two workgroups share a
-// compute unit and the start-up, drain and barrier waits of one (most of the run time of
-// a short sequence) hide behind the other.  The plan chooses per micro-batch.
+// 4 wavefronts = 4 row blocks and 2 ring slots (fetch one tile ahead, a barrier every
+// tile), 70 KB, so that two workgroups share a compute unit and the start-up, drain and
+// barrier waits of one (most of the run time of a short sequence) hide behind the other.
+// The plan chooses per micro-batch.
 constexpr int NW_LARGE = 8, NSLOT_LARGE = 4;
 constexpr int NW_SMALL = 4, NSLOT_SMALL = 2;
 
@@ -115,8 +117,9 @@ __device__ __forceinline__ uint32_t softmax_sum_pack(float t0, float t1, float &
 }
 
 template <int D, int NW, int NSLOT>
-__device__ __forceinline__ void fwd_work(const FwdParams &prm, const int bid)
+__device__ __forceinline__ void fwd_work(const int bid)
 {
+    const kernarg_t<FwdParams> prm = kernarg<FwdParams>();
     static_assert(NSLOT == 2 || NSLOT == 4, "ring logic below covers two and four slots");
     constexpr int SM = NSLOT - 1;  // slot of tile t: t & SM
     constexpr int KS = D / 16;   // MFMA k-steps of Q.K^T
@@ -135,41 +138,30 @@ __device__ __forceinline__ void fwd_work(const FwdParams &prm, const int bid)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform, lives in an SGPR
     const int n = lane & 31, h = lane >> 5;
 
-    // work index -> (item, head).  Consecutive blocks go to consecutive XCDs; the
-    // heads of one KV group are Hkv blocks apart so that they share an XCD (and
+    // work index -> (item, KV head, part).  Consecutive blocks go to consecutive XCDs; the
+    // parts of one (item, KV head) are Hkv blocks apart so that they share an XCD (and
     // its L2 copy of the K/V tiles) whenever Hkv divides 8 or is a multiple of it.
-    // an item of more rows than the workgroup covers is split over `subs` workgroups
-    const int subs = (prm.BM + 32 * NW - 1) / (32 * NW);
-    const int item_id = bid / (prm.Hq * subs), sub = (bid / prm.Hq) % subs;
-    const int hl = bid % prm.Hq;
-    const int g = prm.Hq / prm.Hkv;
-    const int c = hl % prm.Hkv;
-    const int head = c * g + hl / prm.Hkv;
+    const RowBlocks rb = row_blocks(prm, prm->items, bid);
+    const int c = rb.c;
+    if (!rb.has(0)) return;  // the item has no row block for this part (the whole workgroup leaves)
 
     FragAddr<D> fa;
     fa.init(lane);
     Loader ld;
-    ld.init(lane, wave, (uint32_t)prm.Hkv * D * 2);
+    ld.init(lane, wave, (uint32_t)prm->Hkv * D * 2);
     const uint32_t ring_k = lds_addr(&lds_k[0][0]), ring_v = lds_addr(&lds_v[0][0]);
 
-    const int4 it = prm.items[item_id];
-    const int seq = it.x;
-    const int qb = prm.q_begin[seq], ql = prm.q_len[seq], kvl = prm.kv_len[seq];
-    const int kbase = prm.cu_k[seq];
-    const int item_rows = min(prm.BM, ql - it.y * prm.BM);
-    const float cs = prm.scale_log2;
+    const int kvl = rb.kvl, kbase = rb.kbase;
+    const float cs = prm->scale_log2;
+    const uint64_t trace_t0 = trace_begin(prm->trace);
 
-    const int row0 = it.y * prm.BM + sub * 32 * NW;
-    const int qrow0 = it.z + sub * 32 * NW;
-    const int rows = min(32 * NW, item_rows - sub * 32 * NW);
-    if (rows <= 0) return;  // the item ends before this part (the whole workgroup leaves)
-    const uint64_t trace_t0 = trace_begin(prm.trace);
-    const int p0 = qb + row0;  // global position of the pass's first query
-    const int n_tiles = (p0 + rows + KT - 1) / KT;
+    const int p0 = rb.p0;  // global position of the item's first query
+    const int rows = rb.rows, qrow0 = rb.qrow0;
+    const int n_tiles = (p0 + min(rb.block(0) * 32 + 32, rows) + KT - 1) / KT;  // for the workgroup's last row block
 
-    const int wrow0 = 32 * wave;
-    const bool wave_active = wrow0 < rows;
-    const int my_i = wrow0 + n;
+    const bool wave_active = rb.has(wave);
+    const int wrow0 = wave_active ? rb.block(wave) * 32 : 0;  // first row of this wave's block inside the item
+    const int head = rb.head(wave);
     const int w_pmin = p0 + wrow0;
     const int w_pmax = p0 + min(wrow0 + 31, rows - 1);
     // half tiles (32 keys) of this wave: 0..L hold a visible key, those below n_full only visible keys
@@ -179,8 +171,8 @@ __device__ __forceinline__ void fwd_work(const FwdParams &prm, const int bid)
     // Q fragments (B operand of S^T): this lane's query row, 8 head-dims per k-step
     // (loaded below, behind the first tile fetches)
     bf16x8 qf[KS];
-    const i32x4 rk = ld.rsrc(prm.k + ((size_t)kbase * prm.Hkv + c) * D, kvl);
-    const i32x4 rv = ld.rsrc(prm.v + ((size_t)kbase * prm.Hkv + c) * D, kvl);
+    const i32x4 rk = ld.rsrc(prm->k + ((size_t)kbase * prm->Hkv + c) * D, kvl);
+    const i32x4 rv = ld.rsrc(prm->v + ((size_t)kbase * prm->Hkv + c) * D, kvl);
 
     f32x16 oacc[TT];
     zero_acc(oacc);
@@ -373,7 +365,7 @@ __device__ __forceinline__ void fwd_work(const FwdParams &prm, const int bid)
         Stage st;
         st.init(lane);
         u32x4 vq[Stage::N];
-        st.load(vq, prm.q + ((size_t)qrow0 * prm.Hq + head) * D, (uint32_t)prm.Hq * D * 2, wrow0, rows);
+        st.load(vq, prm->q + ((size_t)qrow0 * prm->Hq + head) * D, (uint32_t)prm->Hq * D * 2, wrow0, rows);
         st.put(stage, vq);
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) qf[ks] = fa.rows_at(stage, ks);
@@ -451,6 +443,7 @@ __device__ __forceinline__ void fwd_work(const FwdParams &prm, const int bid)
     for (; t <= n_tiles; ++t) plain_period(t);
 
     __syncthreads();  // nobody reads a tile any more: the staging regions are free
+    const kernarg_t<FwdParams> out = kernarg<FwdParams>();
     if (wave_active) {
         const float l_tot = sum_halves(l_run);
         const float inv = 1.0f / l_tot;
@@ -462,11 +455,11 @@ __device__ __forceinline__ void fwd_work(const FwdParams &prm, const int bid)
         Stage st;
         st.init(li);
         st.put_acc(stage, oacc, inv, on, oh);
-        st.store(stage, prm.o + ((size_t)qrow0 * prm.Hq + head) * D, (uint32_t)prm.Hq * D * 2, wrow0, rows);
+        st.store(stage, out->o + ((size_t)qrow0 * out->Hq + head) * D, (uint32_t)out->Hq * D * 2, wrow0, rows);
         if (oh == 0 && oi < rows)
-            prm.lse[(size_t)head * prm.total_q + qrow0 + oi] = (m_run + __log2f(l_tot)) * 0.6931471805599453f;
+            out->lse[(size_t)head * out->total_q + qrow0 + oi] = (m_run + __log2f(l_tot)) * 0.6931471805599453f;
     }
-    trace_end(prm.trace, trace_t0, bid);
+    trace_end(out->trace, trace_t0, bid);
 }
 
 template <int D, int NW, int NSLOT>
@@ -474,7 +467,7 @@ __global__ __launch_bounds__(64 * NW, 2) void fwd_kernel(const FwdParams prm)
 {
     __shared__ int work_slot;
     work_loop(prm.queue, prm.n_work, &work_slot,
-              [&](int w) __attribute__((always_inline)) { fwd_work<D, NW, NSLOT>(prm, w); });
+              [&](int w) __attribute__((always_inline)) { fwd_work<D, NW, NSLOT>(w); });
 }
 
 template <auto Kernel>
@@ -487,6 +480,7 @@ hipError_t launch_shape(FwdParams prm, int threads, hipStream_t st)
         if (e != hipSuccess) return e;
     } else {
         prm.queue = nullptr;
+        spread_parts(prm.rows);
     }
     return launch_work<Kernel>(threads, prm.n_work, queued, prm, st);
 }
@@ -500,10 +494,11 @@ hipError_t launch_one(const FwdParams &prm, hipStream_t st)
 
 }  // namespace
 
+static RowMap map_fwd(const skrull_attn_plan_t *p) { return row_map(p->BM, p->Hq, p->Hkv, p->wg_query_rows / 32); }
+
 int grid_fwd(const skrull_attn_plan_t *p)
 {
-    const int subs = p->wg_query_rows == 32 * NW_SMALL ? (p->BM + 32 * NW_SMALL - 1) / (32 * NW_SMALL) : 1;
-    return p->n_fwd * p->Hq * subs;
+    return p->n_fwd * p->Hkv * map_fwd(p).parts;
 }
 
 hipError_t launch_fwd(const skrull_attn_plan_t *p, const void *q, const void *k, const void *v,
@@ -514,7 +509,8 @@ hipError_t launch_fwd(const skrull_attn_plan_t *p, const void *q, const void *k,
     prm.o = (uint16_t *)o; prm.lse = lse;
     prm.items = (const int4 *)p->fwd_items;
     prm.cu_k = p->cu_k; prm.q_begin = p->q_begin; prm.q_len = p->q_len; prm.kv_len = p->kv_len;
-    prm.Hq = p->Hq; prm.Hkv = p->Hkv; prm.total_q = p->total_q; prm.BM = p->BM;
+    prm.Hq = p->Hq; prm.Hkv = p->Hkv; prm.total_q = p->total_q;
+    prm.rows = map_fwd(p);
     prm.scale_log2 = p->scale * 1.4426950408889634f;
     prm.trace = trace;
     prm.variant = p->wg_query_rows == 32 * NW_SMALL ? 0 : 1;

@@ -21,6 +21,17 @@ struct WorkQueue {
     int32_t pad[8];
 };
 
+// The kernel's one argument (a struct of parameters), read anew through an opaque pointer: in a
+// persistent kernel every parameter is an invariant of the work loop, and kept from one work
+// item to the next they filled the scalar registers and then, as spilled lanes, vector ones.
+template <typename P> using kernarg_t = const P __attribute__((address_space(4))) *;
+template <typename P> __device__ __forceinline__ kernarg_t<P> kernarg()
+{
+    kernarg_t<P> p = (kernarg_t<P>)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return p;
+}
+
 // Next work item for a workgroup on die `xcd`, or -1 when every queue is empty.  Called by
 // one lane.  Counters are device-scope atomics (the dies' L2 caches are not coherent with
 // each other for plain accesses).

@@ -88,6 +88,85 @@ struct FragAddr {
 };
 
 // ---------------------------------------------------------------------------
+// Which rows the waves of a forward / dQ workgroup own.
+//
+// An item is up to BM query rows of one segment, i.e. `nblk` blocks of 32; the g query heads
+// of a KV group read the same keys, so an (item, KV head) has nblk * g row blocks that may
+// share K/V tiles.  They are taken in the order (block descending, head ascending), NW to a
+// workgroup, one per wave: the waves of a workgroup then end at nearly the same key.  With a
+// workgroup made of the 8 consecutive blocks of ONE head the first wave idled through the
+// last 7/8 of 256 keys at every diagonal, and a sequence of 139 rows left 3 of 8 waves
+// without work.  Measured, that mapping against this one: 114 sequences of about 250 tokens,
+// 32/8 heads of 128: forward 294 -> 256 us, dQ 397 -> 325; 26,624 tokens in 64 sequences, 14/2
+// heads of 64: 107 -> 95 and 123 -> 111; one sequence of 24,576 and without groups: unchanged.
+// ---------------------------------------------------------------------------
+// What the host works out for the mapping: divisions of a work item's index are most of a
+// microsecond of dependent vector instructions at the start of every item.  A quotient x / d is
+// (x * inv) >> 40 with inv = ceil(2^40 / d), exact while x * d < 2^40; here x < 8 * d or
+// x < 2 * (query heads), and a row of heads is below 2^32 bytes.
+struct RowMap {
+    int32_t BM, g, Hkv, parts;  // query heads per KV head; workgroups per (item, KV head)
+    int32_t part_step, wave_step;  // row block of wave w of part p: p * part_step + w * wave_step
+    uint64_t inv_g, inv_hkv;
+};
+static inline RowMap row_map(int BM, int Hq, int Hkv, int NW)
+{
+    const int g = Hq / Hkv;
+    const uint64_t one = 1ull << 40;
+    return RowMap{BM, g, Hkv, (BM / 32 * g + NW - 1) / NW, NW, 1, (one + g - 1) / g, (one + Hkv - 1) / Hkv};
+}
+// The other order, for launches whose workgroups all run at once: neighbouring row blocks go to
+// different workgroups, so that a workgroup has few waves at work near its last key and the longest
+// chain, which is then the time of the launch, runs with the least company (sequences of 300 and
+// 212 tokens, 14/2 heads of 64: forward 12.9 us in the order above, 11.4 in this one).
+static inline void spread_parts(RowMap &m)
+{
+    m.part_step = 1;
+    m.wave_step = m.parts;
+}
+__device__ __forceinline__ int quotient(int x, uint64_t inv) { return (int)(((uint64_t)(uint32_t)x * inv) >> 40); }
+
+struct RowBlocks {
+    int c;                          // KV head
+    int qb, kvl, kbase;             // the segment: position of its first query, its keys, their first packed row
+    int p0, qrow0, rows;            // the item: position and packed row of its first query, its rows
+    int g, first, step, nblk;       // heads per KV head; row blocks of this part: first + wave * step
+    uint64_t inv_g;
+    __device__ __forceinline__ bool has(int wave) const { return first + wave * step < nblk * g; }
+    __device__ __forceinline__ int block(int wave) const { return nblk - 1 - quotient(first + wave * step, inv_g); }
+    __device__ __forceinline__ int head(int wave) const  // query head of the wave's row block
+    {
+        const int b = first + wave * step;
+        return c * g + b - quotient(b, inv_g) * g;
+    }
+};
+
+template <typename P>
+__device__ __forceinline__ RowBlocks row_blocks(const P prm, const int4 *items, int bid)
+{
+    RowBlocks r;
+    const int BM = prm->rows.BM, Hkv = prm->rows.Hkv, per_item = prm->rows.parts * Hkv;
+    const int item = __builtin_amdgcn_readfirstlane(bid / per_item), x = bid - item * per_item;
+    const int part = quotient(x, prm->rows.inv_hkv);
+    r.c = x - part * Hkv;
+    r.first = part * prm->rows.part_step;
+    r.step = prm->rows.wave_step;
+    const int4 it = items[item];
+    const int seq = it.x;
+    const int ql = prm->q_len[seq];
+    r.qb = prm->q_begin[seq];
+    r.kvl = prm->kv_len[seq];
+    r.kbase = prm->cu_k[seq];
+    r.p0 = r.qb + it.y * BM;
+    r.qrow0 = it.z;
+    r.rows = min(BM, ql - it.y * BM);
+    r.g = prm->rows.g;
+    r.inv_g = prm->rows.inv_g;
+    r.nblk = (r.rows + 31) / 32;
+    return r;
+}
+
+// ---------------------------------------------------------------------------
 // Asynchronous fetch of 64-row tiles of one [rows, H, D] matrix restricted to one
 // head.  One instruction makes a wave fill 64 consecutive 16-byte LDS slots (slot =
 // M0 base + lane) from per-lane offsets, so the row permutation and the padding are

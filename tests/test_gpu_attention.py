@@ -870,3 +870,29 @@ def test_mfma_ceiling_probe():
     rate = B.skrull_attn_mfma_ceiling()
     print(f"MFMA-only ceiling: {rate:.0f} TFLOP/s")
     assert 800.0 < rate < 2600.0
+
+
+@pytest.mark.parametrize("heads,d,wg,bm", [((21, 3), 64, 128, 0), ((21, 3), 128, 256, 64), ((40, 2), 64, 256, 0),
+                                           ((12, 1), 128, 128, 0), ((7, 7), 64, 256, 0)])
+def test_row_blocks_of_a_group_in_both_orders(oracle, heads, d, wg, bm):
+    """Forward and dQ workgroups take 32-row blocks of all query heads of a KV group, neighbouring
+    blocks together where the launch fills the chip and spread out where it does not.  Lengths at the
+    edges of a block and of an item, against the oracle in a small launch; the same sequences 13 times
+    over (a launch with a queue) give the same bits."""
+    S = [1, 31, 32, 33, 255, 257, 300]
+    w = W.Workload(f"row_blocks_{heads}", S, [1] * 7, [0] * 7, heads[0], heads[1], d, d ** -0.5, 404)
+    # with 20 heads in a group dV reaches 19 in the one-token sequence, where bf16 numbers are 0.125
+    # apart: the stated bound plus the output's own rounding, half a spacing (at most 2^-8 of it)
+    one = _exhaustive(oracle, w, block_m=bm, rtol=2.0 ** -8, wg_query_rows=wg, head_split=1, keep=True)
+    rep = 13
+    many = W.Workload(f"row_blocks_{heads}_many", S * rep, [1] * 7 * rep, [0] * 7 * rep, heads[0], heads[1], d,
+                      d ** -0.5, 404)
+    vals = {n: np.concatenate([a] * rep) for n, a in one["vals"].items()}
+    out = run_library(many, block_m=bm, vals=vals, wg_query_rows=wg, head_split=1)
+    from paper_2505_19609_amd import binding as B
+    assert B.skrull_attn_trace_layout(out["plan"])[1][0] > 512     # more than the chip holds at once
+    for n in ("o", "dq"):
+        assert np.array_equal(out[n], np.concatenate([one[n]] * rep)), n
+    assert np.array_equal(out["lse"], np.concatenate([one["lse"]] * rep, axis=1))
+    out["plan"].destroy()
+    one["plan"].destroy()
