@@ -31,6 +31,13 @@ namespace {
 
 constexpr float kLog2e = 1.4426950408889634f;
 
+// How a dK/dV work index stands for an item, a KV head, a share of its query heads and a pass over
+// the item's key rows; quotients as in RowMap.
+struct KeyMap {
+    int32_t BN, g, passes, per_item;  // query heads per KV head; workgroups per (item, KV head, share), and per item
+    uint64_t inv_passes, inv_hs;
+};
+
 struct BwdParams {
     const uint16_t *q, *k, *v, *d_o, *o;
     const float *lse;
@@ -39,7 +46,8 @@ struct BwdParams {
     const int4 *fwd_items, *dkv_items;
     const int32_t *cu_q, *cu_k, *q_begin, *q_len, *kv_len, *shares_kv;
     RowMap rows;  // dQ: which row blocks a workgroup's waves take
-    int32_t Hq, Hkv, total_q, BN;
+    KeyMap keys;  // dK/dV: which keys and heads a workgroup takes
+    int32_t Hq, Hkv, total_q;
     float scale, scale_log2;
     // dK/dV head split: the query heads of a KV group are shared out over `head_split`
     // workgroups, which leave unrounded partial sums in dk_part / dv_part
@@ -98,8 +106,9 @@ __device__ __forceinline__ uint32_t ds_mul_pack(float t0, float t1, float g0, fl
 // B(j).  B(j) reads the transposed K of the half tile BEFORE the one A(j+1) reads,
 // which is why the K ring has one slot more than the V ring.  Steps at the start, the
 // end and the causal diagonal of a wave's range take a plain path with guards.
+// Does work item `bid`, whose rows are `rb`; returns the next one and leaves its rows in `rb`.
 template <int D, int NWQ>
-__device__ __forceinline__ void dq_work(const int bid)
+__device__ __forceinline__ int dq_work(const int bid, RowBlocks &rb, WorkFeed &feed)
 {
     const kernarg_t<BwdParams> prm = kernarg<BwdParams>();
     constexpr bool SMALL = NWQ == NWQ_SMALL;
@@ -117,9 +126,7 @@ __device__ __forceinline__ void dq_work(const int bid)
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform, lives in an SGPR
     const int n = lane & 31, h = lane >> 5;
-    const RowBlocks rb = row_blocks(prm, prm->fwd_items, bid);
     const int c = rb.c;
-    if (!rb.has(0)) return;  // the item has no row block for this part (the whole workgroup leaves)
 
     FragAddr<D> fa;
     fa.init(lane);
@@ -385,20 +392,27 @@ __device__ __forceinline__ void dq_work(const int bid)
         steady(std::false_type{}, tk + HALF, tv + HALF, tk, tk, tv, sy, gy, sx, gx, fr);
         period_end(t);
     }
+    feed.ask();
 #pragma unroll 1
     for (; t <= n_tiles; ++t) plain_period(t);
 
-    __syncthreads();  // nobody reads a tile any more: the staging regions are free
+    feed.post();
+    // Nobody reads a tile any more: the staging regions are free.  (The next item needs no barrier
+    // of its own before its first tiles: they go to slots that stage nothing.)
+    __syncthreads();
     const kernarg_t<BwdParams> out = kernarg<BwdParams>();
+    const int next = feed.take();
+    // derived after the loop from opaque copies, so that no part of the
+    // output addresses is kept in registers during the loop
+    int li = lane;
+    asm volatile("" : "+v"(li));
+    const int on = li & 31, oh = li >> 5, oi = wrow0 + on;
+    Stage st;
+    st.init(li);
+    if (wave_active) st.put_acc(stage, acc, out->scale, on, oh);
+    RowBlocks rb_next{};
+    if (next >= 0) rb_next = row_blocks(out, out->fwd_items, next);  // (its loads are under way during the stores)
     if (wave_active) {
-        // derived after the loop from opaque copies, so that no part of the
-        // output addresses is kept in registers during the loop
-        int li = lane;
-        asm volatile("" : "+v"(li));
-        const int on = li & 31, oh = li >> 5, oi = wrow0 + on;
-        Stage st;
-        st.init(li);
-        st.put_acc(stage, acc, out->scale, on, oh);
         st.store(stage, out->dq + ((size_t)qrow0 * out->Hq + head) * D, (uint32_t)out->Hq * D * 2, wrow0, rows);
         if (oh == 0 && oi < rows) {
             out->delta[(size_t)head * out->total_q + qrow0 + oi] = nd;
@@ -406,14 +420,25 @@ __device__ __forceinline__ void dq_work(const int bid)
         }
     }
     trace_end(out->trace_dq, trace_t0, bid);
+    rb = uniform(rb_next);
+    return next;
 }
 
 template <int D, int NWQ>
 __global__ __launch_bounds__(64 * NWQ, 2) void dq_kernel(const BwdParams prm)
 {
     __shared__ int work_slot;
-    work_loop(prm.queue_dq, prm.n_work_dq, &work_slot,
-              [&](int w) __attribute__((always_inline)) { dq_work<D, NWQ>(w); });
+    WorkFeed feed{prm.queue_dq, prm.n_work_dq, 0, &work_slot};
+    int w = feed.first();
+    RowBlocks rb = row_blocks(kernarg<BwdParams>(), prm.fwd_items, max(w, 0));
+    while (w >= 0) {
+        if (rb.has(0)) {
+            w = dq_work<D, NWQ>(w, rb, feed);
+        } else {  // the item is too short for this part (the whole workgroup agrees)
+            w = feed.again();
+            rb = row_blocks(kernarg<BwdParams>(), prm.fwd_items, max(w, 0));
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -486,9 +511,50 @@ __device__ __forceinline__ void ds_quad(uint32_t p01, uint32_t p23, const float 
 // query tile.  The 12-wavefront shape serves work items of block_n = 192.
 constexpr int PAIRS_8W = 4, PAIRS_12W = 6;
 
-template <int D, int PAIRS>
-__device__ __forceinline__ void dkv_work(const BwdParams &prm, const int bid)
+// One work item: SUB key rows of one KV head, or what is left of them, and which of the group's heads.
+struct KeyBlock {
+    int c, head_lo, g, hp;         // KV head; first query head of the share, how many, which share
+    int kv0, item_rows;            // first key position; key rows from there on that belong to the item
+    int qb, ql, kvl, kbase, qbase; // the (late) segment: position of its first query, rows, keys, packed rows
+    int qb_e, ql_e, qbase_e;       // the early chunk that shares the prefix and sees the block (ql_e = 0: none)
+};
+// blockIdx -> (item, SUB-key pass of the item, KV head); an item of more key rows
+// than SUB is several workgroups
+template <typename P>
+__device__ __forceinline__ KeyBlock key_block(const P prm, int SUB, int bid)
 {
+    KeyBlock r;
+    const int BN = prm->keys.BN, hs = prm->head_split;
+    const int item = __builtin_amdgcn_readfirstlane(bid / prm->keys.per_item), x = bid - item * prm->keys.per_item;
+    const int y = quotient(x, prm->keys.inv_passes), sub = x - y * prm->keys.passes;
+    r.c = quotient(y, prm->keys.inv_hs);
+    r.hp = y - r.c * hs;  // which share of the group's query heads
+    const i32x4 it = plan_value((const i32x4 *)prm->dkv_items, item);
+    const int g_all = prm->keys.g;
+    const int lo = quotient(r.hp * g_all, prm->keys.inv_hs);
+    r.g = quotient((r.hp + 1) * g_all, prm->keys.inv_hs) - lo;  // >= 1 since head_split <= g_all
+    r.head_lo = r.c * g_all + lo;
+    const int seq = it.x, prev = max(seq - 1, 0);
+    const int shares = plan_value(prm->shares_kv, seq), kvl_e = plan_value(prm->kv_len, prev);
+    r.qb = plan_value(prm->q_begin, seq);
+    r.ql = plan_value(prm->q_len, seq);
+    r.kvl = plan_value(prm->kv_len, seq);
+    r.kbase = plan_value(prm->cu_k, seq);
+    r.qbase = plan_value(prm->cu_q, seq);
+    r.qb_e = plan_value(prm->q_begin, prev);
+    r.qbase_e = plan_value(prm->cu_q, prev);
+    r.ql_e = plan_value(prm->q_len, prev);
+    r.kv0 = it.y * BN + sub * SUB;
+    r.item_rows = min(BN, r.kvl - it.y * BN) - sub * SUB;
+    if (!shares || r.kv0 >= kvl_e) r.ql_e = 0;
+    return r;
+}
+
+// Does work item `bid`, whose keys are `kb`; returns the next one and leaves its keys in `kb`.
+template <int D, int PAIRS>
+__device__ __forceinline__ int dkv_work(const int bid, KeyBlock &kb, WorkFeed &feed)
+{
+    const kernarg_t<BwdParams> prm = kernarg<BwdParams>();
     constexpr int NWP = 2 * PAIRS;   // wavefronts: PAIRS S waves, then PAIRS dP waves
     constexpr int SUB = 32 * PAIRS;  // key rows per workgroup
     constexpr int KS = D / 16, TT = D / 32, QT = TILE_ROWS;
@@ -501,32 +567,17 @@ __device__ __forceinline__ void dkv_work(const BwdParams &prm, const int bid)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int role = wave / PAIRS, pw = wave % PAIRS;  // waves w and w+PAIRS share 32 key rows
     const int n = lane & 31, h = lane >> 5;
-    // blockIdx -> (item, SUB-key pass of the item, KV head); an item of more key rows
-    // than SUB is several workgroups
-    const int passes = (prm.BN + SUB - 1) / SUB;
-    const int sub = bid % passes;
-    const int hs = prm.head_split;
-    const int hp = (bid / passes) % hs;  // which share of the group's query heads
-    const int c = (bid / passes / hs) % prm.Hkv, item_id = bid / passes / hs / prm.Hkv;
-    const int g_all = prm.Hq / prm.Hkv;
-    const int head_lo = (hp * g_all) / hs;
-    const int g = ((hp + 1) * g_all) / hs - head_lo;  // >= 1 since head_split <= g_all
+    const int c = kb.c, g = kb.g, head_lo = kb.head_lo;
     FragAddr<D> fa;
     fa.init(lane);
     RingLoader<D, NWP> ld;
-    ld.init(lane, wave, (uint32_t)prm.Hq * D * 2);
+    ld.init(lane, wave, (uint32_t)prm->Hq * D * 2);
     const uint32_t ring0 = lds_addr(&lds_ring[0][0]);
 
-    const int4 it = prm.dkv_items[item_id];
-    const int seq = it.x;
-    const int qb = prm.q_begin[seq], ql = prm.q_len[seq], kvl = prm.kv_len[seq];
-    const int kbase = prm.cu_k[seq], qbase = prm.cu_q[seq];
-    const int item_rows = min(prm.BN, kvl - it.y * prm.BN);
-    const float cs = prm.scale_log2;
-
-    if (sub * SUB >= item_rows) return;  // (whole workgroup) this item has no second pass
-    const uint64_t trace_t0 = trace_begin(prm.trace_dkv);
-    const int kv0 = it.y * prm.BN + sub * SUB;  // first key position of the pass
+    const int qb = kb.qb, ql = kb.ql, kvl = kb.kvl, kbase = kb.kbase, qbase = kb.qbase;
+    const float cs = prm->scale_log2;
+    const uint64_t trace_t0 = trace_begin(prm->trace_dkv);
+    const int kv0 = kb.kv0;  // first key position of the pass
     const int krows = min(SUB, kvl - kv0);
     const int wj0 = kv0 + 32 * pw;              // this pair's first key position
     const bool wave_active = 32 * pw < krows;
@@ -545,7 +596,7 @@ __device__ __forceinline__ void dkv_work(const BwdParams &prm, const int bid)
         Stage st;
         st.init(lane);
         u32x4 vk[Stage::N];
-        st.load(vk, (role == 0 ? prm.k : prm.v) + ((size_t)kbase * prm.Hkv + c) * D, (uint32_t)prm.Hkv * D * 2, wj0, kvl);
+        st.load(vk, (role == 0 ? prm->k : prm->v) + ((size_t)kbase * prm->Hkv + c) * D, (uint32_t)prm->Hkv * D * 2, wj0, kvl);
         st.put(stage, vk);
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) bf[ks] = fa.rows_at(stage, ks);
@@ -556,14 +607,9 @@ __device__ __forceinline__ void dkv_work(const BwdParams &prm, const int bid)
     // pass starts inside the early chunk's own prefix) and then those of segment seq.
     const int i_first = (max(0, kv0 - qb) / QT) * QT;
     const int n_qt_own = (ql - i_first + QT - 1) / QT;
-    int qb_e = 0, ql_e = 0, qbase_e = 0, i_first_e = 0, n_qt_e = 0;
-    if (prm.shares_kv[seq] && kv0 < prm.kv_len[seq - 1]) {
-        qb_e = prm.q_begin[seq - 1];
-        ql_e = prm.q_len[seq - 1];
-        qbase_e = prm.cu_q[seq - 1];
-        i_first_e = (max(0, kv0 - qb_e) / QT) * QT;
-        n_qt_e = (ql_e - i_first_e + QT - 1) / QT;
-    }
+    const int qb_e = kb.qb_e, ql_e = kb.ql_e, qbase_e = kb.qbase_e;
+    const int i_first_e = (max(0, kv0 - qb_e) / QT) * QT;
+    const int n_qt_e = ql_e > 0 ? (ql_e - i_first_e + QT - 1) / QT : 0;
     const int n_qt = n_qt_e + n_qt_own;
     const int n_iter = n_qt * g;  // (head, query tile) pairs
     // tile t -> first global position of its segment, rows of the segment, first row of the tile
@@ -576,20 +622,27 @@ __device__ __forceinline__ void dkv_work(const BwdParams &prm, const int bid)
     f32x16 acc[TT];  // dV^T (role 0) or dK^T (role 1) of this lane's key
     zero_acc(acc);
 
+    // wave 2 fetches a tile's LSE', wave 3 its -D (both kept from here on: read again in every
+    // round, the pointers cost these two waves the latency of a scalar load per round)
+    const bool row_scalars = wave == 2 || wave == 3;
+    const float *scalars = wave == 2 ? prm->lse2 : prm->delta;
+    const int scalars_at = 2 * TB + (wave == 2 ? 0 : QT * 4);
+    int total_q = prm->total_q;
+    asm volatile("" : "+s"(scalars), "+s"(total_q));
     // fetch of tile (head th of the group, query tile tq_idx) into ring slot `slot`
     auto fetch = [&](int th, int tq_idx, int slot) __attribute__((always_inline)) {
-        const int head = c * g_all + head_lo + th;
+        const int head = head_lo + th;
         const int i0 = tile_i0(tq_idx);
         const int rows = tile_ql(tq_idx);
         const int first_row = tq_idx < n_qt_e ? qbase_e : qbase;
         const uint32_t base = ring0 + (uint32_t)slot * SLOT;
-        const size_t hoff = ((size_t)first_row * prm.Hq + head) * D;
+        const size_t hoff = ((size_t)first_row * prm->Hq + head) * D;
         // rows past the end of the segment read as zero (and are masked)
-        ld.load(ld.rsrc(prm.q + hoff, rows), base, i0, wave);
-        ld.load(ld.rsrc(prm.d_o + hoff, rows), base + TB, i0, wave);
-        const size_t soff = (size_t)head * prm.total_q + first_row;
-        if (wave == 2) dma_b32(rsrc_words(prm.lse2 + soff, (uint32_t)rows * 4), base + 2 * TB, lane * 4, i0 * 4);
-        if (wave == 3) dma_b32(rsrc_words(prm.delta + soff, (uint32_t)rows * 4), base + 2 * TB + QT * 4, lane * 4, i0 * 4);
+        ld.load(ld.rsrc(prm->q + hoff, rows), base, i0, wave);
+        ld.load(ld.rsrc(prm->d_o + hoff, rows), base + TB, i0, wave);
+        if (row_scalars)
+            dma_b32(rsrc_words(scalars + (size_t)head * total_q + first_row, (uint32_t)rows * 4), base + scalars_at, lane * 4,
+                    i0 * 4);
     };
 
     fetch(0, n_qt - 1, 0);
@@ -679,7 +732,7 @@ __device__ __forceinline__ void dkv_work(const BwdParams &prm, const int bid)
                 fr[nx % 4] = nx < KS ? fa.rows(tq, 0, nx) : fa.rows(tq, 1, nx - KS);
                 SB();
             }
-            if (need_mask) mask_block(s[0], 0);
+            if (__builtin_expect(need_mask, 0)) mask_block(s[0], 0);
             // S of the second 32 rows with the probabilities of the first behind its
             // MFMAs, then dV of the first with the probabilities of the second
             uint32_t w[2][8];
@@ -707,7 +760,7 @@ __device__ __forceinline__ void dkv_work(const BwdParams &prm, const int bid)
                 if (ks >= KS - 3) ft[(ks - (KS - 3))] = fa.cols(tdo, (ks - (KS - 3)) % TT, (ks - (KS - 3)) / TT);
                 SB();
             }
-            if (need_mask) mask_block(s[1], 1);
+            if (__builtin_expect(need_mask, 0)) mask_block(s[1], 1);
             const bf16x8 pb0 = as_bf16x8(make_uint4(w[0][0], w[0][1], w[0][2], w[0][3]));
             const bf16x8 pb1 = as_bf16x8(make_uint4(w[0][4], w[0][5], w[0][6], w[0][7]));
             // dV of rows 0..31 (2 x TT MFMAs); probabilities of rows 32..63 behind them
@@ -887,34 +940,52 @@ __device__ __forceinline__ void dkv_work(const BwdParams &prm, const int bid)
         }
     }
     // rounds without work for this pair: keep fetching and meeting the others
+    feed.ask();
 #pragma unroll 1
     for (; T <= n_iter; ++T) {
         round_begin(T);
+        if (T == n_iter) feed.post();
         round_end();
     }
-    // (the last round ended with a barrier: nobody reads a tile or P any more)
+    // (the last round ended with a barrier: nobody reads a tile or P any more; the next item's
+    // first tile goes to slot 0, where nothing is staged)
+    const kernarg_t<BwdParams> out = kernarg<BwdParams>();
+    const int next = feed.take(), hp = kb.hp;
+    KeyBlock kb_next{};
+    if (next >= 0) kb_next = key_block(out, SUB, next);  // (its loads are under way during the stores)
     if (wave_active) {
-        if (hs == 1) {
+        if (out->head_split == 1) {
             Stage st;
             st.init(lane);
-            st.put_acc(stage, acc, role == 0 ? 1.0f : prm.scale, n, h);
-            st.store(stage, (role == 0 ? prm.dv : prm.dk) + ((size_t)kbase * prm.Hkv + c) * D,
-                     (uint32_t)prm.Hkv * D * 2, wj0, kvl);
+            st.put_acc(stage, acc, role == 0 ? 1.0f : out->scale, n, h);
+            st.store(stage, (role == 0 ? out->dv : out->dk) + ((size_t)kbase * out->Hkv + c) * D,
+                     (uint32_t)out->Hkv * D * 2, wj0, kvl);
         } else if (my_j < kvl) {
-            const size_t off = ((size_t)(kbase + my_j) * prm.Hkv + c) * D;
-            const size_t part = (size_t)hp * prm.total_k * prm.Hkv * D;
-            store_rows_f32<TT>((role == 0 ? prm.dv_part : prm.dk_part) + part + off, acc, h);
+            const size_t off = ((size_t)(kbase + my_j) * out->Hkv + c) * D;
+            const size_t part = (size_t)hp * out->total_k * out->Hkv * D;
+            store_rows_f32<TT>((role == 0 ? out->dv_part : out->dk_part) + part + off, acc, h);
         }
     }
-    trace_end(prm.trace_dkv, trace_t0, bid);
+    trace_end(out->trace_dkv, trace_t0, bid);
+    kb = uniform(kb_next);
+    return next;
 }
 
 template <int D, int PAIRS>
 __global__ __launch_bounds__(128 * PAIRS, PAIRS == PAIRS_12W ? 3 : 2) void dkv_kernel(const BwdParams prm)
 {
     __shared__ int work_slot;
-    work_loop(prm.queue_dkv, prm.n_work_dkv, &work_slot,
-              [&](int w) __attribute__((always_inline)) { dkv_work<D, PAIRS>(prm, w); });
+    WorkFeed feed{prm.queue_dkv, prm.n_work_dkv, 0, &work_slot};
+    int w = feed.first();
+    KeyBlock kb = key_block(kernarg<BwdParams>(), 32 * PAIRS, max(w, 0));
+    while (w >= 0) {
+        if (kb.item_rows > 0) {
+            w = dkv_work<D, PAIRS>(w, kb, feed);
+        } else {  // the item has no second pass (the whole workgroup agrees)
+            w = feed.again();
+            kb = key_block(kernarg<BwdParams>(), 32 * PAIRS, max(w, 0));
+        }
+    }
 }
 
 // Sum of the head-split partial gradients, rounded once: out = bf16(mul * sum_p part[p]).
@@ -1001,11 +1072,13 @@ int grid_dq(const skrull_attn_plan_t *p)
     return p->n_fwd * p->Hkv * map_dq(p).parts;
 }
 
-int grid_dkv(const skrull_attn_plan_t *p)
+static KeyMap map_dkv(const skrull_attn_plan_t *p)
 {
-    const int pairs = dkv_pairs(p);
-    return p->n_dkv * p->Hkv * p->head_split * ((p->BN + 32 * pairs - 1) / (32 * pairs));
+    const int SUB = 32 * dkv_pairs(p), passes = (p->BN + SUB - 1) / SUB;
+    return KeyMap{p->BN, p->Hq / p->Hkv, passes, passes * p->head_split * p->Hkv, inverse_of(passes), inverse_of(p->head_split)};
 }
+
+int grid_dkv(const skrull_attn_plan_t *p) { return p->n_dkv * map_dkv(p).per_item; }
 
 hipError_t launch_bwd(const skrull_attn_plan_t *p, const void *q, const void *k, const void *v,
                       const void *o, const float *lse, const void *d_o, void *dq, void *dk,
@@ -1022,7 +1095,8 @@ hipError_t launch_bwd(const skrull_attn_plan_t *p, const void *q, const void *k,
     prm.cu_q = p->cu_q; prm.cu_k = p->cu_k; prm.q_begin = p->q_begin; prm.q_len = p->q_len;
     prm.kv_len = p->kv_len; prm.shares_kv = p->shares_kv;
     prm.Hq = p->Hq; prm.Hkv = p->Hkv; prm.total_q = p->total_q;
-    prm.rows = map_dq(p); prm.BN = p->BN;
+    prm.rows = map_dq(p);
+    prm.keys = map_dkv(p);
     prm.scale = p->scale; prm.scale_log2 = p->scale * kLog2e;
     prm.head_split = p->head_split; prm.total_k = p->total_k;
     prm.n_work_dq = grid_dq(p);

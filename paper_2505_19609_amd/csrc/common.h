@@ -65,7 +65,8 @@ __device__ __forceinline__ void trace_end(WgTrace *t, uint64_t t0, int work)
         r.hw_id = __builtin_amdgcn_s_getreg((31 << 11) | 4);    // HW_REG_HW_ID, all 32 bits
         r.xcc_id = __builtin_amdgcn_s_getreg((31 << 11) | 20);  // HW_REG_XCC_ID
         r.block = work;
-        r.one = 1;
+        // (formed here: as a constant it was kept, and spilled, through the whole work loop)
+        asm volatile("v_mov_b32 %0, 1" : "=v"(r.one));
         t[work] = r;
     }
 }

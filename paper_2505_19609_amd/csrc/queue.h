@@ -32,12 +32,30 @@ template <typename P> __device__ __forceinline__ kernarg_t<P> kernarg()
     return p;
 }
 
-// Next work item for a workgroup on die `xcd`, or -1 when every queue is empty.  Called by
+// A plan's array, which no kernel that reads it this way writes: read through the scalar cache.
+template <typename T> __device__ __forceinline__ T plan_value(const T *array, int i)
+{
+    return ((const T __attribute__((address_space(4))) *)(uintptr_t)array)[i];
+}
+
+// A struct of wave-uniform values, said to be so (a choice between loaded ones and none lands in
+// vector registers).
+template <typename S> __device__ __forceinline__ S uniform(const S &s)
+{
+    static_assert(sizeof(S) % 4 == 0, "made of 32-bit words");
+    struct W { int w[sizeof(S) / 4]; };
+    W w = __builtin_bit_cast(W, s);
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(S) / 4); ++i) w.w[i] = __builtin_amdgcn_readfirstlane(w.w[i]);
+    return __builtin_bit_cast(S, w);
+}
+
+// The work item that count `k` of die `xcd`'s queue stands for; when that queue is used up, the
+// next item of the queue with the most items left; -1 when every queue is empty.  Called by
 // one lane.  Counters are device-scope atomics (the dies' L2 caches are not coherent with
 // each other for plain accesses).
-__device__ __forceinline__ int claim_work(WorkQueue *q, int n_work, int xcd)
+__device__ __forceinline__ int claimed_work(WorkQueue *q, int n_work, int xcd, int k)
 {
-    int k = __hip_atomic_fetch_add(&q->next[xcd], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (8 * k + xcd < n_work) return 8 * k + xcd;
     for (;;) {
         // the queue with the most items left
@@ -56,31 +74,54 @@ __device__ __forceinline__ int claim_work(WorkQueue *q, int n_work, int xcd)
 }
 
 // Die this wave runs on (XCC_ID register, bits 0-3).
-__device__ __forceinline__ int my_xcd() { return __builtin_amdgcn_s_getreg((31 << 11) | 20) & 7; }
+__device__ __forceinline__ int my_xcd() { return __builtin_amdgcn_readfirstlane(__builtin_amdgcn_s_getreg((31 << 11) | 20) & 7); }
 
-// Work loop of a persistent workgroup: `body(w)` for every work item it takes.  Without a
-// queue (q == nullptr) the workgroup does the one item of its block index, as in a plain
-// grid.  `slot` is one int of LDS.
-template <typename F>
-__device__ __forceinline__ void work_loop(WorkQueue *q, int n_work, int *slot, F body)
-{
-    const int xcd = q ? my_xcd() : 0;
-    bool first = true;
-    for (;;) {
-        int w;
-        if (q) {
-            if (threadIdx.x == 0) *slot = claim_work(q, n_work, xcd);
-            __syncthreads();
-            w = __builtin_amdgcn_readfirstlane(*slot);
-            __syncthreads();  // everyone has read the slot before the next claim overwrites it
-        } else {
-            w = first ? (int)blockIdx.x : -1;
-            first = false;
-        }
-        if (w < 0 || w >= n_work) return;
-        body(w);
+// The work of a persistent workgroup: one item after another until `take` returns -1.  Without a
+// queue (q == nullptr) the workgroup does the one item of its block index, as in a plain grid.
+// The next item is asked for while the current one still computes: `ask` (one lane sends the
+// atomic), `post` (that lane leaves the answer in LDS), a barrier of the caller's, `take`
+// (every wave reads it) -- with the claim, its two barriers and the loads of the item's
+// descriptor between two items, a workgroup stood still for 3 to 3.5 us per item (a quarter
+// of the forward of 64 short sequences, 14/2 heads of 64).  Asked for near the END of an item,
+// so that what a workgroup holds back from the others is at most about to start.
+// `slot` is one int of LDS; the caller has a barrier between a `take` and the next `post`.
+struct WorkFeed {
+    WorkQueue *q;
+    int n_work, pending;
+    int *slot;
+
+    __device__ __forceinline__ int first()
+    {
+        if (!q) return (int)blockIdx.x;
+        return again();
     }
-}
+    __device__ __forceinline__ void ask()
+    {
+        if (q && threadIdx.x == 0) {
+            // (an address the compiler cannot see to be uniform: for a uniform one it adds up the
+            // lanes that are on, one here, and waits for the answer at once to spread it to them)
+            uint32_t die;
+            int one;
+            asm volatile("v_mov_b32 %0, %2\n\tv_mov_b32 %1, 1" : "=v"(die), "=v"(one) : "s"(my_xcd()));
+            pending = __hip_atomic_fetch_add(&q->next[die], one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    __device__ __forceinline__ void post()
+    {
+        if (q && threadIdx.x == 0) *slot = claimed_work(q, n_work, my_xcd(), pending);
+    }
+    __device__ __forceinline__ int take() const { return q ? __builtin_amdgcn_readfirstlane(*slot) : -1; }
+    // all of it at once, for a workgroup that has no work to hide it behind
+    __device__ __forceinline__ int again()
+    {
+        if (!q) return -1;
+        __syncthreads();  // everyone has read the slot
+        ask();
+        post();
+        __syncthreads();
+        return take();
+    }
+};
 
 // Zeroes `n` work queues (a launch's queue must be zero when its kernel starts).
 static __global__ void queue_reset_kernel(WorkQueue *q, int n)

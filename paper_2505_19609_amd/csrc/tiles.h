@@ -24,8 +24,11 @@
 #pragma once
 
 #include "mfma.h"
+#include "queue.h"
 
 constexpr int TILE_ROWS = 64;
+
+typedef int i32x4 __attribute__((ext_vector_type(4)));
 
 // nothing is scheduled across this point: pins the hand-made order of the steps
 #define SB() __builtin_amdgcn_sched_barrier(0)
@@ -109,11 +112,11 @@ struct RowMap {
     int32_t part_step, wave_step;  // row block of wave w of part p: p * part_step + w * wave_step
     uint64_t inv_g, inv_hkv;
 };
+static inline uint64_t inverse_of(int d) { return ((1ull << 40) + d - 1) / d; }
 static inline RowMap row_map(int BM, int Hq, int Hkv, int NW)
 {
     const int g = Hq / Hkv;
-    const uint64_t one = 1ull << 40;
-    return RowMap{BM, g, Hkv, (BM / 32 * g + NW - 1) / NW, NW, 1, (one + g - 1) / g, (one + Hkv - 1) / Hkv};
+    return RowMap{BM, g, Hkv, (BM / 32 * g + NW - 1) / NW, NW, 1, inverse_of(g), inverse_of(Hkv)};
 }
 // The other order, for launches whose workgroups all run at once: neighbouring row blocks go to
 // different workgroups, so that a workgroup has few waves at work near its last key and the longest
@@ -141,6 +144,9 @@ struct RowBlocks {
     }
 };
 
+// work index -> (item, part, KV head).  Consecutive work items go to consecutive XCDs; the parts of
+// one (item, KV head) are Hkv apart so that they share an XCD (and its L2 copy of the K/V tiles)
+// whenever Hkv divides 8 or is a multiple of it.
 template <typename P>
 __device__ __forceinline__ RowBlocks row_blocks(const P prm, const int4 *items, int bid)
 {
@@ -151,12 +157,12 @@ __device__ __forceinline__ RowBlocks row_blocks(const P prm, const int4 *items, 
     r.c = x - part * Hkv;
     r.first = part * prm->rows.part_step;
     r.step = prm->rows.wave_step;
-    const int4 it = items[item];
+    const i32x4 it = plan_value((const i32x4 *)items, item);
     const int seq = it.x;
-    const int ql = prm->q_len[seq];
-    r.qb = prm->q_begin[seq];
-    r.kvl = prm->kv_len[seq];
-    r.kbase = prm->cu_k[seq];
+    const int ql = plan_value(prm->q_len, seq);
+    r.qb = plan_value(prm->q_begin, seq);
+    r.kvl = plan_value(prm->kv_len, seq);
+    r.kbase = plan_value(prm->cu_k, seq);
     r.p0 = r.qb + it.y * BM;
     r.qrow0 = it.z;
     r.rows = min(BM, ql - it.y * BM);
@@ -177,7 +183,6 @@ __device__ __forceinline__ RowBlocks row_blocks(const P prm, const int4 *items, 
 // a fetch in flight, whichever slot a run-time index selects; the kernels order
 // a slot's fetch and its reads themselves (wait_vmem + workgroup barrier).
 // ---------------------------------------------------------------------------
-typedef int i32x4 __attribute__((ext_vector_type(4)));
 
 // raw buffer descriptor words over `bytes` bytes at `base` (wave-uniform)
 __device__ __forceinline__ i32x4 rsrc_words(const void *base, uint32_t bytes)
