@@ -96,7 +96,7 @@ typedef struct {
     int64_t useful_flops_bwd;     /* 10 * pairs * head_dim * Hq                                */
     int64_t bwd_workspace_bytes;  /* device scratch skrull_attn_bwd needs (>= 0)               */
     int32_t num_segments;         /* query segments: K + number of two-chunk sequences         */
-    int32_t head_split;           /* the dK/dV head split in effect (>= 1)                     */
+    int32_t head_split;           /* the dK/dV head split in effect (>= 1; see skrull_attn_plan) */
     int32_t wg_query_rows;        /* query rows per forward / dQ workgroup in effect (128 or 256;
                                      dQ has the 128-row shape at head_dim 64 only)             */
     int32_t reserved;             /* 0                                                         */
@@ -139,13 +139,17 @@ enum {
  * larger items still balance (five blocks of 192 key rows x KV heads per
  * compute unit, or a costliest item under 0.7 of the even share; the dK/dV
  * kernel then runs 12 wavefronts over 192 key rows); head_split above 1
- * when the longest dK/dV chain exceeds an even share of the work list;
+ * when the longest dK/dV chain exceeds an even share of the work list (the library then
+ * shares out the items with long chains only, over up to that many workgroups; a head_split
+ * the caller gives holds for every item; with a choice of 1 items may still be shared over
+ * up to 8 when the longest chain exceeds an even share and the partial sums fit
+ * SKRULL_STATIC_SCRATCH_BYTES with the rest of the workspace);
  * wg_query_rows 128 when the micro-batch holds enough work for the smaller
  * workgroups to pay (head_dim 64: at least 24 blocks of 256 query rows x heads
  * per compute unit or 1.5e9 attended (query, key, head) triples; head_dim 128:
  * at least 16 such blocks and no sequence above 8,192 tokens), else 256.  None
  * of them changes a result beyond the
- * last bit of dK/dV (head_split changes the order of the sum over heads).
+ * last bit of dK/dV (head_split and the sharing of items change the order of a sum).
  *
  * p and the three arrays it points to are HOST memory, read before return.
  * `hip_stream` (a hipStream_t, may be NULL for the default stream) carries the
@@ -214,10 +218,10 @@ int skrull_attn_fwd(const skrull_attn_plan_t *plan, const void *q, const void *k
  * dK/dV of a shard are this rank's partial sums over its own query rows for
  * the whole prefix (a multi-GPU caller would reduce them across ranks; the
  * paper's Eq. 3/Volume(S) is that exchange).  All outputs bf16, rounded once
- * from fp32 accumulators; the group sum is done in registers, or, when the plan's
- * head_split is above 1, over fp32 partial sums in the workspace in a fixed order
- * (no atomics either way, so results are bit-reproducible; two plans with
- * different head_split may differ in the last bit of dK/dV).
+ * from fp32 accumulators; the group sum is done in registers, or, for items that several
+ * workgroups share, over fp32 partial sums in the workspace in a fixed order
+ * (no atomics either way, so results are bit-reproducible; two plans that share items
+ * out differently may differ in the last bit of dK/dV).
  * `workspace` is DEVICE scratch of at least info.bwd_workspace_bytes, 16-byte
  * aligned; contents on entry are ignored and on exit unspecified.
  * Only enqueues on `hip_stream`; never synchronises.
@@ -234,7 +238,7 @@ int skrull_attn_bwd(const skrull_attn_plan_t *plan, const void *q, const void *k
  * code under HIP graph capture, tight serving or training loops, harnesses that forbid
  * hipMalloc.  Same arguments, results and errors as skrull_attn_bwd (bit for bit: the
  * same kernels), but the workspace (-D and LSE*log2(e) per query head and row, and the
- * fp32 partial dK/dV when head_split > 1) is a static device array inside the library of
+ * fp32 partial dK/dV of shared items) is a static device array inside the library of
  * SKRULL_STATIC_SCRATCH_BYTES bytes per GPU, held from library load until the process
  * ends; its address on a device is looked up when the first plan is made on that device.
  * The call allocates and frees nothing, does not synchronise, and only enqueues kernels

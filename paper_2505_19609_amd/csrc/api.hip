@@ -50,6 +50,7 @@ struct TraceState {
 };
 thread_local TraceState g_trace;
 
+constexpr int32_t kMaxParts = 8;  // workgroups that may share one dK/dV item
 constexpr int32_t kMaxItems = 1 << 20;  // per list (lists above 2,048 items are radix sorted)
 
 // Workspace of skrull_attn_bwd_static, the backward entry point for callers that cannot
@@ -89,6 +90,73 @@ int check_device(int *dev_out, int *compute_units)
     *dev_out = dev;
     *compute_units = prop.multiProcessorCount;
     return SKRULL_OK;
+}
+
+// Bytes of backward scratch without partial sums: -D and LSE*log2(e) per (head, row), then 256
+// bytes for the work queues of the two kernels.
+int64_t base_workspace(const skrull_attn_plan_t *plan)
+{
+    return ((((int64_t)plan->Hq * plan->total_q * 8) + 255) & ~(int64_t)255) + 256;
+}
+
+// fp32 partial dK and dV of the items that several workgroups share: a slot per part for every row of
+// K, or for the rows of those items only.
+int64_t partial_bytes(const skrull_attn_plan_t *plan)
+{
+    if (plan->split_parts <= 1) return 0;
+    const int64_t rows = plan->split_compact ? (int64_t)plan->n_split * plan->BN : plan->total_k;
+    return 2 * (int64_t)plan->split_parts * rows * plan->Hkv * plan->d * 4;
+}
+
+// Which dK/dV items are shared out over several workgroups.  A head split the caller asked for holds
+// for every item.  The library's own shares out only items with a long chain: split over the heads,
+// every item of a short sequence cost seven starts, seven ends and seven fp32 partial sums instead of
+// one store (64 sequences, 26,624 tokens, 14/2 heads of 64: dK/dV 202 us all items split 7 ways,
+// 146 this way; 20 sequences, 16,384 tokens: 184 -> 162), and where the heads cannot be split evenly
+// the longest chain was the kernel's time (10 sequences, 13,312 tokens, 28/4 heads of 128: 640 -> 530;
+// one of 2,967, 4/4 heads of 64: 69 -> 36).
+void choose_split(skrull_attn_plan_t *plan, int32_t asked, const PlanTotals &totals, int32_t compute_units)
+{
+    const int32_t group = plan->Hq / plan->Hkv;
+    plan->n_split = plan->n_whole_first = plan->split_chain = plan->split_compact = 0;
+    plan->split_parts = 1;
+    if (asked != 0) {
+        if (asked > 1) {
+            plan->split_parts = asked;
+            plan->n_split = plan->n_dkv;
+        }
+        return;
+    }
+    const int64_t longest = (int64_t)totals.dkv_cost_max * group;
+    // Where the heads are not split by the rule above (nor could be: one head per group, or seven, which
+    // would be too many) items are shared out only if the longest chain exceeds an even share, and as
+    // few as it takes for the partial sums to fit the static workspace.
+    plan->split_compact = plan->head_split == 1;
+    if (plan->split_compact && 10 * longest * compute_units <= 11 * (int64_t)totals.dkv_cost_sum * plan->Hq) return;
+    const int32_t most = plan->split_compact ? kMaxParts : plan->head_split;
+    // When the longest part is then still as long as three quarters of an even share, all items are cut
+    // as fine as it is: what else runs has to fit beside it (3 sequences, 7,417 tokens, 14/2 heads of
+    // 64: dK/dV 137 us all cut, 145 by the limits below).
+    if (!plan->split_compact && 4 * longest * compute_units >= 3 * most * (int64_t)totals.dkv_cost_sum * plan->Hq) {
+        plan->split_parts = most;
+        plan->n_split = plan->n_dkv;
+        return;
+    }
+    int32_t above[SKRULL_CHAIN_LIMITS + 1];  // items that exceed limit k
+    above[SKRULL_CHAIN_LIMITS] = 0;
+    for (int k = SKRULL_CHAIN_LIMITS - 1; k >= 0; --k) above[k] = above[k + 1] + totals.chain_hist[k + 1];
+    for (int k = 2; k < SKRULL_CHAIN_LIMITS; ++k) {
+        const int64_t limit = dkv_chain_limit(totals.chain_base, k), want = (longest + limit - 1) / limit;
+        if (want < 2) break;
+        plan->split_parts = want > most ? most : (int32_t)want;
+        plan->split_chain = (int32_t)(limit > INT32_MAX ? INT32_MAX : limit);
+        plan->n_split = above[k];
+        plan->n_whole_first = above[k - 2] - above[k];
+        if (!plan->split_compact ||
+            base_workspace(plan) + partial_bytes(plan) <= (int64_t)SKRULL_STATIC_SCRATCH_BYTES) return;
+    }
+    plan->split_parts = 1;
+    plan->n_split = plan->n_whole_first = 0;
 }
 
 // A plan's arrays live on the device it was made on: the calls that use them must run there.
@@ -233,7 +301,8 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
                                fwd_off, dkv_off, (int32_t)cap_fwd, (int32_t)cap_dkv, bn_alt, p->num_kv_heads,
                                compute_units, totals_d, st));
     HIP_TRY(launch_plan_items(plan, fwd_off, dkv_off, (int32_t)cap_fwd, (int32_t)cap_dkv, scratch,
-                              scratch + 4 * cap_fwd, scratch + 4 * (cap_fwd + cap_dkv), cost_bound, totals_d, st));
+                              scratch + 4 * cap_fwd, scratch + 4 * (cap_fwd + cap_dkv), cost_bound, compute_units,
+                              totals_d, st));
     HIP_TRY(hipMemcpyAsync(&totals, totals_d, sizeof totals, hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
     if (totals.bad_entry != 0 || totals.n_seg != plan->NS || totals.total_q > INT32_MAX ||
@@ -309,6 +378,7 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
         if (hs >= 3 * asked && want < 1.5) hs = 1;
         plan->head_split = hs < 1 ? 1 : (hs > group ? group : hs);
     }
+    choose_split(plan, p->head_split, totals, compute_units);
     rc = SKRULL_OK;
 done:
     free(host_in);
@@ -340,10 +410,11 @@ int skrull_attn_plan_info(const skrull_attn_plan_t *plan, skrull_attn_plan_info_
     info->attended_pairs = plan->pairs;
     info->useful_flops_fwd = 4 * plan->pairs * plan->d * plan->Hq;
     info->useful_flops_bwd = 10 * plan->pairs * plan->d * plan->Hq;
-    // -D and LSE*log2(e) per (head, row), then 256 bytes for the work queues of the two kernels
-    info->bwd_workspace_bytes = ((((int64_t)plan->Hq * plan->total_q * 8) + 255) & ~(int64_t)255) + 256;
+    info->bwd_workspace_bytes = base_workspace(plan);
     if (plan->head_split > 1)  // fp32 partial dK and dV of every share of the heads
         info->bwd_workspace_bytes += 2 * (int64_t)plan->head_split * plan->total_k * plan->Hkv * plan->d * 4;
+    else
+        info->bwd_workspace_bytes += partial_bytes(plan);
     info->num_segments = plan->NS;
     info->head_split = plan->head_split;
     info->wg_query_rows = plan->wg_query_rows;

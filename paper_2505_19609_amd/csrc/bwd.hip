@@ -31,12 +31,21 @@ namespace {
 
 constexpr float kLog2e = 1.4426950408889634f;
 
-// How a dK/dV work index stands for an item, a KV head, a share of its query heads and a pass over
-// the item's key rows; quotients as in RowMap.
+// How a dK/dV work index stands for an item, a part of its chain, a KV head and a pass over the item's
+// key rows; quotients as in RowMap.  Handed out first are `n_whole_first` items that one workgroup does
+// whole, then the parts of the first `n_split` items of the list, then the rest: the units of all
+// three run from long to short, and the whole items of the middle are as long as the longest parts.
 struct KeyMap {
-    int32_t BN, g, passes, per_item;  // query heads per KV head; workgroups per (item, KV head, share), and per item
-    uint64_t inv_passes, inv_hs;
+    int32_t BN, g, passes, Hkv;                 // query heads per KV head; workgroups per (item, part, KV head)
+    int32_t n_split, n_whole_first, parts, chain;  // see skrull_attn_plan
+    int32_t part_rows;                          // rows of one part's partial sums; 0: the rows of K themselves
+    uint64_t inv_passes, inv_hkv;
 };
+// workgroups that share an item of the first n_split
+__device__ __forceinline__ int parts_of(const KeyMap &m, int cost)
+{
+    return m.chain == 0 ? m.parts : min(m.parts, (cost * m.g + m.chain - 1) / m.chain);
+}
 
 struct BwdParams {
     const uint16_t *q, *k, *v, *d_o, *o;
@@ -49,10 +58,9 @@ struct BwdParams {
     KeyMap keys;  // dK/dV: which keys and heads a workgroup takes
     int32_t Hq, Hkv, total_q;
     float scale, scale_log2;
-    // dK/dV head split: the query heads of a KV group are shared out over `head_split`
-    // workgroups, which leave unrounded partial sums in dk_part / dv_part
-    // ([head_split][total_k][Hkv][D] fp32) for dkv_reduce_kernel; 1 = no split
-    int32_t head_split, total_k;
+    // workgroups that share a dK/dV item leave unrounded partial sums in dk_part / dv_part
+    // ([part][row][Hkv][D] fp32) for dkv_reduce_kernel
+    int32_t total_k;
     float *dk_part, *dv_part;
     WgTrace *trace_dq, *trace_dkv;  // null, or one record per work item (measurement aid)
     WorkQueue *queue_dq, *queue_dkv;  // work queues of the persistent launches (workspace), zeroed before use
@@ -511,29 +519,32 @@ __device__ __forceinline__ void ds_quad(uint32_t p01, uint32_t p23, const float 
 // query tile.  The 12-wavefront shape serves work items of block_n = 192.
 constexpr int PAIRS_8W = 4, PAIRS_12W = 6;
 
-// One work item: SUB key rows of one KV head, or what is left of them, and which of the group's heads.
+// One work item: SUB key rows of one KV head, or what is left of them, and which part of the walk
+// over the query heads and tiles that see them.
 struct KeyBlock {
-    int c, head_lo, g, hp;         // KV head; first query head of the share, how many, which share
+    int c, part, parts;            // KV head; part of the work, and of how many
+    int head_lo, g;                // the query heads this part walks over
+    int piece, pieces;             // which piece of that walk, and of how many
     int kv0, item_rows;            // first key position; key rows from there on that belong to the item
+    int part_row;                  // first row of the pass in a part's partial sums
     int qb, ql, kvl, kbase, qbase; // the (late) segment: position of its first query, rows, keys, packed rows
     int qb_e, ql_e, qbase_e;       // the early chunk that shares the prefix and sees the block (ql_e = 0: none)
 };
-// blockIdx -> (item, SUB-key pass of the item, KV head); an item of more key rows
-// than SUB is several workgroups
 template <typename P>
 __device__ __forceinline__ KeyBlock key_block(const P prm, int SUB, int bid)
 {
     KeyBlock r;
-    const int BN = prm->keys.BN, hs = prm->head_split;
-    const int item = __builtin_amdgcn_readfirstlane(bid / prm->keys.per_item), x = bid - item * prm->keys.per_item;
-    const int y = quotient(x, prm->keys.inv_passes), sub = x - y * prm->keys.passes;
-    r.c = quotient(y, prm->keys.inv_hs);
-    r.hp = y - r.c * hs;  // which share of the group's query heads
+    const int BN = prm->keys.BN, Hkv = prm->keys.Hkv, passes = prm->keys.passes, n_split = prm->keys.n_split;
+    const int whole = Hkv * passes, first = prm->keys.n_whole_first * whole, split = n_split * prm->keys.parts * whole;
+    const bool is_split = bid >= first && bid < first + split;
+    const int per_item = is_split ? whole * prm->keys.parts : whole;
+    const int rel = bid < first ? bid : (is_split ? bid - first : bid - split);
+    const int at = __builtin_amdgcn_readfirstlane(rel / per_item), x = rel - at * per_item;
+    const int item = is_split ? at : at + n_split;
+    const int y = quotient(x, prm->keys.inv_passes), sub = x - y * passes;
+    r.part = quotient(y, prm->keys.inv_hkv);
+    r.c = y - r.part * Hkv;
     const i32x4 it = plan_value((const i32x4 *)prm->dkv_items, item);
-    const int g_all = prm->keys.g;
-    const int lo = quotient(r.hp * g_all, prm->keys.inv_hs);
-    r.g = quotient((r.hp + 1) * g_all, prm->keys.inv_hs) - lo;  // >= 1 since head_split <= g_all
-    r.head_lo = r.c * g_all + lo;
     const int seq = it.x, prev = max(seq - 1, 0);
     const int shares = plan_value(prm->shares_kv, seq), kvl_e = plan_value(prm->kv_len, prev);
     r.qb = plan_value(prm->q_begin, seq);
@@ -544,8 +555,24 @@ __device__ __forceinline__ KeyBlock key_block(const P prm, int SUB, int bid)
     r.qb_e = plan_value(prm->q_begin, prev);
     r.qbase_e = plan_value(prm->cu_q, prev);
     r.ql_e = plan_value(prm->q_len, prev);
+    r.parts = 1;
+    if (is_split) {
+        const int chain = prm->keys.chain;
+        r.parts = chain == 0 ? prm->keys.parts
+                             : min(prm->keys.parts, __builtin_amdgcn_readfirstlane((it.w * prm->keys.g + chain - 1) / max(chain, 1)));
+    }
+    // A part takes an equal share of the heads where there is one (the parts of neighbouring key
+    // blocks then walk the same query tiles at the same time), else an equal piece of the walk over
+    // all of them.
+    const int g = prm->keys.g, share = __builtin_amdgcn_readfirstlane(g / r.parts);
+    const bool by_heads = share * r.parts == g;
+    r.g = by_heads ? share : g;
+    r.head_lo = r.c * g + (by_heads ? r.part * share : 0);
+    r.piece = by_heads ? 0 : r.part;
+    r.pieces = by_heads ? 1 : r.parts;
     r.kv0 = it.y * BN + sub * SUB;
-    r.item_rows = min(BN, r.kvl - it.y * BN) - sub * SUB;
+    r.item_rows = r.part < r.parts ? min(BN, r.kvl - it.y * BN) - sub * SUB : 0;
+    r.part_row = prm->keys.part_rows ? item * BN + sub * SUB : r.kbase + r.kv0;
     if (!shares || r.kv0 >= kvl_e) r.ql_e = 0;
     return r;
 }
@@ -578,7 +605,7 @@ __device__ __forceinline__ int dkv_work(const int bid, KeyBlock &kb, WorkFeed &f
     const float cs = prm->scale_log2;
     const uint64_t trace_t0 = trace_begin(prm->trace_dkv);
     const int kv0 = kb.kv0;  // first key position of the pass
-    const int krows = min(SUB, kvl - kv0);
+    const int krows = min(SUB, kb.item_rows);
     const int wj0 = kv0 + 32 * pw;              // this pair's first key position
     const bool wave_active = 32 * pw < krows;
     const int my_j = wj0 + n;                   // this lane's key position
@@ -611,7 +638,12 @@ __device__ __forceinline__ int dkv_work(const int bid, KeyBlock &kb, WorkFeed &f
     const int i_first_e = (max(0, kv0 - qb_e) / QT) * QT;
     const int n_qt_e = ql_e > 0 ? (ql_e - i_first_e + QT - 1) / QT : 0;
     const int n_qt = n_qt_e + n_qt_own;
-    const int n_iter = n_qt * g;  // (head, query tile) pairs
+    // (head, query tile) pairs of the walk described below: this part takes n_iter of them from r0 on
+    const bool all = kb.pieces == 1;
+    const int r0 = all ? 0 : __builtin_amdgcn_readfirstlane(kb.piece * (n_qt * g) / kb.pieces);
+    const int n_iter = (all ? n_qt * g : __builtin_amdgcn_readfirstlane((kb.piece + 1) * (n_qt * g) / kb.pieces)) - r0;
+    const int first_up = r0 == 0 ? 0 : __builtin_amdgcn_readfirstlane(r0 / g);
+    const int head0 = r0 - first_up * g, tile0 = n_qt - 1 - first_up;
     // tile t -> first global position of its segment, rows of the segment, first row of the tile
     auto tile_qb = [&](int t) __attribute__((always_inline)) { return t < n_qt_e ? qb_e : qb; };
     auto tile_ql = [&](int t) __attribute__((always_inline)) { return t < n_qt_e ? ql_e : ql; };
@@ -645,11 +677,11 @@ __device__ __forceinline__ int dkv_work(const int bid, KeyBlock &kb, WorkFeed &f
                     i0 * 4);
     };
 
-    fetch(0, n_qt - 1, 0);
+    fetch(head0, tile0, 0);
     wait_vmem();
     __syncthreads();
 
-    // Round T: ring slot T % 3 holds (head T % g, query tile n_qt - 1 - T / g): heads
+    // Round T: ring slot T % 3 holds (head t % g, query tile n_qt - 1 - t / g), t = r0 + T: heads
     // innermost, query tiles from the end of the sequence down to the block's
     // diagonal.  Every workgroup of a sequence then starts at the same tile and the
     // ones running together walk the same tiles at the same time, which is what
@@ -672,9 +704,9 @@ __device__ __forceinline__ int dkv_work(const int bid, KeyBlock &kb, WorkFeed &f
         } else {
             while (dead_tiles < n_qt && !tile_live(dead_tiles)) ++dead_tiles;
         }
-        n_live = (n_qt - dead_tiles) * g;
+        n_live = max(0, min(n_iter, (n_qt - dead_tiles) * g - r0));
     }
-    int nh = 1, nq = n_qt - 1, cq = n_qt - 1, slot = 0;  // cq: tile of this round; (nh, nq): head, tile of the next
+    int nh = head0 + 1, nq = tile0, cq = tile0, slot = 0;  // cq: tile of this round; (nh, nq): head, tile of the next
     if (nh == g) { nh = 0; --nq; }
     // start of a round: fetch the next round's tile; end: wait, barrier, advance
     auto round_begin = [&](int T) __attribute__((always_inline)) {
@@ -950,20 +982,20 @@ __device__ __forceinline__ int dkv_work(const int bid, KeyBlock &kb, WorkFeed &f
     // (the last round ended with a barrier: nobody reads a tile or P any more; the next item's
     // first tile goes to slot 0, where nothing is staged)
     const kernarg_t<BwdParams> out = kernarg<BwdParams>();
-    const int next = feed.take(), hp = kb.hp;
+    const int next = feed.take(), parts = kb.parts, part = kb.part, part_row = kb.part_row;
     KeyBlock kb_next{};
     if (next >= 0) kb_next = key_block(out, SUB, next);  // (its loads are under way during the stores)
     if (wave_active) {
-        if (out->head_split == 1) {
+        if (parts == 1) {
             Stage st;
             st.init(lane);
             st.put_acc(stage, acc, role == 0 ? 1.0f : out->scale, n, h);
             st.store(stage, (role == 0 ? out->dv : out->dk) + ((size_t)kbase * out->Hkv + c) * D,
                      (uint32_t)out->Hkv * D * 2, wj0, kvl);
         } else if (my_j < kvl) {
-            const size_t off = ((size_t)(kbase + my_j) * out->Hkv + c) * D;
-            const size_t part = (size_t)hp * out->total_k * out->Hkv * D;
-            store_rows_f32<TT>((role == 0 ? out->dv_part : out->dk_part) + part + off, acc, h);
+            const size_t rows = out->keys.part_rows ? out->keys.part_rows : out->total_k;
+            const size_t at = (part * rows + part_row + (my_j - kv0)) * out->Hkv + c;
+            store_rows_f32<TT>((role == 0 ? out->dv_part : out->dk_part) + at * D, acc, h);
         }
     }
     trace_end(out->trace_dkv, trace_t0, bid);
@@ -988,28 +1020,46 @@ __global__ __launch_bounds__(128 * PAIRS, PAIRS == PAIRS_12W ? 3 : 2) void dkv_k
     }
 }
 
-// Sum of the head-split partial gradients, rounded once: out = bf16(mul * sum_p part[p]).
-__global__ __launch_bounds__(256) void dkv_reduce_kernel(const float *__restrict__ part, int32_t parts,
-                                                         int64_t n4, float mul, uint16_t *__restrict__ out)
+// Sum of the partial gradients of the items that several workgroups shared, rounded once:
+// out = bf16(mul * sum_p part[p]).  Block (x, y, z): KV head x % Hkv of item x / Hkv, 32 of its rows,
+// dK or dV.  Bound by the partial sums' bytes; only rows that were shared are touched.
+constexpr int REDUCE_ROWS = 32;
+template <int D>
+__global__ __launch_bounds__(256) void dkv_reduce_kernel(const BwdParams prm)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n4) return;
-    float4 a = ((const float4 *)part)[i];
-    for (int32_t p = 1; p < parts; ++p) {
-        const float4 b = ((const float4 *)part)[(int64_t)p * n4 + i];
-        a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
+    const int item = blockIdx.x / prm.Hkv, c = blockIdx.x - item * prm.Hkv;
+    const int4 it = prm.dkv_items[item];
+    const int row0 = blockIdx.y * REDUCE_ROWS;
+    const int kv0 = it.y * prm.keys.BN;
+    const int rows = min(REDUCE_ROWS, min(prm.keys.BN, prm.kv_len[it.x] - kv0) - row0);
+    const int krow = prm.cu_k[it.x] + kv0 + row0;
+    const int parts = parts_of(prm.keys, it.w);
+    const size_t part_rows = prm.keys.part_rows ? prm.keys.part_rows : prm.total_k;
+    const size_t prow = prm.keys.part_rows ? (size_t)item * prm.keys.BN + row0 : (size_t)krow;
+    const bool dk = blockIdx.z == 0;
+    const float4 *part = (const float4 *)(dk ? prm.dk_part : prm.dv_part);
+    uint2 *out = (uint2 *)(dk ? prm.dk : prm.dv);
+    const float mul = dk ? prm.scale : 1.0f;
+    for (int i = threadIdx.x; i < rows * (D / 4); i += 256) {
+        const int r = i / (D / 4), q = i % (D / 4);
+        const float4 *src = part + ((prow + r) * prm.Hkv + c) * (D / 4) + q;
+        float4 a = *src;
+        for (int p = 1; p < parts; ++p) {
+            const float4 b = src[(size_t)p * part_rows * prm.Hkv * (D / 4)];
+            a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w;
+        }
+        uint2 w;
+        w.x = pack_bf16(a.x * mul, a.y * mul);
+        w.y = pack_bf16(a.z * mul, a.w * mul);
+        out[((size_t)(krow + r) * prm.Hkv + c) * (D / 4) + q] = w;
     }
-    uint2 w;
-    w.x = pack_bf16(a.x * mul, a.y * mul);
-    w.y = pack_bf16(a.z * mul, a.w * mul);
-    ((uint2 *)out)[i] = w;
 }
 
 // true when the dQ kernel runs in its 4-wavefront shape (it fits the LDS twice only at head_dim 64)
 bool small_dq_shape(const skrull_attn_plan_t *p) { return p->d == 64 && p->wg_query_rows == 32 * NWQ_SMALL; }
 int dkv_pairs(const skrull_attn_plan_t *p) { return (p->d == 64 && p->BN == 32 * PAIRS_12W) ? PAIRS_12W : PAIRS_8W; }
 
-template <auto KernelQ, auto KernelKV>
+template <int D, auto KernelQ, auto KernelKV>
 hipError_t launch_pair(const skrull_attn_plan_t *p, BwdParams prm, int threads_q, int threads_kv, hipStream_t st,
                        hipEvent_t *ev)
 {
@@ -1033,11 +1083,9 @@ hipError_t launch_pair(const skrull_attn_plan_t *p, BwdParams prm, int threads_q
     if (ev) (void)hipEventRecord(ev[1], st);
     e = launch_work<KernelKV>(threads_kv, prm.n_work_dkv, queued_kv, prm, st);
     if (e != hipSuccess) return e;
-    if (p->head_split > 1) {
-        const int64_t n4 = (int64_t)p->total_k * p->Hkv * p->d / 4;
-        const unsigned blocks = (unsigned)((n4 + 255) / 256);
-        dkv_reduce_kernel<<<blocks, 256, 0, st>>>(prm.dk_part, p->head_split, n4, prm.scale, prm.dk);
-        dkv_reduce_kernel<<<blocks, 256, 0, st>>>(prm.dv_part, p->head_split, n4, 1.0f, prm.dv);
+    if (p->n_split > 0) {
+        const dim3 grid((unsigned)p->n_split * p->Hkv, (unsigned)(p->BN + REDUCE_ROWS - 1) / REDUCE_ROWS, 2);
+        dkv_reduce_kernel<D><<<grid, 256, 0, st>>>(prm);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -1051,13 +1099,13 @@ hipError_t launch_d(const skrull_attn_plan_t *p, const BwdParams &prm, hipStream
     if constexpr (D == 64) {  // the small dQ shape fits the LDS twice, and dK/dV has its 12-wavefront shape, only here
         const bool small_q = small_dq_shape(p), wide_kv = dkv_pairs(p) == PAIRS_12W;
         if (small_q && wide_kv)
-            return launch_pair<dq_kernel<D, NWQ_SMALL>, dkv_kernel<D, PAIRS_12W>>(p, prm, 64 * NWQ_SMALL, 128 * PAIRS_12W, st, ev);
+            return launch_pair<D, dq_kernel<D, NWQ_SMALL>, dkv_kernel<D, PAIRS_12W>>(p, prm, 64 * NWQ_SMALL, 128 * PAIRS_12W, st, ev);
         if (small_q)
-            return launch_pair<dq_kernel<D, NWQ_SMALL>, dkv_kernel<D, PAIRS_8W>>(p, prm, 64 * NWQ_SMALL, 128 * PAIRS_8W, st, ev);
+            return launch_pair<D, dq_kernel<D, NWQ_SMALL>, dkv_kernel<D, PAIRS_8W>>(p, prm, 64 * NWQ_SMALL, 128 * PAIRS_8W, st, ev);
         if (wide_kv)
-            return launch_pair<dq_kernel<D, NWQ_LARGE>, dkv_kernel<D, PAIRS_12W>>(p, prm, 64 * NWQ_LARGE, 128 * PAIRS_12W, st, ev);
+            return launch_pair<D, dq_kernel<D, NWQ_LARGE>, dkv_kernel<D, PAIRS_12W>>(p, prm, 64 * NWQ_LARGE, 128 * PAIRS_12W, st, ev);
     }
-    return launch_pair<dq_kernel<D, NWQ_LARGE>, dkv_kernel<D, PAIRS_8W>>(p, prm, 64 * NWQ_LARGE, 128 * PAIRS_8W, st, ev);
+    return launch_pair<D, dq_kernel<D, NWQ_LARGE>, dkv_kernel<D, PAIRS_8W>>(p, prm, 64 * NWQ_LARGE, 128 * PAIRS_8W, st, ev);
 }
 
 }  // namespace
@@ -1075,10 +1123,14 @@ int grid_dq(const skrull_attn_plan_t *p)
 static KeyMap map_dkv(const skrull_attn_plan_t *p)
 {
     const int SUB = 32 * dkv_pairs(p), passes = (p->BN + SUB - 1) / SUB;
-    return KeyMap{p->BN, p->Hq / p->Hkv, passes, passes * p->head_split * p->Hkv, inverse_of(passes), inverse_of(p->head_split)};
+    return KeyMap{p->BN, p->Hq / p->Hkv, passes, p->Hkv, p->n_split, p->n_whole_first, p->split_parts, p->split_chain,
+                  p->split_compact ? p->n_split * p->BN : 0, inverse_of(passes), inverse_of(p->Hkv)};
 }
 
-int grid_dkv(const skrull_attn_plan_t *p) { return p->n_dkv * map_dkv(p).per_item; }
+int grid_dkv(const skrull_attn_plan_t *p)
+{
+    return (p->n_dkv + p->n_split * (p->split_parts - 1)) * p->Hkv * map_dkv(p).passes;
+}
 
 hipError_t launch_bwd(const skrull_attn_plan_t *p, const void *q, const void *k, const void *v,
                       const void *o, const float *lse, const void *d_o, void *dq, void *dk,
@@ -1098,7 +1150,7 @@ hipError_t launch_bwd(const skrull_attn_plan_t *p, const void *q, const void *k,
     prm.rows = map_dq(p);
     prm.keys = map_dkv(p);
     prm.scale = p->scale; prm.scale_log2 = p->scale * kLog2e;
-    prm.head_split = p->head_split; prm.total_k = p->total_k;
+    prm.total_k = p->total_k;
     prm.n_work_dq = grid_dq(p);
     prm.n_work_dkv = grid_dkv(p);
     {
@@ -1107,7 +1159,8 @@ hipError_t launch_bwd(const skrull_attn_plan_t *p, const void *q, const void *k,
         prm.queue_dq = (WorkQueue *)((char *)delta + rows);
         prm.queue_dkv = prm.queue_dq + 1;
         prm.dk_part = (float *)((char *)delta + rows + 256);
-        prm.dv_part = prm.dk_part + (size_t)p->head_split * p->total_k * p->Hkv * p->d;
+        const size_t part_rows = p->split_compact ? (size_t)p->n_split * p->BN : (size_t)p->total_k;
+        prm.dv_part = prm.dk_part + (size_t)p->split_parts * part_rows * p->Hkv * p->d;
     }
     if (p->d == 128) return launch_d<128>(p, prm, st, ev);
     if (p->d == 64) return launch_d<64>(p, prm, st, ev);

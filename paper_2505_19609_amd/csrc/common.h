@@ -11,6 +11,8 @@ struct WorkQueue;
 // forward calls of one plan that may be in flight at once (each takes one queue slot in turn)
 #define SKRULL_FWD_QUEUE_SLOTS 64
 
+#define SKRULL_CHAIN_LIMITS 9
+
 // Device-resident descriptor + work lists of one micro-batch.
 struct skrull_attn_plan {
     int32_t K, NS, Hq, Hkv, d, BM, BN;  // K sequences, NS >= K query segments
@@ -19,6 +21,11 @@ struct skrull_attn_plan {
     int64_t pairs;
     int32_t head_split;  // workgroups that share the query heads of one KV group in dK/dV
     int32_t wg_query_rows;  // query rows per forward / dQ workgroup: 128 (4 wavefronts) or 256 (8)
+    // dK/dV items that several workgroups share (the first n_split of the sorted list), and how:
+    // an item of cost c takes min(split_parts, ceil(c * heads per group / split_chain)) of them
+    // (split_chain 0: split_parts).  n_whole_first more items are handed out before those.
+    int32_t n_split, n_whole_first, split_parts, split_chain;
+    int32_t split_compact;  // 1: partial sums hold the rows of split items only; 0: every row of K
     int device;
     // one allocation (descriptor arrays, then the two item lists); the pointers below index into it
     int32_t *pool;
@@ -36,9 +43,19 @@ struct PlanTotals {
     // cost (query blocks) of the dK/dV items, accumulated by the emit kernel
     unsigned long long dkv_cost_sum;
     int32_t dkv_cost_max;
+    // chains of dK/dV items (query blocks x heads of a group, walked one after another by a workgroup
+    // that has the item to itself): how many exceed exactly the first k of dkv_chain_limit()
+    int32_t chain_base, chain_hist[SKRULL_CHAIN_LIMITS + 1];
     int32_t cap_fwd, cap_dkv;  // room in the item arrays (the host's upper bounds)
     int32_t block_n;           // key rows per dK/dV item in effect (the ranges kernel's choice where open)
 };
+
+// The k-th of the limits that a dK/dV item's chain is compared with: `base` times 2^((k - 2) / 2).
+__host__ __device__ inline int64_t dkv_chain_limit(int32_t base, int k)
+{
+    const int32_t c = (k & 1) ? 181 : 128;  // 256 / sqrt(2), 256 / 2
+    return ((int64_t)base * c << (k >> 1)) >> 8;
+}
 
 // Opt-in per-workgroup trace (measurement aid): one record per work item of a launch.
 struct WgTrace {
@@ -86,7 +103,7 @@ hipError_t launch_plan_ranges(const int32_t *S, const int32_t *N, const int32_t 
 hipError_t launch_plan_items(const skrull_attn_plan_t *p, const int32_t *fwd_off,
                              const int32_t *dkv_off, int32_t cap_fwd, int32_t cap_dkv,
                              int32_t *scratch_fwd, int32_t *scratch_dkv, int32_t *radix_hist,
-                             int32_t cost_bound, PlanTotals *totals, hipStream_t st);
+                             int32_t cost_bound, int32_t compute_units, PlanTotals *totals, hipStream_t st);
 int64_t plan_radix_ints(int32_t cap_fwd, int32_t cap_dkv, int32_t cost_bound);
 
 // fwd.hip / bwd.hip

@@ -203,6 +203,7 @@ __global__ __launch_bounds__(kScanThreads) void plan_ranges_kernel(
         totals->n_seg = (int32_t)base_s;
         totals->dkv_cost_sum = 0;
         totals->dkv_cost_max = 0;
+        for (int i = 0; i <= SKRULL_CHAIN_LIMITS; ++i) totals->chain_hist[i] = 0;
         totals->cap_fwd = cap_fwd;
         totals->cap_dkv = cap_dkv;
         totals->block_n = BN;
@@ -263,13 +264,32 @@ __global__ __launch_bounds__(256) void plan_emit_kernel(
     }
 }
 
+// Counts a dK/dV item of cost `cost` by the length of its chain of `group` heads.  The base of the
+// limits balances two losses: workgroups that share an item each pay its start, its end and its
+// partial sums (as much as one to two blocks' rounds), so short parts are dear, and units that are
+// long against an even share s of the whole list per compute unit balance badly.  The first loss
+// falls and the second grows with the length: sqrt(8 s), at least 2 blocks and, at head_dim 64, at
+// most 13.  Swept over 0.2 to 20 times that on 60 micro-batches of s = 0.2 to 580 blocks.
+__device__ inline void count_chain(int32_t cost, int32_t group, int32_t q_heads, int32_t head_dim,
+                                   int32_t compute_units, PlanTotals *totals)
+{
+    const float share = (float)totals->dkv_cost_sum * (float)q_heads / (float)compute_units;
+    const float best = fminf(sqrtf(8.0f * share), head_dim == 64 ? 13.0f : 1e6f);
+    const int32_t base = max(2, (int32_t)best);
+    const int64_t chain = (int64_t)cost * group;
+    int above = 0;
+    while (above < SKRULL_CHAIN_LIMITS && chain > dkv_chain_limit(base, above)) ++above;
+    atomicAdd(&totals->chain_hist[above], 1);
+    totals->chain_base = base;  // (the same from every thread)
+}
+
 // Stable sort by descending .w: item a goes to slot
 //   #{b : cost_b > cost_a} + #{b < a : cost_b == cost_a}.
 // Costs are streamed through LDS in tiles; every thread of a block walks the
 // same tile, so the reads are broadcasts.
-__global__ __launch_bounds__(256) void plan_sort_kernel(const int4 *__restrict__ in,
-                                                        const PlanTotals *__restrict__ totals,
-                                                        int which, int4 *__restrict__ out)
+__global__ __launch_bounds__(256) void plan_sort_kernel(const int4 *__restrict__ in, PlanTotals *totals,
+                                                        int which, int32_t group, int32_t q_heads,
+                                                        int32_t head_dim, int32_t compute_units, int4 *__restrict__ out)
 {
     __shared__ int32_t tile[1024];
     const int32_t n = which == 0 ? (int32_t)min((long long)totals->n_fwd, (long long)totals->cap_fwd)
@@ -288,7 +308,10 @@ __global__ __launch_bounds__(256) void plan_sort_kernel(const int4 *__restrict__
             rank += (cb > me.w) || (cb == me.w && b0 + i < a);
         }
     }
-    if (a < n) out[rank] = me;
+    if (a < n) {
+        out[rank] = me;
+        if (which == 1) count_chain(me.w, group, q_heads, head_dim, compute_units, totals);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -307,8 +330,9 @@ __device__ inline int32_t list_length(const PlanTotals *totals, int which)
                       : (int32_t)min((long long)totals->n_dkv, (long long)totals->cap_dkv);
 }
 
-__global__ __launch_bounds__(256) void radix_hist_kernel(const int4 *__restrict__ in,
-                                                         const PlanTotals *__restrict__ totals, int which,
+__global__ __launch_bounds__(256) void radix_hist_kernel(const int4 *__restrict__ in, PlanTotals *totals, int which,
+                                                         int32_t group, int32_t q_heads, int32_t head_dim,
+                                                         int32_t compute_units,
                                                          int32_t key_max, int shift, int32_t nb,
                                                          int32_t *__restrict__ hist)
 {
@@ -318,7 +342,11 @@ __global__ __launch_bounds__(256) void radix_hist_kernel(const int4 *__restrict_
     __syncthreads();
     const int32_t base = blockIdx.x * kRadixBlock;
     for (int32_t i = threadIdx.x; i < kRadixBlock; i += 256)
-        if (base + i < n) atomicAdd(&h[((key_max - in[base + i].w) >> shift) & 255], 1);
+        if (base + i < n) {
+            const int32_t cost = in[base + i].w;
+            atomicAdd(&h[((key_max - cost) >> shift) & 255], 1);
+            if (which == 1 && shift == 0) count_chain(cost, group, q_heads, head_dim, compute_units, totals);
+        }
     __syncthreads();
     hist[threadIdx.x * nb + blockIdx.x] = h[threadIdx.x];
 }
@@ -410,12 +438,13 @@ int64_t plan_radix_ints(int32_t cap_fwd, int32_t cap_dkv, int32_t cost_bound)
 
 // Sort one list.  `a` holds the emitted items when the number of passes is odd (or zero), `b`
 // when it is even, so that the last pass (or the rank sort) always writes the plan's array `b`.
-static hipError_t sort_list(int which, int32_t cap, int32_t cost_bound, int4 *a, int4 *b, int32_t *hist,
-                            PlanTotals *totals, hipStream_t st)
+static hipError_t sort_list(const skrull_attn_plan_t *p, int which, int32_t cap, int32_t cost_bound,
+                            int32_t compute_units, int4 *a, int4 *b, int32_t *hist, PlanTotals *totals, hipStream_t st)
 {
+    const int32_t group = p->Hq / p->Hkv;
     const int passes = plan_radix_passes(cap, cost_bound);
     if (passes == 0) {
-        plan_sort_kernel<<<(cap + 255) / 256, 256, 0, st>>>(a, totals, which, b);
+        plan_sort_kernel<<<(cap + 255) / 256, 256, 0, st>>>(a, totals, which, group, p->Hq, p->d, compute_units, b);
         return hipGetLastError();
     }
     int key_bits = 8 * passes;
@@ -423,7 +452,7 @@ static hipError_t sort_list(int which, int32_t cap, int32_t cost_bound, int4 *a,
     const int32_t nb = (cap + kRadixBlock - 1) / kRadixBlock;
     int4 *src = (passes & 1) ? a : b, *dst = (passes & 1) ? b : a;
     for (int pass = 0; pass < passes; ++pass) {
-        radix_hist_kernel<<<nb, 256, 0, st>>>(src, totals, which, key_max, 8 * pass, nb, hist);
+        radix_hist_kernel<<<nb, 256, 0, st>>>(src, totals, which, group, p->Hq, p->d, compute_units, key_max, 8 * pass, nb, hist);
         radix_scan_kernel<<<1, 256, 0, st>>>(hist, nb);
         radix_scatter_kernel<<<nb, 256, 0, st>>>(src, totals, which, key_max, 8 * pass, nb, hist, dst);
         hipError_t e = hipGetLastError();
@@ -436,7 +465,7 @@ static hipError_t sort_list(int which, int32_t cap, int32_t cost_bound, int4 *a,
 hipError_t launch_plan_items(const skrull_attn_plan_t *p, const int32_t *fwd_off,
                              const int32_t *dkv_off, int32_t cap_fwd, int32_t cap_dkv,
                              int32_t *scratch_fwd, int32_t *scratch_dkv, int32_t *radix_hist,
-                             int32_t cost_bound, PlanTotals *totals, hipStream_t st)
+                             int32_t cost_bound, int32_t compute_units, PlanTotals *totals, hipStream_t st)
 {
     // grids are sized by the host's upper bounds of the item counts; the kernels take the
     // counts from `totals` on the device, so no round trip to the host is needed in between
@@ -451,7 +480,7 @@ hipError_t launch_plan_items(const skrull_attn_plan_t *p, const int32_t *fwd_off
     if (e != hipSuccess) return e;
     int32_t *hist_dkv = radix_hist;
     if (plan_radix_passes(cap_fwd, cost_bound)) hist_dkv += 256 * (int64_t)((cap_fwd + kRadixBlock - 1) / kRadixBlock);
-    e = sort_list(0, cap_fwd, cost_bound, (int4 *)scratch_fwd, (int4 *)p->fwd_items, radix_hist, totals, st);
+    e = sort_list(p, 0, cap_fwd, cost_bound, compute_units, (int4 *)scratch_fwd, (int4 *)p->fwd_items, radix_hist, totals, st);
     if (e != hipSuccess) return e;
-    return sort_list(1, cap_dkv, cost_bound, (int4 *)scratch_dkv, (int4 *)p->dkv_items, hist_dkv, totals, st);
+    return sort_list(p, 1, cap_dkv, cost_bound, compute_units, (int4 *)scratch_dkv, (int4 *)p->dkv_items, hist_dkv, totals, st);
 }

@@ -896,3 +896,44 @@ def test_row_blocks_of_a_group_in_both_orders(oracle, heads, d, wg, bm):
     assert np.array_equal(out["lse"], np.concatenate([one["lse"]] * rep, axis=1))
     out["plan"].destroy()
     one["plan"].destroy()
+
+
+SHARED = {  # lengths, degrees, indices, cuts, heads, head_dim, block_n, what the plan does
+    "one head per group": ([2967], [1], [0], [0], (4, 4), 64, 0, "compact"),
+    "short blocks": ([1100, 37, 700], [1] * 3, [0] * 3, [0] * 3, (3, 3), 128, 64, "compact"),
+    "two passes per block": ([1500, 129, 64], [1] * 3, [0] * 3, [0] * 3, (2, 2), 128, 256, "compact"),
+    "two chunks": ([5200, 333], [2, 1], [1, 0], [1, 0], (3, 3), 64, 0, "compact"),
+    "seven heads, ratio under 1.5": ([1700] + [300] * 60, [1] * 61, [0] * 61, [0] * 61, (28, 4), 128, 0, "compact"),
+    "some items": ([1700] + [300] * 30, [1] * 31, [0] * 31, [0] * 31, (28, 4), 128, 0, "some"),
+    "some items of 192 keys": ([1700] + [300] * 60, [1] * 61, [0] * 61, [0] * 61, (14, 2), 64, 0, "some"),
+    "all items": ([2048, 100], [1] * 2, [0] * 2, [0] * 2, (14, 2), 64, 0, "all"),
+}
+
+
+@pytest.mark.parametrize("name", sorted(SHARED))
+def test_long_dkv_items_are_shared_out(oracle, name):
+    """dK/dV items with a long chain are walked by several workgroups (pieces of the walk where the
+    heads do not divide), the others by one; outputs and workspace stay inside their tensors."""
+    from paper_2505_19609_amd import binding as B
+    S, N, R, Z, heads, d, bn, what = SHARED[name]
+    w = W.Workload("shared", S, N, R, heads[0], heads[1], d, d ** -0.5, 505, shard_cut=Z)
+    out = run_library(w, block_n=bn, guard=True)
+    assert out["margins"] == []
+    info = out["plan"].info
+    units = B.skrull_attn_trace_layout(out["plan"])[1][2]
+    wide = 192 if d == 64 and info.block_n == 192 else 128
+    whole = info.n_dkv_items * heads[1] * -(-info.block_n // wide)      # one workgroup per pass and KV head
+    base = (heads[0] * info.total_q * 8 + 255) // 256 * 256 + 256
+    if what == "compact":
+        assert info.head_split == 1 and units > whole and base < info.bwd_workspace_bytes <= B.STATIC_SCRATCH_BYTES
+    else:
+        assert info.head_split > 1 and (whole < units < whole * info.head_split if what == "some"
+                                        else units == whole * info.head_split)
+    f = widen(out["vals"])
+    desc = oracle.ranges(S, N, R, Z)
+    _, dK, dV, _ = oracle.attention_bwd(f["q"], f["k"], f["v"], f["do"], desc, w.softmax_scale)
+    _report("dK", out["dk"], dK, TOL_G)
+    # (a key that few rows see has |dV| above 8, where half a bf16 spacing is 2^-8 of the value: the
+    # output's own rounding beside the stated bound)
+    _report("dV", out["dv"], dV, TOL_G, rtol=2.0 ** -8)
+    out["plan"].destroy()
