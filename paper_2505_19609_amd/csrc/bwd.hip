@@ -65,6 +65,7 @@ struct BwdParams {
     WgTrace *trace_dq, *trace_dkv;  // null, or one record per work item (measurement aid)
     WorkQueue *queue_dq, *queue_dkv;  // work queues of the persistent launches (workspace), zeroed before use
     int32_t n_work_dq, n_work_dkv;    // work items: what a plain grid would have as workgroups
+    int32_t n_first_dq;               // workgroups of the dQ launch
 };
 
 // ---------------------------------------------------------------------------
@@ -436,7 +437,7 @@ template <int D, int NWQ>
 __global__ __launch_bounds__(64 * NWQ, 2) void dq_kernel(const BwdParams prm)
 {
     __shared__ int work_slot;
-    WorkFeed feed{prm.queue_dq, prm.n_work_dq, 0, &work_slot};
+    WorkFeed feed{prm.queue_dq, prm.n_work_dq, D == 128 ? prm.n_first_dq : 0, 0, &work_slot};  // (by index: +0 to 4 % at 128, -0 to 2 % at 64)
     int w = feed.first();
     RowBlocks rb = row_blocks(kernarg<BwdParams>(), prm.fwd_items, max(w, 0));
     while (w >= 0) {
@@ -1007,7 +1008,7 @@ template <int D, int PAIRS>
 __global__ __launch_bounds__(128 * PAIRS, PAIRS == PAIRS_12W ? 3 : 2) void dkv_kernel(const BwdParams prm)
 {
     __shared__ int work_slot;
-    WorkFeed feed{prm.queue_dkv, prm.n_work_dkv, 0, &work_slot};
+    WorkFeed feed{prm.queue_dkv, prm.n_work_dkv, 0, 0, &work_slot};
     int w = feed.first();
     KeyBlock kb = key_block(kernarg<BwdParams>(), 32 * PAIRS, max(w, 0));
     while (w >= 0) {
@@ -1078,10 +1079,13 @@ hipError_t launch_pair(const skrull_attn_plan_t *p, BwdParams prm, int threads_q
         spread_parts(prm.rows);
     }
     if (!queued_kv) prm.queue_dkv = nullptr;
-    hipError_t e = launch_work<KernelQ>(threads_q, prm.n_work_dq, queued_q, prm, st);
+    prm.n_first_dq = launch_size<KernelQ>(threads_q, prm.n_work_dq, queued_q);
+    KernelQ<<<prm.n_first_dq, threads_q, 0, st>>>(prm);
+    hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (ev) (void)hipEventRecord(ev[1], st);
-    e = launch_work<KernelKV>(threads_kv, prm.n_work_dkv, queued_kv, prm, st);
+    KernelKV<<<launch_size<KernelKV>(threads_kv, prm.n_work_dkv, queued_kv), threads_kv, 0, st>>>(prm);
+    e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (p->n_split > 0) {
         const dim3 grid((unsigned)p->n_split * p->Hkv, (unsigned)(p->BN + REDUCE_ROWS - 1) / REDUCE_ROWS, 2);

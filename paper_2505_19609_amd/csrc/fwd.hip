@@ -52,7 +52,7 @@ struct FwdParams {
     float scale_log2;  // softmax_scale * log2(e)
     WgTrace *trace;    // null, or one record per work item (measurement aid)
     WorkQueue *queue;  // work queue of the persistent launch, zeroed before use
-    int32_t n_work;    // work items: what a plain grid would have as workgroups
+    int32_t n_work, n_first;  // work items: what a plain grid would have as workgroups; workgroups launched
 };
 
 // Two shapes of the one kernel.  Large: 8 wavefronts = 8 row blocks per workgroup and
@@ -481,9 +481,9 @@ template <int D, int NW, int NSLOT>
 __global__ __launch_bounds__(64 * NW, 2) void fwd_kernel(const FwdParams prm)
 {
     __shared__ int work_slot;
-    WorkFeed feed{prm.queue, prm.n_work, 0, &work_slot};
+    WorkFeed feed{prm.queue, prm.n_work, prm.n_first, 0, &work_slot};
     int w = feed.first();
-    RowBlocks rb = row_blocks(kernarg<FwdParams>(), prm.items, max(w, 0));
+    RowBlocks rb = row_blocks(kernarg<FwdParams>(), prm.items, w);
     while (w >= 0) {
         if (rb.has(0)) {
             w = fwd_work<D, NW, NSLOT>(w, rb, feed);
@@ -506,7 +506,9 @@ hipError_t launch_shape(FwdParams prm, int threads, hipStream_t st)
         prm.queue = nullptr;
         spread_parts(prm.rows);
     }
-    return launch_work<Kernel>(threads, prm.n_work, queued, prm, st);
+    prm.n_first = launch_size<Kernel>(threads, prm.n_work, queued);
+    Kernel<<<prm.n_first, threads, 0, st>>>(prm);
+    return hipGetLastError();
 }
 
 template <int D>

@@ -5,10 +5,10 @@
 // at one speed (on the measured parts the same list of work items took one die 6 % longer
 // than another), so a grid with one workgroup per work item ends with the fast dies idle for
 // the last 3-5 % of the launch.  Here a launch instead starts as many workgroups as the chip
-// holds at once, and each takes work items until none is left: first from its own die's
-// queue (work items w = die, die + 8, die + 16, ... in list order, which keeps the heads of
-// one KV group on one die and its L2, as the static mapping did), then from the queue with
-// the most items left.  The work lists are sorted by descending cost, so what is stolen at
+// holds at once, and each takes work items until none is left: the one of its block index,
+// then from its own die's queue (work items w = die, die + 8, die + 16, ... in list order,
+// which keeps the heads of one KV group on one die and its L2, as the static mapping did),
+// then from the queue with the most items left.  The work lists are sorted by descending cost, so what is stolen at
 // the end are the smallest items: the paper's rule (Alg. 1: the next piece goes to argmin of
 // the loads) applied across dies at run time, since their speeds are not known beforehand.
 #pragma once
@@ -17,7 +17,7 @@
 #include <stdint.h>
 
 struct WorkQueue {
-    int32_t next[8];  // per die: how many of its work items have been handed out
+    int32_t next[8];  // per die: how many of its work items have been handed out (but the first ones)
     int32_t pad[8];
 };
 
@@ -50,24 +50,28 @@ template <typename S> __device__ __forceinline__ S uniform(const S &s)
     return __builtin_bit_cast(S, w);
 }
 
-// The work item that count `k` of die `xcd`'s queue stands for; when that queue is used up, the
+// The work item that count `k` of die `xcd`'s queue stands for (a queue starts behind the items that
+// the launch's workgroups took by their block index); when that queue is used up, the
 // next item of the queue with the most items left; -1 when every queue is empty.  Called by
 // one lane.  Counters are device-scope atomics (the dies' L2 caches are not coherent with
 // each other for plain accesses).
-__device__ __forceinline__ int claimed_work(WorkQueue *q, int n_work, int xcd, int k)
+__device__ __forceinline__ int claimed_work(WorkQueue *q, int n_work, int n_first, int xcd, int k)
 {
-    if (8 * k + xcd < n_work) return 8 * k + xcd;
+    const int w = 8 * (k + (n_first - xcd + 7) / 8) + xcd;
+    if (w < n_work) return w;
     for (;;) {
         // the queue with the most items left
         int best = -1, best_left = 0;
         for (int y = 0; y < 8; ++y) {
             const int ky = __hip_atomic_load(&q->next[y], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const int left = (n_work - y + 7) / 8 - ky;  // items of queue y: ceil((n_work - y) / 8)
+            // items of queue y: ceil((n_work - y) / 8), without the first ones
+            const int left = (n_work - y + 7) / 8 - (n_first - y + 7) / 8 - ky;
             if (left > best_left) { best_left = left; best = y; }
         }
         if (best < 0) return -1;
         k = __hip_atomic_fetch_add(&q->next[best], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (8 * k + best < n_work) return 8 * k + best;
+        const int v = 8 * (k + (n_first - best + 7) / 8) + best;
+        if (v < n_work) return v;
         // someone else took its last item in between: look again (every failed attempt
         // means a queue has run empty, so this ends after at most eight rounds)
     }
@@ -84,15 +88,21 @@ __device__ __forceinline__ int my_xcd() { return __builtin_amdgcn_readfirstlane(
 // descriptor between two items, a workgroup stood still for 3 to 3.5 us per item (a quarter
 // of the forward of 64 short sequences, 14/2 heads of 64).  Asked for near the END of an item,
 // so that what a workgroup holds back from the others is at most about to start.
+// With `by_index` the first item is the one of the block index.  Blocks go to the compute units of a
+// die in turn, so the workgroups that share a unit start with items a third or half of the first
+// round apart; with items claimed in order of arrival a unit could start with three of the longest
+// (30,934 tokens in 3 sequences, 4/4 heads of 64: forward 0.64 ms claimed, 0.48 by index).  Where a
+// unit holds one workgroup and the items are alike, the order of arrival staggers them a little, and
+// they run faster than in step (dK/dV, 27 sequences, 20,011 tokens, 32/8 heads of 128: 3 %).
 // `slot` is one int of LDS; the caller has a barrier between a `take` and the next `post`.
 struct WorkFeed {
     WorkQueue *q;
-    int n_work, pending;
+    int n_work, n_first, pending;  // items; how many are taken by block index (the workgroups of the launch, or none)
     int *slot;
 
     __device__ __forceinline__ int first()
     {
-        if (!q) return (int)blockIdx.x;
+        if (n_first > 0 || !q) return (int)blockIdx.x;
         return again();
     }
     __device__ __forceinline__ void ask()
@@ -108,7 +118,7 @@ struct WorkFeed {
     }
     __device__ __forceinline__ void post()
     {
-        if (q && threadIdx.x == 0) *slot = claimed_work(q, n_work, my_xcd(), pending);
+        if (q && threadIdx.x == 0) *slot = claimed_work(q, n_work, n_first, my_xcd(), pending);
     }
     __device__ __forceinline__ int take() const { return q ? __builtin_amdgcn_readfirstlane(*slot) : -1; }
     // all of it at once, for a workgroup that has no work to hide it behind
@@ -163,12 +173,6 @@ static bool wants_queue(int threads, int n_work)
 }
 
 // Persistent launch when `queued` (as many workgroups as fit the chip at once, each taking work
-// items from the queue in `prm` until none is left), else a plain grid of one workgroup per item
-// (`prm` then carries no queue).
-template <auto Kernel, typename P>
-static hipError_t launch_work(int threads, int n_work, bool queued, const P &prm, hipStream_t st)
-{
-    const int grid = queued ? resident_of<Kernel>(threads) : n_work;
-    Kernel<<<grid, threads, 0, st>>>(prm);
-    return hipGetLastError();
-}
+// items until none is left), else a plain grid of one workgroup per item (`prm` then carries no queue).
+template <auto Kernel>
+static int launch_size(int threads, int n_work, bool queued) { return queued ? resident_of<Kernel>(threads) : n_work; }
