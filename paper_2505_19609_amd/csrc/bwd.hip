@@ -443,6 +443,10 @@ __global__ __launch_bounds__(64 * NWQ, 2) void dq_kernel(const BwdParams prm)
     while (w >= 0) {
         if (rb.has(0)) {
             w = dq_work<D, NWQ>(w, rb, feed);
+            if (w == kQueueEmpty) {
+                w = feed.other();
+                rb = row_blocks(kernarg<BwdParams>(), prm.fwd_items, max(w, 0));
+            }
         } else {  // the item is too short for this part (the whole workgroup agrees)
             w = feed.again();
             rb = row_blocks(kernarg<BwdParams>(), prm.fwd_items, max(w, 0));
@@ -1014,6 +1018,10 @@ __global__ __launch_bounds__(128 * PAIRS, PAIRS == PAIRS_12W ? 3 : 2) void dkv_k
     while (w >= 0) {
         if (kb.item_rows > 0) {
             w = dkv_work<D, PAIRS>(w, kb, feed);
+            if (w == kQueueEmpty) {
+                w = feed.other();
+                kb = key_block(kernarg<BwdParams>(), 32 * PAIRS, max(w, 0));
+            }
         } else {  // the item has no second pass (the whole workgroup agrees)
             w = feed.again();
             kb = key_block(kernarg<BwdParams>(), 32 * PAIRS, max(w, 0));

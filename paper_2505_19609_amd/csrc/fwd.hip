@@ -487,6 +487,10 @@ __global__ __launch_bounds__(64 * NW, 2) void fwd_kernel(const FwdParams prm)
     while (w >= 0) {
         if (rb.has(0)) {
             w = fwd_work<D, NW, NSLOT>(w, rb, feed);
+            if (w == kQueueEmpty) {
+                w = feed.other();
+                rb = row_blocks(kernarg<FwdParams>(), prm.items, max(w, 0));
+            }
         } else {  // the item is too short for this part (the whole workgroup agrees)
             w = feed.again();
             rb = row_blocks(kernarg<FwdParams>(), prm.items, max(w, 0));

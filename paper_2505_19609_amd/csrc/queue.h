@@ -51,16 +51,20 @@ template <typename S> __device__ __forceinline__ S uniform(const S &s)
 }
 
 // The work item that count `k` of die `xcd`'s queue stands for (a queue starts behind the items that
-// the launch's workgroups took by their block index); when that queue is used up, the
-// next item of the queue with the most items left; -1 when every queue is empty.  Called by
-// one lane.  Counters are device-scope atomics (the dies' L2 caches are not coherent with
-// each other for plain accesses).
-__device__ __forceinline__ int claimed_work(WorkQueue *q, int n_work, int n_first, int xcd, int k)
+// the launch's workgroups took by their block index), or kQueueEmpty.
+constexpr int kNoWork = -1, kQueueEmpty = -2;
+__device__ __forceinline__ int queued_work(int n_work, int n_first, int xcd, int k)
 {
     const int w = 8 * (k + (n_first - xcd + 7) / 8) + xcd;
-    if (w < n_work) return w;
+    return w < n_work ? w : kQueueEmpty;
+}
+
+// The next item of the queue with the most items left; kNoWork when every queue is empty.  Called by
+// one lane.  Counters are device-scope atomics (the dies' L2 caches are not coherent with
+// each other for plain accesses).
+__device__ __forceinline__ int stolen_work(WorkQueue *q, int n_work, int n_first)
+{
     for (;;) {
-        // the queue with the most items left
         int best = -1, best_left = 0;
         for (int y = 0; y < 8; ++y) {
             const int ky = __hip_atomic_load(&q->next[y], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -68,10 +72,10 @@ __device__ __forceinline__ int claimed_work(WorkQueue *q, int n_work, int n_firs
             const int left = (n_work - y + 7) / 8 - (n_first - y + 7) / 8 - ky;
             if (left > best_left) { best_left = left; best = y; }
         }
-        if (best < 0) return -1;
-        k = __hip_atomic_fetch_add(&q->next[best], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const int v = 8 * (k + (n_first - best + 7) / 8) + best;
-        if (v < n_work) return v;
+        if (best < 0) return kNoWork;
+        const int k = __hip_atomic_fetch_add(&q->next[best], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int w = queued_work(n_work, n_first, best, k);
+        if (w >= 0) return w;
         // someone else took its last item in between: look again (every failed attempt
         // means a queue has run empty, so this ends after at most eight rounds)
     }
@@ -80,14 +84,18 @@ __device__ __forceinline__ int claimed_work(WorkQueue *q, int n_work, int n_firs
 // Die this wave runs on (XCC_ID register, bits 0-3).
 __device__ __forceinline__ int my_xcd() { return __builtin_amdgcn_readfirstlane(__builtin_amdgcn_s_getreg((31 << 11) | 20) & 7); }
 
-// The work of a persistent workgroup: one item after another until `take` returns -1.  Without a
+// The work of a persistent workgroup: one item after another until there is none (kNoWork).  Without a
 // queue (q == nullptr) the workgroup does the one item of its block index, as in a plain grid.
 // The next item is asked for while the current one still computes: `ask` (one lane sends the
 // atomic), `post` (that lane leaves the answer in LDS), a barrier of the caller's, `take`
 // (every wave reads it) -- with the claim, its two barriers and the loads of the item's
 // descriptor between two items, a workgroup stood still for 3 to 3.5 us per item (a quarter
 // of the forward of 64 short sequences, 14/2 heads of 64).  Asked for near the END of an item,
-// so that what a workgroup holds back from the others is at most about to start.
+// so that what a workgroup holds back from the others is at most about to start.  `take` says
+// kQueueEmpty when the die's own queue is used up: the search of the others (`other`) is left until
+// the item's results are stored, because at the end of a launch, when most workgroups search at
+// once, it takes up to 20 us and held back the last stores (114 sequences of about 250 tokens, 32/8
+// heads of 128: the last items of the forward took 27 us instead of 7).
 // With `by_index` the first item is the one of the block index.  Blocks go to the compute units of a
 // die in turn, so the workgroups that share a unit start with items a third or half of the first
 // round apart; with items claimed in order of arrival a unit could start with three of the longest
@@ -118,18 +126,27 @@ struct WorkFeed {
     }
     __device__ __forceinline__ void post()
     {
-        if (q && threadIdx.x == 0) *slot = claimed_work(q, n_work, n_first, my_xcd(), pending);
+        if (q && threadIdx.x == 0) *slot = queued_work(n_work, n_first, my_xcd(), pending);
     }
-    __device__ __forceinline__ int take() const { return q ? __builtin_amdgcn_readfirstlane(*slot) : -1; }
+    __device__ __forceinline__ int take() const { return q ? __builtin_amdgcn_readfirstlane(*slot) : kNoWork; }
+    // after kQueueEmpty: an item of another die's queue
+    __device__ __forceinline__ int other()
+    {
+        __syncthreads();  // everyone has read the slot
+        if (threadIdx.x == 0) *slot = stolen_work(q, n_work, n_first);
+        __syncthreads();
+        return take();
+    }
     // all of it at once, for a workgroup that has no work to hide it behind
     __device__ __forceinline__ int again()
     {
-        if (!q) return -1;
+        if (!q) return kNoWork;
         __syncthreads();  // everyone has read the slot
         ask();
         post();
         __syncthreads();
-        return take();
+        const int w = take();
+        return w == kQueueEmpty ? other() : w;
     }
 };
 
