@@ -133,10 +133,15 @@ def _check(rc: int):
 
 
 def _stream_ptr(stream):
+    """The hipStream_t of `stream`, or of torch's current one, as an integer.  (The current stream is asked
+    for as a raw pointer: torch.cuda.current_stream() builds a Stream object, 3 us of the 7 that a
+    forward call cost the host.)"""
     if stream is None:
         import torch
+        if torch.cuda.is_initialized():
+            return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
         stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(int(getattr(stream, "cuda_stream", stream)))
+    return int(getattr(stream, "cuda_stream", stream))
 
 
 class Plan:
@@ -176,7 +181,7 @@ def skrull_attn_plan(seq_len, shard_degree, shard_index, num_q_heads, num_kv_hea
                    float(softmax_scale), block_m, block_n,
                    None if Z is None else Z.ctypes.data_as(i32p), int(head_split), int(wg_query_rows))
     handle = ctypes.c_void_p()
-    st = ctypes.c_void_p(raw_stream) if raw_stream is not None else _stream_ptr(stream)
+    st = raw_stream if raw_stream is not None else _stream_ptr(stream)
     _check(lib().skrull_attn_plan(ctypes.byref(prob), st, ctypes.byref(handle)))
     info = PlanInfo()
     _check(lib().skrull_attn_plan_info(handle, ctypes.byref(info)))
@@ -201,7 +206,7 @@ def skrull_attn_plan_export(plan: Plan, which: int) -> np.ndarray:
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()   # (the argument types say that it is a pointer)
 
 
 def skrull_attn_fwd(plan: Plan, q, k, v, o, lse, stream=None):
