@@ -45,6 +45,20 @@ __device__ inline int64_t block_exclusive_scan(int64_t v, int64_t *lds, int64_t 
     return before + incl - v;
 }
 
+// Block-wide maximum of one non-negative int64 per thread, in every thread.
+__device__ inline int64_t block_max(int64_t v, int64_t *lds)
+{
+    for (int off = 32; off > 0; off >>= 1) {
+        const int64_t o = __shfl_xor(v, off, 64);
+        v = o > v ? o : v;
+    }
+    if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = v;
+    __syncthreads();
+    for (int w = 0; w < kScanThreads / 64; ++w) v = lds[w] > v ? lds[w] : v;
+    __syncthreads();  // lds may be reused
+    return v;
+}
+
 __device__ inline int64_t ceil_div64(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // One thread per sequence.  A sequence cut the contiguous way is one query
@@ -78,26 +92,30 @@ __global__ __launch_bounds__(kScanThreads) void plan_ranges_kernel(
     // uniform and ragged lengths) but balance worse: with few items and a costliest one between
     // 0.7 and 1.0 of the even share, ragged micro-batches lost 4-15 % by them.
     if (bn_alt != 0) {
+        // (BM is a power of two and positions fit 32 bits: divided in 64 bits, this walk over the blocks
+        // of one 3,629-token sequence was most of the 16 us that the kernel took; now 11)
         int64_t c_sum = 0, c_max = 0, n_alt = 0, longest = 0;
+        const int log_bm = __ffs(BM) - 1;
         for (int32_t k = t; k < K; k += kScanThreads) {
             const int64_t s = S[k], n = N[k], r = R[k], z = Z[k];
             const int64_t chunks = n * (z ? 2 : 1);
             if (s < 1 || n < 1 || r < 0 || r >= n || (z != 0 && z != 1) || chunks > s) continue;
             const int64_t idx[2] = {r, 2 * n - 1 - r};
             const int nseg = (int)z + 1;
-            int64_t qb[2], qe[2];
+            int32_t qb[2] = {0, 0}, qe[2] = {0, 0};
             for (int part = 0; part < nseg; ++part) {
-                qb[part] = (idx[part] * s) / chunks;
-                qe[part] = ((idx[part] + 1) * s) / chunks;
+                qb[part] = chunks == 1 ? 0 : (int32_t)((idx[part] * s) / chunks);
+                qe[part] = chunks == 1 ? (int32_t)s : (int32_t)(((idx[part] + 1) * s) / chunks);
             }
-            n_alt += ceil_div64(qe[nseg - 1], bn_alt);
-            longest = qe[nseg - 1] > longest ? qe[nseg - 1] : longest;
-            for (int64_t j0 = 0; j0 < qe[nseg - 1]; j0 += BN) {
-                int64_t cost = 0;
+            const int32_t end = qe[nseg - 1];
+            n_alt += (uint32_t)(end + bn_alt - 1) / (uint32_t)bn_alt;
+            longest = end > longest ? end : longest;
+            for (int64_t j0 = 0; j0 < end; j0 += BN) {
+                int32_t cost = 0;
                 for (int part = 0; part < nseg; ++part) {
                     if (j0 >= qe[part]) continue;
-                    const int64_t i0 = j0 > qb[part] ? j0 - qb[part] : 0;
-                    cost += ceil_div64(qe[part] - qb[part], BM) - i0 / BM;
+                    const int32_t i0 = j0 > qb[part] ? (int32_t)j0 - qb[part] : 0;
+                    cost += ((qe[part] - qb[part] - 1) >> log_bm) + 1 - (i0 >> log_bm);
                 }
                 c_sum += cost;
                 c_max = cost > c_max ? cost : c_max;
@@ -106,25 +124,10 @@ __global__ __launch_bounds__(kScanThreads) void plan_ranges_kernel(
         int64_t tot;
         block_exclusive_scan(c_sum, lds, &tot);
         c_sum = tot;
-        // maximum over the block through the same LDS array
-        lds[t] = c_max;
-        __syncthreads();
-        for (int off = kScanThreads / 2; off > 0; off >>= 1) {
-            if (t < off && lds[t + off] > lds[t]) lds[t] = lds[t + off];
-            __syncthreads();
-        }
-        c_max = lds[0];
-        __syncthreads();
+        c_max = block_max(c_max, lds);
         block_exclusive_scan(n_alt, lds, &tot);
         n_alt = tot;
-        lds[t] = longest;
-        __syncthreads();
-        for (int off = kScanThreads / 2; off > 0; off >>= 1) {
-            if (t < off && lds[t + off] > lds[t]) lds[t] = lds[t + off];
-            __syncthreads();
-        }
-        longest = lds[0];
-        __syncthreads();
+        longest = block_max(longest, lds);
         const bool long_list = n_alt * kv_heads >= 5 * (int64_t)compute_units;
         const bool even_list = 10 * c_max * compute_units <= 7 * c_sum * kv_heads;
         if (c_max * compute_units > c_sum * kv_heads ||
@@ -210,6 +213,10 @@ __global__ __launch_bounds__(kScanThreads) void plan_ranges_kernel(
     }
 }
 
+// Offsets of up to this many segments are searched in LDS: a search in memory is a chain of
+// log2(K) loads, half of the emit kernel's time for a few dozen sequences.
+constexpr int32_t kEmitSegments = 1024;
+
 // Largest k with off[k] <= item (off is an exclusive scan with off[K] = n).
 __device__ inline int32_t owner_of(const int32_t *off, int32_t K, int32_t item)
 {
@@ -235,28 +242,37 @@ __global__ __launch_bounds__(256) void plan_emit_kernel(
     const int32_t n_dkv = (int32_t)min((long long)totals->n_dkv, (long long)totals->cap_dkv);
     const int32_t BN = totals->block_n;  // the ranges kernel's choice where the caller left it open
     const int32_t t = blockIdx.x * blockDim.x + threadIdx.x;
+    __shared__ int32_t off_f[kEmitSegments + 1], off_d[kEmitSegments + 1];
+    if (K <= kEmitSegments) {
+        for (int32_t i = threadIdx.x; i <= K; i += blockDim.x) {
+            off_f[i] = fwd_off[i];
+            off_d[i] = dkv_off[i];
+        }
+        __syncthreads();
+    }
     if (t < n_fwd) {
-        const int32_t k = owner_of(fwd_off, K, t);
+        const int32_t k = K <= kEmitSegments ? owner_of(off_f, K, t) : owner_of(fwd_off, K, t);
         const int32_t m = t - fwd_off[k];
         const int64_t row0 = (int64_t)m * BM;
         const int64_t left = q_len[k] - row0;
         const int64_t rows = left < BM ? left : BM;
         fwd_items[t] = make_int4(k, m, (int32_t)(cu_q[k] + row0),
-                                 (int32_t)ceil_div64((int64_t)q_begin[k] + row0 + rows, BN));
+                                 (int32_t)((uint32_t)(q_begin[k] + row0 + rows + BN - 1) / (uint32_t)BN));  // (below 2^31 + 256)
     }
     if (t < n_dkv) {
         // equal offsets (an early chunk and its partner) resolve to the later segment,
         // the one that owns the shared prefix
-        const int32_t k = owner_of(dkv_off, K, t);
+        const int32_t k = K <= kEmitSegments ? owner_of(off_d, K, t) : owner_of(dkv_off, K, t);
         const int32_t b = t - dkv_off[k];
         int64_t i0 = (int64_t)b * BN - q_begin[k];
         if (i0 < 0) i0 = 0;
-        const int32_t m0 = (int32_t)(i0 / BM);
-        int32_t cost = (int32_t)ceil_div64(q_len[k], BM) - m0;
+        const int log_bm = __ffs(BM) - 1;  // a power of two
+        const int32_t m0 = (int32_t)(i0 >> log_bm);
+        int32_t cost = ((q_len[k] - 1) >> log_bm) + 1 - m0;
         if (shares_kv[k] && (int64_t)b * BN < kv_len[k - 1]) {  // query blocks of the early chunk
             int64_t j0 = (int64_t)b * BN - q_begin[k - 1];
             if (j0 < 0) j0 = 0;
-            cost += (int32_t)ceil_div64(q_len[k - 1], BM) - (int32_t)(j0 / BM);
+            cost += ((q_len[k - 1] - 1) >> log_bm) + 1 - (int32_t)(j0 >> log_bm);
         }
         dkv_items[t] = make_int4(k, b, m0, cost);
         atomicAdd(&totals->dkv_cost_sum, (unsigned long long)cost);
@@ -285,30 +301,48 @@ __device__ inline void count_chain(int32_t cost, int32_t group, int32_t q_heads,
 
 // Stable sort by descending .w: item a goes to slot
 //   #{b : cost_b > cost_a} + #{b < a : cost_b == cost_a}.
-// Costs are streamed through LDS in tiles; every thread of a block walks the
-// same tile, so the reads are broadcasts.
-__global__ __launch_bounds__(256) void plan_sort_kernel(const int4 *__restrict__ in, PlanTotals *totals,
-                                                        int which, int32_t group, int32_t q_heads,
-                                                        int32_t head_dim, int32_t compute_units, int4 *__restrict__ out)
+// Costs are streamed through LDS in tiles; four threads walk a tile for one item, four costs to a
+// read.  (One thread per item and one cost to a read, each waited for, took 12 us for 180 items and
+// 25 us for 310; both lists together now take 9 to 12.)  blockIdx.y: the list (0 forward / dQ, 1 dK/dV).
+constexpr int32_t kSortItems = 64;  // items of a block
+struct SortJob {
+    const int4 *in;
+    int4 *out;
+};
+__global__ __launch_bounds__(256) void plan_sort_kernel(SortJob fwd, SortJob dkv, int first_list, PlanTotals *totals,
+                                                        int32_t group, int32_t q_heads, int32_t head_dim,
+                                                        int32_t compute_units)
 {
-    __shared__ int32_t tile[1024];
+    __shared__ __align__(16) int32_t tile[1024];
+    const int which = first_list + blockIdx.y;
+    const int4 *__restrict__ in = which == 0 ? fwd.in : dkv.in;
+    int4 *__restrict__ out = which == 0 ? fwd.out : dkv.out;
     const int32_t n = which == 0 ? (int32_t)min((long long)totals->n_fwd, (long long)totals->cap_fwd)
                                  : (int32_t)min((long long)totals->n_dkv, (long long)totals->cap_dkv);
-    const int32_t a = blockIdx.x * blockDim.x + threadIdx.x;
+    const int32_t first = blockIdx.x * kSortItems;
+    if (first >= n) return;  // (the whole block)
+    const int32_t a = first + threadIdx.x / 4, quarter = threadIdx.x % 4;
     const int4 me = (a < n) ? in[a] : make_int4(0, 0, 0, 0);
     int32_t rank = 0;
     for (int32_t b0 = 0; b0 < n; b0 += 1024) {
         __syncthreads();
-        for (int32_t i = threadIdx.x; i < 1024; i += blockDim.x)
-            tile[i] = (b0 + i < n) ? in[b0 + i].w : -1;
-        __syncthreads();
         const int32_t lim = (n - b0 < 1024) ? n - b0 : 1024;
-        for (int32_t i = 0; i < lim; ++i) {
-            const int32_t cb = tile[i];
-            rank += (cb > me.w) || (cb == me.w && b0 + i < a);
+        for (int32_t i = threadIdx.x; i < ((lim + 15) & ~15); i += blockDim.x)
+            tile[i] = (i < lim) ? in[b0 + i].w : -1;  // (below every cost)
+        __syncthreads();
+        // cost_b > cost_a, or equal and earlier: cost_b >= cost_a + (b >= a)
+        const int32_t before = a - b0;
+        for (int32_t x = 4 * quarter; x < lim; x += 16) {
+            const int4 c = *(const int4 *)&tile[x];
+            rank += c.x >= me.w + (x >= before);
+            rank += c.y >= me.w + (x + 1 >= before);
+            rank += c.z >= me.w + (x + 2 >= before);
+            rank += c.w >= me.w + (x + 3 >= before);
         }
     }
-    if (a < n) {
+    rank += __shfl_xor(rank, 1, 64);
+    rank += __shfl_xor(rank, 2, 64);
+    if (a < n && quarter == 0) {
         out[rank] = me;
         if (which == 1) count_chain(me.w, group, q_heads, head_dim, compute_units, totals);
     }
@@ -436,17 +470,12 @@ int64_t plan_radix_ints(int32_t cap_fwd, int32_t cap_dkv, int32_t cost_bound)
     return n;
 }
 
-// Sort one list.  `a` holds the emitted items when the number of passes is odd (or zero), `b`
-// when it is even, so that the last pass (or the rank sort) always writes the plan's array `b`.
-static hipError_t sort_list(const skrull_attn_plan_t *p, int which, int32_t cap, int32_t cost_bound,
-                            int32_t compute_units, int4 *a, int4 *b, int32_t *hist, PlanTotals *totals, hipStream_t st)
+// Radix sort of one list.  `a` holds the emitted items when the number of passes is odd, `b`
+// when it is even, so that the last pass always writes the plan's array `b`.
+static hipError_t radix_sort_list(const skrull_attn_plan_t *p, int which, int32_t cap, int passes, int32_t compute_units,
+                                  int4 *a, int4 *b, int32_t *hist, PlanTotals *totals, hipStream_t st)
 {
     const int32_t group = p->Hq / p->Hkv;
-    const int passes = plan_radix_passes(cap, cost_bound);
-    if (passes == 0) {
-        plan_sort_kernel<<<(cap + 255) / 256, 256, 0, st>>>(a, totals, which, group, p->Hq, p->d, compute_units, b);
-        return hipGetLastError();
-    }
     int key_bits = 8 * passes;
     const int32_t key_max = key_bits >= 31 ? INT32_MAX : (1 << key_bits) - 1;  // >= any cost
     const int32_t nb = (cap + kRadixBlock - 1) / kRadixBlock;
@@ -471,16 +500,29 @@ hipError_t launch_plan_items(const skrull_attn_plan_t *p, const int32_t *fwd_off
     // counts from `totals` on the device, so no round trip to the host is needed in between
     const int32_t n = cap_fwd > cap_dkv ? cap_fwd : cap_dkv;
     // the emit kernel writes each list where its sort starts from
-    const bool fwd_even = plan_radix_passes(cap_fwd, cost_bound) != 0 && plan_radix_passes(cap_fwd, cost_bound) % 2 == 0;
-    const bool dkv_even = plan_radix_passes(cap_dkv, cost_bound) != 0 && plan_radix_passes(cap_dkv, cost_bound) % 2 == 0;
+    const int passes_f = plan_radix_passes(cap_fwd, cost_bound), passes_d = plan_radix_passes(cap_dkv, cost_bound);
+    const bool fwd_even = passes_f != 0 && passes_f % 2 == 0, dkv_even = passes_d != 0 && passes_d % 2 == 0;
     plan_emit_kernel<<<(n + 255) / 256, 256, 0, st>>>(
         p->NS, p->BM, p->q_begin, p->q_len, p->kv_len, p->cu_q, p->shares_kv, fwd_off, dkv_off,
         (int4 *)(fwd_even ? p->fwd_items : scratch_fwd), (int4 *)(dkv_even ? p->dkv_items : scratch_dkv), totals);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
+    // short lists by rank counting, both in one launch when both are short
+    if (passes_f == 0 || passes_d == 0) {
+        const int first = passes_f == 0 ? 0 : 1, lists = (passes_f == 0) + (passes_d == 0);
+        const int32_t most = passes_f == 0 && passes_d == 0 ? n : (passes_f == 0 ? cap_fwd : cap_dkv);
+        plan_sort_kernel<<<dim3((most + kSortItems - 1) / kSortItems, lists), 256, 0, st>>>(
+            SortJob{(const int4 *)scratch_fwd, (int4 *)p->fwd_items}, SortJob{(const int4 *)scratch_dkv, (int4 *)p->dkv_items},
+            first, totals, p->Hq / p->Hkv, p->Hq, p->d, compute_units);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
     int32_t *hist_dkv = radix_hist;
-    if (plan_radix_passes(cap_fwd, cost_bound)) hist_dkv += 256 * (int64_t)((cap_fwd + kRadixBlock - 1) / kRadixBlock);
-    e = sort_list(p, 0, cap_fwd, cost_bound, compute_units, (int4 *)scratch_fwd, (int4 *)p->fwd_items, radix_hist, totals, st);
-    if (e != hipSuccess) return e;
-    return sort_list(p, 1, cap_dkv, cost_bound, compute_units, (int4 *)scratch_dkv, (int4 *)p->dkv_items, hist_dkv, totals, st);
+    if (passes_f) hist_dkv += 256 * (int64_t)((cap_fwd + kRadixBlock - 1) / kRadixBlock);
+    if (passes_f) {
+        e = radix_sort_list(p, 0, cap_fwd, passes_f, compute_units, (int4 *)scratch_fwd, (int4 *)p->fwd_items, radix_hist, totals, st);
+        if (e != hipSuccess) return e;
+    }
+    if (passes_d) e = radix_sort_list(p, 1, cap_dkv, passes_d, compute_units, (int4 *)scratch_dkv, (int4 *)p->dkv_items, hist_dkv, totals, st);
+    return e;
 }
