@@ -263,6 +263,7 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
     const int64_t queue_ints = SKRULL_FWD_QUEUE_SLOTS * 16;  // 64-byte work queues of the forward launches
     int32_t *fwd_off = nullptr, *dkv_off = nullptr, *scratch = nullptr;
     PlanTotals *totals_d = nullptr;
+    int64_t unit_ints[2] = {0, 0};
 
     plan = new (std::nothrow) skrull_attn_plan_t();
     if (!plan) return SKRULL_ENOMEM;
@@ -278,7 +279,9 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
     if (p->shard_cut) memcpy(host_in + 3 * kin, p->shard_cut, (size_t)K * 4);
 
     HIP_TRY(hipMalloc((void **)&tmp, (size_t)tmp_ints * sizeof(int32_t)));
-    HIP_TRY(hipMalloc((void **)&plan->pool, (size_t)(queue_ints + desc_ints + 4 * (cap_fwd + cap_dkv)) * sizeof(int32_t)));
+    unit_ints[0] = plan_unit_ints(plan, (int32_t)cap_fwd, 0);
+    unit_ints[1] = plan_unit_ints(plan, (int32_t)cap_fwd, 1);
+    HIP_TRY(hipMalloc((void **)&plan->pool, (size_t)(queue_ints + desc_ints + 4 * (cap_fwd + cap_dkv) + unit_ints[0] + unit_ints[1]) * sizeof(int32_t)));
     plan->fwd_queues = (WorkQueue *)plan->pool;   // (zeroed by every forward call before its launch)
     plan->cu_q = plan->pool + queue_ints;
     plan->cu_k = plan->cu_q + kpad;
@@ -288,6 +291,10 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
     plan->shares_kv = plan->cu_q + 5 * kpad;
     plan->fwd_items = plan->cu_q + desc_ints;
     plan->dkv_items = plan->fwd_items + 4 * cap_fwd;
+    if (unit_ints[0] > 0) {
+        plan->units[0] = plan->dkv_items + 4 * cap_dkv;
+        plan->units[1] = plan->units[0] + unit_ints[0];
+    }
     fwd_off = tmp + 4 * kin;
     dkv_off = fwd_off + kpad;
     totals_d = (PlanTotals *)(dkv_off + kpad);
@@ -319,6 +326,8 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
     plan->n_fwd = (int32_t)totals.n_fwd;
     plan->n_dkv = (int32_t)totals.n_dkv;
     plan->pairs = totals.pairs;
+    plan->n_units[0] = totals.n_units[0];
+    plan->n_units[1] = totals.n_units[1];
     // dK/dV head split.  A workgroup of that kernel walks all query tiles of one key
     // block for every query head of the KV group, one after another; its longest chain
     // is cost_max * group.  Spread evenly, the whole list is cost_sum * group * Hkv over

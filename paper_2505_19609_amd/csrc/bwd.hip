@@ -420,7 +420,7 @@ __device__ __forceinline__ int dq_work(const int bid, RowBlocks &rb, WorkFeed &f
     st.init(li);
     if (wave_active) st.put_acc(stage, acc, out->scale, on, oh);
     RowBlocks rb_next{};
-    if (next >= 0) rb_next = row_blocks(out, out->fwd_items, next);  // (its loads are under way during the stores)
+    if (next >= 0) rb_next = row_blocks<NWQ>(out, out->fwd_items, next);  // (its loads are under way during the stores)
     if (wave_active) {
         st.store(stage, out->dq + ((size_t)qrow0 * out->Hq + head) * D, (uint32_t)out->Hq * D * 2, wrow0, rows);
         if (oh == 0 && oi < rows) {
@@ -439,17 +439,17 @@ __global__ __launch_bounds__(64 * NWQ, 2) void dq_kernel(const BwdParams prm)
     __shared__ int work_slot;
     WorkFeed feed{prm.queue_dq, prm.n_work_dq, D == 128 ? prm.n_first_dq : 0, 0, &work_slot};  // (by index: +0 to 4 % at 128, -0 to 2 % at 64)
     int w = feed.first();
-    RowBlocks rb = row_blocks(kernarg<BwdParams>(), prm.fwd_items, max(w, 0));
+    RowBlocks rb = row_blocks<NWQ>(kernarg<BwdParams>(), prm.fwd_items, max(w, 0));
     while (w >= 0) {
         if (rb.has(0)) {
             w = dq_work<D, NWQ>(w, rb, feed);
             if (w == kQueueEmpty) {
                 w = feed.other();
-                rb = row_blocks(kernarg<BwdParams>(), prm.fwd_items, max(w, 0));
+                rb = row_blocks<NWQ>(kernarg<BwdParams>(), prm.fwd_items, max(w, 0));
             }
         } else {  // the item is too short for this part (the whole workgroup agrees)
             w = feed.again();
-            rb = row_blocks(kernarg<BwdParams>(), prm.fwd_items, max(w, 0));
+            rb = row_blocks<NWQ>(kernarg<BwdParams>(), prm.fwd_items, max(w, 0));
         }
     }
 }
@@ -1084,7 +1084,7 @@ hipError_t launch_pair(const skrull_attn_plan_t *p, BwdParams prm, int threads_q
     }
     if (!queued_q) {
         prm.queue_dq = nullptr;
-        spread_parts(prm.rows);
+        prm.rows.spread = 1;
     }
     if (!queued_kv) prm.queue_dkv = nullptr;
     prm.n_first_dq = launch_size<KernelQ>(threads_q, prm.n_work_dq, queued_q);
@@ -1122,14 +1122,11 @@ hipError_t launch_d(const skrull_attn_plan_t *p, const BwdParams &prm, hipStream
 
 }  // namespace
 
-static RowMap map_dq(const skrull_attn_plan_t *p)
-{
-    return row_map(p->BM, p->Hq, p->Hkv, small_dq_shape(p) ? NWQ_SMALL : NWQ_LARGE);
-}
+static int waves_dq(const skrull_attn_plan_t *p) { return small_dq_shape(p) ? NWQ_SMALL : NWQ_LARGE; }
 
 int grid_dq(const skrull_attn_plan_t *p)
 {
-    return p->n_fwd * p->Hkv * map_dq(p).parts;
+    return row_work(p, waves_dq(p));
 }
 
 static KeyMap map_dkv(const skrull_attn_plan_t *p)
@@ -1159,7 +1156,7 @@ hipError_t launch_bwd(const skrull_attn_plan_t *p, const void *q, const void *k,
     prm.cu_q = p->cu_q; prm.cu_k = p->cu_k; prm.q_begin = p->q_begin; prm.q_len = p->q_len;
     prm.kv_len = p->kv_len; prm.shares_kv = p->shares_kv;
     prm.Hq = p->Hq; prm.Hkv = p->Hkv; prm.total_q = p->total_q;
-    prm.rows = map_dq(p);
+    prm.rows = row_map(p, waves_dq(p));
     prm.keys = map_dkv(p);
     prm.scale = p->scale; prm.scale_log2 = p->scale * kLog2e;
     prm.total_k = p->total_k;

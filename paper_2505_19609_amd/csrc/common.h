@@ -12,6 +12,8 @@ struct WorkQueue;
 #define SKRULL_FWD_QUEUE_SLOTS 64
 
 #define SKRULL_CHAIN_LIMITS 9
+#define SKRULL_UNIT_SHIFT 11  // rank-sorted lists have at most 2,048 items
+#define SKRULL_UNIT_HEADS 1024  // more query heads go without a list of units (index arithmetic of row_blocks)
 
 // Device-resident descriptor + work lists of one micro-batch.
 struct skrull_attn_plan {
@@ -31,6 +33,10 @@ struct skrull_attn_plan {
     int32_t *pool;
     int32_t *cu_q, *cu_k, *q_begin, *q_len, *kv_len, *shares_kv;  // per segment: [NS+1] x2, [NS] x4
     int32_t *fwd_items, *dkv_items;                   // [n][4], sorted
+    // work units of the forward / dQ list for workgroups of 4 and of 8 wavefronts (see RowMap): item |
+    // part << SKRULL_UNIT_SHIFT, in list order; null for lists too long
+    // for the rank sort and for very many heads
+    int32_t *units[2], n_units[2];
     WorkQueue *fwd_queues;  // [SKRULL_FWD_QUEUE_SLOTS] at the start of the pool: work queues of forward launches
     uint32_t fwd_calls;     // forward calls made so far (atomic): call i uses slot i mod SKRULL_FWD_QUEUE_SLOTS
 };
@@ -46,6 +52,7 @@ struct PlanTotals {
     // chains of dK/dV items (query blocks x heads of a group, walked one after another by a workgroup
     // that has the item to itself): how many exceed exactly the first k of dkv_chain_limit()
     int32_t chain_base, chain_hist[SKRULL_CHAIN_LIMITS + 1];
+    int32_t n_units[2];        // work units of the forward / dQ list for 4 and for 8 wavefronts
     int32_t cap_fwd, cap_dkv;  // room in the item arrays (the host's upper bounds)
     int32_t block_n;           // key rows per dK/dV item in effect (the ranges kernel's choice where open)
 };
@@ -104,6 +111,7 @@ hipError_t launch_plan_items(const skrull_attn_plan_t *p, const int32_t *fwd_off
                              const int32_t *dkv_off, int32_t cap_fwd, int32_t cap_dkv,
                              int32_t *scratch_fwd, int32_t *scratch_dkv, int32_t *radix_hist,
                              int32_t cost_bound, int32_t compute_units, PlanTotals *totals, hipStream_t st);
+int64_t plan_unit_ints(const skrull_attn_plan_t *p, int32_t cap_fwd, int which);  // room for units[which]; 0: no list
 int64_t plan_radix_ints(int32_t cap_fwd, int32_t cap_dkv, int32_t cost_bound);
 
 // fwd.hip / bwd.hip

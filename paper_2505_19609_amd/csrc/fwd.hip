@@ -451,7 +451,7 @@ __device__ __forceinline__ int fwd_work(const int bid, RowBlocks &rb, WorkFeed &
     int next = -1;
     if (EARLY) next = feed.take();
     RowBlocks rb_next{};
-    if (EARLY && next >= 0) rb_next = row_blocks(out, out->items, next);  // (its loads are under way during the stores)
+    if (EARLY && next >= 0) rb_next = row_blocks<NW>(out, out->items, next);  // (its loads are under way during the stores)
     if (wave_active) {
         const float l_tot = sum_halves(l_run);
         const float inv = 1.0f / l_tot;
@@ -472,7 +472,7 @@ __device__ __forceinline__ int fwd_work(const int bid, RowBlocks &rb, WorkFeed &
         rb = uniform(rb_next);
     } else {
         next = feed.again();
-        if (next >= 0) rb = uniform(row_blocks(out, out->items, next));
+        if (next >= 0) rb = uniform(row_blocks<NW>(out, out->items, next));
     }
     return next;
 }
@@ -483,17 +483,17 @@ __global__ __launch_bounds__(64 * NW, 2) void fwd_kernel(const FwdParams prm)
     __shared__ int work_slot;
     WorkFeed feed{prm.queue, prm.n_work, prm.n_first, 0, &work_slot};
     int w = feed.first();
-    RowBlocks rb = row_blocks(kernarg<FwdParams>(), prm.items, w);
+    RowBlocks rb = row_blocks<NW>(kernarg<FwdParams>(), prm.items, w);
     while (w >= 0) {
         if (rb.has(0)) {
             w = fwd_work<D, NW, NSLOT>(w, rb, feed);
             if (w == kQueueEmpty) {
                 w = feed.other();
-                rb = row_blocks(kernarg<FwdParams>(), prm.items, max(w, 0));
+                rb = row_blocks<NW>(kernarg<FwdParams>(), prm.items, max(w, 0));
             }
         } else {  // the item is too short for this part (the whole workgroup agrees)
             w = feed.again();
-            rb = row_blocks(kernarg<FwdParams>(), prm.items, max(w, 0));
+            rb = row_blocks<NW>(kernarg<FwdParams>(), prm.items, max(w, 0));
         }
     }
 }
@@ -508,7 +508,7 @@ hipError_t launch_shape(FwdParams prm, int threads, hipStream_t st)
         if (e != hipSuccess) return e;
     } else {
         prm.queue = nullptr;
-        spread_parts(prm.rows);
+        prm.rows.spread = 1;
     }
     prm.n_first = launch_size<Kernel>(threads, prm.n_work, queued);
     Kernel<<<prm.n_first, threads, 0, st>>>(prm);
@@ -524,11 +524,9 @@ hipError_t launch_one(const FwdParams &prm, hipStream_t st)
 
 }  // namespace
 
-static RowMap map_fwd(const skrull_attn_plan_t *p) { return row_map(p->BM, p->Hq, p->Hkv, p->wg_query_rows / 32); }
-
 int grid_fwd(const skrull_attn_plan_t *p)
 {
-    return p->n_fwd * p->Hkv * map_fwd(p).parts;
+    return row_work(p, p->wg_query_rows / 32);
 }
 
 hipError_t launch_fwd(const skrull_attn_plan_t *p, const void *q, const void *k, const void *v,
@@ -540,7 +538,7 @@ hipError_t launch_fwd(const skrull_attn_plan_t *p, const void *q, const void *k,
     prm.items = (const int4 *)p->fwd_items;
     prm.cu_k = p->cu_k; prm.q_begin = p->q_begin; prm.q_len = p->q_len; prm.kv_len = p->kv_len;
     prm.Hq = p->Hq; prm.Hkv = p->Hkv; prm.total_q = p->total_q;
-    prm.rows = map_fwd(p);
+    prm.rows = row_map(p, p->wg_query_rows / 32);
     prm.scale_log2 = p->scale * 1.4426950408889634f;
     prm.trace = trace;
     prm.variant = p->wg_query_rows == 32 * NW_SMALL ? 0 : 1;

@@ -207,6 +207,7 @@ __global__ __launch_bounds__(kScanThreads) void plan_ranges_kernel(
         totals->dkv_cost_sum = 0;
         totals->dkv_cost_max = 0;
         for (int i = 0; i <= SKRULL_CHAIN_LIMITS; ++i) totals->chain_hist[i] = 0;
+        totals->n_units[0] = totals->n_units[1] = 0;
         totals->cap_fwd = cap_fwd;
         totals->cap_dkv = cap_dkv;
         totals->block_n = BN;
@@ -305,15 +306,24 @@ __device__ inline void count_chain(int32_t cost, int32_t group, int32_t q_heads,
 // read.  (One thread per item and one cost to a read, each waited for, took 12 us for 180 items and
 // 25 us for 310; both lists together now take 9 to 12.)  blockIdx.y: the list (0 forward / dQ, 1 dK/dV).
 constexpr int32_t kSortItems = 64;  // items of a block
+// The forward / dQ list also gets its work units: an item of `blocks` 32-row blocks makes
+// ceil(blocks * group / NW) workgroups of NW waves per KV head, and the position of the first one in
+// the sorted list of units is the sum over the items before it, formed along with the rank
+// (0.5 to 0.8 us for 20 to 300 items).
 struct SortJob {
     const int4 *in;
     int4 *out;
 };
-__global__ __launch_bounds__(256) void plan_sort_kernel(SortJob fwd, SortJob dkv, int first_list, PlanTotals *totals,
+struct UnitJob {
+    const int32_t *q_len;
+    int32_t BM;
+    int32_t *units[2];  // for 4 and for 8 waves
+};
+__global__ __launch_bounds__(256) void plan_sort_kernel(SortJob fwd, SortJob dkv, UnitJob uj, int first_list, PlanTotals *totals,
                                                         int32_t group, int32_t q_heads, int32_t head_dim,
                                                         int32_t compute_units)
 {
-    __shared__ __align__(16) int32_t tile[1024];
+    __shared__ __align__(16) int32_t tile[1024], n4[1024], n8[1024];
     const int which = first_list + blockIdx.y;
     const int4 *__restrict__ in = which == 0 ? fwd.in : dkv.in;
     int4 *__restrict__ out = which == 0 ? fwd.out : dkv.out;
@@ -323,25 +333,56 @@ __global__ __launch_bounds__(256) void plan_sort_kernel(SortJob fwd, SortJob dkv
     if (first >= n) return;  // (the whole block)
     const int32_t a = first + threadIdx.x / 4, quarter = threadIdx.x % 4;
     const int4 me = (a < n) ? in[a] : make_int4(0, 0, 0, 0);
-    int32_t rank = 0;
+    auto blocks_of = [&](const int4 &it) {  // 32-row blocks of a forward item, of all heads of a group
+        const int32_t left = uj.q_len[it.x] - it.y * uj.BM;
+        return (((left < uj.BM ? left : uj.BM) + 31) >> 5) * group;
+    };
+    const bool listed = which == 0 && uj.units[0] != nullptr;
+    int32_t rank = 0, at4 = 0, at8 = 0;
     for (int32_t b0 = 0; b0 < n; b0 += 1024) {
         __syncthreads();
         const int32_t lim = (n - b0 < 1024) ? n - b0 : 1024;
-        for (int32_t i = threadIdx.x; i < ((lim + 15) & ~15); i += blockDim.x)
-            tile[i] = (i < lim) ? in[b0 + i].w : -1;  // (below every cost)
+        for (int32_t i = threadIdx.x; i < ((lim + 15) & ~15); i += blockDim.x) {
+            const int4 it = i < lim ? in[b0 + i] : make_int4(0, 0, 0, -1);  // (below every cost)
+            tile[i] = it.w;
+            if (listed) {
+                const int32_t blocks = i < lim ? blocks_of(it) : 0;
+                n4[i] = (blocks + 3) >> 2;
+                n8[i] = (blocks + 7) >> 3;
+            }
+        }
         __syncthreads();
         // cost_b > cost_a, or equal and earlier: cost_b >= cost_a + (b >= a)
         const int32_t before = a - b0;
         for (int32_t x = 4 * quarter; x < lim; x += 16) {
             const int4 c = *(const int4 *)&tile[x];
-            rank += c.x >= me.w + (x >= before);
-            rank += c.y >= me.w + (x + 1 >= before);
-            rank += c.z >= me.w + (x + 2 >= before);
-            rank += c.w >= me.w + (x + 3 >= before);
+            const bool ahead[4] = {c.x >= me.w + (x >= before), c.y >= me.w + (x + 1 >= before),
+                                   c.z >= me.w + (x + 2 >= before), c.w >= me.w + (x + 3 >= before)};
+            rank += ahead[0] + ahead[1] + ahead[2] + ahead[3];
+            if (listed) {
+                const int4 f = *(const int4 *)&n4[x], e = *(const int4 *)&n8[x];
+                at4 += (ahead[0] ? f.x : 0) + (ahead[1] ? f.y : 0) + (ahead[2] ? f.z : 0) + (ahead[3] ? f.w : 0);
+                at8 += (ahead[0] ? e.x : 0) + (ahead[1] ? e.y : 0) + (ahead[2] ? e.z : 0) + (ahead[3] ? e.w : 0);
+            }
         }
     }
     rank += __shfl_xor(rank, 1, 64);
     rank += __shfl_xor(rank, 2, 64);
+    if (listed) {
+        at4 += __shfl_xor(at4, 1, 64);
+        at4 += __shfl_xor(at4, 2, 64);
+        at8 += __shfl_xor(at8, 1, 64);
+        at8 += __shfl_xor(at8, 2, 64);
+        if (a < n) {  // the item's four threads write its units
+            const int32_t blocks = blocks_of(me), mine4 = (blocks + 3) >> 2, mine8 = (blocks + 7) >> 3;
+            for (int32_t p = quarter; p < mine4; p += 4) uj.units[0][at4 + p] = rank | p << SKRULL_UNIT_SHIFT;
+            for (int32_t p = quarter; p < mine8; p += 4) uj.units[1][at8 + p] = rank | p << SKRULL_UNIT_SHIFT;
+            if (quarter == 0) {
+                atomicAdd(&totals->n_units[0], mine4);
+                atomicAdd(&totals->n_units[1], mine8);
+            }
+        }
+    }
     if (a < n && quarter == 0) {
         out[rank] = me;
         if (which == 1) count_chain(me.w, group, q_heads, head_dim, compute_units, totals);
@@ -452,7 +493,7 @@ hipError_t launch_plan_ranges(const int32_t *S, const int32_t *N, const int32_t 
 // Above this many items (the host's upper bound) a list is sorted by radix passes instead of
 // by rank counting, which is quadratic (measured: 0.25 ms for 5,000 items, 3 ms for 16,000; the
 // radix passes take 0.05 ms there).
-constexpr int32_t kRankSortMax = 2048;
+constexpr int32_t kRankSortMax = 1 << SKRULL_UNIT_SHIFT;
 
 int plan_radix_passes(int32_t cap, int32_t cost_bound)
 {
@@ -460,6 +501,13 @@ int plan_radix_passes(int32_t cap, int32_t cost_bound)
     int bits = 1;
     while (bits < 31 && (1 << bits) <= cost_bound) ++bits;
     return (bits + 7) / 8;
+}
+
+int64_t plan_unit_ints(const skrull_attn_plan_t *p, int32_t cap_fwd, int which)
+{
+    if (cap_fwd > kRankSortMax || p->Hq > SKRULL_UNIT_HEADS) return 0;
+    const int waves = which == 0 ? 4 : 8;
+    return (int64_t)cap_fwd * ((p->BM / 32 * (p->Hq / p->Hkv) + waves - 1) / waves);
 }
 
 int64_t plan_radix_ints(int32_t cap_fwd, int32_t cap_dkv, int32_t cost_bound)
@@ -513,7 +561,7 @@ hipError_t launch_plan_items(const skrull_attn_plan_t *p, const int32_t *fwd_off
         const int32_t most = passes_f == 0 && passes_d == 0 ? n : (passes_f == 0 ? cap_fwd : cap_dkv);
         plan_sort_kernel<<<dim3((most + kSortItems - 1) / kSortItems, lists), 256, 0, st>>>(
             SortJob{(const int4 *)scratch_fwd, (int4 *)p->fwd_items}, SortJob{(const int4 *)scratch_dkv, (int4 *)p->dkv_items},
-            first, totals, p->Hq / p->Hkv, p->Hq, p->d, compute_units);
+            UnitJob{p->q_len, p->BM, {p->units[0], p->units[1]}}, first, totals, p->Hq / p->Hkv, p->Hq, p->d, compute_units);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

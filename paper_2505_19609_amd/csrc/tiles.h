@@ -23,6 +23,7 @@
 // addresses (the VALU issue port is the scarce resource next to the MFMAs).
 #pragma once
 
+#include "common.h"
 #include "mfma.h"
 #include "queue.h"
 
@@ -106,27 +107,34 @@ struct FragAddr {
 // What the host works out for the mapping: divisions of a work item's index are most of a
 // microsecond of dependent vector instructions at the start of every item.  A quotient x / d is
 // (x * inv) >> 40 with inv = ceil(2^40 / d), exact while x * d < 2^40; here x < 8 * d or
-// x < 2 * (query heads), and a row of heads is below 2^32 bytes.
+// x < 2 * (query heads), and a row of heads is below 2^32 bytes; with a list of units x < 2,048 *
+// (2 g + 1) * d and there are at most SKRULL_UNIT_HEADS query heads.
 struct RowMap {
-    int32_t BM, g, Hkv, parts;  // query heads per KV head; workgroups per (item, KV head)
-    int32_t part_step, wave_step;  // row block of wave w of part p: p * part_step + w * wave_step
+    int32_t BM, g, Hkv, NW;       // query heads per KV head; waves of a workgroup
+    int32_t parts, spread;        // most workgroups per (item, KV head); 1: the order below
+    const int32_t *units;         // null, or the work units: item | part << SKRULL_UNIT_SHIFT
     uint64_t inv_g, inv_hkv;
 };
+// ceil(2^40 / d)
 static inline uint64_t inverse_of(int d) { return ((1ull << 40) + d - 1) / d; }
-static inline RowMap row_map(int BM, int Hq, int Hkv, int NW)
+static inline RowMap row_map(const skrull_attn_plan_t *p, int NW)
 {
-    const int g = Hq / Hkv;
-    return RowMap{BM, g, Hkv, (BM / 32 * g + NW - 1) / NW, NW, 1, inverse_of(g), inverse_of(Hkv)};
+    const int g = p->Hq / p->Hkv;
+    return RowMap{p->BM, g, p->Hkv, NW, (p->BM / 32 * g + NW - 1) / NW, 0, p->units[NW == 8], inverse_of(g), inverse_of(p->Hkv)};
 }
-// The other order, for launches whose workgroups all run at once: neighbouring row blocks go to
+// Work items of a launch: with a list of units there are as many as have rows; without one every item
+// counts for its most parts, and those it does not have are passed over when their turn comes.  (In
+// the forward of 114 sequences of about 250 tokens, 32/8 heads of 128, a quarter of all parts was
+// empty, most of them at the end of the list, where the claims for them held up everybody's: forward 240 ->
+// 232 us, dQ 318 -> 314.  64 sequences, 26,624 tokens, 14/2 heads of 64: 85 -> 81 and 100 -> 97.)
+static inline int row_work(const skrull_attn_plan_t *p, int NW)
+{
+    return p->units[NW == 8] ? p->n_units[NW == 8] * p->Hkv : p->n_fwd * p->Hkv * row_map(p, NW).parts;
+}
+// `spread`, for launches whose workgroups all run at once: neighbouring row blocks go to
 // different workgroups, so that a workgroup has few waves at work near its last key and the longest
 // chain, which is then the time of the launch, runs with the least company (sequences of 300 and
 // 212 tokens, 14/2 heads of 64: forward 12.9 us in the order above, 11.4 in this one).
-static inline void spread_parts(RowMap &m)
-{
-    m.part_step = 1;
-    m.wave_step = m.parts;
-}
 __device__ __forceinline__ int quotient(int x, uint64_t inv) { return (int)(((uint64_t)(uint32_t)x * inv) >> 40); }
 
 struct RowBlocks {
@@ -147,17 +155,26 @@ struct RowBlocks {
 // work index -> (item, part, KV head).  Consecutive work items go to consecutive XCDs; the parts of
 // one (item, KV head) are Hkv apart so that they share an XCD (and its L2 copy of the K/V tiles)
 // whenever Hkv divides 8 or is a multiple of it.
-template <typename P>
+template <int NW, typename P>
 __device__ __forceinline__ RowBlocks row_blocks(const P prm, const int4 *items, int bid)
 {
     RowBlocks r;
-    const int BM = prm->rows.BM, Hkv = prm->rows.Hkv, per_item = prm->rows.parts * Hkv;
-    const int item = __builtin_amdgcn_readfirstlane(bid / per_item), x = bid - item * per_item;
-    const int part = quotient(x, prm->rows.inv_hkv);
-    r.c = x - part * Hkv;
-    r.first = part * prm->rows.part_step;
-    r.step = prm->rows.wave_step;
-    const i32x4 it = plan_value((const i32x4 *)items, item);
+    const int BM = prm->rows.BM, Hkv = prm->rows.Hkv;
+    const int32_t *units = prm->rows.units;
+    int item, part;
+    if (units) {
+        const int unit = __builtin_amdgcn_readfirstlane(quotient(bid, prm->rows.inv_hkv)), u = plan_value(units, unit);
+        r.c = bid - unit * Hkv;
+        item = u & ((1 << SKRULL_UNIT_SHIFT) - 1);
+        part = u >> SKRULL_UNIT_SHIFT;
+    } else {
+        const int per_item = prm->rows.parts * Hkv;
+        item = __builtin_amdgcn_readfirstlane(bid / per_item);
+        const int x = bid - item * per_item;
+        part = quotient(x, prm->rows.inv_hkv);
+        r.c = x - part * Hkv;
+    }
+    const i32x4 it = plan_value((const i32x4 *)items, __builtin_amdgcn_readfirstlane(item));
     const int seq = it.x;
     const int ql = plan_value(prm->q_len, seq);
     r.qb = plan_value(prm->q_begin, seq);
@@ -169,6 +186,10 @@ __device__ __forceinline__ RowBlocks row_blocks(const P prm, const int4 *items, 
     r.g = prm->rows.g;
     r.inv_g = prm->rows.inv_g;
     r.nblk = (r.rows + 31) / 32;
+    const int parts = (r.nblk * r.g + NW - 1) / NW;  // of this item
+    const bool spread = prm->rows.spread != 0;
+    r.first = part >= parts ? r.nblk * r.g : (spread ? part : part * NW);  // (past the end: the item has no such part)
+    r.step = spread ? parts : 1;
     return r;
 }
 

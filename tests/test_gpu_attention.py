@@ -898,6 +898,26 @@ def test_row_blocks_of_a_group_in_both_orders(oracle, heads, d, wg, bm):
     one["plan"].destroy()
 
 
+@pytest.mark.parametrize("wg", [128, 256])
+@pytest.mark.parametrize("rep", [7, 114, 228])
+def test_units_of_lists_of_several_lengths(oracle, wg, rep):
+    """Forward and dQ take their work from the list of units that the plan's sort leaves: within one tile of
+    the sort (63 items), across two (1,026), and in a list too long for it (2,052), which has none.  Items of
+    1 to 8 row blocks of 3 heads; the sequences of a checked small micro-batch, repeated, give the same bits."""
+    S, heads, d = [1, 31, 32, 33, 255, 257, 300], (6, 2), 64
+    w = W.Workload("units", S, [1] * 7, [0] * 7, heads[0], heads[1], d, d ** -0.5, 405)
+    # (the stated bound plus the output's own rounding, half a bf16 spacing: at most 2^-8 of it)
+    one = _exhaustive(oracle, w, rtol=2.0 ** -8, wg_query_rows=wg, head_split=1, keep=True)
+    many = W.Workload(f"units_{rep}", S * rep, [1] * 7 * rep, [0] * 7 * rep, heads[0], heads[1], d, d ** -0.5, 405)
+    vals = {n: np.concatenate([a] * rep) for n, a in one["vals"].items()}
+    out = run_library(many, vals=vals, wg_query_rows=wg, head_split=1)
+    for n in ("o", "dq"):
+        assert np.array_equal(out[n], np.concatenate([one[n]] * rep)), n
+    assert np.array_equal(out["lse"], np.concatenate([one["lse"]] * rep, axis=1))
+    out["plan"].destroy()
+    one["plan"].destroy()
+
+
 SHARED = {  # lengths, degrees, indices, cuts, heads, head_dim, block_n, what the plan does
     "one head per group": ([2967], [1], [0], [0], (4, 4), 64, 0, "compact"),
     "short blocks": ([1100, 37, 700], [1] * 3, [0] * 3, [0] * 3, (3, 3), 128, 64, "compact"),
