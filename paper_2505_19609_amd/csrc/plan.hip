@@ -304,7 +304,7 @@ __device__ inline void count_chain(int32_t cost, int32_t group, int32_t q_heads,
 //   #{b : cost_b > cost_a} + #{b < a : cost_b == cost_a}.
 // Costs are streamed through LDS in tiles; four threads walk a tile for one item, four costs to a
 // read.  (One thread per item and one cost to a read, each waited for, took 12 us for 180 items and
-// 25 us for 310; both lists together now take 9 to 12.)  blockIdx.y: the list (0 forward / dQ, 1 dK/dV).
+// 25 us for 310; both lists together now take 6 to 10, 25 for 1,368.)  blockIdx.y: the list (0 forward / dQ, 1 dK/dV).
 constexpr int32_t kSortItems = 64;  // items of a block
 // The forward / dQ list also gets its work units: an item of `blocks` 32-row blocks makes
 // ceil(blocks * group / NW) workgroups of NW waves per KV head, and the position of the first one in
