@@ -135,11 +135,12 @@ def _check(rc: int):
 def _stream_ptr(stream):
     """The hipStream_t of `stream`, or of torch's current one, as an integer.  (The current stream is asked
     for as a raw pointer: torch.cuda.current_stream() builds a Stream object, 3 us of the 7 that a
-    forward call cost the host.)"""
+    forward call cost the host.  That function is private to torch, so it may be missing.)"""
     if stream is None:
         import torch
-        if torch.cuda.is_initialized():
-            return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is not None and torch.cuda.is_initialized():
+            return raw(torch.cuda.current_device())
         stream = torch.cuda.current_stream()
     return int(getattr(stream, "cuda_stream", stream))
 

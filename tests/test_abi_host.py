@@ -99,3 +99,18 @@ def test_valid_problem_without_gpu_is_unsupported_not_a_crash(B):
     with pytest.raises(B.SkrullError) as e:
         B.skrull_attn_plan([10], [1], [0], 4, 2, 64, 0.125, raw_stream=0)
     assert e.value.code == B.SKRULL_EUNSUPPORTED
+
+
+def test_current_stream_where_torch_has_no_raw_accessor(B, monkeypatch):
+    """The current stream is asked for through a private function of torch where there is one, and through the
+    public one where there is none."""
+    import types
+    import torch
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: types.SimpleNamespace(cuda_stream=77))
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda dev: 100 + dev, raising=False)
+    assert B._stream_ptr(None) == 103
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream")
+    assert B._stream_ptr(None) == 77
+    assert B._stream_ptr(0) == 0 and B._stream_ptr(types.SimpleNamespace(cuda_stream=5)) == 5
