@@ -115,9 +115,13 @@ __device__ __forceinline__ uint32_t ds_mul_pack(float t0, float t1, float g0, fl
 // B(j).  B(j) reads the transposed K of the half tile BEFORE the one A(j+1) reads,
 // which is why the K ring has one slot more than the V ring.  Steps at the start, the
 // end and the causal diagonal of a wave's range take a plain path with guards.
+// dQ's first items are taken by index where that is faster: by 0 to 4 % at 128, but 0 to 2 % slower at 64
+template <int D> using DqFeed = WorkFeed<kQueueStrideBwd, D == 128>;
+using DkvFeed = WorkFeed<kQueueStrideBwd, false>;
+
 // Does work item `bid`, whose rows are `rb`; returns the next one and leaves its rows in `rb`.
 template <int D, int NWQ>
-__device__ __forceinline__ int dq_work(const int bid, RowBlocks &rb, WorkFeed &feed)
+__device__ __forceinline__ int dq_work(const int bid, RowBlocks &rb, DqFeed<D> &feed)
 {
     const kernarg_t<BwdParams> prm = kernarg<BwdParams>();
     constexpr bool SMALL = NWQ == NWQ_SMALL;
@@ -436,10 +440,14 @@ __device__ __forceinline__ int dq_work(const int bid, RowBlocks &rb, WorkFeed &f
 template <int D, int NWQ>
 __global__ __launch_bounds__(64 * NWQ, 2) void dq_kernel(const BwdParams prm)
 {
-    __shared__ int work_slot;
-    WorkFeed feed{prm.queue_dq, prm.n_work_dq, D == 128 ? prm.n_first_dq : 0, 0, &work_slot};  // (by index: +0 to 4 % at 128, -0 to 2 % at 64)
-    int w = feed.first();
-    RowBlocks rb = row_blocks<NWQ>(kernarg<BwdParams>(), prm.fwd_items, max(w, 0));
+    __shared__ int work_slot[2];
+    constexpr bool BY_INDEX = DqFeed<D>::kByIndex;
+    DqFeed<D> feed{prm.queue_dq, prm.n_work_dq, BY_INDEX ? prm.n_first_dq : 0, 0, work_slot};
+    const uint32_t marks = feed.begin();
+    RowBlocks rb{};
+    if (BY_INDEX) rb = uniform(row_blocks<NWQ>(kernarg<BwdParams>(), prm.fwd_items, (int)blockIdx.x));
+    int w = feed.first(marks);
+    if (!BY_INDEX || w != (int)blockIdx.x) rb = row_blocks<NWQ>(kernarg<BwdParams>(), prm.fwd_items, max(w, 0));
     while (w >= 0) {
         if (rb.has(0)) {
             w = dq_work<D, NWQ>(w, rb, feed);
@@ -584,7 +592,7 @@ __device__ __forceinline__ KeyBlock key_block(const P prm, int SUB, int bid)
 
 // Does work item `bid`, whose keys are `kb`; returns the next one and leaves its keys in `kb`.
 template <int D, int PAIRS>
-__device__ __forceinline__ int dkv_work(const int bid, KeyBlock &kb, WorkFeed &feed)
+__device__ __forceinline__ int dkv_work(const int bid, KeyBlock &kb, DkvFeed &feed)
 {
     const kernarg_t<BwdParams> prm = kernarg<BwdParams>();
     constexpr int NWP = 2 * PAIRS;   // wavefronts: PAIRS S waves, then PAIRS dP waves
@@ -1011,9 +1019,9 @@ __device__ __forceinline__ int dkv_work(const int bid, KeyBlock &kb, WorkFeed &f
 template <int D, int PAIRS>
 __global__ __launch_bounds__(128 * PAIRS, PAIRS == PAIRS_12W ? 3 : 2) void dkv_kernel(const BwdParams prm)
 {
-    __shared__ int work_slot;
-    WorkFeed feed{prm.queue_dkv, prm.n_work_dkv, 0, 0, &work_slot};
-    int w = feed.first();
+    __shared__ int work_slot[2];
+    DkvFeed feed{prm.queue_dkv, prm.n_work_dkv, 0, 0, work_slot};
+    int w = feed.first(feed.begin());
     KeyBlock kb = key_block(kernarg<BwdParams>(), 32 * PAIRS, max(w, 0));
     while (w >= 0) {
         if (kb.item_rows > 0) {
@@ -1078,7 +1086,7 @@ hipError_t launch_pair(const skrull_attn_plan_t *p, BwdParams prm, int threads_q
     const bool queued_q = wants_queue<KernelQ>(threads_q, prm.n_work_dq);
     const bool queued_kv = wants_queue<KernelKV>(threads_kv, prm.n_work_dkv);
     if (queued_q || queued_kv) {
-        queue_reset_kernel<<<1, 64, 0, st>>>(prm.queue_dq, 2);
+        queue_reset_kernel<<<1, 64, 0, st>>>(prm.queue_dq, 2, kQueueStrideBwd);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -1087,8 +1095,9 @@ hipError_t launch_pair(const skrull_attn_plan_t *p, BwdParams prm, int threads_q
         prm.rows.spread = 1;
     }
     if (!queued_kv) prm.queue_dkv = nullptr;
-    prm.n_first_dq = launch_size<KernelQ>(threads_q, prm.n_work_dq, queued_q);
-    KernelQ<<<prm.n_first_dq, threads_q, 0, st>>>(prm);
+    const int blocks_q = launch_size<KernelQ>(threads_q, prm.n_work_dq, queued_q);
+    prm.n_first_dq = blocks_q < kMaxFirst ? blocks_q : kMaxFirst;
+    KernelQ<<<blocks_q, threads_q, 0, st>>>(prm);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (ev) (void)hipEventRecord(ev[1], st);
@@ -1163,10 +1172,11 @@ hipError_t launch_bwd(const skrull_attn_plan_t *p, const void *q, const void *k,
     prm.n_work_dq = grid_dq(p);
     prm.n_work_dkv = grid_dkv(p);
     {
-        // workspace: -D | LSE*log2e | (256-byte aligned) two work queues in 256 bytes | dK partials | dV partials
+        // workspace: -D | LSE*log2e | (256-byte aligned) work queues of two launches in 256 bytes | dK partials | dV partials
+        static_assert(2 * 8 * kQueueStrideBwd * sizeof(WorkQueue) == 256, "the queues' part of the workspace");
         const size_t rows = (((size_t)p->Hq * p->total_q * 8) + 255) & ~(size_t)255;
         prm.queue_dq = (WorkQueue *)((char *)delta + rows);
-        prm.queue_dkv = prm.queue_dq + 1;
+        prm.queue_dkv = prm.queue_dq + 8;
         prm.dk_part = (float *)((char *)delta + rows + 256);
         const size_t part_rows = p->split_compact ? (size_t)p->n_split * p->BN : (size_t)p->total_k;
         prm.dv_part = prm.dk_part + (size_t)p->split_parts * part_rows * p->Hkv * p->d;

@@ -10,6 +10,7 @@
 struct WorkQueue;
 // forward calls of one plan that may be in flight at once (each takes one queue slot in turn)
 #define SKRULL_FWD_QUEUE_SLOTS 64
+#define SKRULL_FWD_QUEUE_INTS 256  // of a slot: eight dies' queues, a 128-byte line each
 
 #define SKRULL_CHAIN_LIMITS 9
 #define SKRULL_UNIT_SHIFT 11  // rank-sorted lists have at most 2,048 items
@@ -37,7 +38,7 @@ struct skrull_attn_plan {
     // part << SKRULL_UNIT_SHIFT, in list order; null for lists too long
     // for the rank sort and for very many heads
     int32_t *units[2], n_units[2];
-    WorkQueue *fwd_queues;  // [SKRULL_FWD_QUEUE_SLOTS] at the start of the pool: work queues of forward launches
+    WorkQueue *fwd_queues;  // SKRULL_FWD_QUEUE_SLOTS times eight dies' queues, at the start of the pool: for forward launches
     uint32_t fwd_calls;     // forward calls made so far (atomic): call i uses slot i mod SKRULL_FWD_QUEUE_SLOTS
 };
 

@@ -116,9 +116,11 @@ __device__ __forceinline__ uint32_t softmax_sum_pack(float t0, float t1, float &
     return pk;
 }
 
+using FwdFeed = WorkFeed<kQueueStrideFwd, true>;
+
 // Does work item `bid`, whose rows are `rb`; returns the next one and leaves its rows in `rb`.
 template <int D, int NW, int NSLOT>
-__device__ __forceinline__ int fwd_work(const int bid, RowBlocks &rb, WorkFeed &feed)
+__device__ __forceinline__ int fwd_work(const int bid, RowBlocks &rb, FwdFeed &feed)
 {
     const kernarg_t<FwdParams> prm = kernarg<FwdParams>();
     static_assert(NSLOT == 2 || NSLOT == 4, "ring logic below covers two and four slots");
@@ -480,10 +482,12 @@ __device__ __forceinline__ int fwd_work(const int bid, RowBlocks &rb, WorkFeed &
 template <int D, int NW, int NSLOT>
 __global__ __launch_bounds__(64 * NW, 2) void fwd_kernel(const FwdParams prm)
 {
-    __shared__ int work_slot;
-    WorkFeed feed{prm.queue, prm.n_work, prm.n_first, 0, &work_slot};
-    int w = feed.first();
-    RowBlocks rb = row_blocks<NW>(kernarg<FwdParams>(), prm.items, w);
+    __shared__ int work_slot[2];
+    FwdFeed feed{prm.queue, prm.n_work, prm.n_first, 0, work_slot};
+    const uint32_t marks = feed.begin();
+    RowBlocks rb = uniform(row_blocks<NW>(kernarg<FwdParams>(), prm.items, (int)blockIdx.x));
+    int w = feed.first(marks);
+    if (w != (int)blockIdx.x) rb = row_blocks<NW>(kernarg<FwdParams>(), prm.items, max(w, 0));
     while (w >= 0) {
         if (rb.has(0)) {
             w = fwd_work<D, NW, NSLOT>(w, rb, feed);
@@ -503,15 +507,16 @@ hipError_t launch_shape(FwdParams prm, int threads, hipStream_t st)
 {
     const bool queued = wants_queue<Kernel>(threads, prm.n_work);
     if (queued) {
-        queue_reset_kernel<<<1, 64, 0, st>>>(prm.queue, 1);
+        queue_reset_kernel<<<1, 64, 0, st>>>(prm.queue, 1, kQueueStrideFwd);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     } else {
         prm.queue = nullptr;
         prm.rows.spread = 1;
     }
-    prm.n_first = launch_size<Kernel>(threads, prm.n_work, queued);
-    Kernel<<<prm.n_first, threads, 0, st>>>(prm);
+    const int blocks = launch_size<Kernel>(threads, prm.n_work, queued);
+    prm.n_first = blocks < kMaxFirst ? blocks : kMaxFirst;
+    Kernel<<<blocks, threads, 0, st>>>(prm);
     return hipGetLastError();
 }
 
@@ -545,7 +550,8 @@ hipError_t launch_fwd(const skrull_attn_plan_t *p, const void *q, const void *k,
     prm.n_work = grid_fwd(p);
     // One of the plan's queue slots per call, taken in turn, so that forward calls of one plan
     // that overlap on different streams do not share a queue.
-    prm.queue = p->fwd_queues + (__atomic_fetch_add(&const_cast<skrull_attn_plan_t *>(p)->fwd_calls, 1u, __ATOMIC_RELAXED) % SKRULL_FWD_QUEUE_SLOTS);
+    static_assert(8 * kQueueStrideFwd * sizeof(WorkQueue) == 4 * SKRULL_FWD_QUEUE_INTS, "a slot holds eight queues");
+    prm.queue = p->fwd_queues + 8 * kQueueStrideFwd * (__atomic_fetch_add(&const_cast<skrull_attn_plan_t *>(p)->fwd_calls, 1u, __ATOMIC_RELAXED) % SKRULL_FWD_QUEUE_SLOTS);
     if (p->d == 128) return launch_one<128>(prm, st);
     if (p->d == 64) return launch_one<64>(prm, st);
     return hipErrorInvalidValue;

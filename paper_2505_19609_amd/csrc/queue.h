@@ -11,15 +11,30 @@
 // then from the queue with the most items left.  The work lists are sorted by descending cost, so what is stolen at
 // the end are the smallest items: the paper's rule (Alg. 1: the next piece goes to argmin of
 // the loads) applied across dies at run time, since their speeds are not known beforehand.
+//
+// The longest items, as many as a launch has workgroups ("first items"), carry a mark each that says
+// whether they are taken, and a die's first counts, one for each of its first items, stand for any of
+// those that has no mark yet.  So a workgroup takes the item of its block index when it starts, but one that
+// starts late, for instance because another stream's kernel holds its compute unit, has kept it from nobody.
+// (Without marks, with half of the chip held by another launch, the items of the workgroups that had to wait
+// began when all the short ones were done: after 310 us of a forward of 24 sequences of 1,500 tokens and
+// 600 of 40, 8/8 heads of 128; now all the long ones begin within 65 us.)
 #pragma once
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-struct WorkQueue {
-    int32_t next[8];  // per die: how many of its work items have been handed out (but the first ones)
-    int32_t pad[8];
+constexpr int kFirstWords = 3;
+constexpr int kMaxFirst = 8 * 32 * kFirstWords;  // most first items of a launch
+struct WorkQueue {                // of one die
+    int32_t next;                 // how many of the die's work items have been handed out
+    uint32_t taken[kFirstWords];  // marks of its first items, a bit each
 };
+// A launch has eight of them, this many apart.  Atomics on one 128-byte line wait for each other, and all
+// workgroups of a launch send their first ones together: with the eight queues in one line the forward of 64
+// sequences, 26,624 tokens, 14/2 heads of 64, takes 83 us, with a line each 75, and one of 10,573 tokens 45
+// and 38.  (The workspace of a backward has room for one line per launch.)
+constexpr int kQueueStrideFwd = 8, kQueueStrideBwd = 1;
 
 // The kernel's one argument (a struct of parameters), read anew through an opaque pointer: in a
 // persistent kernel every parameter is an invariant of the work loop, and kept from one work
@@ -50,31 +65,57 @@ template <typename S> __device__ __forceinline__ S uniform(const S &s)
     return __builtin_bit_cast(S, w);
 }
 
-// The work item that count `k` of die `xcd`'s queue stands for (a queue starts behind the items that
-// the launch's workgroups took by their block index), or kQueueEmpty.
-constexpr int kNoWork = -1, kQueueEmpty = -2;
-__device__ __forceinline__ int queued_work(int n_work, int n_first, int xcd, int k)
+// (The atomics of one lane below take an address and a value that the compiler cannot see to be uniform:
+// for uniform ones it combines the lanes that are on, one here, and waits for the answer at once to
+// spread it to them.)
+__device__ __forceinline__ int opaque(int x)
 {
-    const int w = 8 * (k + (n_first - xcd + 7) / 8) + xcd;
+    asm volatile("" : "+v"(x));
+    return x;
+}
+template <int STRIDE> __device__ __forceinline__ int next_count(WorkQueue *q, int xcd)
+{
+    return __hip_atomic_fetch_add(&q[(uint32_t)opaque(STRIDE * xcd)].next, opaque(1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Marks first item 32 * word + bit of a die; the word's marks before that.
+template <int STRIDE> __device__ __forceinline__ uint32_t mark_first(WorkQueue *q, int xcd, int word, int bit)
+{
+    return __hip_atomic_fetch_or(&q[(uint32_t)opaque(STRIDE * xcd)].taken[word], (uint32_t)opaque(1 << bit), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The work item that count `k` of die `xcd`'s queue stands for, or kQueueEmpty.
+constexpr int kNoWork = -1, kQueueEmpty = -2;
+template <int STRIDE, bool FIRST> __device__ __forceinline__ int counted_work(WorkQueue *q, int n_work, int n_first, int xcd, int k)
+{
+    const int mine = (n_first - xcd + 7) / 8;  // this die's first items
+    while (FIRST && __builtin_expect(k < mine, 0)) {
+        for (int i = 0; 32 * i < mine;) {
+            const uint32_t seen = __hip_atomic_load(&q[STRIDE * xcd].taken[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const int bit = __ffs(~seen) - 1;
+            if (~seen == 0 || 32 * i + bit >= mine) { ++i; continue; }
+            if (!(mark_first<STRIDE>(q, xcd, i, bit) >> bit & 1)) return 8 * (32 * i + bit) + xcd;
+        }
+        // all marked, one by a late workgroup whose own count was past them: that one has two items
+        k = next_count<STRIDE>(q, xcd);
+    }
+    const int w = 8 * k + xcd;
     return w < n_work ? w : kQueueEmpty;
 }
 
 // The next item of the queue with the most items left; kNoWork when every queue is empty.  Called by
 // one lane.  Counters are device-scope atomics (the dies' L2 caches are not coherent with
 // each other for plain accesses).
-__device__ __forceinline__ int stolen_work(WorkQueue *q, int n_work, int n_first)
+template <int STRIDE, bool FIRST> __device__ __forceinline__ int stolen_work(WorkQueue *q, int n_work, int n_first)
 {
     for (;;) {
         int best = -1, best_left = 0;
         for (int y = 0; y < 8; ++y) {
-            const int ky = __hip_atomic_load(&q->next[y], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            // items of queue y: ceil((n_work - y) / 8), without the first ones
-            const int left = (n_work - y + 7) / 8 - (n_first - y + 7) / 8 - ky;
+            const int ky = __hip_atomic_load(&q[STRIDE * y].next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const int left = (n_work - y + 7) / 8 - ky;  // items of queue y: ceil((n_work - y) / 8)
             if (left > best_left) { best_left = left; best = y; }
         }
         if (best < 0) return kNoWork;
-        const int k = __hip_atomic_fetch_add(&q->next[best], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const int w = queued_work(n_work, n_first, best, k);
+        const int w = counted_work<STRIDE, FIRST>(q, n_work, n_first, best, next_count<STRIDE>(q, best));
         if (w >= 0) return w;
         // someone else took its last item in between: look again (every failed attempt
         // means a queue has run empty, so this ends after at most eight rounds)
@@ -96,44 +137,73 @@ __device__ __forceinline__ int my_xcd() { return __builtin_amdgcn_readfirstlane(
 // the item's results are stored, because at the end of a launch, when most workgroups search at
 // once, it takes up to 20 us and held back the last stores (114 sequences of about 250 tokens, 32/8
 // heads of 128: the last items of the forward took 27 us instead of 7).
-// With `by_index` the first item is the one of the block index.  Blocks go to the compute units of a
-// die in turn, so the workgroups that share a unit start with items a third or half of the first
-// round apart; with items claimed in order of arrival a unit could start with three of the longest
-// (30,934 tokens in 3 sequences, 4/4 heads of 64: forward 0.64 ms claimed, 0.48 by index).  Where a
+// With FIRST the first item is the one of the block index, if nobody has taken it.  Blocks go to
+// the compute units of a die in turn, so the workgroups that share a unit start with items a third or
+// half of the first round apart; with items claimed in order of arrival a unit could start with three of the longest
+// (30,934 tokens in 3 sequences, 4/4 heads of 64: forward 547 us claimed, 503 by index).  Where a
 // unit holds one workgroup and the items are alike, the order of arrival staggers them a little, and
 // they run faster than in step (dK/dV, 27 sequences, 20,011 tokens, 32/8 heads of 128: 3 %).
-// `slot` is one int of LDS; the caller has a barrier between a `take` and the next `post`.
-struct WorkFeed {
+// `slot` is two ints of LDS; the caller has a barrier between a `take` and the next `post`.
+template <int STRIDE, bool FIRST> struct WorkFeed {
+    static constexpr bool kByIndex = FIRST;
     WorkQueue *q;
-    int n_work, n_first, pending;  // items; how many are taken by block index (the workgroups of the launch, or none)
-    int *slot;
+    int n_work, n_first, pending;  // items; how many of them are first items; the count asked for, or ~ an item
+    int *slot;                     // the next item; with FIRST also one more that this workgroup has taken, or -1
 
-    __device__ __forceinline__ int first()
+    // The first item.  `begin` sends the atomics, so that the loads of its descriptor are under way with
+    // them; `first` says which item it is.
+    __device__ __forceinline__ uint32_t begin()
     {
-        if (n_first > 0 || !q) return (int)blockIdx.x;
-        return again();
+        const int b = (int)blockIdx.x;
+        uint32_t marks = ~0u;
+        if (FIRST && q && b < n_first && threadIdx.x == 0) {
+            pending = next_count<STRIDE>(q, b & 7);
+            marks = mark_first<STRIDE>(q, b & 7, b >> 8, b >> 3 & 31);
+        }
+        return marks;
+    }
+    __device__ __forceinline__ int first(uint32_t marks)
+    {
+        const int b = (int)blockIdx.x;
+        if (!q) return b;
+        if (FIRST && threadIdx.x == 0) slot[1] = -1;
+        if (!FIRST || b >= n_first) return again();
+        if (threadIdx.x == 0) {
+            const bool own = !(marks >> (b >> 3 & 31) & 1);
+            slot[0] = b;
+            if (__builtin_expect(!own || pending >= (n_first - (b & 7) + 7) / 8, 0)) {
+                // late: another item instead, or, where others had the rights to all first items but had
+                // not marked this one, another item as well
+                const int w = counted_work<STRIDE, FIRST>(q, n_work, n_first, b & 7, pending);
+                slot[own ? 1 : 0] = w;
+            }
+        }
+        __syncthreads();
+        const int w = take();
+        return w == kQueueEmpty ? other() : w;
     }
     __device__ __forceinline__ void ask()
     {
         if (q && threadIdx.x == 0) {
-            // (an address the compiler cannot see to be uniform: for a uniform one it adds up the
-            // lanes that are on, one here, and waits for the answer at once to spread it to them)
-            uint32_t die;
-            int one;
-            asm volatile("v_mov_b32 %0, %2\n\tv_mov_b32 %1, 1" : "=v"(die), "=v"(one) : "s"(my_xcd()));
-            pending = __hip_atomic_fetch_add(&q->next[die], one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const int more = FIRST ? slot[1] : -1;
+            if (__builtin_expect(more >= 0, 0)) {
+                pending = ~more;
+                slot[1] = -1;
+            } else {
+                pending = next_count<STRIDE>(q, my_xcd());
+            }
         }
     }
     __device__ __forceinline__ void post()
     {
-        if (q && threadIdx.x == 0) *slot = queued_work(n_work, n_first, my_xcd(), pending);
+        if (q && threadIdx.x == 0) *slot = FIRST && pending < 0 ? ~pending : counted_work<STRIDE, FIRST>(q, n_work, n_first, my_xcd(), pending);
     }
     __device__ __forceinline__ int take() const { return q ? __builtin_amdgcn_readfirstlane(*slot) : kNoWork; }
     // after kQueueEmpty: an item of another die's queue
     __device__ __forceinline__ int other()
     {
         __syncthreads();  // everyone has read the slot
-        if (threadIdx.x == 0) *slot = stolen_work(q, n_work, n_first);
+        if (threadIdx.x == 0) *slot = stolen_work<STRIDE, FIRST>(q, n_work, n_first);
         __syncthreads();
         return take();
     }
@@ -150,11 +220,11 @@ struct WorkFeed {
     }
 };
 
-// Zeroes `n` work queues (a launch's queue must be zero when its kernel starts).
-static __global__ void queue_reset_kernel(WorkQueue *q, int n)
+// Zeroes `n` launches' work queues (they must be zero when their kernel starts).
+static __global__ void queue_reset_kernel(WorkQueue *q, int n, int stride)
 {
-    int32_t *w = (int32_t *)q;
-    for (int i = threadIdx.x; i < n * (int)(sizeof(WorkQueue) / 4); i += blockDim.x) w[i] = 0;
+    int4 *w = (int4 *)q;
+    for (int i = threadIdx.x; i < 8 * n; i += blockDim.x) w[i * stride] = make_int4(0, 0, 0, 0);
 }
 
 // Workgroups of `kernel` that the whole chip holds at once.

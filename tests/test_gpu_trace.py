@@ -90,3 +90,65 @@ def test_profiling_switch_belongs_to_the_calling_thread():
     with pytest.raises(B.SkrullError):
         B.skrull_attn_profile_read()          # switched off again
     plan.destroy()
+
+
+@pytest.mark.parametrize("what,d,wg", [("fwd", 128, 256), ("fwd", 64, 128), ("dq", 128, 256)])
+def test_longest_items_start_first_beside_another_launch(what, d, wg):
+    """Half of the compute units are held by another stream's launch when a forward / dQ with a work queue
+    starts, so half of its workgroups start late.  The longest items, one for every workgroup of the launch,
+    must not wait for those: on each die's list they begin before any item of its second half does."""
+    import time
+    import torch
+    from paper_2505_19609_amd import binding as B
+    from paper_2505_19609_amd.balance import REC
+
+    def tensors(plan, hq, hkv, d):
+        q, do = (torch.randn(plan.total_q, hq, d, device="cuda").bfloat16() for _ in range(2))
+        k, v = (torch.randn(plan.total_k, hkv, d, device="cuda").bfloat16() for _ in range(2))
+        return q, k, v, do, torch.empty_like(q), torch.empty((hq, plan.total_q), device="cuda")
+
+    # 128 workgroups that fill a compute unit's LDS and run for over a millisecond
+    hold = B.skrull_attn_plan([65536], [8], [7], 4, 1, 128, 128 ** -0.5, wg_query_rows=256)
+    assert B.skrull_attn_trace_layout(hold)[1][0] == 128
+    hq, hk, hv, _, ho, hlse = tensors(hold, 4, 1, 128)
+    S = [1500] * 24 + [40] * 600
+    plan = B.skrull_attn_plan(S, [1] * len(S), [0] * len(S), 8, 8, d, d ** -0.5, head_split=1, wg_query_rows=wg)
+    q, k, v, do, o, lse = tensors(plan, 8, 8, d)
+    dq, dk, dv = torch.empty_like(q), torch.empty_like(k), torch.empty_like(v)
+    ws = torch.empty(int(plan.bwd_workspace_bytes), dtype=torch.uint8, device="cuda")
+    first, num = B.skrull_attn_trace_layout(plan)
+    at = 0 if what == "fwd" else 1
+    longest = 256 * (3 if wg == 128 else 1)         # workgroups that the empty chip holds at once
+    for _ in range(4):                              # (two streams may share a hardware queue: then take others)
+        records = torch.zeros((sum(num), REC.itemsize), dtype=torch.uint8, device="cuda")
+        torch.cuda.synchronize()
+        other, mine = torch.cuda.Stream(), torch.cuda.Stream()
+        B.skrull_attn_fwd(plan, q, k, v, o, lse, stream=mine)  # (what a backward needs; a stream's first launch sets up its queue)
+        B.skrull_attn_fwd(hold, hq, hk, hv, ho, hlse, stream=other)
+        torch.cuda.synchronize()
+        B.skrull_attn_fwd(hold, hq, hk, hv, ho, hlse, stream=other)
+        time.sleep(2e-4)                            # (the other launch is under way)
+        B.skrull_attn_trace(records)
+        if what == "fwd":
+            B.skrull_attn_fwd(plan, q, k, v, o, lse, stream=mine)
+        else:
+            B.skrull_attn_bwd(plan, q, k, v, o, lse, do, dq, dk, dv, ws, stream=mine)
+        torch.cuda.synchronize()
+        B.skrull_attn_trace(None)
+        rec = records.cpu().numpy().view(REC).reshape(-1)[first[at]:first[at] + num[at]]
+        assert (rec["one"] == 1).all()
+        t0 = rec["t0"].astype(np.int64)
+        t0 -= t0.min()
+        unit = rec["xcc_id"].astype(np.int64) << 32 | rec["hw_id"] & 0xff00
+        units = len(np.unique(unit[t0 < 2000]))
+        print(f"{what} d {d}: {num[at]} items, on {units} compute units in the first 20 us; the longest {longest} begin by "
+              f"{t0[:longest].max() / 100:.0f} us, the second half from {t0[num[at] // 2:].min() / 100:.0f} us on")
+        if units <= 160:
+            break
+    else:
+        pytest.skip("the two launches did not run side by side")
+    for die in range(8):                            # (items die, die + 8, ... are one die's list)
+        mine = t0[die::8]
+        assert mine[:longest // 8].max() < mine[len(mine) // 2:].min(), die
+    hold.destroy()
+    plan.destroy()
