@@ -957,3 +957,25 @@ def test_long_dkv_items_are_shared_out(oracle, name):
     # output's own rounding beside the stated bound)
     _report("dV", out["dv"], dV, TOL_G, rtol=2.0 ** -8)
     out["plan"].destroy()
+
+
+def test_a_piece_of_a_shared_item_may_be_empty(oracle):
+    """672 keys in items of 256 (two passes of 128 each), blocks of 64 query rows, one head per group: the
+    last item (160 keys, three query blocks) is shared by two workgroups, and the one query tile that sees its
+    second pass leaves the first of them nothing to walk: its partial sums there are zero."""
+    from paper_2505_19609_amd import binding as B
+    w = W.Workload("empty_piece", [672], [1], [0], 2, 2, 128, 128 ** -0.5, 506)
+    out = run_library(w, block_m=64, block_n=256, guard=True)
+    assert out["margins"] == []
+    info = out["plan"].info
+    items = B.skrull_attn_plan_export(out["plan"], B.ARRAY_DKV_ITEMS)
+    assert [int(x) for x in items[:, 3]] == [11, 7, 3] and info.head_split == 1
+    # every item in parts: the workspace has rows for all three (of 256 keys)
+    base = (2 * 672 * 8 + 255) // 256 * 256 + 256
+    assert (info.bwd_workspace_bytes - base) % (2 * 3 * 256 * 2 * 128 * 4) == 0 and info.bwd_workspace_bytes > base
+    f = widen(out["vals"])
+    desc = oracle.ranges([672], [1], [0])
+    _, dK, dV, _ = oracle.attention_bwd(f["q"], f["k"], f["v"], f["do"], desc, w.softmax_scale)
+    _report("dK", out["dk"], dK, TOL_G)
+    _report("dV", out["dv"], dV, TOL_G)
+    out["plan"].destroy()

@@ -59,6 +59,19 @@ def test_static_workspace_gives_the_same_bits_on_two_calls_in_a_row():
     _both(small)
 
 
+@pytest.mark.parametrize("S,heads,d", [([2967], (4, 4), 64), ([1100, 37, 700], (3, 3), 128)])
+def test_static_workspace_holds_the_partial_sums_of_shared_items(S, heads, d):
+    """Plans that do not split the heads but share out their long dK/dV items keep the partial sums within the
+    array's size: both entry points run them and give the same bits."""
+    from paper_2505_19609_amd import binding as B
+    w = W.Workload("static_shared", S, [1] * len(S), [0] * len(S), heads[0], heads[1], d, d ** -0.5, 34)
+    plan = B.skrull_attn_plan(S, [1] * len(S), [0] * len(S), heads[0], heads[1], d, w.softmax_scale)
+    base = (heads[0] * sum(S) * 8 + 255) // 256 * 256 + 256
+    assert plan.info.head_split == 1 and base < plan.bwd_workspace_bytes <= B.STATIC_SCRATCH_BYTES
+    plan.destroy()
+    _both(w)
+
+
 def test_static_workspace_rejects_what_does_not_fit():
     from paper_2505_19609_amd import binding as B
     import torch
