@@ -110,7 +110,7 @@ struct FragAddr {
 // x < 2 * (query heads), and a row of heads is below 2^32 bytes; with a list of units x < 2,048 *
 // (2 g + 1) * d and there are at most SKRULL_UNIT_HEADS query heads.
 struct RowMap {
-    int32_t BM, g, Hkv, NW;       // query heads per KV head; waves of a workgroup
+    int32_t BM, g, Hkv;           // rows of an item; query heads per KV head; KV heads
     int32_t parts, spread;        // most workgroups per (item, KV head); 1: the order below
     const int32_t *units;         // null, or the work units: item | part << SKRULL_UNIT_SHIFT
     uint64_t inv_g, inv_hkv;
@@ -120,7 +120,7 @@ static inline uint64_t inverse_of(int d) { return ((1ull << 40) + d - 1) / d; }
 static inline RowMap row_map(const skrull_attn_plan_t *p, int NW)
 {
     const int g = p->Hq / p->Hkv;
-    return RowMap{p->BM, g, p->Hkv, NW, (p->BM / 32 * g + NW - 1) / NW, 0, p->units[NW == 8], inverse_of(g), inverse_of(p->Hkv)};
+    return RowMap{p->BM, g, p->Hkv, (p->BM / 32 * g + NW - 1) / NW, 0, p->units[NW == 8], inverse_of(g), inverse_of(p->Hkv)};
 }
 // Work items of a launch: with a list of units there are as many as have rows; without one every item
 // counts for its most parts, and those it does not have are passed over when their turn comes.  (In
@@ -139,7 +139,7 @@ __device__ __forceinline__ int quotient(int x, uint64_t inv) { return (int)(((ui
 
 struct RowBlocks {
     int c;                          // KV head
-    int qb, kvl, kbase;             // the segment: position of its first query, its keys, their first packed row
+    int kvl, kbase;                 // the segment: its keys, their first packed row
     int p0, qrow0, rows;            // the item: position and packed row of its first query, its rows
     int g, first, step, nblk;       // heads per KV head; row blocks of this part: first + wave * step
     uint64_t inv_g;
@@ -177,10 +177,9 @@ __device__ __forceinline__ RowBlocks row_blocks(const P prm, const int4 *items, 
     const i32x4 it = plan_value((const i32x4 *)items, __builtin_amdgcn_readfirstlane(item));
     const int seq = it.x;
     const int ql = plan_value(prm->q_len, seq);
-    r.qb = plan_value(prm->q_begin, seq);
+    r.p0 = plan_value(prm->q_begin, seq) + it.y * BM;
     r.kvl = plan_value(prm->kv_len, seq);
     r.kbase = plan_value(prm->cu_k, seq);
-    r.p0 = r.qb + it.y * BM;
     r.qrow0 = it.z;
     r.rows = min(BM, ql - it.y * BM);
     r.g = prm->rows.g;
@@ -284,23 +283,8 @@ __device__ __forceinline__ bf16x8 acc_to_b(const f32x16 &s, int kb)
     return as_bf16x8(pk);
 }
 
-// Store a 32-column (t) x 32-row accumulator tile set as bf16 rows of a
-// [rows, H, D] tensor: this lane's row pointer `dst` (column 0), its half h.
-template <int TT>
-__device__ __forceinline__ void store_rows_bf16(uint16_t *dst, const f32x16 (&acc)[TT], float mul, int h)
-{
-#pragma unroll
-    for (int tt = 0; tt < TT; ++tt)
-#pragma unroll
-        for (int vb = 0; vb < 4; ++vb) {
-            uint2 w;
-            w.x = pack_bf16(acc[tt][4 * vb + 0] * mul, acc[tt][4 * vb + 1] * mul);
-            w.y = pack_bf16(acc[tt][4 * vb + 2] * mul, acc[tt][4 * vb + 3] * mul);
-            *(uint2 *)(dst + 32 * tt + 8 * vb + 4 * h) = w;
-        }
-}
-
-// The same tile set as unrounded fp32 rows of a [rows, H, D] float tensor.
+// Store a 32-column (t) x 32-row accumulator tile set as unrounded fp32 rows of a [rows, H, D] float
+// tensor: this lane's row pointer `dst` (column 0), its half h.
 template <int TT>
 __device__ __forceinline__ void store_rows_f32(float *dst, const f32x16 (&acc)[TT], int h)
 {
