@@ -1083,16 +1083,11 @@ hipError_t launch_pair(const skrull_attn_plan_t *p, BwdParams prm, int threads_q
     // dQ first: it also leaves -D and LSE*log2(e) of every (head, row) in the workspace,
     // which dK/dV reads.  Events: ev[0] start, ev[1] after dQ, ev[2] after dK/dV.
     if (ev) (void)hipEventRecord(ev[0], st);
-    const bool queued_q = wants_queue<KernelQ>(threads_q, prm.n_work_dq);
-    const bool queued_kv = wants_queue<KernelKV>(threads_kv, prm.n_work_dkv);
+    const bool queued_q = prm.queue_dq != nullptr, queued_kv = wants_queue<KernelKV>(threads_kv, prm.n_work_dkv);
     if (queued_q || queued_kv) {
-        queue_reset_kernel<<<1, 64, 0, st>>>(prm.queue_dq, 2, kQueueStrideBwd);
+        queue_reset_kernel<<<1, 64, 0, st>>>(prm.queue_dkv - 8 * kQueueStrideBwd, 2, kQueueStrideBwd);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-    }
-    if (!queued_q) {
-        prm.queue_dq = nullptr;
-        prm.rows.spread = 1;
     }
     if (!queued_kv) prm.queue_dkv = nullptr;
     const int blocks_q = launch_size<KernelQ>(threads_q, prm.n_work_dq, queued_q);
@@ -1131,12 +1126,13 @@ hipError_t launch_d(const skrull_attn_plan_t *p, const BwdParams &prm, hipStream
 
 }  // namespace
 
-static int waves_dq(const skrull_attn_plan_t *p) { return small_dq_shape(p) ? NWQ_SMALL : NWQ_LARGE; }
-
-int grid_dq(const skrull_attn_plan_t *p)
+static RowLaunch rows_dq(const skrull_attn_plan_t *p)
 {
-    return row_work(p, waves_dq(p));
+    if (p->d == 128) return row_launch<dq_kernel<128, NWQ_LARGE>>(p, NWQ_LARGE);
+    return small_dq_shape(p) ? row_launch<dq_kernel<64, NWQ_SMALL>>(p, NWQ_SMALL) : row_launch<dq_kernel<64, NWQ_LARGE>>(p, NWQ_LARGE);
 }
+
+int grid_dq(const skrull_attn_plan_t *p) { return rows_dq(p).n_work; }
 
 static KeyMap map_dkv(const skrull_attn_plan_t *p)
 {
@@ -1156,7 +1152,8 @@ hipError_t launch_bwd(const skrull_attn_plan_t *p, const void *q, const void *k,
 {
     BwdParams prm;
     prm.trace_dq = trace;
-    prm.trace_dkv = trace ? trace + grid_dq(p) : nullptr;
+    const RowLaunch rows_q = rows_dq(p);
+    prm.trace_dkv = trace ? trace + rows_q.n_work : nullptr;
     prm.q = (const uint16_t *)q; prm.k = (const uint16_t *)k; prm.v = (const uint16_t *)v;
     prm.d_o = (const uint16_t *)d_o; prm.o = (const uint16_t *)o; prm.lse = lse; prm.delta = delta;
     prm.lse2 = delta + (size_t)p->Hq * p->total_q;
@@ -1165,18 +1162,19 @@ hipError_t launch_bwd(const skrull_attn_plan_t *p, const void *q, const void *k,
     prm.cu_q = p->cu_q; prm.cu_k = p->cu_k; prm.q_begin = p->q_begin; prm.q_len = p->q_len;
     prm.kv_len = p->kv_len; prm.shares_kv = p->shares_kv;
     prm.Hq = p->Hq; prm.Hkv = p->Hkv; prm.total_q = p->total_q;
-    prm.rows = row_map(p, waves_dq(p));
+    prm.rows = rows_q.rows;
     prm.keys = map_dkv(p);
     prm.scale = p->scale; prm.scale_log2 = p->scale * kLog2e;
     prm.total_k = p->total_k;
-    prm.n_work_dq = grid_dq(p);
+    prm.n_work_dq = rows_q.n_work;
     prm.n_work_dkv = grid_dkv(p);
     {
         // workspace: -D | LSE*log2e | (256-byte aligned) work queues of two launches in 256 bytes | dK partials | dV partials
         static_assert(2 * 8 * kQueueStrideBwd * sizeof(WorkQueue) == 256, "the queues' part of the workspace");
         const size_t rows = (((size_t)p->Hq * p->total_q * 8) + 255) & ~(size_t)255;
         prm.queue_dq = (WorkQueue *)((char *)delta + rows);
-        prm.queue_dkv = prm.queue_dq + 8;
+        prm.queue_dkv = prm.queue_dq + 8 * kQueueStrideBwd;
+        if (!rows_q.queued) prm.queue_dq = nullptr;
         prm.dk_part = (float *)((char *)delta + rows + 256);
         const size_t part_rows = p->split_compact ? (size_t)p->n_split * p->BN : (size_t)p->total_k;
         prm.dv_part = prm.dk_part + (size_t)p->split_parts * part_rows * p->Hkv * p->d;

@@ -505,16 +505,12 @@ __global__ __launch_bounds__(64 * NW, 2) void fwd_kernel(const FwdParams prm)
 template <auto Kernel>
 hipError_t launch_shape(FwdParams prm, int threads, hipStream_t st)
 {
-    const bool queued = wants_queue<Kernel>(threads, prm.n_work);
-    if (queued) {
+    if (prm.queue) {
         queue_reset_kernel<<<1, 64, 0, st>>>(prm.queue, 1, kQueueStrideFwd);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-    } else {
-        prm.queue = nullptr;
-        prm.rows.spread = 1;
     }
-    const int blocks = launch_size<Kernel>(threads, prm.n_work, queued);
+    const int blocks = launch_size<Kernel>(threads, prm.n_work, prm.queue != nullptr);
     prm.n_first = blocks < kMaxFirst ? blocks : kMaxFirst;
     Kernel<<<blocks, threads, 0, st>>>(prm);
     return hipGetLastError();
@@ -527,12 +523,18 @@ hipError_t launch_one(const FwdParams &prm, hipStream_t st)
     return launch_shape<fwd_kernel<D, NW_LARGE, NSLOT_LARGE>>(prm, 64 * NW_LARGE, st);
 }
 
+template <int D>
+RowLaunch rows_fwd(const skrull_attn_plan_t *p)
+{
+    if (p->wg_query_rows == 32 * NW_SMALL) return row_launch<fwd_kernel<D, NW_SMALL, NSLOT_SMALL>>(p, NW_SMALL);
+    return row_launch<fwd_kernel<D, NW_LARGE, NSLOT_LARGE>>(p, NW_LARGE);
+}
+
 }  // namespace
 
-int grid_fwd(const skrull_attn_plan_t *p)
-{
-    return row_work(p, p->wg_query_rows / 32);
-}
+static RowLaunch rows_fwd(const skrull_attn_plan_t *p) { return p->d == 128 ? rows_fwd<128>(p) : rows_fwd<64>(p); }
+
+int grid_fwd(const skrull_attn_plan_t *p) { return rows_fwd(p).n_work; }
 
 hipError_t launch_fwd(const skrull_attn_plan_t *p, const void *q, const void *k, const void *v,
                       void *o, float *lse, hipStream_t st, WgTrace *trace)
@@ -543,15 +545,17 @@ hipError_t launch_fwd(const skrull_attn_plan_t *p, const void *q, const void *k,
     prm.items = (const int4 *)p->fwd_items;
     prm.cu_k = p->cu_k; prm.q_begin = p->q_begin; prm.q_len = p->q_len; prm.kv_len = p->kv_len;
     prm.Hq = p->Hq; prm.Hkv = p->Hkv; prm.total_q = p->total_q;
-    prm.rows = row_map(p, p->wg_query_rows / 32);
+    const RowLaunch rows = rows_fwd(p);
+    prm.rows = rows.rows;
     prm.scale_log2 = p->scale * 1.4426950408889634f;
     prm.trace = trace;
     prm.variant = p->wg_query_rows == 32 * NW_SMALL ? 0 : 1;
-    prm.n_work = grid_fwd(p);
+    prm.n_work = rows.n_work;
     // One of the plan's queue slots per call, taken in turn, so that forward calls of one plan
     // that overlap on different streams do not share a queue.
     static_assert(8 * kQueueStrideFwd * sizeof(WorkQueue) == 4 * SKRULL_FWD_QUEUE_INTS, "a slot holds eight queues");
     prm.queue = p->fwd_queues + 8 * kQueueStrideFwd * (__atomic_fetch_add(&const_cast<skrull_attn_plan_t *>(p)->fwd_calls, 1u, __ATOMIC_RELAXED) % SKRULL_FWD_QUEUE_SLOTS);
+    if (!rows.queued) prm.queue = nullptr;
     if (p->d == 128) return launch_one<128>(prm, st);
     if (p->d == 64) return launch_one<64>(prm, st);
     return hipErrorInvalidValue;

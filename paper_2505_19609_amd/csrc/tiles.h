@@ -111,7 +111,7 @@ struct FragAddr {
 // (2 g + 1) * d and there are at most SKRULL_UNIT_HEADS query heads.
 struct RowMap {
     int32_t BM, g, Hkv;           // rows of an item; query heads per KV head; KV heads
-    int32_t parts, spread;        // most workgroups per (item, KV head); 1: the order below
+    int32_t parts, spread;        // most workgroups per (item, KV head); 1: see RowLaunch
     const int32_t *units;         // null, or the work units: item | part << SKRULL_UNIT_SHIFT
     uint64_t inv_g, inv_hkv;
 };
@@ -122,19 +122,39 @@ static inline RowMap row_map(const skrull_attn_plan_t *p, int NW)
     const int g = p->Hq / p->Hkv;
     return RowMap{p->BM, g, p->Hkv, (p->BM / 32 * g + NW - 1) / NW, 0, p->units[NW == 8], inverse_of(g), inverse_of(p->Hkv)};
 }
-// Work items of a launch: with a list of units there are as many as have rows; without one every item
-// counts for its most parts, and those it does not have are passed over when their turn comes.  (In
-// the forward of 114 sequences of about 250 tokens, 32/8 heads of 128, a quarter of all parts was
-// empty, most of them at the end of the list, where the claims for them held up everybody's: forward 240 ->
-// 232 us, dQ 318 -> 314.  64 sequences, 26,624 tokens, 14/2 heads of 64: 85 -> 81 and 100 -> 97.)
-static inline int row_work(const skrull_attn_plan_t *p, int NW)
+// How a forward / dQ launch is laid out.
+//  `spread`, for launches whose workgroups all run at once: neighbouring row blocks go to
+//    different workgroups, so that a workgroup has few waves at work near its last key and the longest
+//    chain, which is then the time of the launch, runs with the least company.
+//  A launch that fits the chip with one workgroup per head (and 32 NW rows) has that many: the row blocks
+//    of a short item are fewer waves each then, and there is no list of units to look into.  (One sequence
+//    of 600 tokens, 14/2 heads of 64: forward 14.8 us and dQ 16.8 with its blocks eight to a workgroup, 12.9
+//    and 14.7 this way; sequences of 700, 300 and 900, 28/4 heads of 128: 29.7 and 38.7, 28.8 and 37.0.)
+//  Else the work items are the units that have rows; without a list of units every item counts for its
+//    most parts, and those it does not have are passed over when their turn comes.  (In
+//    the forward of 114 sequences of about 250 tokens, 32/8 heads of 128, a quarter of all parts was
+//    empty, most of them at the end of the list, where the claims for them held up everybody's: forward
+//    240 -> 232 us, dQ 318 -> 314.  64 sequences, 26,624 tokens, 14/2 heads of 64: 85 -> 81 and 100 -> 97.)
+struct RowLaunch {
+    RowMap rows;
+    int n_work;   // what a plain grid has as workgroups
+    bool queued;  // more than the chip holds at once
+};
+template <auto Kernel>
+static RowLaunch row_launch(const skrull_attn_plan_t *p, int NW)
 {
-    return p->units[NW == 8] ? p->n_units[NW == 8] * p->Hkv : p->n_fwd * p->Hkv * row_map(p, NW).parts;
+    RowLaunch r{row_map(p, NW), 0, false};
+    const int resident = resident_of<Kernel>(64 * NW);
+    const int per_head = (p->BM + 32 * NW - 1) / (32 * NW);  // workgroups of an item's rows of one head
+    if ((int64_t)p->n_fwd * p->Hq * per_head <= resident) {
+        r.rows.units = nullptr;
+        r.rows.parts = r.rows.g * per_head;
+    }
+    r.n_work = r.rows.units ? p->n_units[NW == 8] * p->Hkv : p->n_fwd * p->Hkv * r.rows.parts;
+    r.queued = resident > 0 && r.n_work > resident;
+    r.rows.spread = !r.queued;
+    return r;
 }
-// `spread`, for launches whose workgroups all run at once: neighbouring row blocks go to
-// different workgroups, so that a workgroup has few waves at work near its last key and the longest
-// chain, which is then the time of the launch, runs with the least company (sequences of 300 and
-// 212 tokens, 14/2 heads of 64: forward 12.9 us in the order above, 11.4 in this one).
 __device__ __forceinline__ int quotient(int x, uint64_t inv) { return (int)(((uint64_t)(uint32_t)x * inv) >> 40); }
 
 struct RowBlocks {
@@ -185,8 +205,8 @@ __device__ __forceinline__ RowBlocks row_blocks(const P prm, const int4 *items, 
     r.g = prm->rows.g;
     r.inv_g = prm->rows.inv_g;
     r.nblk = (r.rows + 31) / 32;
-    const int parts = (r.nblk * r.g + NW - 1) / NW;  // of this item
     const bool spread = prm->rows.spread != 0;
+    const int parts = spread && !units ? min(prm->rows.parts, r.nblk * r.g) : (r.nblk * r.g + NW - 1) / NW;  // of this item
     r.first = part >= parts ? r.nblk * r.g : (spread ? part : part * NW);  // (past the end: the item has no such part)
     r.step = spread ? parts : 1;
     return r;

@@ -979,3 +979,27 @@ def test_a_piece_of_a_shared_item_may_be_empty(oracle):
     _report("dK", out["dk"], dK, TOL_G)
     _report("dV", out["dv"], dV, TOL_G)
     out["plan"].destroy()
+
+
+@pytest.mark.parametrize("S,heads,d,wg", [([600], (14, 2), 64, 256), ([300, 212], (14, 2), 64, 128),
+                                          ([700, 300, 900], (28, 4), 128, 256), ([33, 64, 1], (12, 1), 128, 128),
+                                          ([700, 300, 900, 33], (28, 4), 128, 256)])
+def test_small_launches_have_a_workgroup_per_head(oracle, S, heads, d, wg):
+    """Forward and dQ launches that the chip holds at once with one workgroup per head and 256 (128) query rows
+    have that many, so that a short item's row blocks are few waves each; one item more than fits (the last
+    case) and the row blocks of a KV group are put together, as many as a workgroup has waves."""
+    from paper_2505_19609_amd import binding as B
+    import torch
+    w = W.Workload("small_launch", S, [1] * len(S), [0] * len(S), heads[0], heads[1], d, d ** -0.5, 606)
+    # (with 12 heads in a group dV is large where few rows see a key: the stated bound plus the output's
+    # own rounding, half a bf16 spacing, at most 2^-8 of it)
+    out = _exhaustive(oracle, w, rtol=2.0 ** -8, wg_query_rows=wg, head_split=1, keep=True)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    num = B.skrull_attn_trace_layout(out["plan"])[1]
+    for n, rows, per_unit in ((num[0], wg, 1 if wg == 256 else 2), (num[1], wg if d == 64 else 256, 1)):
+        per_head = out["plan"].info.n_fwd_items * heads[0] * (256 // rows)
+        if per_head <= cus:
+            assert n == per_head
+        elif per_head > per_unit * cus:
+            assert n < per_head
+    out["plan"].destroy()
