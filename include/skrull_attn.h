@@ -64,7 +64,8 @@ typedef struct {
     int32_t        block_n;       /* key rows per dK/dV work item: 64, 128, 192 or 256; 0 = library's choice */
     const int32_t *shard_cut;     /* [K] HOST or NULL (= all SKRULL_CUT_CONTIGUOUS)             */
     int32_t        head_split;    /* dK/dV workgroups per KV group, 1..Hq/Hkv; 0 = library's choice */
-    int32_t        wg_query_rows; /* query rows per forward / dQ workgroup: 128 or 256; 0 = library's choice */
+    int32_t        wg_query_rows; /* query rows per forward / dQ workgroup, in blocks of 32 rows of one head, of any
+                                     heads of a KV group: 128 or 256; 0 = library's choice */
 } skrull_attn_problem_t;
 
 /*
@@ -94,9 +95,11 @@ typedef struct {
     int64_t attended_pairs;       /* exact number of (query, key) pairs under the causal mask  */
     int64_t useful_flops_fwd;     /*  4 * pairs * head_dim * Hq                                */
     int64_t useful_flops_bwd;     /* 10 * pairs * head_dim * Hq                                */
-    int64_t bwd_workspace_bytes;  /* device scratch skrull_attn_bwd needs (>= 0)               */
+    int64_t bwd_workspace_bytes;  /* device scratch skrull_attn_bwd asks for (>= 0)            */
     int32_t num_segments;         /* query segments: K + number of two-chunk sequences         */
-    int32_t head_split;           /* the dK/dV head split in effect (>= 1; see skrull_attn_plan) */
+    int32_t head_split;           /* most workgroups that share a dK/dV item by its heads (>= 1; see
+                                     skrull_attn_plan); the workspace has room for so many partial
+                                     sums of every row of K, also where fewer items are shared  */
     int32_t wg_query_rows;        /* query rows per forward / dQ workgroup in effect (128 or 256;
                                      dQ has the 128-row shape at head_dim 64 only)             */
     int32_t reserved;             /* 0                                                         */
@@ -140,10 +143,11 @@ enum {
  * compute unit, or a costliest item under 0.7 of the even share; the dK/dV
  * kernel then runs 12 wavefronts over 192 key rows); head_split above 1
  * when the longest dK/dV chain exceeds an even share of the work list (the library then
- * shares out the items with long chains only, over up to that many workgroups; a head_split
- * the caller gives holds for every item; with a choice of 1 items may still be shared over
- * up to 8 when the longest chain exceeds an even share and the partial sums fit
- * SKRULL_STATIC_SCRATCH_BYTES with the rest of the workspace);
+ * shares out the items with long chains only, over up to that many workgroups, or none if no
+ * chain is long enough; a head_split the caller gives holds for every item; with a choice of 1
+ * items may still be shared over up to 8 when the longest chain exceeds 1.1 even shares by
+ * enough to pay for the partial sums, and these fit SKRULL_STATIC_SCRATCH_BYTES with the rest
+ * of the workspace);
  * wg_query_rows 128 when the micro-batch holds enough work for the smaller
  * workgroups to pay (head_dim 64: at least 24 blocks of 256 query rows x heads
  * per compute unit or 1.5e9 attended (query, key, head) triples; head_dim 128:

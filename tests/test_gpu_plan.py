@@ -115,3 +115,22 @@ def test_plan_long_lists_are_radix_sorted(oracle, longest, passes):
         N[7], R[7] = 1, 0
     assert 2 * (longest // 64 + 2) >= 256 ** (passes - 1) and 2 * (longest // 64 + 2) < 256 ** passes
     _check(oracle, S, N, R, 1, 1, 64, 64, 64)
+
+
+@pytest.mark.parametrize("S,N,R,shared", [([19104] + [300] * 30, 8, 3, False), ([19104], 8, 3, False),
+                                          ([12000] + [300] * 280, 1, 0, True), ([2967], 1, 0, True)])
+def test_items_are_shared_out_only_where_that_pays(S, N, R, shared):
+    """With one head per group, sharing a dK/dV item costs fp32 partial sums.  The plan leaves the items of a
+    slice of a long sequence (chains of ten blocks, 1.1 and 1.4 even shares) to one workgroup each, and shares
+    those of a chain of 47 blocks at the same ratio and of one with nothing beside it."""
+    from paper_2505_19609_amd import binding as B
+    import torch
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the shares are those of 256 compute units")
+    K = len(S)
+    plan = B.skrull_attn_plan(S, [N] + [1] * (K - 1), [R] + [0] * (K - 1), 4, 4, 64, 0.125)
+    items = B.skrull_attn_plan_export(plan, B.ARRAY_DKV_ITEMS)
+    assert int(items[:, 3].max()) * 256 > 1.1 * int(items[:, 3].sum()) * 4 and plan.info.head_split == 1
+    base = (4 * plan.info.total_q * 8 + 255) // 256 * 256 + 256
+    assert (plan.bwd_workspace_bytes > base) == shared
+    plan.destroy()
