@@ -350,14 +350,16 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
     // unit hide each other's start-up, drain and barriers, but they also stretch each other's
     // work items (three share a unit and its oldest wave is served first), and a launch ends only
     // when its last stretched item does; so the small shape pays once the launch holds enough
-    // work to bury that tail.  Measured on 8 to 64 query heads x 16,384 to 32,768 tokens x
-    // sequences of 256 to 32,768 tokens: at head_dim 64 the small shape wins (forward by 3-15 %,
-    // dQ by 1-6 %) when the micro-batch has at least 24 blocks of 256 query rows x heads per
-    // compute unit or at least 1.5e9 attended (query, key, head) triples, and loses by 2-90 %
-    // (forward) below that; at head_dim 128 (forward only: the small dQ shape does not fit the LDS
-    // twice) it wins by 1-8 % from 16 such blocks per compute unit on while no sequence exceeds
-    // 8,192 tokens, where the 8-wavefront workgroup's deeper tile ring and halved tile traffic
-    // take over.
+    // work to bury that tail: at head_dim 64 from 24 blocks of 256 query rows x heads per compute unit or
+    // 1.5e9 attended (query, key, head) triples on, at head_dim 128 (forward only: the small dQ shape
+    // does not fit the LDS twice) from 16 such blocks on while no sequence exceeds 8,192 tokens, where the
+    // 8-wavefront workgroup's deeper tile ring and halved tile traffic take over.  Measured on 8 to 64
+    // query heads x 16,384 to 32,768 tokens x sequences of 256 to 32,768 tokens (profiles/shape_sweep_wg.txt):
+    // where this picks it the small forward is 4-15 % faster at head_dim 64 (dQ within 1.6 %) and up to 10 %
+    // at 128, 0.3 % slower at worst; where it does not, the small dQ loses up to 25 % at head_dim 64 while
+    // the small forward is between 14 % faster and 5 % slower (one choice serves both), and at 128 the
+    // forward is between 9 % faster (few heads) and 3 % slower.  Forward and dQ together: 0.6 % behind the better
+    // shape on average, 7 % at worst.
     if (p->wg_query_rows != 0) {
         plan->wg_query_rows = p->wg_query_rows;
     } else {

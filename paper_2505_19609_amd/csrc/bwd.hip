@@ -527,7 +527,7 @@ __device__ __forceinline__ void ds_quad(uint32_t p01, uint32_t p23, const float 
 }
 
 // PAIRS wave pairs per workgroup: 4 (8 wavefronts, 128 key rows, two wavefronts per SIMD), or,
-// at head_dim 64 where 136 registers and 106 KB of LDS allow it, 6 (12 wavefronts, 192 key
+// at head_dim 64 where 157 registers and 106 KB of LDS allow it, 6 (12 wavefronts, 192 key
 // rows, three per SIMD): more wavefronts to overlap with and a third fewer fetches of each
 // query tile.  The 12-wavefront shape serves work items of block_n = 192.
 constexpr int PAIRS_8W = 4, PAIRS_12W = 6;

@@ -286,7 +286,8 @@ __global__ __launch_bounds__(256) void plan_emit_kernel(
 // partial sums (as much as one to two blocks' rounds), so short parts are dear, and units that are
 // long against an even share s of the whole list per compute unit balance badly.  The first loss
 // falls and the second grows with the length: sqrt(8 s), at least 2 blocks and, at head_dim 64, at
-// most 13.  Swept over 0.2 to 20 times that on 60 micro-batches of s = 0.2 to 580 blocks.
+// most 13.  On 82 micro-batches a quarter, half, twice and four times that change dK/dV on 22, by
+// +9, +4, +1 and +28 % on (geometric) average (profiles/chain_limit_sweep.txt).
 __device__ inline void count_chain(int32_t cost, int32_t group, int32_t q_heads, int32_t head_dim,
                                    int32_t compute_units, PlanTotals *totals)
 {
@@ -491,8 +492,9 @@ hipError_t launch_plan_ranges(const int32_t *S, const int32_t *N, const int32_t 
 }
 
 // Above this many items (the host's upper bound) a list is sorted by radix passes instead of
-// by rank counting, which is quadratic (measured: 0.25 ms for 5,000 items, 3 ms for 16,000; the
-// radix passes take 0.05 ms there).
+// by rank counting, which is quadratic: both lists together take 5 us at 64 items of dK/dV, 9 at 256, 26 at
+// 1,024 and 47 at 2,000; one radix pass takes 95 us at 2,060 and 121 at 4,000.  (The line could lie a little
+// higher, but the lists of units hold an item's position in SKRULL_UNIT_SHIFT bits.)
 constexpr int32_t kRankSortMax = 1 << SKRULL_UNIT_SHIFT;
 
 int plan_radix_passes(int32_t cap, int32_t cost_bound)

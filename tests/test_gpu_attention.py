@@ -899,10 +899,10 @@ def test_row_blocks_of_a_group_in_both_orders(oracle, heads, d, wg, bm):
 
 
 @pytest.mark.parametrize("wg", [128, 256])
-@pytest.mark.parametrize("rep", [7, 114, 228])
+@pytest.mark.parametrize("rep", [7, 8, 114, 228])
 def test_units_of_lists_of_several_lengths(oracle, wg, rep):
     """Forward and dQ take their work from the list of units that the plan's sort leaves: within one tile of
-    the sort (63 items), across two (1,026), and in a list too long for it (2,052), which has none.  Items of
+    the sort (63 and 72 items), across two (1,026), and in a list too long for it (2,052), which has none.  Items of
     1 to 8 row blocks of 3 heads; the sequences of a checked small micro-batch, repeated, give the same bits."""
     S, heads, d = [1, 31, 32, 33, 255, 257, 300], (6, 2), 64
     w = W.Workload("units", S, [1] * 7, [0] * 7, heads[0], heads[1], d, d ** -0.5, 405)
