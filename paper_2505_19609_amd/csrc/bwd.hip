@@ -65,7 +65,6 @@ struct BwdParams {
     WgTrace *trace_dq, *trace_dkv;  // null, or one record per work item (measurement aid)
     WorkQueue *queue_dq, *queue_dkv;  // work queues of the persistent launches (workspace), zeroed before use
     int32_t n_work_dq, n_work_dkv;    // work items: what a plain grid would have as workgroups
-    int32_t n_first_dq;               // workgroups of the dQ launch
 };
 
 // ---------------------------------------------------------------------------
@@ -115,13 +114,11 @@ __device__ __forceinline__ uint32_t ds_mul_pack(float t0, float t1, float g0, fl
 // B(j).  B(j) reads the transposed K of the half tile BEFORE the one A(j+1) reads,
 // which is why the K ring has one slot more than the V ring.  Steps at the start, the
 // end and the causal diagonal of a wave's range take a plain path with guards.
-// dQ's first items are taken by index where that is faster: by 0 to 4 % at 128, but 0 to 2 % slower at 64
-template <int D> using DqFeed = WorkFeed<kQueueStrideBwd, D == 128>;
-using DkvFeed = WorkFeed<kQueueStrideBwd, false>;
+using BwdFeed = WorkFeed<kQueueStrideBwd, false>;
 
 // Does work item `bid`, whose rows are `rb`; returns the next one and leaves its rows in `rb`.
 template <int D, int NWQ>
-__device__ __forceinline__ int dq_work(const int bid, RowBlocks &rb, DqFeed<D> &feed)
+__device__ __forceinline__ int dq_work(const int bid, RowBlocks &rb, BwdFeed &feed)
 {
     const kernarg_t<BwdParams> prm = kernarg<BwdParams>();
     constexpr bool SMALL = NWQ == NWQ_SMALL;
@@ -441,13 +438,9 @@ template <int D, int NWQ>
 __global__ __launch_bounds__(64 * NWQ, 2) void dq_kernel(const BwdParams prm)
 {
     __shared__ int work_slot[2];
-    constexpr bool BY_INDEX = DqFeed<D>::kByIndex;
-    DqFeed<D> feed{prm.queue_dq, prm.n_work_dq, BY_INDEX ? prm.n_first_dq : 0, 0, work_slot};
-    const uint32_t marks = feed.begin();
-    RowBlocks rb{};
-    if (BY_INDEX) rb = uniform(row_blocks<NWQ>(kernarg<BwdParams>(), prm.fwd_items, (int)blockIdx.x));
-    int w = feed.first(marks);
-    if (!BY_INDEX || w != (int)blockIdx.x) rb = row_blocks<NWQ>(kernarg<BwdParams>(), prm.fwd_items, max(w, 0));
+    BwdFeed feed{prm.queue_dq, prm.n_work_dq, 0, 0, work_slot};
+    int w = feed.first(feed.begin());
+    RowBlocks rb = row_blocks<NWQ>(kernarg<BwdParams>(), prm.fwd_items, max(w, 0));
     while (w >= 0) {
         if (rb.has(0)) {
             w = dq_work<D, NWQ>(w, rb, feed);
@@ -592,7 +585,7 @@ __device__ __forceinline__ KeyBlock key_block(const P prm, int SUB, int bid)
 
 // Does work item `bid`, whose keys are `kb`; returns the next one and leaves its keys in `kb`.
 template <int D, int PAIRS>
-__device__ __forceinline__ int dkv_work(const int bid, KeyBlock &kb, DkvFeed &feed)
+__device__ __forceinline__ int dkv_work(const int bid, KeyBlock &kb, BwdFeed &feed)
 {
     const kernarg_t<BwdParams> prm = kernarg<BwdParams>();
     constexpr int NWP = 2 * PAIRS;   // wavefronts: PAIRS S waves, then PAIRS dP waves
@@ -1020,7 +1013,7 @@ template <int D, int PAIRS>
 __global__ __launch_bounds__(128 * PAIRS, PAIRS == PAIRS_12W ? 3 : 2) void dkv_kernel(const BwdParams prm)
 {
     __shared__ int work_slot[2];
-    DkvFeed feed{prm.queue_dkv, prm.n_work_dkv, 0, 0, work_slot};
+    BwdFeed feed{prm.queue_dkv, prm.n_work_dkv, 0, 0, work_slot};
     int w = feed.first(feed.begin());
     KeyBlock kb = key_block(kernarg<BwdParams>(), 32 * PAIRS, max(w, 0));
     while (w >= 0) {
@@ -1091,9 +1084,7 @@ hipError_t launch_pair(const skrull_attn_plan_t *p, BwdParams prm, int threads_q
         if (e != hipSuccess) return e;
     }
     if (!queued_kv) prm.queue_dkv = nullptr;
-    const int blocks_q = launch_size<KernelQ>(threads_q, prm.n_work_dq, queued_q);
-    prm.n_first_dq = blocks_q < kMaxFirst ? blocks_q : kMaxFirst;
-    KernelQ<<<blocks_q, threads_q, 0, st>>>(prm);
+    KernelQ<<<launch_size<KernelQ>(threads_q, prm.n_work_dq, queued_q), threads_q, 0, st>>>(prm);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (ev) (void)hipEventRecord(ev[1], st);

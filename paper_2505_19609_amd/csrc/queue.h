@@ -12,8 +12,8 @@
 // the end are the smallest items: the paper's rule (Alg. 1: the next piece goes to argmin of
 // the loads) applied across dies at run time, since their speeds are not known beforehand.
 //
-// The longest items, as many as a launch has workgroups ("first items"), carry a mark each that says
-// whether they are taken, and a die's first counts, one for each of its first items, stand for any of
+// In the forward the longest items, as many as a launch has workgroups ("first items"), carry a mark each that
+// says whether they are taken, and a die's first counts, one for each of its first items, stand for any of
 // those that has no mark yet.  So a workgroup takes the item of its block index when it starts, but one that
 // starts late, for instance because another stream's kernel holds its compute unit, has kept it from nobody.
 // (Without marks, with half of the chip held by another launch, the items of the workgroups that had to wait
@@ -142,10 +142,11 @@ __device__ __forceinline__ int my_xcd() { return __builtin_amdgcn_readfirstlane(
 // half of the first round apart; with items claimed in order of arrival a unit could start with three of the longest
 // (30,934 tokens in 3 sequences, 4/4 heads of 64: forward 547 us claimed, 503 by index).  Where a
 // unit holds one workgroup and the items are alike, the order of arrival staggers them a little, and
-// they run faster than in step (dK/dV, 27 sequences, 20,011 tokens, 32/8 heads of 128: 3 %).
+// they run faster than in step (dK/dV, 27 sequences, 20,011 tokens, 32/8 heads of 128: 3 %).  dQ claims
+// too: by index it was as fast at head_dim 128 without marks, but with them 1 to 3 % slower on short lists,
+// because the backward's counts share a line.
 // `slot` is two ints of LDS; the caller has a barrier between a `take` and the next `post`.
 template <int STRIDE, bool FIRST> struct WorkFeed {
-    static constexpr bool kByIndex = FIRST;
     WorkQueue *q;
     int n_work, n_first, pending;  // items; how many of them are first items; the count asked for, or ~ an item
     int *slot;                     // the next item; with FIRST also one more that this workgroup has taken, or -1
