@@ -135,7 +135,7 @@ void choose_split(skrull_attn_plan_t *plan, int32_t asked, const PlanTotals &tot
     plan->split_compact = plan->head_split == 1;
     if (plan->split_compact && 10 * longest * compute_units <= 11 * (int64_t)totals.dkv_cost_sum * plan->Hq) return;
     // Microseconds: a block of 256 query rows of one head takes a workgroup 6, the partial sums are written
-    // and read at 4.4 TB/s, and a part's start and end take 6, or 2 where compute units are idle beside it.
+    // and read at 4.4 TB/s, and a part's start and end take 6, or 1 where compute units are idle beside it.
     // Measured on 170 micro-batches of ratios from 1.1 up, shared against whole: where this says no, up to 27 %
     // slower (a slice of 2,388 tokens, 4/4 heads of 64, ratio 1.43 and 33 MB: 86 us shared, 68 whole); where
     // it says yes, 3 % slower (a microsecond of 40) to 50 % faster (28/4 heads of 128, ratio 1.14 and 17 MB:
@@ -143,7 +143,7 @@ void choose_split(skrull_attn_plan_t *plan, int32_t asked, const PlanTotals &tot
     auto pays = [&](int64_t limit) {
         const double share = (double)totals.dkv_cost_sum * plan->Hq / compute_units;
         const double saved = (double)longest - (share > (double)limit ? share : (double)limit);
-        return 6.0 * saved > ((double)longest < 2.0 * share ? 6.0 : 2.0) + 2.0 * (double)partial_bytes(plan) / 4.4e6;
+        return 6.0 * saved > ((double)longest < 2.0 * share ? 6.0 : 1.0) + 2.0 * (double)partial_bytes(plan) / 4.4e6;
     };
     const int32_t most = plan->split_compact ? kMaxParts : plan->head_split;
     // When the longest part is then still as long as three quarters of an even share, all items are cut
