@@ -138,9 +138,13 @@ def _stream_ptr(stream):
     forward call cost the host.  That function is private to torch, so it may be missing.)"""
     if stream is None:
         import torch
-        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-        if raw is not None and torch.cuda.is_initialized():
-            return raw(torch.cuda.current_device())
+        if torch.cuda.is_initialized():
+            try:
+                raw = torch._C._cuda_getCurrentRawStream
+            except AttributeError:
+                pass
+            else:
+                return raw(torch.cuda.current_device())
         stream = torch.cuda.current_stream()
     return int(getattr(stream, "cuda_stream", stream))
 
