@@ -50,7 +50,6 @@ struct TraceState {
 };
 thread_local TraceState g_trace;
 
-constexpr int32_t kMaxParts = 8;  // workgroups that may share one dK/dV item
 constexpr int32_t kMaxItems = 1 << 20;  // per list (lists above 2,048 items are radix sorted)
 
 // Workspace of skrull_attn_bwd_static, the backward entry point for callers that cannot
@@ -90,85 +89,6 @@ int check_device(int *dev_out, int *compute_units)
     *dev_out = dev;
     *compute_units = prop.multiProcessorCount;
     return SKRULL_OK;
-}
-
-// Bytes of backward scratch without partial sums: -D and LSE*log2(e) per (head, row), then 256
-// bytes for the work queues of the two kernels.
-int64_t base_workspace(const skrull_attn_plan_t *plan)
-{
-    return ((((int64_t)plan->Hq * plan->total_q * 8) + 255) & ~(int64_t)255) + 256;
-}
-
-// fp32 partial dK and dV of the items that several workgroups share: a slot per part for every row of
-// K, or for the rows of those items only.
-int64_t partial_bytes(const skrull_attn_plan_t *plan)
-{
-    if (plan->split_parts <= 1) return 0;
-    const int64_t rows = plan->split_compact ? (int64_t)plan->n_split * plan->BN : plan->total_k;
-    return 2 * (int64_t)plan->split_parts * rows * plan->Hkv * plan->d * 4;
-}
-
-// Which dK/dV items are shared out over several workgroups.  A head split the caller asked for holds
-// for every item.  The library's own shares out only items with a long chain: split over the heads,
-// every item of a short sequence cost seven starts, seven ends and seven fp32 partial sums instead of
-// one store (64 sequences, 26,624 tokens, 14/2 heads of 64: dK/dV 202 us all items split 7 ways,
-// 146 this way; 20 sequences, 16,384 tokens: 184 -> 162), and where the heads cannot be split evenly
-// the longest chain was the kernel's time (10 sequences, 13,312 tokens, 28/4 heads of 128: 640 -> 530;
-// one of 2,967, 4/4 heads of 64: 69 -> 36).
-void choose_split(skrull_attn_plan_t *plan, int32_t asked, const PlanTotals &totals, int32_t compute_units)
-{
-    const int32_t group = plan->Hq / plan->Hkv;
-    plan->n_split = plan->n_whole_first = plan->split_chain = plan->split_compact = 0;
-    plan->split_parts = 1;
-    if (asked != 0) {
-        if (asked > 1) {
-            plan->split_parts = asked;
-            plan->n_split = plan->n_dkv;
-        }
-        return;
-    }
-    const int64_t longest = (int64_t)totals.dkv_cost_max * group;
-    // Where the heads are not split (nor could be: one head per group, or seven, which would be too many)
-    // items are shared out only if the longest chain exceeds 1.1 even shares, if its shortening saves more
-    // than the partial sums cost, and as few as it takes for these to fit the static workspace, so that a
-    // plan that skrull_attn_bwd_static takes without them is not refused for them.
-    plan->split_compact = plan->head_split == 1;
-    if (plan->split_compact && 10 * longest * compute_units <= 11 * (int64_t)totals.dkv_cost_sum * plan->Hq) return;
-    // Microseconds: a block of 256 query rows of one head takes a workgroup 6, the partial sums are written
-    // and read at 4.4 TB/s, and a part's start and end take 6, or 1 where compute units are idle beside it.
-    // Measured on 170 micro-batches of ratios from 1.1 up, shared against whole: where this says no, up to 27 %
-    // slower (a slice of 2,388 tokens, 4/4 heads of 64, ratio 1.43 and 33 MB: 86 us shared, 68 whole); where
-    // it says yes, 3 % slower (a microsecond of 40) to 50 % faster (28/4 heads of 128, ratio 1.14 and 17 MB:
-    // 662 us shared, 816 whole; one sequence of 2,967, 4/4 heads of 64, ratio 7 and 19 MB: 34 and 69).
-    auto pays = [&](int64_t limit) {
-        const double share = (double)totals.dkv_cost_sum * plan->Hq / compute_units;
-        const double saved = (double)longest - (share > (double)limit ? share : (double)limit);
-        return 6.0 * saved > ((double)longest < 2.0 * share ? 6.0 : 1.0) + 2.0 * (double)partial_bytes(plan) / 4.4e6;
-    };
-    const int32_t most = plan->split_compact ? kMaxParts : plan->head_split;
-    // When the longest part is then still as long as three quarters of an even share, all items are cut
-    // as fine as it is: what else runs has to fit beside it (3 sequences, 7,417 tokens, 14/2 heads of
-    // 64: dK/dV 137 us all cut, 145 by the limits below).
-    if (!plan->split_compact && 4 * longest * compute_units >= 3 * most * (int64_t)totals.dkv_cost_sum * plan->Hq) {
-        plan->split_parts = most;
-        plan->n_split = plan->n_dkv;
-        return;
-    }
-    int32_t above[SKRULL_CHAIN_LIMITS + 1];  // items that exceed limit k
-    above[SKRULL_CHAIN_LIMITS] = 0;
-    for (int k = SKRULL_CHAIN_LIMITS - 1; k >= 0; --k) above[k] = above[k + 1] + totals.chain_hist[k + 1];
-    for (int k = 2; k < SKRULL_CHAIN_LIMITS; ++k) {
-        const int64_t limit = dkv_chain_limit(totals.chain_base, k), want = (longest + limit - 1) / limit;
-        if (want < 2) break;
-        plan->split_parts = want > most ? most : (int32_t)want;
-        plan->split_chain = (int32_t)(limit > INT32_MAX ? INT32_MAX : limit);
-        plan->n_split = above[k];
-        plan->n_whole_first = above[k - 2] - above[k];
-        if (!plan->split_compact ||
-            (pays(limit) && base_workspace(plan) + partial_bytes(plan) <= (int64_t)SKRULL_STATIC_SCRATCH_BYTES)) return;
-    }
-    plan->split_parts = 1;
-    plan->n_split = plan->n_whole_first = 0;
 }
 
 // A plan's arrays live on the device it was made on: the calls that use them must run there.
@@ -275,7 +195,7 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
     const int64_t queue_ints = SKRULL_FWD_QUEUE_INTS * SKRULL_FWD_QUEUE_SLOTS;  // work queues of the forward launches
     int32_t *fwd_off = nullptr, *dkv_off = nullptr, *scratch = nullptr;
     PlanTotals *totals_d = nullptr;
-    int64_t unit_ints[2] = {0, 0};
+    int64_t unit_ints[2] = {0, 0}, dkv_unit_ints = 0;
 
     plan = new (std::nothrow) skrull_attn_plan_t();
     if (!plan) return SKRULL_ENOMEM;
@@ -293,7 +213,8 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
     HIP_TRY(hipMalloc((void **)&tmp, (size_t)tmp_ints * sizeof(int32_t)));
     unit_ints[0] = plan_unit_ints(plan, (int32_t)cap_fwd, 0);
     unit_ints[1] = plan_unit_ints(plan, (int32_t)cap_fwd, 1);
-    HIP_TRY(hipMalloc((void **)&plan->pool, (size_t)(queue_ints + desc_ints + 4 * (cap_fwd + cap_dkv) + unit_ints[0] + unit_ints[1]) * sizeof(int32_t)));
+    dkv_unit_ints = plan_dkv_unit_ints(plan, p->head_split, (int32_t)cap_dkv);
+    HIP_TRY(hipMalloc((void **)&plan->pool, (size_t)(queue_ints + desc_ints + 4 * (cap_fwd + cap_dkv) + unit_ints[0] + unit_ints[1] + dkv_unit_ints) * sizeof(int32_t)));
     plan->fwd_queues = (WorkQueue *)plan->pool;   // (zeroed by every forward call before its launch)
     plan->cu_q = plan->pool + queue_ints;
     plan->cu_k = plan->cu_q + kpad;
@@ -307,6 +228,7 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
         plan->units[0] = plan->dkv_items + 4 * cap_dkv;
         plan->units[1] = plan->units[0] + unit_ints[0];
     }
+    if (dkv_unit_ints > 0) plan->dkv_units = plan->dkv_items + 4 * cap_dkv + unit_ints[0] + unit_ints[1];
     fwd_off = tmp + 4 * kin;
     dkv_off = fwd_off + kpad;
     totals_d = (PlanTotals *)(dkv_off + kpad);
@@ -322,6 +244,7 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
     HIP_TRY(launch_plan_items(plan, fwd_off, dkv_off, (int32_t)cap_fwd, (int32_t)cap_dkv, scratch,
                               scratch + 4 * cap_fwd, scratch + 4 * (cap_fwd + cap_dkv), cost_bound, compute_units,
                               totals_d, st));
+    HIP_TRY(launch_plan_units(plan, p->head_split, longest_seq, (int32_t)cap_fwd, (int32_t)cap_dkv, compute_units, totals_d, st));
     HIP_TRY(hipMemcpyAsync(&totals, totals_d, sizeof totals, hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
     if (totals.bad_entry != 0 || totals.n_seg != plan->NS || totals.total_q > INT32_MAX ||
@@ -340,12 +263,6 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
     plan->pairs = totals.pairs;
     plan->n_units[0] = totals.n_units[0];
     plan->n_units[1] = totals.n_units[1];
-    // dK/dV head split.  A workgroup of that kernel walks all query tiles of one key
-    // block for every query head of the KV group, one after another; its longest chain
-    // is cost_max * group.  Spread evenly, the whole list is cost_sum * group * Hkv over
-    // the compute units.  When the longest chain exceeds that share (few KV heads, one
-    // long sequence in a small micro-batch) the heads of a group are shared out over
-    // several workgroups until it no longer does, with a factor two of slack.
     // Workgroup shape of the forward and dQ kernels.  Several 4-wavefront workgroups per compute
     // unit hide each other's start-up, drain and barriers, but they also stretch each other's
     // work items (three share a unit and its oldest wave is served first), and a launch ends only
@@ -369,39 +286,13 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
                                                    : (longest_seq <= 8192 && blocks_per_cu >= 16.0);
         plan->wg_query_rows = small_shape ? 128 : 256;
     }
-    plan->head_split = p->head_split;
-    if (plan->head_split == 0) {
-        // Split only when the longest chain of the work list (its costliest item, all the
-        // heads of a group) exceeds an even share of the whole list over the compute units:
-        // then that chain bounds the kernel's time and shortening it pays for the fp32
-        // partial sums and their reduction; below that the unsplit kernel is 5-40 % faster
-        // (measured on 45 micro-batches of three head shapes; the ratio below was the
-        // dividing line at 1.0: splits won from 1.27 up, lost or tied up to 0.98).
-        // The 12-wavefront shape (fewer, larger workgroups: rounding of workgroups per compute
-        // unit weighs more) gains from the split from half that ratio on: at 14/2 heads x 64
-        // every batch measured from 2 x 8,192 to 65,536 tokens was 7-50 % faster split 7 ways
-        // (65,536 tokens, ratio 0.75: 17.4 -> 16.1 ms; eight 8,192-token sequences, 0.72: equal).
-        const double share = (double)totals.dkv_cost_sum * plan->Hkv / (double)compute_units;
-        // (that factor of two only where it was measured to pay: a sequence of 8,192 tokens or more
-        // and a short list, under five items x KV heads per compute unit; with longer lists of
-        // 192-key items, 16-64 heads on ragged 32,768-token micro-batches, a split at ratios of
-        // 0.6-0.9 cost 6-16 %, and on short lists of short sequences up to 90 %)
-        const bool short_list = (int64_t)totals.n_dkv * plan->Hkv < 5 * (int64_t)compute_units;
-        const double scale = (plan->d == 64 && plan->BN == 192 && short_list && longest_seq >= 8192) ? 2.0 : 1.0;
-        const double want = share > 0.0 ? scale * (double)totals.dkv_cost_max / share : 1.0;
-        int32_t hs = want <= 1.0 ? 1 : (want >= (double)group ? group : (int32_t)ceil(want));
-        // only equal shares: workgroups with different numbers of heads walk the query
-        // tiles at different paces, stop sharing them in L2 and run 10 % slower (measured
-        // with 7 heads per group split 3 + 4), so take the next divisor of the group size
-        const int32_t asked = hs;
-        while (hs < group && group % hs != 0) ++hs;
-        // ... unless that divisor is three times what was asked for and the chain is less than
-        // 1.5 even shares (7 heads per group at ratios of 1.0-1.4: split 7 ways 6-14 % slower
-        // than unsplit, equal at 1.7)
-        if (hs >= 3 * asked && want < 1.5) hs = 1;
-        plan->head_split = hs < 1 ? 1 : (hs > group ? group : hs);
-    }
-    choose_split(plan, p->head_split, totals, compute_units);
+    plan->head_split = totals.split.head_split;
+    plan->n_split = totals.split.n_split;
+    plan->n_whole_first = totals.split.n_whole_first;
+    plan->split_parts = totals.split.parts;
+    plan->split_chain = totals.split.chain;
+    plan->split_compact = totals.split.compact;
+    plan->n_dkv_units = totals.n_dkv_units;
     rc = SKRULL_OK;
 done:
     free(host_in);
@@ -433,11 +324,12 @@ int skrull_attn_plan_info(const skrull_attn_plan_t *plan, skrull_attn_plan_info_
     info->attended_pairs = plan->pairs;
     info->useful_flops_fwd = 4 * plan->pairs * plan->d * plan->Hq;
     info->useful_flops_bwd = 10 * plan->pairs * plan->d * plan->Hq;
-    info->bwd_workspace_bytes = base_workspace(plan);
+    info->bwd_workspace_bytes = base_workspace(plan->Hq, plan->total_q);
     if (plan->head_split > 1)  // fp32 partial dK and dV of every share of the heads
         info->bwd_workspace_bytes += 2 * (int64_t)plan->head_split * plan->total_k * plan->Hkv * plan->d * 4;
     else
-        info->bwd_workspace_bytes += partial_bytes(plan);
+        info->bwd_workspace_bytes += partial_bytes(SplitChoice{plan->head_split, plan->n_split, plan->n_whole_first, plan->split_parts, plan->split_chain, plan->split_compact},
+                                                   plan->BN, plan->total_k, plan->Hkv, plan->d);
     info->num_segments = plan->NS;
     info->head_split = plan->head_split;
     info->wg_query_rows = plan->wg_query_rows;

@@ -40,6 +40,8 @@ struct KeyMap {
     int32_t n_split, n_whole_first, parts, chain;  // see skrull_attn_plan
     int32_t part_rows;                          // rows of one part's partial sums; 0: the rows of K themselves
     uint64_t inv_passes, inv_hkv;
+    const int32_t *units;                       // null, or the work units: item | part << SKRULL_UNIT_SHIFT
+    uint64_t inv_whole;
 };
 // workgroups that share an item of the first n_split
 __device__ __forceinline__ int parts_of(const KeyMap &m, int cost)
@@ -541,15 +543,31 @@ __device__ __forceinline__ KeyBlock key_block(const P prm, int SUB, int bid)
 {
     KeyBlock r;
     const int BN = prm->keys.BN, Hkv = prm->keys.Hkv, passes = prm->keys.passes, n_split = prm->keys.n_split;
-    const int whole = Hkv * passes, first = prm->keys.n_whole_first * whole, split = n_split * prm->keys.parts * whole;
-    const bool is_split = bid >= first && bid < first + split;
-    const int per_item = is_split ? whole * prm->keys.parts : whole;
-    const int rel = bid < first ? bid : (is_split ? bid - first : bid - split);
-    const int at = __builtin_amdgcn_readfirstlane(rel / per_item), x = rel - at * per_item;
-    const int item = is_split ? at : at + n_split;
-    const int y = quotient(x, prm->keys.inv_passes), sub = x - y * passes;
-    r.part = quotient(y, prm->keys.inv_hkv);
-    r.c = y - r.part * Hkv;
+    const int whole = Hkv * passes;
+    const int32_t *units = prm->keys.units;
+    int item, y, sub;
+    bool is_split;
+    if (units) {
+        const int unit = __builtin_amdgcn_readfirstlane(quotient(bid, prm->keys.inv_whole)), u = plan_value(units, unit);
+        const int x = bid - unit * whole;
+        y = quotient(x, prm->keys.inv_passes);
+        sub = x - y * passes;
+        item = u & ((1 << SKRULL_UNIT_SHIFT) - 1);
+        r.part = u >> SKRULL_UNIT_SHIFT;
+        r.c = y;
+        is_split = item < n_split;
+    } else {
+        const int first = prm->keys.n_whole_first * whole, split = n_split * prm->keys.parts * whole;
+        is_split = bid >= first && bid < first + split;
+        const int per_item = is_split ? whole * prm->keys.parts : whole;
+        const int rel = bid < first ? bid : (is_split ? bid - first : bid - split);
+        const int at = __builtin_amdgcn_readfirstlane(rel / per_item), x = rel - at * per_item;
+        item = is_split ? at : at + n_split;
+        y = quotient(x, prm->keys.inv_passes);
+        sub = x - y * passes;
+        r.part = quotient(y, prm->keys.inv_hkv);
+        r.c = y - r.part * Hkv;
+    }
     const i32x4 it = plan_value((const i32x4 *)prm->dkv_items, item);
     const int seq = it.x, prev = max(seq - 1, 0);
     const int shares = plan_value(prm->shares_kv, seq), kvl_e = plan_value(prm->kv_len, prev);
@@ -1130,12 +1148,14 @@ static KeyMap map_dkv(const skrull_attn_plan_t *p)
 {
     const int SUB = 32 * dkv_pairs(p), passes = (p->BN + SUB - 1) / SUB;
     return KeyMap{p->BN, p->Hq / p->Hkv, passes, p->Hkv, p->n_split, p->n_whole_first, p->split_parts, p->split_chain,
-                  p->split_compact ? p->n_split * p->BN : 0, inverse_of(passes), inverse_of(p->Hkv)};
+                  p->split_compact ? p->n_split * p->BN : 0, inverse_of(passes), inverse_of(p->Hkv), p->dkv_units,
+                  inverse_of(passes * p->Hkv)};
 }
 
 int grid_dkv(const skrull_attn_plan_t *p)
 {
-    return (p->n_dkv + p->n_split * (p->split_parts - 1)) * p->Hkv * map_dkv(p).passes;
+    const int n = p->dkv_units ? p->n_dkv_units : p->n_dkv + p->n_split * (p->split_parts - 1);
+    return n * p->Hkv * map_dkv(p).passes;
 }
 
 hipError_t launch_bwd(const skrull_attn_plan_t *p, const void *q, const void *k, const void *v,

@@ -38,11 +38,17 @@ struct skrull_attn_plan {
     // part << SKRULL_UNIT_SHIFT, in list order; null for lists too long
     // for the rank sort and for very many heads
     int32_t *units[2], n_units[2];
+    int32_t *dkv_units, n_dkv_units;  // the same of the dK/dV list (item | part << SKRULL_UNIT_SHIFT), or null
     WorkQueue *fwd_queues;  // SKRULL_FWD_QUEUE_SLOTS times eight dies' queues, at the start of the pool: for forward launches
     uint32_t fwd_calls;     // forward calls made so far (atomic): call i uses slot i mod SKRULL_FWD_QUEUE_SLOTS
 };
 
-// Totals written by the ranges kernel and read back by the host.
+// Which dK/dV items several workgroups share, and how; see skrull_attn_plan.
+struct SplitChoice {
+    int32_t head_split, n_split, n_whole_first, parts, chain, compact;
+};
+
+// Totals written by the plan kernels and read back by the host.
 struct PlanTotals {
     int64_t total_q, total_k, n_fwd, n_dkv, pairs;
     int32_t bad_entry;   // index+1 of the first invalid sequence, 0 if none
@@ -54,9 +60,29 @@ struct PlanTotals {
     // that has the item to itself): how many exceed exactly the first k of dkv_chain_limit()
     int32_t chain_base, chain_hist[SKRULL_CHAIN_LIMITS + 1];
     int32_t n_units[2];        // work units of the forward / dQ list for 4 and for 8 wavefronts
+    int32_t n_dkv_units;
+    SplitChoice split;         // how dK/dV items are shared (the units kernel's choice)
     int32_t cap_fwd, cap_dkv;  // room in the item arrays (the host's upper bounds)
     int32_t block_n;           // key rows per dK/dV item in effect (the ranges kernel's choice where open)
 };
+
+constexpr int32_t kMaxParts = 8;  // workgroups that may share one dK/dV item whose heads are not split
+
+// Bytes of backward scratch without partial sums: -D and LSE*log2(e) per (head, row), then 256
+// bytes for the work queues of the two kernels.
+__host__ __device__ inline int64_t base_workspace(int32_t q_heads, int64_t total_q)
+{
+    return ((((int64_t)q_heads * total_q * 8) + 255) & ~(int64_t)255) + 256;
+}
+
+// fp32 partial dK and dV of the items that several workgroups share: a slot per part for every row of
+// K, or for the rows of those items only.
+__host__ __device__ inline int64_t partial_bytes(const SplitChoice &c, int32_t block_n, int64_t total_k, int32_t kv_heads, int32_t head_dim)
+{
+    if (c.parts <= 1) return 0;
+    const int64_t rows = c.compact ? (int64_t)c.n_split * block_n : total_k;
+    return 2 * (int64_t)c.parts * rows * kv_heads * head_dim * 4;
+}
 
 // The k-th of the limits that a dK/dV item's chain is compared with: `base` times 2^((k - 2) / 2).
 __host__ __device__ inline int64_t dkv_chain_limit(int32_t base, int k)
@@ -112,6 +138,10 @@ hipError_t launch_plan_items(const skrull_attn_plan_t *p, const int32_t *fwd_off
                              const int32_t *dkv_off, int32_t cap_fwd, int32_t cap_dkv,
                              int32_t *scratch_fwd, int32_t *scratch_dkv, int32_t *radix_hist,
                              int32_t cost_bound, int32_t compute_units, PlanTotals *totals, hipStream_t st);
+// after launch_plan_items: how dK/dV items are shared (`asked`: the caller's head split, 0: the library's own) and the lists of work units
+hipError_t launch_plan_units(const skrull_attn_plan_t *p, int32_t asked, int32_t longest_seq, int32_t cap_fwd, int32_t cap_dkv,
+                             int32_t compute_units, PlanTotals *totals, hipStream_t st);
+int64_t plan_dkv_unit_ints(const skrull_attn_plan_t *p, int32_t asked, int32_t cap_dkv);  // room for dkv_units; 0: no list
 int64_t plan_unit_ints(const skrull_attn_plan_t *p, int32_t cap_fwd, int which);  // room for units[which]; 0: no list
 int64_t plan_radix_ints(int32_t cap_fwd, int32_t cap_dkv, int32_t cost_bound);
 

@@ -207,7 +207,7 @@ __global__ __launch_bounds__(kScanThreads) void plan_ranges_kernel(
         totals->dkv_cost_sum = 0;
         totals->dkv_cost_max = 0;
         for (int i = 0; i <= SKRULL_CHAIN_LIMITS; ++i) totals->chain_hist[i] = 0;
-        totals->n_units[0] = totals->n_units[1] = 0;
+        totals->n_units[0] = totals->n_units[1] = totals->n_dkv_units = 0;
         totals->cap_fwd = cap_fwd;
         totals->cap_dkv = cap_dkv;
         totals->block_n = BN;
@@ -307,24 +307,15 @@ __device__ inline void count_chain(int32_t cost, int32_t group, int32_t q_heads,
 // read.  (One thread per item and one cost to a read, each waited for, took 12 us for 180 items and
 // 25 us for 310; both lists together now take 6 to 10, 25 for 1,368.)  blockIdx.y: the list (0 forward / dQ, 1 dK/dV).
 constexpr int32_t kSortItems = 64;  // items of a block
-// The forward / dQ list also gets its work units: an item of `blocks` 32-row blocks makes
-// ceil(blocks * group / NW) workgroups of NW waves per KV head, and the position of the first one in
-// the sorted list of units is the sum over the items before it, formed along with the rank
-// (0.5 to 0.8 us for 20 to 300 items).
 struct SortJob {
     const int4 *in;
     int4 *out;
 };
-struct UnitJob {
-    const int32_t *q_len;
-    int32_t BM;
-    int32_t *units[2];  // for 4 and for 8 waves
-};
-__global__ __launch_bounds__(256) void plan_sort_kernel(SortJob fwd, SortJob dkv, UnitJob uj, int first_list, PlanTotals *totals,
+__global__ __launch_bounds__(256) void plan_sort_kernel(SortJob fwd, SortJob dkv, int first_list, PlanTotals *totals,
                                                         int32_t group, int32_t q_heads, int32_t head_dim,
                                                         int32_t compute_units)
 {
-    __shared__ __align__(16) int32_t tile[1024], n4[1024], n8[1024];
+    __shared__ __align__(16) int32_t tile[1024];
     const int which = first_list + blockIdx.y;
     const int4 *__restrict__ in = which == 0 ? fwd.in : dkv.in;
     int4 *__restrict__ out = which == 0 ? fwd.out : dkv.out;
@@ -334,60 +325,228 @@ __global__ __launch_bounds__(256) void plan_sort_kernel(SortJob fwd, SortJob dkv
     if (first >= n) return;  // (the whole block)
     const int32_t a = first + threadIdx.x / 4, quarter = threadIdx.x % 4;
     const int4 me = (a < n) ? in[a] : make_int4(0, 0, 0, 0);
-    auto blocks_of = [&](const int4 &it) {  // 32-row blocks of a forward item, of all heads of a group
-        const int32_t left = uj.q_len[it.x] - it.y * uj.BM;
-        return (((left < uj.BM ? left : uj.BM) + 31) >> 5) * group;
-    };
-    const bool listed = which == 0 && uj.units[0] != nullptr;
-    int32_t rank = 0, at4 = 0, at8 = 0;
+    int32_t rank = 0;
     for (int32_t b0 = 0; b0 < n; b0 += 1024) {
         __syncthreads();
         const int32_t lim = (n - b0 < 1024) ? n - b0 : 1024;
         for (int32_t i = threadIdx.x; i < ((lim + 15) & ~15); i += blockDim.x) {
-            const int4 it = i < lim ? in[b0 + i] : make_int4(0, 0, 0, -1);  // (below every cost)
-            tile[i] = it.w;
-            if (listed) {
-                const int32_t blocks = i < lim ? blocks_of(it) : 0;
-                n4[i] = (blocks + 3) >> 2;
-                n8[i] = (blocks + 7) >> 3;
-            }
+            tile[i] = i < lim ? in[b0 + i].w : -1;  // (below every cost)
         }
         __syncthreads();
         // cost_b > cost_a, or equal and earlier: cost_b >= cost_a + (b >= a)
         const int32_t before = a - b0;
         for (int32_t x = 4 * quarter; x < lim; x += 16) {
             const int4 c = *(const int4 *)&tile[x];
-            const bool ahead[4] = {c.x >= me.w + (x >= before), c.y >= me.w + (x + 1 >= before),
-                                   c.z >= me.w + (x + 2 >= before), c.w >= me.w + (x + 3 >= before)};
-            rank += ahead[0] + ahead[1] + ahead[2] + ahead[3];
-            if (listed) {
-                const int4 f = *(const int4 *)&n4[x], e = *(const int4 *)&n8[x];
-                at4 += (ahead[0] ? f.x : 0) + (ahead[1] ? f.y : 0) + (ahead[2] ? f.z : 0) + (ahead[3] ? f.w : 0);
-                at8 += (ahead[0] ? e.x : 0) + (ahead[1] ? e.y : 0) + (ahead[2] ? e.z : 0) + (ahead[3] ? e.w : 0);
-            }
+            rank += (c.x >= me.w + (x >= before)) + (c.y >= me.w + (x + 1 >= before)) +
+                    (c.z >= me.w + (x + 2 >= before)) + (c.w >= me.w + (x + 3 >= before));
         }
     }
     rank += __shfl_xor(rank, 1, 64);
     rank += __shfl_xor(rank, 2, 64);
-    if (listed) {
-        at4 += __shfl_xor(at4, 1, 64);
-        at4 += __shfl_xor(at4, 2, 64);
-        at8 += __shfl_xor(at8, 1, 64);
-        at8 += __shfl_xor(at8, 2, 64);
-        if (a < n) {  // the item's four threads write its units
-            const int32_t blocks = blocks_of(me), mine4 = (blocks + 3) >> 2, mine8 = (blocks + 7) >> 3;
-            for (int32_t p = quarter; p < mine4; p += 4) uj.units[0][at4 + p] = rank | p << SKRULL_UNIT_SHIFT;
-            for (int32_t p = quarter; p < mine8; p += 4) uj.units[1][at8 + p] = rank | p << SKRULL_UNIT_SHIFT;
-            if (quarter == 0) {
-                atomicAdd(&totals->n_units[0], mine4);
-                atomicAdd(&totals->n_units[1], mine8);
-            }
-        }
-    }
     if (a < n && quarter == 0) {
         out[rank] = me;
         if (which == 1) count_chain(me.w, group, q_heads, head_dim, compute_units, totals);
     }
+}
+
+// ---------------------------------------------------------------------------
+// How dK/dV items are shared, and in which order work is handed out.
+// ---------------------------------------------------------------------------
+
+// dK/dV head split.  A workgroup of that kernel walks all query tiles of one key
+// block for every query head of the KV group, one after another; its longest chain
+// is cost_max * group.  Spread evenly, the whole list is cost_sum * group * Hkv over
+// the compute units.  When the longest chain exceeds that share (few KV heads, one
+// long sequence in a small micro-batch) the heads of a group are shared out over
+// several workgroups until it no longer does, with a factor two of slack.
+//
+// Split only when the longest chain of the work list (its costliest item, all the
+// heads of a group) exceeds an even share of the whole list over the compute units:
+// then that chain bounds the kernel's time and shortening it pays for the fp32
+// partial sums and their reduction; below that the unsplit kernel is 5-40 % faster
+// (measured on 45 micro-batches of three head shapes; the ratio below was the
+// dividing line at 1.0: splits won from 1.27 up, lost or tied up to 0.98).
+// The 12-wavefront shape (fewer, larger workgroups: rounding of workgroups per compute
+// unit weighs more) gains from the split from half that ratio on: at 14/2 heads x 64
+// every batch measured from 2 x 8,192 to 65,536 tokens was 7-50 % faster split 7 ways
+// (65,536 tokens, ratio 0.75: 17.4 -> 16.1 ms; eight 8,192-token sequences, 0.72: equal).
+__device__ inline int32_t choose_head_split(const PlanTotals &totals, int32_t q_heads, int32_t kv_heads, int32_t head_dim,
+                                            int32_t longest_seq, int32_t compute_units)
+{
+    const int32_t group = q_heads / kv_heads;
+    const double share = (double)totals.dkv_cost_sum * kv_heads / (double)compute_units;
+    // (that factor of two only where it was measured to pay: a sequence of 8,192 tokens or more
+    // and a short list, under five items x KV heads per compute unit; with longer lists of
+    // 192-key items, 16-64 heads on ragged 32,768-token micro-batches, a split at ratios of
+    // 0.6-0.9 cost 6-16 %, and on short lists of short sequences up to 90 %)
+    const bool short_list = (int64_t)totals.n_dkv * kv_heads < 5 * (int64_t)compute_units;
+    const double scale = (head_dim == 64 && totals.block_n == 192 && short_list && longest_seq >= 8192) ? 2.0 : 1.0;
+    const double want = share > 0.0 ? scale * (double)totals.dkv_cost_max / share : 1.0;
+    int32_t hs = want <= 1.0 ? 1 : (want >= (double)group ? group : (int32_t)ceil(want));
+    // only equal shares: workgroups with different numbers of heads walk the query
+    // tiles at different paces, stop sharing them in L2 and run 10 % slower (measured
+    // with 7 heads per group split 3 + 4), so take the next divisor of the group size
+    const int32_t wanted = hs;
+    while (hs < group && group % hs != 0) ++hs;
+    // ... unless that divisor is three times what was asked for and the chain is less than
+    // 1.5 even shares (7 heads per group at ratios of 1.0-1.4: split 7 ways 6-14 % slower
+    // than unsplit, equal at 1.7)
+    if (hs >= 3 * wanted && want < 1.5) hs = 1;
+    return hs < 1 ? 1 : (hs > group ? group : hs);
+}
+
+// Which dK/dV items are shared out over several workgroups.  A head split the caller asked for holds
+// for every item.  The library's own shares out only items with a long chain: split over the heads,
+// every item of a short sequence cost seven starts, seven ends and seven fp32 partial sums instead of
+// one store (64 sequences, 26,624 tokens, 14/2 heads of 64: dK/dV 202 us all items split 7 ways,
+// 146 this way; 20 sequences, 16,384 tokens: 184 -> 162), and where the heads cannot be split evenly
+// the longest chain was the kernel's time (10 sequences, 13,312 tokens, 28/4 heads of 128: 640 -> 530;
+// one of 2,967, 4/4 heads of 64: 69 -> 36).
+__device__ inline SplitChoice choose_split(int32_t asked, const PlanTotals &totals, int32_t q_heads, int32_t kv_heads, int32_t head_dim,
+                                           int32_t longest_seq, int32_t compute_units)
+{
+    const int32_t group = q_heads / kv_heads;
+    SplitChoice r{asked, 0, 0, 1, 0, 0};
+    if (asked != 0) {
+        if (asked > 1) {
+            r.parts = asked;
+            r.n_split = (int32_t)totals.n_dkv;
+        }
+        return r;
+    }
+    r.head_split = choose_head_split(totals, q_heads, kv_heads, head_dim, longest_seq, compute_units);
+    const int64_t longest = (int64_t)totals.dkv_cost_max * group;
+    // Where the heads are not split (nor could be: one head per group, or seven, which would be too many)
+    // items are shared out only if the longest chain exceeds 1.1 even shares, if its shortening saves more
+    // than the partial sums cost, and as few as it takes for these to fit the static workspace, so that a
+    // plan that skrull_attn_bwd_static takes without them is not refused for them.
+    r.compact = r.head_split == 1;
+    if (r.compact && 10 * longest * compute_units <= 11 * (int64_t)totals.dkv_cost_sum * q_heads) return r;
+    // Microseconds: a block of 256 query rows of one head takes a workgroup 6, the partial sums are written
+    // and read at 4.4 TB/s, and a part's start and end take 6, or 1 where compute units are idle beside it.
+    // Measured on 170 micro-batches of ratios from 1.1 up, shared against whole: where this says no, up to 27 %
+    // slower (a slice of 2,388 tokens, 4/4 heads of 64, ratio 1.43 and 33 MB: 86 us shared, 68 whole); where
+    // it says yes, 3 % slower (a microsecond of 40) to 50 % faster (28/4 heads of 128, ratio 1.14 and 17 MB:
+    // 662 us shared, 816 whole; one sequence of 2,967, 4/4 heads of 64, ratio 7 and 19 MB: 34 and 69).
+    auto pays = [&](int64_t limit) {
+        const double share = (double)totals.dkv_cost_sum * q_heads / compute_units;
+        const double saved = (double)longest - (share > (double)limit ? share : (double)limit);
+        return 6.0 * saved > ((double)longest < 2.0 * share ? 6.0 : 1.0) + 2.0 * (double)partial_bytes(r, totals.block_n, totals.total_k, kv_heads, head_dim) / 4.4e6;
+    };
+    const int32_t most = r.compact ? kMaxParts : r.head_split;
+    // When the longest part is then still as long as three quarters of an even share, all items are cut
+    // as fine as it is: what else runs has to fit beside it (3 sequences, 7,417 tokens, 14/2 heads of
+    // 64: dK/dV 137 us all cut, 145 by the limits below).
+    if (!r.compact && 4 * longest * compute_units >= 3 * most * (int64_t)totals.dkv_cost_sum * q_heads) {
+        r.parts = most;
+        r.n_split = (int32_t)totals.n_dkv;
+        return r;
+    }
+    int32_t above[SKRULL_CHAIN_LIMITS + 1];  // items that exceed limit k
+    above[SKRULL_CHAIN_LIMITS] = 0;
+    for (int k = SKRULL_CHAIN_LIMITS - 1; k >= 0; --k) above[k] = above[k + 1] + totals.chain_hist[k + 1];
+    for (int k = 2; k < SKRULL_CHAIN_LIMITS; ++k) {
+        const int64_t limit = dkv_chain_limit(totals.chain_base, k), want = (longest + limit - 1) / limit;
+        if (want < 2) break;
+        r.parts = want > most ? most : (int32_t)want;
+        r.chain = (int32_t)(limit > INT32_MAX ? INT32_MAX : limit);
+        r.n_split = above[k];
+        r.n_whole_first = above[k - 2] - above[k];
+        if (!r.compact ||
+            (pays(limit) && base_workspace(q_heads, totals.total_q) + partial_bytes(r, totals.block_n, totals.total_k, kv_heads, head_dim) <= (int64_t)SKRULL_STATIC_SCRATCH_BYTES)) return r;
+    }
+    r.parts = 1;
+    r.n_split = r.n_whole_first = 0;
+    return r;
+}
+
+// A dK/dV item of cost `cost` among the first n_split is shared by this many workgroups.
+__device__ inline int32_t parts_of_item(const SplitChoice &c, int32_t item, int32_t cost, int32_t group)
+{
+    if (item >= c.n_split) return 1;
+    return c.chain == 0 ? c.parts : (int32_t)min((int64_t)c.parts, ((int64_t)cost * group + c.chain - 1) / c.chain);
+}
+
+// The order in which work is handed out: the longest first, as in the item lists, but by what a work
+// unit takes: for dK/dV an item's part by its rounds (64-row query tiles x heads), for the forward and dQ
+// an item by its half tiles of keys.  The items' own costs count blocks of 256 rows, in which most short
+// sequences look alike, and whole items went out before the parts of shared ones, whatever their
+// length: launches ended with long units that had begun late.  dQ and dK/dV together, by the items' costs
+// and this way: 64 sequences, 26,624 tokens, 14/2 heads of 64: 240 -> 229 us; 20 sequences, 16,384 tokens: 248 ->
+// 236; 114 sequences of 16 to 1,024, 32,768 tokens: 218 -> 198; 10 sequences, 13,312 tokens, 28/4 heads of 128: 857
+// -> 845.  The forward gains 1 % at head_dim 64.
+// What is not done: the parts of a forward / dQ item apart from each other by their own half tiles
+// (114 sequences of about 250 tokens, 32/8 heads of 128: forward 215 -> 236, dQ 303 -> 328; they read the same
+// keys and find them in their die's L2 only when they run together), and key blocks with less work than an eighth of
+// an even share per compute unit (`small`, in rounds; a cost counts for four) in any other order than the list's, which has those of a
+// sequence together (the same 114 sequences, backward: 650 -> 662 us without that line, 26,624 tokens 229
+// -> 241 with it at a quarter).
+struct UnitsJob {
+    const int4 *fwd_items, *dkv_items;
+    const int32_t *q_begin, *q_len, *kv_len, *shares_kv;
+    int32_t BM, q_heads, kv_heads, head_dim, asked, longest_seq, compute_units;
+    int32_t *units[2], *dkv_units;  // forward / dQ for 4 and 8 waves; dK/dV; null: no list
+};
+__global__ __launch_bounds__(256) void plan_units_kernel(UnitsJob j, PlanTotals *totals)
+{
+    __shared__ __align__(16) int32_t t_cost[1024], t_parts[1024];
+    __shared__ SplitChoice shared_choice;
+    const int32_t group = j.q_heads / j.kv_heads;
+    const int32_t first = blockIdx.x * kSortItems;
+    const bool dkv = blockIdx.y == 0;
+    if (dkv && threadIdx.x == 0) {
+        const PlanTotals t = *totals;
+        shared_choice = choose_split(j.asked, t, j.q_heads, j.kv_heads, j.head_dim, j.longest_seq, j.compute_units);
+        if (blockIdx.x == 0) totals->split = shared_choice;  // (read by the host only)
+    }
+    const int32_t n = dkv ? (int32_t)min((long long)totals->n_dkv, (long long)totals->cap_dkv)
+                          : (int32_t)min((long long)totals->n_fwd, (long long)totals->cap_fwd);
+    const int32_t log_nw = blockIdx.y + 1;  // forward / dQ: 4 or 8 waves
+    int32_t *units = dkv ? j.dkv_units : j.units[max((int)blockIdx.y - 1, 0)];
+    if (!units || first >= n) return;  // (the whole block)
+    __syncthreads();
+    const SplitChoice choice = shared_choice;
+    const int32_t BN = totals->block_n;
+    const int32_t small = (int32_t)min(totals->dkv_cost_sum * j.q_heads / (2 * (unsigned long long)j.compute_units), 1ull << 29);
+    auto tiles = [&](int32_t seq, int32_t kv0) {  // query tiles of a segment that see key kv0 or later ones
+        const int32_t i0 = max(0, kv0 - j.q_begin[seq]);
+        return ((j.q_len[seq] + 63) >> 6) - (i0 >> 6);
+    };
+    auto unit_of = [&](int32_t i, int32_t &cost, int32_t &parts) {
+        if (dkv) {
+            const int4 it = j.dkv_items[i];
+            int32_t c = tiles(it.x, it.y * BN);
+            if (j.shares_kv[it.x] && it.y * BN < j.kv_len[it.x - 1]) c += tiles(it.x - 1, it.y * BN);
+            parts = parts_of_item(choice, i, it.w, group);
+            cost = max((min(c, 1 << 20) * group + parts - 1) / parts, small);
+        } else {
+            const int4 it = j.fwd_items[i];
+            const int32_t row0 = it.y * j.BM, rows = min(j.BM, j.q_len[it.x] - row0);
+            cost = (int32_t)(((uint32_t)(j.q_begin[it.x] + row0 + rows) + 31u) >> 5);
+            parts = (((rows + 31) >> 5) * group + (1 << log_nw) - 1) >> log_nw;
+        }
+    };
+    const int32_t a = first + threadIdx.x / 4, quarter = threadIdx.x % 4;
+    int32_t my_cost = 0, my_parts = 0, rank = 0, sum = 0;
+    if (a < n) unit_of(a, my_cost, my_parts);
+    for (int32_t b0 = 0; b0 < n; b0 += 1024) {
+        __syncthreads();
+        const int32_t lim = min(1024, n - b0);
+        for (int32_t i = threadIdx.x; i < lim; i += blockDim.x) unit_of(b0 + i, t_cost[i], t_parts[i]);
+        __syncthreads();
+        for (int32_t x = quarter; x < lim; x += 4) {
+            // ahead of this item: a larger cost, or an equal one and earlier in the list
+            rank += t_cost[x] >= my_cost + (b0 + x >= a) ? t_parts[x] : 0;
+            sum += t_parts[x];
+        }
+    }
+    rank += __shfl_xor(rank, 1, 64);
+    rank += __shfl_xor(rank, 2, 64);
+    sum += __shfl_xor(sum, 1, 64);
+    sum += __shfl_xor(sum, 2, 64);
+    if (a < n)
+        for (int32_t p = quarter; p < my_parts; p += 4) units[rank + p] = a | p << SKRULL_UNIT_SHIFT;
+    if (first == 0 && threadIdx.x == 0) *(dkv ? &totals->n_dkv_units : &totals->n_units[log_nw - 2]) = sum;
 }
 
 // ---------------------------------------------------------------------------
@@ -563,7 +722,7 @@ hipError_t launch_plan_items(const skrull_attn_plan_t *p, const int32_t *fwd_off
         const int32_t most = passes_f == 0 && passes_d == 0 ? n : (passes_f == 0 ? cap_fwd : cap_dkv);
         plan_sort_kernel<<<dim3((most + kSortItems - 1) / kSortItems, lists), 256, 0, st>>>(
             SortJob{(const int4 *)scratch_fwd, (int4 *)p->fwd_items}, SortJob{(const int4 *)scratch_dkv, (int4 *)p->dkv_items},
-            UnitJob{p->q_len, p->BM, {p->units[0], p->units[1]}}, first, totals, p->Hq / p->Hkv, p->Hq, p->d, compute_units);
+            first, totals, p->Hq / p->Hkv, p->Hq, p->d, compute_units);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -575,4 +734,22 @@ hipError_t launch_plan_items(const skrull_attn_plan_t *p, const int32_t *fwd_off
     }
     if (passes_d) e = radix_sort_list(p, 1, cap_dkv, passes_d, compute_units, (int4 *)scratch_dkv, (int4 *)p->dkv_items, hist_dkv, totals, st);
     return e;
+}
+
+int64_t plan_dkv_unit_ints(const skrull_attn_plan_t *p, int32_t asked, int32_t cap_dkv)
+{
+    const int32_t group = p->Hq / p->Hkv, parts = asked ? asked : (group > kMaxParts ? group : kMaxParts);
+    if (cap_dkv > kRankSortMax || p->Hq > SKRULL_UNIT_HEADS) return 0;
+    return (int64_t)cap_dkv * parts;
+}
+
+hipError_t launch_plan_units(const skrull_attn_plan_t *p, int32_t asked, int32_t longest_seq, int32_t cap_fwd, int32_t cap_dkv,
+                             int32_t compute_units, PlanTotals *totals, hipStream_t st)
+{
+    const int32_t f = p->units[0] ? cap_fwd : 1, d = p->dkv_units ? cap_dkv : 1, most = f > d ? f : d;
+    plan_units_kernel<<<dim3((most + kSortItems - 1) / kSortItems, p->units[0] ? 3 : 1), 256, 0, st>>>(
+        UnitsJob{(const int4 *)p->fwd_items, (const int4 *)p->dkv_items, p->q_begin, p->q_len, p->kv_len, p->shares_kv, p->BM, p->Hq,
+                 p->Hkv, p->d, asked, longest_seq, compute_units, {p->units[0], p->units[1]}, p->dkv_units},
+        totals);
+    return hipGetLastError();
 }

@@ -1003,3 +1003,34 @@ def test_small_launches_have_a_workgroup_per_head(oracle, S, heads, d, wg):
         elif per_head > per_unit * cus:
             assert n < per_head
     out["plan"].destroy()
+
+
+@pytest.mark.parametrize("heads,d", [((14, 2), 64), ((8, 8), 64), ((8, 2), 128)])
+def test_dkv_units_of_items_of_many_lengths(oracle, heads, d):
+    """dK/dV takes its work from a list of units ordered by their rounds: key blocks of sequences of 1 to 20 query
+    tiles, of a slice and of a two-chunk cut (both chunks' tiles), some shared by several workgroups, most
+    below the line under which the list's own order stays.  Every unit is walked once."""
+    from paper_2505_19609_amd import binding as B
+    import torch
+    S = [1250, 1, 63, 64, 65, 130, 2000, 193, 900, 257, 383, 30]
+    N, R, Z = [1] * 6 + [2] + [1] + [3] + [1] * 3, [0] * 6 + [1] + [0] + [2] + [0] * 3, [0] * 6 + [1] + [0] * 5
+    w = W.Workload("dkv_units", S, N, R, heads[0], heads[1], d, d ** -0.5, 607, shard_cut=Z)
+    out = _exhaustive(oracle, w, rtol=2.0 ** -8, keep=True)
+    plan = out["plan"]
+    first, num = B.skrull_attn_trace_layout(plan)
+    rec = torch.zeros(sum(num) * 32, dtype=torch.uint8, device="cuda")
+    dev = run_library(w, vals=out["vals"], keep_device=True)
+    t, i = dev["dev"], dev["dev_in"]
+    ws = torch.zeros(max(int(plan.bwd_workspace_bytes), 16), dtype=torch.uint8, device="cuda")
+    B.skrull_attn_trace(rec)
+    try:
+        B.skrull_attn_bwd(plan, i["q"], i["k"], i["v"], t["o"], t["lse"], i["do"], t["dq"], t["dk"], t["dv"], ws)
+        torch.cuda.synchronize()
+    finally:
+        B.skrull_attn_trace(None)
+    block = rec.cpu().numpy().view(np.uint32).reshape(-1, 8)[first[2]:first[2] + num[2], 6:8]
+    assert np.array_equal(block[:, 0], np.arange(num[2])) and (block[:, 1] == 1).all()
+    for n in ("dq", "dk", "dv"):
+        assert np.array_equal(t[n].float().cpu().numpy(), out[n]), n
+    plan.destroy()
+    dev["plan"].destroy()
