@@ -195,7 +195,7 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
     const int64_t queue_ints = SKRULL_FWD_QUEUE_INTS * SKRULL_FWD_QUEUE_SLOTS;  // work queues of the forward launches
     int32_t *fwd_off = nullptr, *dkv_off = nullptr, *scratch = nullptr;
     PlanTotals *totals_d = nullptr;
-    int64_t unit_ints[2] = {0, 0}, dkv_unit_ints = 0;
+    int64_t unit_ints[SKRULL_UNIT_LISTS] = {}, all_unit_ints = 0, dkv_unit_ints = 0;
 
     plan = new (std::nothrow) skrull_attn_plan_t();
     if (!plan) return SKRULL_ENOMEM;
@@ -211,10 +211,9 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
     if (p->shard_cut) memcpy(host_in + 3 * kin, p->shard_cut, (size_t)K * 4);
 
     HIP_TRY(hipMalloc((void **)&tmp, (size_t)tmp_ints * sizeof(int32_t)));
-    unit_ints[0] = plan_unit_ints(plan, (int32_t)cap_fwd, 0);
-    unit_ints[1] = plan_unit_ints(plan, (int32_t)cap_fwd, 1);
+    for (int i = 0; i < SKRULL_UNIT_LISTS; ++i) all_unit_ints += unit_ints[i] = plan_unit_ints(plan, (int32_t)cap_fwd, i);
     dkv_unit_ints = plan_dkv_unit_ints(plan, p->head_split, (int32_t)cap_dkv);
-    HIP_TRY(hipMalloc((void **)&plan->pool, (size_t)(queue_ints + desc_ints + 4 * (cap_fwd + cap_dkv) + unit_ints[0] + unit_ints[1] + dkv_unit_ints) * sizeof(int32_t)));
+    HIP_TRY(hipMalloc((void **)&plan->pool, (size_t)(queue_ints + desc_ints + 4 * (cap_fwd + cap_dkv) + all_unit_ints + dkv_unit_ints) * sizeof(int32_t)));
     plan->fwd_queues = (WorkQueue *)plan->pool;   // (zeroed by every forward call before its launch)
     plan->cu_q = plan->pool + queue_ints;
     plan->cu_k = plan->cu_q + kpad;
@@ -224,11 +223,14 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
     plan->shares_kv = plan->cu_q + 5 * kpad;
     plan->fwd_items = plan->cu_q + desc_ints;
     plan->dkv_items = plan->fwd_items + 4 * cap_fwd;
-    if (unit_ints[0] > 0) {
-        plan->units[0] = plan->dkv_items + 4 * cap_dkv;
-        plan->units[1] = plan->units[0] + unit_ints[0];
+    {
+        int32_t *next = plan->dkv_items + 4 * cap_dkv;
+        for (int i = 0; i < SKRULL_UNIT_LISTS; ++i) {
+            if (unit_ints[i] > 0) plan->units[i] = next;
+            next += unit_ints[i];
+        }
+        if (dkv_unit_ints > 0) plan->dkv_units = next;
     }
-    if (dkv_unit_ints > 0) plan->dkv_units = plan->dkv_items + 4 * cap_dkv + unit_ints[0] + unit_ints[1];
     fwd_off = tmp + 4 * kin;
     dkv_off = fwd_off + kpad;
     totals_d = (PlanTotals *)(dkv_off + kpad);
@@ -261,8 +263,7 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
     plan->n_fwd = (int32_t)totals.n_fwd;
     plan->n_dkv = (int32_t)totals.n_dkv;
     plan->pairs = totals.pairs;
-    plan->n_units[0] = totals.n_units[0];
-    plan->n_units[1] = totals.n_units[1];
+    for (int i = 0; i < SKRULL_UNIT_LISTS; ++i) plan->n_units[i] = totals.n_units[i];
     // Workgroup shape of the forward and dQ kernels.  Several 4-wavefront workgroups per compute
     // unit hide each other's start-up, drain and barriers, but they also stretch each other's
     // work items (three share a unit and its oldest wave is served first), and a launch ends only
@@ -286,6 +287,16 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
                                                    : (longest_seq <= 8192 && blocks_per_cu >= 16.0);
         plan->wg_query_rows = small_shape ? 128 : 256;
     }
+    // The forward at head_dim 64 also has a shape of 12 wavefronts to a workgroup, three per SIMD, which share the tiles of
+    // keys that two per SIMD would wait for.  Each wavefront runs slower, so the longest unit must not be what
+    // the launch waits for, and its row blocks must fill 12 about as well as 8 (they do not with one head per group).
+    // Against 8 wavefronts, by r = the longest unit / an even share per compute unit, on 28 micro-batches of 14/2 heads:
+    // 2 to 8 % less time up to r = 0.89, 6 % more at 0.91, 8 % less at 0.95, 15 to 30 % more from 1.1 on; on 54
+    // more of 9 to 48 heads, by what 12 leave empty beside 8: 5 to 15 % less up to 16 % (24/8 heads, 8,192 tokens
+    // of 8 to 511: 33.5 -> 28.4 us), between 6 % less and 1 % more at 30 % (two heads per group).
+    plan->fwd_wide = p->wg_query_rows == 0 && plan->wg_query_rows == 256 && plan->units[2] && group > 1 &&
+                     5 * 12 * (int64_t)plan->n_units[2] <= 6 * 8 * (int64_t)plan->n_units[1] &&
+                     10 * (int64_t)totals.fwd_longest * compute_units <= 9 * totals.fwd_load * plan->Hkv;
     plan->head_split = totals.split.head_split;
     plan->n_split = totals.split.n_split;
     plan->n_whole_first = totals.split.n_whole_first;

@@ -14,6 +14,7 @@ struct WorkQueue;
 
 #define SKRULL_CHAIN_LIMITS 9
 #define SKRULL_UNIT_SHIFT 11  // rank-sorted lists have at most 2,048 items
+#define SKRULL_UNIT_LISTS 3   // of forward / dQ work: for workgroups of 4, 8 and (head_dim 64) 12 wavefronts
 #define SKRULL_UNIT_HEADS 1024  // more query heads go without a list of units (index arithmetic of row_blocks)
 
 // Device-resident descriptor + work lists of one micro-batch.
@@ -24,6 +25,7 @@ struct skrull_attn_plan {
     int64_t pairs;
     int32_t head_split;  // workgroups that share the query heads of one KV group in dK/dV
     int32_t wg_query_rows;  // query rows per forward / dQ workgroup: 128 (4 wavefronts) or 256 (8)
+    int32_t fwd_wide;       // 1: the forward's workgroups have 12 wavefronts instead of 8
     // dK/dV items that several workgroups share (the first n_split of the sorted list), and how:
     // an item of cost c takes min(split_parts, ceil(c * heads per group / split_chain)) of them
     // (split_chain 0: split_parts).  n_whole_first more items are handed out before those.
@@ -34,10 +36,10 @@ struct skrull_attn_plan {
     int32_t *pool;
     int32_t *cu_q, *cu_k, *q_begin, *q_len, *kv_len, *shares_kv;  // per segment: [NS+1] x2, [NS] x4
     int32_t *fwd_items, *dkv_items;                   // [n][4], sorted
-    // work units of the forward / dQ list for workgroups of 4 and of 8 wavefronts (see RowMap): item |
+    // work units of the forward / dQ list for workgroups of 4, 8 and 12 wavefronts (see RowMap): item |
     // part << SKRULL_UNIT_SHIFT, in list order; null for lists too long
     // for the rank sort and for very many heads
-    int32_t *units[2], n_units[2];
+    int32_t *units[SKRULL_UNIT_LISTS], n_units[SKRULL_UNIT_LISTS];
     int32_t *dkv_units, n_dkv_units;  // the same of the dK/dV list (item | part << SKRULL_UNIT_SHIFT), or null
     WorkQueue *fwd_queues;  // SKRULL_FWD_QUEUE_SLOTS times eight dies' queues, at the start of the pool: for forward launches
     uint32_t fwd_calls;     // forward calls made so far (atomic): call i uses slot i mod SKRULL_FWD_QUEUE_SLOTS
@@ -59,8 +61,12 @@ struct PlanTotals {
     // chains of dK/dV items (query blocks x heads of a group, walked one after another by a workgroup
     // that has the item to itself): how many exceed exactly the first k of dkv_chain_limit()
     int32_t chain_base, chain_hist[SKRULL_CHAIN_LIMITS + 1];
-    int32_t n_units[2];        // work units of the forward / dQ list for 4 and for 8 wavefronts
+    int32_t n_units[SKRULL_UNIT_LISTS];  // work units of the forward / dQ list for 4, 8 and 12 wavefronts
     int32_t n_dkv_units;
+    // forward work in workgroups of 12 wavefronts, in half tiles of keys: of all units of a KV head, of the longest one
+    // (16 half tiles for a unit's start and end included)
+    int64_t fwd_load;
+    int32_t fwd_longest;
     SplitChoice split;         // how dK/dV items are shared (the units kernel's choice)
     int32_t cap_fwd, cap_dkv;  // room in the item arrays (the host's upper bounds)
     int32_t block_n;           // key rows per dK/dV item in effect (the ranges kernel's choice where open)

@@ -48,22 +48,25 @@ struct FwdParams {
     const int32_t *cu_k, *q_begin, *q_len, *kv_len;
     RowMap rows;               // which row blocks a workgroup's waves take
     int32_t Hq, Hkv, total_q;
-    int32_t variant;  // 0: 4 wavefronts, 128 rows per workgroup; 1: 8 wavefronts, 256 rows
+    int32_t variant;  // 0: 4 wavefronts, 128 rows per workgroup; 1: 8 wavefronts, 256 rows; 2: 12 wavefronts
     float scale_log2;  // softmax_scale * log2(e)
     WgTrace *trace;    // null, or one record per work item (measurement aid)
     WorkQueue *queue;  // work queue of the persistent launch, zeroed before use
     int32_t n_work, n_first;  // work items: what a plain grid would have as workgroups; workgroups launched
 };
 
-// Two shapes of the one kernel.  Large: 8 wavefronts = 8 row blocks per workgroup and
+// Shapes of the one kernel.  Large: 8 wavefronts = 8 row blocks per workgroup and
 // 4 ring slots per operand (two tiles being read, two being fetched; a barrier every
 // second tile); its 139 KB of LDS leave room for one workgroup per compute unit.  Small:
 // 4 wavefronts = 4 row blocks and 2 ring slots (fetch one tile ahead, a barrier every
 // tile), 70 KB, so that two workgroups share a compute unit and the start-up, drain and
 // barrier waits of one (most of the run time of a short sequence) hide behind the other.
-// The plan chooses per micro-batch.
+// The plan chooses per micro-batch.  At head_dim 64, where 152 registers allow three wavefronts per SIMD, there is
+// also a wide shape: the large one's rings (83 KB) with 12 wavefronts.  In a list of short sequences its third
+// wavefront per SIMD fills the starts, ends and latencies of the two others.
 constexpr int NW_LARGE = 8, NSLOT_LARGE = 4;
 constexpr int NW_SMALL = 4, NSLOT_SMALL = 2;
+constexpr int NW_WIDE = 12;
 
 // max / sum of a value over the two halves of the wavefront (lanes l and l ^ 32)
 // without going through LDS: two copies of x, the upper half of the first
@@ -358,9 +361,11 @@ __device__ __forceinline__ int fwd_work(const int bid, RowBlocks &rb, FwdFeed &f
     // for waves 2-3)
     typedef WaveStage<D> Stage;
     static_assert(2 * Stage::BYTES == TB, "two staging regions per ring slot");
-    static_assert((NSLOT == 4 && NW == 8) || (NSLOT == 2 && NW == 4), "staging regions are laid out for these shapes");
-    const uint32_t stage = NSLOT == 4 ? (wave < 4 ? ring_k + 2 * TB + (uint32_t)wave * Stage::BYTES
-                                                  : ring_v + TB + (uint32_t)(wave - 4) * Stage::BYTES)
+    static_assert((NSLOT == 4 && NW == 8) || (NSLOT == 4 && NW == 12) || (NSLOT == 2 && NW == 4), "staging regions are laid out for these shapes");
+    __shared__ __align__(16) unsigned char lds_more[NW > 10 ? (NW - 10) * Stage::BYTES : 16];
+    const uint32_t stage = NSLOT == 4 ? (wave < 4    ? ring_k + 2 * TB + (uint32_t)wave * Stage::BYTES
+                                         : wave < 10 ? ring_v + TB + (uint32_t)(wave - 4) * Stage::BYTES
+                                                     : lds_addr(lds_more) + (uint32_t)(wave - 10) * Stage::BYTES)
                                       : (wave < 2 ? ring_k + TB + (uint32_t)wave * Stage::BYTES
                                                   : ring_v + TB + (uint32_t)(wave - 2) * Stage::BYTES);
     {
@@ -480,7 +485,7 @@ __device__ __forceinline__ int fwd_work(const int bid, RowBlocks &rb, FwdFeed &f
 }
 
 template <int D, int NW, int NSLOT>
-__global__ __launch_bounds__(64 * NW, 2) void fwd_kernel(const FwdParams prm)
+__global__ __launch_bounds__(64 * NW, NW == NW_WIDE ? 3 : 2) void fwd_kernel(const FwdParams prm)
 {
     __shared__ int work_slot[2];
     FwdFeed feed{prm.queue, prm.n_work, prm.n_first, 0, work_slot};
@@ -520,6 +525,8 @@ template <int D>
 hipError_t launch_one(const FwdParams &prm, hipStream_t st)
 {
     if (prm.variant == 0) return launch_shape<fwd_kernel<D, NW_SMALL, NSLOT_SMALL>>(prm, 64 * NW_SMALL, st);
+    if constexpr (D == 64)
+        if (prm.variant == 2) return launch_shape<fwd_kernel<D, NW_WIDE, NSLOT_LARGE>>(prm, 64 * NW_WIDE, st);
     return launch_shape<fwd_kernel<D, NW_LARGE, NSLOT_LARGE>>(prm, 64 * NW_LARGE, st);
 }
 
@@ -527,6 +534,8 @@ template <int D>
 RowLaunch rows_fwd(const skrull_attn_plan_t *p)
 {
     if (p->wg_query_rows == 32 * NW_SMALL) return row_launch<fwd_kernel<D, NW_SMALL, NSLOT_SMALL>>(p, NW_SMALL);
+    if constexpr (D == 64)
+        if (p->fwd_wide) return row_launch<fwd_kernel<D, NW_WIDE, NSLOT_LARGE>>(p, NW_WIDE);
     return row_launch<fwd_kernel<D, NW_LARGE, NSLOT_LARGE>>(p, NW_LARGE);
 }
 
@@ -549,7 +558,7 @@ hipError_t launch_fwd(const skrull_attn_plan_t *p, const void *q, const void *k,
     prm.rows = rows.rows;
     prm.scale_log2 = p->scale * 1.4426950408889634f;
     prm.trace = trace;
-    prm.variant = p->wg_query_rows == 32 * NW_SMALL ? 0 : 1;
+    prm.variant = p->wg_query_rows == 32 * NW_SMALL ? 0 : (p->fwd_wide ? 2 : 1);
     prm.n_work = rows.n_work;
     // One of the plan's queue slots per call, taken in turn, so that forward calls of one plan
     // that overlap on different streams do not share a queue.

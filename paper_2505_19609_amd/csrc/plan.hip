@@ -207,7 +207,9 @@ __global__ __launch_bounds__(kScanThreads) void plan_ranges_kernel(
         totals->dkv_cost_sum = 0;
         totals->dkv_cost_max = 0;
         for (int i = 0; i <= SKRULL_CHAIN_LIMITS; ++i) totals->chain_hist[i] = 0;
-        totals->n_units[0] = totals->n_units[1] = totals->n_dkv_units = 0;
+        for (int i = 0; i < SKRULL_UNIT_LISTS; ++i) totals->n_units[i] = 0;
+        totals->n_dkv_units = totals->fwd_longest = 0;
+        totals->fwd_load = 0;
         totals->cap_fwd = cap_fwd;
         totals->cap_dkv = cap_dkv;
         totals->block_n = BN;
@@ -485,7 +487,7 @@ struct UnitsJob {
     const int4 *fwd_items, *dkv_items;
     const int32_t *q_begin, *q_len, *kv_len, *shares_kv;
     int32_t BM, q_heads, kv_heads, head_dim, asked, longest_seq, compute_units;
-    int32_t *units[2], *dkv_units;  // forward / dQ for 4 and 8 waves; dK/dV; null: no list
+    int32_t *units[SKRULL_UNIT_LISTS], *dkv_units;  // null: no list
 };
 __global__ __launch_bounds__(256) void plan_units_kernel(UnitsJob j, PlanTotals *totals)
 {
@@ -501,7 +503,7 @@ __global__ __launch_bounds__(256) void plan_units_kernel(UnitsJob j, PlanTotals 
     }
     const int32_t n = dkv ? (int32_t)min((long long)totals->n_dkv, (long long)totals->cap_dkv)
                           : (int32_t)min((long long)totals->n_fwd, (long long)totals->cap_fwd);
-    const int32_t log_nw = blockIdx.y + 1;  // forward / dQ: 4 or 8 waves
+    const int32_t NW = 4 * blockIdx.y;  // forward / dQ: waves of a workgroup
     int32_t *units = dkv ? j.dkv_units : j.units[max((int)blockIdx.y - 1, 0)];
     if (!units || first >= n) return;  // (the whole block)
     __syncthreads();
@@ -523,11 +525,12 @@ __global__ __launch_bounds__(256) void plan_units_kernel(UnitsJob j, PlanTotals 
             const int4 it = j.fwd_items[i];
             const int32_t row0 = it.y * j.BM, rows = min(j.BM, j.q_len[it.x] - row0);
             cost = (int32_t)(((uint32_t)(j.q_begin[it.x] + row0 + rows) + 31u) >> 5);
-            parts = (((rows + 31) >> 5) * group + (1 << log_nw) - 1) >> log_nw;
+            parts = (((rows + 31) >> 5) * group + NW - 1) / NW;
         }
     };
     const int32_t a = first + threadIdx.x / 4, quarter = threadIdx.x % 4;
-    int32_t my_cost = 0, my_parts = 0, rank = 0, sum = 0;
+    int32_t my_cost = 0, my_parts = 0, rank = 0, sum = 0, longest = 0;
+    int64_t load = 0;
     if (a < n) unit_of(a, my_cost, my_parts);
     for (int32_t b0 = 0; b0 < n; b0 += 1024) {
         __syncthreads();
@@ -538,6 +541,8 @@ __global__ __launch_bounds__(256) void plan_units_kernel(UnitsJob j, PlanTotals 
             // ahead of this item: a larger cost, or an equal one and earlier in the list
             rank += t_cost[x] >= my_cost + (b0 + x >= a) ? t_parts[x] : 0;
             sum += t_parts[x];
+            load += (int64_t)t_parts[x] * (t_cost[x] + 16);
+            longest = max(longest, t_cost[x] + 16);
         }
     }
     rank += __shfl_xor(rank, 1, 64);
@@ -546,7 +551,17 @@ __global__ __launch_bounds__(256) void plan_units_kernel(UnitsJob j, PlanTotals 
     sum += __shfl_xor(sum, 2, 64);
     if (a < n)
         for (int32_t p = quarter; p < my_parts; p += 4) units[rank + p] = a | p << SKRULL_UNIT_SHIFT;
-    if (first == 0 && threadIdx.x == 0) *(dkv ? &totals->n_dkv_units : &totals->n_units[log_nw - 2]) = sum;
+    if (NW == 12) {
+        load += __shfl_xor(load, 1, 64);
+        load += __shfl_xor(load, 2, 64);
+        longest = max(longest, __shfl_xor(longest, 1, 64));
+        longest = max(longest, __shfl_xor(longest, 2, 64));
+        if (first == 0 && threadIdx.x == 0) {
+            totals->fwd_load = load;
+            totals->fwd_longest = longest;
+        }
+    }
+    if (first == 0 && threadIdx.x == 0) *(dkv ? &totals->n_dkv_units : &totals->n_units[blockIdx.y - 1]) = sum;
 }
 
 // ---------------------------------------------------------------------------
@@ -666,8 +681,8 @@ int plan_radix_passes(int32_t cap, int32_t cost_bound)
 
 int64_t plan_unit_ints(const skrull_attn_plan_t *p, int32_t cap_fwd, int which)
 {
-    if (cap_fwd > kRankSortMax || p->Hq > SKRULL_UNIT_HEADS) return 0;
-    const int waves = which == 0 ? 4 : 8;
+    const int waves = 4 * (which + 1);
+    if (cap_fwd > kRankSortMax || p->Hq > SKRULL_UNIT_HEADS || (waves == 12 && p->d != 64)) return 0;
     return (int64_t)cap_fwd * ((p->BM / 32 * (p->Hq / p->Hkv) + waves - 1) / waves);
 }
 
@@ -747,9 +762,9 @@ hipError_t launch_plan_units(const skrull_attn_plan_t *p, int32_t asked, int32_t
                              int32_t compute_units, PlanTotals *totals, hipStream_t st)
 {
     const int32_t f = p->units[0] ? cap_fwd : 1, d = p->dkv_units ? cap_dkv : 1, most = f > d ? f : d;
-    plan_units_kernel<<<dim3((most + kSortItems - 1) / kSortItems, p->units[0] ? 3 : 1), 256, 0, st>>>(
+    plan_units_kernel<<<dim3((most + kSortItems - 1) / kSortItems, p->units[0] ? 1 + SKRULL_UNIT_LISTS : 1), 256, 0, st>>>(
         UnitsJob{(const int4 *)p->fwd_items, (const int4 *)p->dkv_items, p->q_begin, p->q_len, p->kv_len, p->shares_kv, p->BM, p->Hq,
-                 p->Hkv, p->d, asked, longest_seq, compute_units, {p->units[0], p->units[1]}, p->dkv_units},
+                 p->Hkv, p->d, asked, longest_seq, compute_units, {p->units[0], p->units[1], p->units[2]}, p->dkv_units},
         totals);
     return hipGetLastError();
 }

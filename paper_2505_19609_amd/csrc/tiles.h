@@ -120,7 +120,7 @@ static inline uint64_t inverse_of(int d) { return ((1ull << 40) + d - 1) / d; }
 static inline RowMap row_map(const skrull_attn_plan_t *p, int NW)
 {
     const int g = p->Hq / p->Hkv;
-    return RowMap{p->BM, g, p->Hkv, (p->BM / 32 * g + NW - 1) / NW, 0, p->units[NW == 8], inverse_of(g), inverse_of(p->Hkv)};
+    return RowMap{p->BM, g, p->Hkv, (p->BM / 32 * g + NW - 1) / NW, 0, p->units[NW / 4 - 1], inverse_of(g), inverse_of(p->Hkv)};
 }
 // How a forward / dQ launch is laid out.
 //  `spread`, for launches whose workgroups all run at once: neighbouring row blocks go to
@@ -150,7 +150,7 @@ static RowLaunch row_launch(const skrull_attn_plan_t *p, int NW)
         r.rows.units = nullptr;
         r.rows.parts = r.rows.g * per_head;
     }
-    r.n_work = r.rows.units ? p->n_units[NW == 8] * p->Hkv : p->n_fwd * p->Hkv * r.rows.parts;
+    r.n_work = r.rows.units ? p->n_units[NW / 4 - 1] * p->Hkv : p->n_fwd * p->Hkv * r.rows.parts;
     r.queued = resident > 0 && r.n_work > resident;
     r.rows.spread = !r.queued;
     return r;

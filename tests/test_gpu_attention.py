@@ -1034,3 +1034,23 @@ def test_dkv_units_of_items_of_many_lengths(oracle, heads, d):
         assert np.array_equal(t[n].float().cpu().numpy(), out[n]), n
     plan.destroy()
     dev["plan"].destroy()
+
+
+@pytest.mark.parametrize("heads", [(14, 2), (9, 3), (16, 1), (24, 8)])
+def test_wide_forward_changes_no_bit(heads):
+    """At head_dim 64 the plan gives the forward of a list of many short sequences workgroups of 12 wavefronts
+    (fewer work items than with 8); asked for 256 rows it has 8.  Row blocks of 1 to 8 x g blocks, slices and
+    both chunks of a cut, some parts with one row block; every output has the same bits."""
+    from paper_2505_19609_amd import binding as B
+    S = [1, 31, 32, 33, 255, 256, 257, 300, 511, 700, 97] * 8 + [640, 900]
+    N, R, Z = [1] * 88 + [2, 3], [0] * 88 + [1, 1], [0] * 88 + [0, 1]
+    w = W.Workload("wide", S, N, R, heads[0], heads[1], 64, 64 ** -0.5, 609, shard_cut=Z)
+    out = run_library(w, backward=False)
+    ref = run_library(w, backward=False, vals=out["vals"], wg_query_rows=256)
+    assert out["plan"].info.wg_query_rows == 256
+    n, n8 = (B.skrull_attn_trace_layout(x["plan"])[1][0] for x in (out, ref))
+    assert n < n8 <= 3 * n // 2
+    for k in ("o", "lse"):
+        assert np.array_equal(out[k], ref[k]), k
+    out["plan"].destroy()
+    ref["plan"].destroy()
