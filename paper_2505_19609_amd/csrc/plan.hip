@@ -471,18 +471,20 @@ __device__ inline int32_t parts_of_item(const SplitChoice &c, int32_t item, int3
 
 // The order in which work is handed out: the longest first, as in the item lists, but by what a work
 // unit takes: for dK/dV an item's part by its rounds (64-row query tiles x heads), for the forward and dQ
-// an item by its half tiles of keys.  The items' own costs count blocks of 256 rows, in which most short
+// at head_dim 64 an item by its half tiles of keys.  The items' own costs count blocks of 256 rows, in which most short
 // sequences look alike, and whole items went out before the parts of shared ones, whatever their
 // length: launches ended with long units that had begun late.  dQ and dK/dV together, by the items' costs
 // and this way: 64 sequences, 26,624 tokens, 14/2 heads of 64: 240 -> 229 us; 20 sequences, 16,384 tokens: 248 ->
 // 236; 114 sequences of 16 to 1,024, 32,768 tokens: 218 -> 198; 10 sequences, 13,312 tokens, 28/4 heads of 128: 857
-// -> 845.  The forward gains 1 % at head_dim 64.
-// What is not done: the parts of a forward / dQ item apart from each other by their own half tiles
-// (114 sequences of about 250 tokens, 32/8 heads of 128: forward 215 -> 236, dQ 303 -> 328; they read the same
-// keys and find them in their die's L2 only when they run together), and key blocks with less work than an eighth of
-// an even share per compute unit (`small`, in rounds; a cost counts for four) in any other order than the list's, which has those of a
-// sequence together (the same 114 sequences, backward: 650 -> 662 us without that line, 26,624 tokens 229
-// -> 241 with it at a quarter).
+// -> 845.  The forward gains 1 % at head_dim 64 (at 128 neither it nor dQ gains).
+// What is not done, because units that read the same tiles find them in their die's L2 when they run together:
+//  the parts of a forward / dQ item apart from each other by their own half tiles (114 sequences of about 250
+//    tokens, 32/8 heads of 128: forward 215 -> 236, dQ 303 -> 328);
+//  key blocks with less work than a part (an eighth, or a quarter at head_dim 128 where no item is shared) of an
+//    even share per compute unit (`small`, in rounds; a cost counts for four) apart from the others of their sequence: they go
+//    out by their sequence's length (the same 114 sequences, backward: 653 us, by their own rounds 666, by the
+//    items' costs 663; 26,624 tokens above 237, 249 with a quarter);
+//  any order but the list's where all units run at once (4,923 tokens, 28/4 heads of 128: 111 us, else 114).
 struct UnitsJob {
     const int4 *fwd_items, *dkv_items;
     const int32_t *q_begin, *q_len, *kv_len, *shares_kv;
@@ -509,7 +511,8 @@ __global__ __launch_bounds__(256) void plan_units_kernel(UnitsJob j, PlanTotals 
     __syncthreads();
     const SplitChoice choice = shared_choice;
     const int32_t BN = totals->block_n;
-    const int32_t small = (int32_t)min(totals->dkv_cost_sum * j.q_heads / (2 * (unsigned long long)j.compute_units), 1ull << 29);
+    const int32_t fine = j.head_dim == 64 || choice.parts > 1 ? 2 : 1;
+    const int32_t small = (int32_t)min(totals->dkv_cost_sum * j.q_heads / (fine * (unsigned long long)j.compute_units), 1ull << 29);
     auto tiles = [&](int32_t seq, int32_t kv0) {  // query tiles of a segment that see key kv0 or later ones
         const int32_t i0 = max(0, kv0 - j.q_begin[seq]);
         return ((j.q_len[seq] + 63) >> 6) - (i0 >> 6);
@@ -520,16 +523,18 @@ __global__ __launch_bounds__(256) void plan_units_kernel(UnitsJob j, PlanTotals 
             int32_t c = tiles(it.x, it.y * BN);
             if (j.shares_kv[it.x] && it.y * BN < j.kv_len[it.x - 1]) c += tiles(it.x - 1, it.y * BN);
             parts = parts_of_item(choice, i, it.w, group);
-            cost = max((min(c, 1 << 20) * group + parts - 1) / parts, small);
+            int32_t whole = tiles(it.x, 0);
+            if (j.shares_kv[it.x]) whole += tiles(it.x - 1, 0);
+            cost = max((min(c, 1 << 20) * group + parts - 1) / parts, min(min(whole, 1 << 20) * group, small));
         } else {
             const int4 it = j.fwd_items[i];
             const int32_t row0 = it.y * j.BM, rows = min(j.BM, j.q_len[it.x] - row0);
-            cost = (int32_t)(((uint32_t)(j.q_begin[it.x] + row0 + rows) + 31u) >> 5);
+            cost = j.head_dim == 64 ? (int32_t)(((uint32_t)(j.q_begin[it.x] + row0 + rows) + 31u) >> 5) : 0;
             parts = (((rows + 31) >> 5) * group + NW - 1) / NW;
         }
     };
     const int32_t a = first + threadIdx.x / 4, quarter = threadIdx.x % 4;
-    int32_t my_cost = 0, my_parts = 0, rank = 0, sum = 0, longest = 0;
+    int32_t my_cost = 0, my_parts = 0, rank = 0, before = 0, sum = 0, longest = 0;
     int64_t load = 0;
     if (a < n) unit_of(a, my_cost, my_parts);
     for (int32_t b0 = 0; b0 < n; b0 += 1024) {
@@ -540,6 +545,7 @@ __global__ __launch_bounds__(256) void plan_units_kernel(UnitsJob j, PlanTotals 
         for (int32_t x = quarter; x < lim; x += 4) {
             // ahead of this item: a larger cost, or an equal one and earlier in the list
             rank += t_cost[x] >= my_cost + (b0 + x >= a) ? t_parts[x] : 0;
+            before += b0 + x < a ? t_parts[x] : 0;
             sum += t_parts[x];
             load += (int64_t)t_parts[x] * (t_cost[x] + 16);
             longest = max(longest, t_cost[x] + 16);
@@ -547,8 +553,11 @@ __global__ __launch_bounds__(256) void plan_units_kernel(UnitsJob j, PlanTotals 
     }
     rank += __shfl_xor(rank, 1, 64);
     rank += __shfl_xor(rank, 2, 64);
+    before += __shfl_xor(before, 1, 64);
+    before += __shfl_xor(before, 2, 64);
     sum += __shfl_xor(sum, 1, 64);
     sum += __shfl_xor(sum, 2, 64);
+    if (dkv && (int64_t)sum * j.kv_heads * (BN == 256 ? 2 : 1) <= j.compute_units) rank = before;
     if (a < n)
         for (int32_t p = quarter; p < my_parts; p += 4) units[rank + p] = a | p << SKRULL_UNIT_SHIFT;
     if (NW == 12) {
