@@ -10,6 +10,7 @@
 #include <string.h>
 
 #include <atomic>
+#include <mutex>
 #include <new>
 
 #include "common.h"
@@ -74,6 +75,42 @@ int resolve_scratch(int dev, void **out)
     return SKRULL_OK;
 }
 
+// Pinned host memory through which a plan's kernels get their input and give its totals back: a few
+// slots for the whole process, one for the time of a call; a call that finds none copies instead.
+struct PinnedSlots {
+    static constexpr int kSlots = 16;
+    static constexpr size_t kIn = 4 * (size_t)SKRULL_SMALL_PLAN * sizeof(int32_t), kBytes = (kIn + sizeof(PlanTotals) + 255) & ~(size_t)255;
+    std::mutex made;
+    unsigned char *base = nullptr;  // held until the process ends
+    bool tried = false;
+    std::atomic<uint32_t> used{0};
+
+    int32_t *take()
+    {
+        {
+            std::lock_guard<std::mutex> lock(made);
+            if (!tried) {
+                tried = true;
+                void *p = nullptr;
+                if (hipHostMalloc(&p, kSlots * kBytes, hipHostMallocPortable) == hipSuccess) base = (unsigned char *)p;
+                else (void)hipGetLastError();
+            }
+        }
+        uint32_t u = used.load(std::memory_order_relaxed);
+        while (base) {
+            const int free_slot = __builtin_ffs(~u & ((1u << kSlots) - 1)) - 1;
+            if (free_slot < 0) break;
+            if (used.compare_exchange_weak(u, u | 1u << free_slot, std::memory_order_acquire)) return (int32_t *)(base + free_slot * kBytes);
+        }
+        return nullptr;
+    }
+    void give_back(int32_t *slot)
+    {
+        if (slot) used.fetch_and(~(1u << (((unsigned char *)slot - base) / kBytes)), std::memory_order_release);
+    }
+};
+PinnedSlots g_pinned;
+
 int check_device(int *dev_out, int *compute_units)
 {
     int n = 0;
@@ -126,7 +163,7 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
     // them next to the range computation.  The same pass bounds the number of work
     // items from above (chunk lengths differ by at most one row; a prefix is no longer
     // than its sequence), which sizes the allocations and the grids, so that the whole
-    // plan is built with one copy in, one copy out and one synchronisation.
+    // plan is built with one synchronisation.
     int64_t n_seg = 0;  // query segments: a two-chunk cut contributes two
     int32_t longest_seq = 0;
     const int64_t q_row_bytes = (int64_t)p->num_q_heads * p->head_dim * 2;
@@ -180,10 +217,12 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
 
     hipStream_t st = (hipStream_t)hip_stream;
     skrull_attn_plan_t *plan = nullptr;
-    int32_t *tmp = nullptr, *host_in = nullptr;
-    PlanTotals totals;
+    int32_t *tmp = nullptr, *host_in = nullptr, *pinned = nullptr;
+    PlanTotals totals, *totals_h = nullptr;
+    int64_t in_stride = 0;
+    bool small = false;  // made by one workgroup
     // tmp (released before return): S, N, R, cut [K each] | fwd_off, dkv_off [n_seg+1 each] |
-    // totals | unsorted items
+    // totals | unsorted items; a small plan needs none
     const int64_t kin = align4(K), kpad = align4(n_seg + 1);
     const int64_t totals_ints = align4((int64_t)((sizeof(PlanTotals) + 3) / 4));
     // no work item costs more than this many blocks (64 rows is the smallest block; a two-chunk
@@ -203,14 +242,18 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
     plan->K = K; plan->NS = (int32_t)n_seg; plan->Hq = p->num_q_heads; plan->Hkv = p->num_kv_heads; plan->d = p->head_dim;
     plan->BM = BM; plan->BN = BN; plan->scale = p->softmax_scale; plan->device = dev;
 
-    host_in = (int32_t *)calloc((size_t)(4 * kin), sizeof(int32_t));
+    if (K <= SKRULL_SMALL_PLAN) pinned = g_pinned.take();
+    small = pinned && n_seg <= SKRULL_SMALL_PLAN && cap_fwd <= SKRULL_SMALL_PLAN && cap_dkv <= SKRULL_SMALL_PLAN;
+    in_stride = pinned ? SKRULL_SMALL_PLAN : kin;
+    host_in = pinned ? pinned : (int32_t *)calloc((size_t)(4 * kin), sizeof(int32_t));
     if (!host_in) { rc = SKRULL_ENOMEM; goto done; }
     memcpy(host_in, p->seq_len, (size_t)K * 4);
-    memcpy(host_in + kin, p->shard_degree, (size_t)K * 4);
-    memcpy(host_in + 2 * kin, p->shard_index, (size_t)K * 4);
-    if (p->shard_cut) memcpy(host_in + 3 * kin, p->shard_cut, (size_t)K * 4);
+    memcpy(host_in + in_stride, p->shard_degree, (size_t)K * 4);
+    memcpy(host_in + 2 * in_stride, p->shard_index, (size_t)K * 4);
+    if (p->shard_cut) memcpy(host_in + 3 * in_stride, p->shard_cut, (size_t)K * 4);
+    else memset(host_in + 3 * in_stride, 0, (size_t)K * 4);
 
-    HIP_TRY(hipMalloc((void **)&tmp, (size_t)tmp_ints * sizeof(int32_t)));
+    if (!small) HIP_TRY(hipMalloc((void **)&tmp, (size_t)tmp_ints * sizeof(int32_t)));
     for (int i = 0; i < SKRULL_UNIT_LISTS; ++i) all_unit_ints += unit_ints[i] = plan_unit_ints(plan, (int32_t)cap_fwd, i);
     dkv_unit_ints = plan_dkv_unit_ints(plan, p->head_split, (int32_t)cap_dkv);
     HIP_TRY(hipMalloc((void **)&plan->pool, (size_t)(queue_ints + desc_ints + 4 * (cap_fwd + cap_dkv) + all_unit_ints + dkv_unit_ints) * sizeof(int32_t)));
@@ -231,24 +274,38 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
         }
         if (dkv_unit_ints > 0) plan->dkv_units = next;
     }
-    fwd_off = tmp + 4 * kin;
-    dkv_off = fwd_off + kpad;
-    totals_d = (PlanTotals *)(dkv_off + kpad);
-    scratch = dkv_off + kpad + totals_ints;
-    // a pageable source is staged by the runtime before the call returns
-    HIP_TRY(hipMemcpyAsync(tmp, host_in, (size_t)(4 * kin) * 4, hipMemcpyHostToDevice, st));
-    HIP_TRY(launch_plan_ranges(tmp, tmp + kin, tmp + 2 * kin, tmp + 3 * kin, K, BM, BN,
-                               INT32_MAX / (p->num_q_heads * p->head_dim),
-                               INT32_MAX / (p->num_kv_heads * p->head_dim), plan->q_begin,
-                               plan->q_len, plan->kv_len, plan->cu_q, plan->cu_k, plan->shares_kv,
-                               fwd_off, dkv_off, (int32_t)cap_fwd, (int32_t)cap_dkv, bn_alt, p->num_kv_heads,
-                               compute_units, totals_d, st));
-    HIP_TRY(launch_plan_items(plan, fwd_off, dkv_off, (int32_t)cap_fwd, (int32_t)cap_dkv, scratch,
-                              scratch + 4 * cap_fwd, scratch + 4 * (cap_fwd + cap_dkv), cost_bound, compute_units,
-                              totals_d, st));
-    HIP_TRY(launch_plan_units(plan, p->head_split, longest_seq, (int32_t)cap_fwd, (int32_t)cap_dkv, compute_units, totals_d, st));
-    HIP_TRY(hipMemcpyAsync(&totals, totals_d, sizeof totals, hipMemcpyDeviceToHost, st));
+    if (pinned) totals_h = (PlanTotals *)((unsigned char *)pinned + PinnedSlots::kIn);
+    if (small) {
+        HIP_TRY(launch_plan_small(SmallPlan{pinned, totals_h, K, (int32_t)in_stride, BM, BN, bn_alt,
+                                            INT32_MAX / (p->num_q_heads * p->head_dim), INT32_MAX / (p->num_kv_heads * p->head_dim),
+                                            (int32_t)cap_fwd, (int32_t)cap_dkv, p->num_q_heads, p->num_kv_heads, p->head_dim, p->head_split,
+                                            longest_seq, compute_units, plan->q_begin, plan->q_len, plan->kv_len, plan->cu_q, plan->cu_k,
+                                            plan->shares_kv, plan->fwd_items, plan->dkv_items,
+                                            {plan->units[0], plan->units[1], plan->units[2]}, plan->dkv_units}, st));
+    } else {
+        fwd_off = tmp + 4 * kin;
+        dkv_off = fwd_off + kpad;
+        totals_d = (PlanTotals *)(dkv_off + kpad);
+        scratch = dkv_off + kpad + totals_ints;
+        const int32_t *in = pinned;  // (the kernel reads pinned memory itself)
+        if (!pinned) {  // a pageable source is staged by the runtime before the call returns
+            HIP_TRY(hipMemcpyAsync(tmp, host_in, (size_t)(4 * kin) * 4, hipMemcpyHostToDevice, st));
+            in = tmp;
+        }
+        HIP_TRY(launch_plan_ranges(in, in + in_stride, in + 2 * in_stride, in + 3 * in_stride, K, BM, BN,
+                                   INT32_MAX / (p->num_q_heads * p->head_dim),
+                                   INT32_MAX / (p->num_kv_heads * p->head_dim), plan->q_begin,
+                                   plan->q_len, plan->kv_len, plan->cu_q, plan->cu_k, plan->shares_kv,
+                                   fwd_off, dkv_off, (int32_t)cap_fwd, (int32_t)cap_dkv, bn_alt, p->num_kv_heads,
+                                   compute_units, totals_d, st));
+        HIP_TRY(launch_plan_items(plan, fwd_off, dkv_off, (int32_t)cap_fwd, (int32_t)cap_dkv, scratch,
+                                  scratch + 4 * cap_fwd, scratch + 4 * (cap_fwd + cap_dkv), cost_bound, compute_units,
+                                  totals_d, st));
+        HIP_TRY(launch_plan_units(plan, p->head_split, longest_seq, (int32_t)cap_fwd, (int32_t)cap_dkv, compute_units, totals_d, st));
+        HIP_TRY(hipMemcpyAsync(pinned ? totals_h : &totals, totals_d, sizeof totals, hipMemcpyDeviceToHost, st));
+    }
     HIP_TRY(hipStreamSynchronize(st));
+    if (pinned) memcpy(&totals, totals_h, sizeof totals);
     if (totals.bad_entry != 0 || totals.n_seg != plan->NS || totals.total_q > INT32_MAX ||
         totals.total_k > INT32_MAX || totals.n_fwd > kMaxItems || totals.n_dkv > kMaxItems ||
         totals.n_fwd > cap_fwd || totals.n_dkv > cap_dkv) {
@@ -306,7 +363,8 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
     plan->n_dkv_units = totals.n_dkv_units;
     rc = SKRULL_OK;
 done:
-    free(host_in);
+    if (pinned) g_pinned.give_back(pinned);
+    else free(host_in);
     if (tmp) (void)hipFree(tmp);
     if (rc != SKRULL_OK) {
         if (plan) {

@@ -130,6 +130,17 @@ __device__ __forceinline__ void trace_end(WgTrace *t, uint64_t t0, int work)
 #endif
 
 // plan.hip
+// A plan made by one workgroup: at most SKRULL_SMALL_PLAN sequences, segments and items of either list.
+#define SKRULL_SMALL_PLAN 512
+struct SmallPlan {
+    const int32_t *in;      // pinned host memory: S, N, R, cut, `stride` ints apart
+    PlanTotals *totals;     // pinned host memory
+    int32_t K, stride, BM, BN, bn_alt, max_q_rows, max_k_rows, cap_fwd, cap_dkv;
+    int32_t q_heads, kv_heads, head_dim, asked, longest_seq, compute_units;
+    int32_t *q_begin, *q_len, *kv_len, *cu_q, *cu_k, *shares_kv, *fwd_items, *dkv_items;
+    int32_t *units[SKRULL_UNIT_LISTS], *dkv_units;
+};
+hipError_t launch_plan_small(const SmallPlan &job, hipStream_t st);
 hipError_t launch_plan_ranges(const int32_t *S, const int32_t *N, const int32_t *r,
                               const int32_t *cut, int32_t K, int32_t BM, int32_t BN,
                               int32_t max_q_rows, int32_t max_k_rows, int32_t *q_begin,

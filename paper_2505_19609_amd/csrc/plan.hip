@@ -4,7 +4,7 @@
 // full lengths S[K] plus, per sequence, local (degree 1) or distributed over N
 // ranks with this GPU holding slice `index` (Eq. 8: S_k/N tokens per rank), cut
 // either as one contiguous slice or as two chunks that balance the causal work.
-// Three small kernels:
+// Four small kernels, or, for a small micro-batch, one workgroup that does what they do (plan_small):
 //   1. plan_ranges : per-segment query/KV ranges, the packed offsets
 //                    (exclusive scans), per-segment work-item offsets, totals
 //   2. plan_emit   : one thread per work item writes {seq, block, x, cost}
@@ -14,6 +14,7 @@
 //                    first compute unit that frees up -- the paper's
 //                    least-loaded-first rule (Alg. 1, argmin over L) applied
 //                    to compute units instead of ranks.
+//   4. plan_units  : which dK/dV items several workgroups share, and the lists of work units
 #include "common.h"
 
 namespace {
@@ -59,7 +60,36 @@ __device__ inline int64_t block_max(int64_t v, int64_t *lds)
     return v;
 }
 
+__device__ inline int64_t wave_sum(int64_t v)
+{
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
+}
+__device__ inline int32_t wave_max(int32_t v)
+{
+    for (int off = 32; off > 0; off >>= 1) v = max(v, __shfl_xor(v, off, 64));
+    return v;
+}
+
 __device__ inline int64_t ceil_div64(int64_t a, int64_t b) { return (a + b - 1) / b; }
+
+// Choice between BN and a larger dK/dV block bn_alt (0 = no choice to make).  The larger
+// one is taken when, with blocks of BN key rows, the costliest work item exceeds an even
+// share of the whole list over the compute units (cost_max > cost_sum * Hkv / CUs), the
+// same ratio that decides the head split; the costs are those of the dK/dV items that
+// plan_emit_kernel would write for BN.  It is also taken, given a sequence of at least two
+// of the larger blocks, when their list is still long (at least five x KV heads per compute
+// unit) or when the costliest item stays under 0.7 of that even share.  Fewer, larger
+// workgroups run the rounds 7-18 % faster (measured on 14 to 64 heads x 16,384-65,536 tokens,
+// uniform and ragged lengths) but balance worse: with few items and a costliest one between
+// 0.7 and 1.0 of the even share, ragged micro-batches lost 4-15 % by them.
+__device__ inline bool larger_key_blocks(int64_t c_sum, int64_t c_max, int64_t n_alt, int64_t longest, int32_t bn_alt, int32_t kv_heads,
+                                         int32_t compute_units)
+{
+    const bool long_list = n_alt * kv_heads >= 5 * (int64_t)compute_units;
+    const bool even_list = 10 * c_max * compute_units <= 7 * c_sum * kv_heads;
+    return c_max * compute_units > c_sum * kv_heads || ((long_list || even_list) && longest >= 2 * (int64_t)bn_alt);
+}
 
 // One thread per sequence.  A sequence cut the contiguous way is one query
 // segment; one cut the load-balanced way (chunks r and 2N-1-r of 2N) is two
@@ -81,16 +111,6 @@ __global__ __launch_bounds__(kScanThreads) void plan_ranges_kernel(
     const int t = threadIdx.x;
     if (t == 0) first_bad = 0x7fffffff;
     __syncthreads();
-    // Choice between BN and a larger dK/dV block bn_alt (0 = no choice to make).  The larger
-    // one is taken when, with blocks of BN key rows, the costliest work item exceeds an even
-    // share of the whole list over the compute units (cost_max > cost_sum * Hkv / CUs), the
-    // same ratio that decides the head split; the costs are those of the dK/dV items that
-    // plan_emit_kernel would write for BN.  It is also taken, given a sequence of at least two
-    // of the larger blocks, when their list is still long (at least five x KV heads per compute
-    // unit) or when the costliest item stays under 0.7 of that even share.  Fewer, larger
-    // workgroups run the rounds 7-18 % faster (measured on 14 to 64 heads x 16,384-65,536 tokens,
-    // uniform and ragged lengths) but balance worse: with few items and a costliest one between
-    // 0.7 and 1.0 of the even share, ragged micro-batches lost 4-15 % by them.
     if (bn_alt != 0) {
         // (BM is a power of two and positions fit 32 bits: divided in 64 bits, this walk over the blocks
         // of one 3,629-token sequence was most of the 16 us that the kernel took; now 11)
@@ -128,10 +148,7 @@ __global__ __launch_bounds__(kScanThreads) void plan_ranges_kernel(
         block_exclusive_scan(n_alt, lds, &tot);
         n_alt = tot;
         longest = block_max(longest, lds);
-        const bool long_list = n_alt * kv_heads >= 5 * (int64_t)compute_units;
-        const bool even_list = 10 * c_max * compute_units <= 7 * c_sum * kv_heads;
-        if (c_max * compute_units > c_sum * kv_heads ||
-            ((long_list || even_list) && longest >= 2 * (int64_t)bn_alt))
+        if (larger_key_blocks(c_sum, c_max, n_alt, longest, bn_alt, kv_heads, compute_units))
             BN = bn_alt;
     }
     int64_t base_s = 0, base_q = 0, base_k = 0, base_f = 0, base_d = 0, pairs = 0;
@@ -485,6 +502,41 @@ __device__ inline int32_t parts_of_item(const SplitChoice &c, int32_t item, int3
 //    out by their sequence's length (the same 114 sequences, backward: 653 us, by their own rounds 666, by the
 //    items' costs 663; 26,624 tokens above 237, 249 with a quarter);
 //  any order but the list's where all units run at once (4,923 tokens, 28/4 heads of 128: 111 us, else 114).
+struct UnitCosts {
+    const int32_t *q_begin, *q_len, *kv_len, *shares_kv;
+    int32_t BM, BN, group, head_dim;
+    SplitChoice choice;
+    int32_t small;
+    // query tiles of a segment that see key kv0 or later ones
+    __device__ int32_t tiles(int32_t seq, int32_t kv0) const
+    {
+        const int32_t i0 = max(0, kv0 - q_begin[seq]);
+        return ((q_len[seq] + 63) >> 6) - (i0 >> 6);
+    }
+    // item `i` of the sorted dK/dV list: what a part of it costs, and how many there are
+    __device__ void dkv(const int4 &it, int32_t i, int32_t &cost, int32_t &parts) const
+    {
+        int32_t c = tiles(it.x, it.y * BN), whole = tiles(it.x, 0);
+        if (shares_kv[it.x]) {
+            whole += tiles(it.x - 1, 0);
+            if (it.y * BN < kv_len[it.x - 1]) c += tiles(it.x - 1, it.y * BN);
+        }
+        parts = parts_of_item(choice, i, it.w, group);
+        cost = max((min(c, 1 << 20) * group + parts - 1) / parts, min(min(whole, 1 << 20) * group, small));
+    }
+    // item of the forward / dQ list for workgroups of `waves` waves
+    __device__ void fwd(const int4 &it, int32_t waves, int32_t &cost, int32_t &parts) const
+    {
+        const int32_t row0 = it.y * BM, rows = min(BM, q_len[it.x] - row0);
+        cost = head_dim == 64 ? (int32_t)(((uint32_t)(q_begin[it.x] + row0 + rows) + 31u) >> 5) : 0;
+        parts = (((rows + 31) >> 5) * group + waves - 1) / waves;
+    }
+};
+__device__ inline int32_t small_block(const PlanTotals &totals, const SplitChoice &choice, int32_t q_heads, int32_t head_dim, int32_t compute_units)
+{
+    const int32_t fine = head_dim == 64 || choice.parts > 1 ? 2 : 1;
+    return (int32_t)min(totals.dkv_cost_sum * q_heads / (fine * (unsigned long long)compute_units), 1ull << 29);
+}
 struct UnitsJob {
     const int4 *fwd_items, *dkv_items;
     const int32_t *q_begin, *q_len, *kv_len, *shares_kv;
@@ -511,44 +563,33 @@ __global__ __launch_bounds__(256) void plan_units_kernel(UnitsJob j, PlanTotals 
     __syncthreads();
     const SplitChoice choice = shared_choice;
     const int32_t BN = totals->block_n;
-    const int32_t fine = j.head_dim == 64 || choice.parts > 1 ? 2 : 1;
-    const int32_t small = (int32_t)min(totals->dkv_cost_sum * j.q_heads / (fine * (unsigned long long)j.compute_units), 1ull << 29);
-    auto tiles = [&](int32_t seq, int32_t kv0) {  // query tiles of a segment that see key kv0 or later ones
-        const int32_t i0 = max(0, kv0 - j.q_begin[seq]);
-        return ((j.q_len[seq] + 63) >> 6) - (i0 >> 6);
-    };
+    const UnitCosts uc{j.q_begin, j.q_len, j.kv_len, j.shares_kv, j.BM, BN, group, j.head_dim, choice,
+                       dkv ? small_block(*totals, choice, j.q_heads, j.head_dim, j.compute_units) : 0};
     auto unit_of = [&](int32_t i, int32_t &cost, int32_t &parts) {
-        if (dkv) {
-            const int4 it = j.dkv_items[i];
-            int32_t c = tiles(it.x, it.y * BN);
-            if (j.shares_kv[it.x] && it.y * BN < j.kv_len[it.x - 1]) c += tiles(it.x - 1, it.y * BN);
-            parts = parts_of_item(choice, i, it.w, group);
-            int32_t whole = tiles(it.x, 0);
-            if (j.shares_kv[it.x]) whole += tiles(it.x - 1, 0);
-            cost = max((min(c, 1 << 20) * group + parts - 1) / parts, min(min(whole, 1 << 20) * group, small));
-        } else {
-            const int4 it = j.fwd_items[i];
-            const int32_t row0 = it.y * j.BM, rows = min(j.BM, j.q_len[it.x] - row0);
-            cost = j.head_dim == 64 ? (int32_t)(((uint32_t)(j.q_begin[it.x] + row0 + rows) + 31u) >> 5) : 0;
-            parts = (((rows + 31) >> 5) * group + NW - 1) / NW;
-        }
+        if (dkv) uc.dkv(j.dkv_items[i], i, cost, parts);
+        else uc.fwd(j.fwd_items[i], NW, cost, parts);
     };
     const int32_t a = first + threadIdx.x / 4, quarter = threadIdx.x % 4;
-    int32_t my_cost = 0, my_parts = 0, rank = 0, before = 0, sum = 0, longest = 0;
-    int64_t load = 0;
+    int32_t my_cost = 0, my_parts = 0, rank = 0, before = 0, sum = 0;
     if (a < n) unit_of(a, my_cost, my_parts);
     for (int32_t b0 = 0; b0 < n; b0 += 1024) {
         __syncthreads();
         const int32_t lim = min(1024, n - b0);
-        for (int32_t i = threadIdx.x; i < lim; i += blockDim.x) unit_of(b0 + i, t_cost[i], t_parts[i]);
+        for (int32_t i = threadIdx.x; i < ((lim + 15) & ~15); i += blockDim.x) {
+            t_cost[i] = -1;
+            t_parts[i] = 0;
+            if (i < lim) unit_of(b0 + i, t_cost[i], t_parts[i]);
+        }
         __syncthreads();
-        for (int32_t x = quarter; x < lim; x += 4) {
+#pragma unroll 2
+        for (int32_t x = 4 * quarter; x < lim; x += 16) {
+            const int4 c = *(const int4 *)&t_cost[x], p = *(const int4 *)&t_parts[x];
+            const int32_t y = b0 + x;
             // ahead of this item: a larger cost, or an equal one and earlier in the list
-            rank += t_cost[x] >= my_cost + (b0 + x >= a) ? t_parts[x] : 0;
-            before += b0 + x < a ? t_parts[x] : 0;
-            sum += t_parts[x];
-            load += (int64_t)t_parts[x] * (t_cost[x] + 16);
-            longest = max(longest, t_cost[x] + 16);
+            rank += (c.x >= my_cost + (y >= a) ? p.x : 0) + (c.y >= my_cost + (y + 1 >= a) ? p.y : 0) +
+                    (c.z >= my_cost + (y + 2 >= a) ? p.z : 0) + (c.w >= my_cost + (y + 3 >= a) ? p.w : 0);
+            before += (y < a ? p.x : 0) + (y + 1 < a ? p.y : 0) + (y + 2 < a ? p.z : 0) + (y + 3 < a ? p.w : 0);
+            sum += p.x + p.y + p.z + p.w;
         }
     }
     rank += __shfl_xor(rank, 1, 64);
@@ -560,17 +601,296 @@ __global__ __launch_bounds__(256) void plan_units_kernel(UnitsJob j, PlanTotals 
     if (dkv && (int64_t)sum * j.kv_heads * (BN == 256 ? 2 : 1) <= j.compute_units) rank = before;
     if (a < n)
         for (int32_t p = quarter; p < my_parts; p += 4) units[rank + p] = a | p << SKRULL_UNIT_SHIFT;
-    if (NW == 12) {
-        load += __shfl_xor(load, 1, 64);
-        load += __shfl_xor(load, 2, 64);
-        longest = max(longest, __shfl_xor(longest, 1, 64));
-        longest = max(longest, __shfl_xor(longest, 2, 64));
-        if (first == 0 && threadIdx.x == 0) {
-            totals->fwd_load = load;
-            totals->fwd_longest = longest;
+    if (NW == 12 && first == 0) {
+        int64_t load = 0;
+        int32_t longest = 0;
+        for (int32_t i = threadIdx.x; i < n; i += blockDim.x) {
+            int32_t cost, parts;
+            unit_of(i, cost, parts);
+            load += (int64_t)parts * (cost + 16);
+            longest = max(longest, cost + 16);
+        }
+        load = wave_sum(load);
+        longest = wave_max(longest);
+        if ((threadIdx.x & 63) == 0) {  // (zeroed by the ranges kernel)
+            atomicAdd((unsigned long long *)&totals->fwd_load, (unsigned long long)load);
+            atomicMax(&totals->fwd_longest, longest);
         }
     }
     if (first == 0 && threadIdx.x == 0) *(dkv ? &totals->n_dkv_units : &totals->n_units[blockIdx.y - 1]) = sum;
+}
+
+// ---------------------------------------------------------------------------
+// The whole plan of a small micro-batch in one workgroup: what the four kernels above write, with everything
+// in between in LDS.  A plan is a chain of small dependent steps that nothing overlaps: four launches, a copy in, a
+// copy out and scratch memory around them took most of its time.  The input is read from pinned host memory
+// and the totals are written there.  The call (without destroying the plan), before and after: 3 sequences 49 ->
+// 37 us, 20 sequences with 76 and 95 items 62 -> 42, 64 with 135 and 173 items 67 -> 54, 114 with 181 and 310
+// items 73 -> 70 (the ranks are quadratic: 512 items of a list are the line, where it is as fast as the others);
+// the kernel itself takes 12, 16, 19 and 30 us.
+// ---------------------------------------------------------------------------
+constexpr int kSmallThreads = SKRULL_SMALL_PLAN, kSmallWaves = kSmallThreads / 64;
+
+// Exclusive scans of N values per thread over the workgroup, and their totals.
+template <int N>
+__device__ inline void scan_all(const int32_t (&v)[N], int32_t (&excl)[N], int32_t (&total)[N], int32_t (*lds)[kSmallWaves])
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int32_t incl[N];
+    for (int i = 0; i < N; ++i) incl[i] = v[i];
+    for (int off = 1; off < 64; off <<= 1)
+        for (int i = 0; i < N; ++i) {
+            const int32_t up = __shfl_up(incl[i], off, 64);
+            if (lane >= off) incl[i] += up;
+        }
+    __syncthreads();  // (the last scan's totals have been read)
+    if (lane == 63)
+        for (int i = 0; i < N; ++i) lds[i][wave] = incl[i];
+    __syncthreads();
+    for (int i = 0; i < N; ++i) {
+        int32_t before = 0, all = 0;
+#pragma unroll
+        for (int w = 0; w < kSmallWaves; w += 4) {
+            const int4 x = *(const int4 *)&lds[i][w];
+            before += (w < wave ? x.x : 0) + (w + 1 < wave ? x.y : 0) + (w + 2 < wave ? x.z : 0) + (w + 3 < wave ? x.w : 0);
+            all += x.x + x.y + x.z + x.w;
+        }
+        excl[i] = before + incl[i] - v[i];
+        total[i] = all;
+    }
+}
+
+// Position of item `a` of `n` in the stable order of descending cost (costs padded with -1 to a multiple of
+// 16); 1 << log_t neighbouring threads, this one being `sub` of them, share an item.
+__device__ inline int32_t rank_in(const int32_t *costs, int32_t n, int32_t a, int32_t sub, int32_t log_t)
+{
+    const int32_t mine = costs[a];
+    int32_t rank = 0;
+    for (int32_t x = 16 * sub; x < n; x += 16 << log_t) {
+        int4 c[4];  // (four reads under way: one at a time, each took the latency of the LDS)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) c[i] = *(const int4 *)&costs[x + 4 * i];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int32_t y = x + 4 * i;
+            rank += (c[i].x >= mine + (y >= a)) + (c[i].y >= mine + (y + 1 >= a)) + (c[i].z >= mine + (y + 2 >= a)) + (c[i].w >= mine + (y + 3 >= a));
+        }
+    }
+    if (log_t > 0) rank += __shfl_xor(rank, 1, 64);
+    if (log_t > 1) rank += __shfl_xor(rank, 2, 64);
+    return rank;
+}
+
+__global__ __launch_bounds__(kSmallThreads) void plan_small_kernel(SmallPlan j)
+{
+    __shared__ __align__(16) int32_t q_begin[kSmallThreads + 1], q_len[kSmallThreads + 1], kv_len[kSmallThreads + 1], cu_q[kSmallThreads + 1];
+    __shared__ __align__(16) int32_t shares[kSmallThreads + 1], fwd_off[kSmallThreads + 1], dkv_off[kSmallThreads + 1], alt_off[kSmallThreads + 1];
+    __shared__ __align__(16) int4 fwd[kSmallThreads], dkv[kSmallThreads];
+    __shared__ __align__(16) int32_t cost_f[kSmallThreads], cost_d[kSmallThreads], at[4][kSmallThreads], order[2][kSmallThreads];
+    __shared__ __align__(16) int32_t scans[6][kSmallWaves];
+    __shared__ int32_t first_bad, longest_s, cost_max;
+    __shared__ unsigned long long sum_s, pairs_s, load_s;
+    __shared__ PlanTotals tot;
+    const int t = threadIdx.x;
+    const int32_t group = j.q_heads / j.kv_heads, log_bm = __ffs(j.BM) - 1;  // (BM is a power of two)
+    if (t == 0) {
+        first_bad = 0x7fffffff;
+        longest_s = cost_max = 0;
+        sum_s = pairs_s = load_s = 0;
+    }
+    for (int i = t; i < (int)(sizeof tot / 4); i += kSmallThreads) ((int32_t *)&tot)[i] = 0;
+    // --- ranges of the sequences' segments
+    int32_t qb[2] = {0, 0}, qe[2] = {0, 0}, nseg = 0;
+    int64_t pr = 0;
+    bool bad = false;
+    if (t < j.K) {
+        const int32_t s = j.in[t], n = j.in[j.stride + t], r = j.in[2 * j.stride + t], z = j.in[3 * j.stride + t];
+        const int64_t chunks = (int64_t)n * (z ? 2 : 1);
+        bad = s < 1 || n < 1 || r < 0 || r >= n || (z != 0 && z != 1) || chunks > s;
+        if (!bad) {
+            nseg = z + 1;
+            const int64_t idx[2] = {r, 2 * (int64_t)n - 1 - r};
+            for (int part = 0; part < nseg; ++part) {
+                qb[part] = chunks == 1 ? 0 : (int32_t)((idx[part] * s) / chunks);
+                qe[part] = chunks == 1 ? s : (int32_t)(((idx[part] + 1) * s) / chunks);
+                pr += ((int64_t)qe[part] * (qe[part] + 1) - (int64_t)qb[part] * (qb[part] + 1)) / 2;
+            }
+        }
+    }
+    const int32_t end = nseg ? qe[nseg - 1] : 0;
+    if (nseg) bad = qe[0] - qb[0] + qe[1] - qb[1] > j.max_q_rows || end > j.max_k_rows;
+    __syncthreads();
+    if (bad) atomicMin(&first_bad, t);
+    // --- offsets, for both sizes of key blocks that may be taken
+    int32_t nf[2];
+    for (int part = 0; part < 2; ++part) nf[part] = (qe[part] - qb[part] + j.BM - 1) >> log_bm;
+    const int32_t bn_alt = j.bn_alt ? j.bn_alt : j.BN;
+    const int32_t v[6] = {nseg, qe[0] - qb[0] + qe[1] - qb[1], end, nf[0] + nf[1], (int32_t)((uint32_t)(end + j.BN - 1) / (uint32_t)j.BN),
+                          (int32_t)((uint32_t)(end + bn_alt - 1) / (uint32_t)bn_alt)};
+    int32_t e[6], n_all[6];
+    scan_all<6>(v, e, n_all, scans);
+    for (int part = 0; part < nseg; ++part) {
+        const int32_t sg = e[0] + part;
+        j.q_begin[sg] = q_begin[sg] = qb[part];
+        j.q_len[sg] = q_len[sg] = qe[part] - qb[part];
+        j.kv_len[sg] = kv_len[sg] = qe[part];
+        j.cu_q[sg] = cu_q[sg] = e[1] + (part ? qe[0] - qb[0] : 0);
+        j.cu_k[sg] = e[2];
+        j.shares_kv[sg] = shares[sg] = part;
+        fwd_off[sg] = e[3] + (part ? nf[0] : 0);
+        dkv_off[sg] = e[4];
+        alt_off[sg] = e[5];
+    }
+    pr = wave_sum(pr);
+    const int32_t longest_end = wave_max(end);
+    if ((t & 63) == 0) {
+        atomicAdd(&pairs_s, (unsigned long long)pr);
+        atomicMax(&longest_s, longest_end);
+    }
+    const int32_t NS = n_all[0], n_fwd = min(n_all[3], j.cap_fwd);
+    if (t == 0) {
+        j.cu_q[NS] = n_all[1];
+        j.cu_k[NS] = n_all[2];
+        fwd_off[NS] = n_all[3];
+        dkv_off[NS] = n_all[4];
+        alt_off[NS] = n_all[5];
+    }
+    __syncthreads();
+    // --- items and their costs, as in plan_emit_kernel
+    int4 f = make_int4(0, 0, 0, -1), d = make_int4(0, 0, 0, -1);
+    // dK/dV item `i` for key blocks of `bn` rows, whose offsets are `off`
+    auto key_item = [&](const int32_t *off, int32_t bn, int32_t i) {
+        const int32_t k = owner_of(off, NS, i), b = i - off[k], m0 = max(b * bn - q_begin[k], 0) >> log_bm;
+        int32_t cost = ((q_len[k] - 1) >> log_bm) + 1 - m0;
+        if (shares[k] && b * bn < kv_len[k - 1]) cost += ((q_len[k - 1] - 1) >> log_bm) + 1 - (max(b * bn - q_begin[k - 1], 0) >> log_bm);
+        return make_int4(k, b, m0, cost);
+    };
+    // sum and maximum of the items' costs
+    auto add_costs = [&]() {
+        const int64_t c_sum = wave_sum(max(d.w, 0));
+        const int32_t c_max = wave_max(d.w);
+        if ((t & 63) == 0 && c_sum > 0) {
+            atomicAdd(&sum_s, (unsigned long long)c_sum);
+            atomicMax(&cost_max, c_max);
+        }
+        __syncthreads();
+    };
+    int32_t BN = j.BN, n_dkv = min(n_all[4], j.cap_dkv);
+    if (t < n_dkv) d = key_item(dkv_off, BN, t);
+    add_costs();
+    if (j.bn_alt != 0 &&
+        larger_key_blocks((int64_t)sum_s, cost_max, n_all[5], longest_s, j.bn_alt, j.kv_heads, j.compute_units)) {
+        BN = j.bn_alt;
+        n_dkv = min(n_all[5], j.cap_dkv);
+        d = make_int4(0, 0, 0, -1);
+        if (t < n_dkv) d = key_item(alt_off, BN, t);
+        __syncthreads();
+        if (t == 0) {
+            sum_s = 0;
+            cost_max = 0;
+        }
+        __syncthreads();
+        add_costs();
+    }
+    if (t < n_fwd) {
+        const int32_t k = owner_of(fwd_off, NS, t), m = t - fwd_off[k], row0 = m << log_bm;
+        f = make_int4(k, m, cu_q[k] + row0, (int32_t)((uint32_t)(q_begin[k] + row0 + min(q_len[k] - row0, j.BM) + BN - 1) / (uint32_t)BN));
+    }
+    fwd[t] = f;
+    dkv[t] = d;
+    cost_f[t] = f.w;
+    cost_d[t] = d.w;
+    // --- sorted lists
+    if (t == 0) {
+        tot.total_q = n_all[1];
+        tot.total_k = n_all[2];
+        tot.n_fwd = n_all[3];
+        tot.n_dkv = BN == j.BN ? n_all[4] : n_all[5];
+        tot.pairs = (int64_t)pairs_s;
+        tot.bad_entry = first_bad == 0x7fffffff ? 0 : first_bad + 1;
+        tot.n_seg = NS;
+        tot.dkv_cost_sum = sum_s;
+        tot.dkv_cost_max = cost_max;
+        tot.cap_fwd = j.cap_fwd;
+        tot.cap_dkv = j.cap_dkv;
+        tot.block_n = BN;
+    }
+    __syncthreads();
+    const int32_t log_t = max(n_fwd, n_dkv) <= kSmallThreads / 4 ? 2 : (max(n_fwd, n_dkv) <= kSmallThreads / 2 ? 1 : 0);
+    const int32_t a = t >> log_t, sub = t & ((1 << log_t) - 1);  // threads of an item
+    f = fwd[a];
+    d = dkv[a];
+    const int32_t at_f = rank_in(cost_f, n_fwd, a, sub, log_t), at_d = rank_in(cost_d, n_dkv, a, sub, log_t);
+    __syncthreads();
+    if (a < n_fwd && sub == 0) {
+        fwd[at_f] = f;
+        ((int4 *)j.fwd_items)[at_f] = f;
+    }
+    if (a < n_dkv && sub == (1 << log_t) - 1) {
+        dkv[at_d] = d;
+        ((int4 *)j.dkv_items)[at_d] = d;
+        count_chain(d.w, group, j.q_heads, j.head_dim, j.compute_units, &tot);
+    }
+    __syncthreads();
+    // --- work units, as in plan_units_kernel
+    if (t == 0) tot.split = choose_split(j.asked, tot, j.q_heads, j.kv_heads, j.head_dim, j.longest_seq, j.compute_units);
+    __syncthreads();
+    const UnitCosts uc{q_begin, q_len, kv_len, shares, j.BM, BN, group, j.head_dim, tot.split,
+                       small_block(tot, tot.split, j.q_heads, j.head_dim, j.compute_units)};
+    int32_t parts[4] = {0, 0, 0, 0}, cf = -1, cd = -1;  // dK/dV, then 4, 8 and 12 waves
+    if (t < n_dkv) uc.dkv(dkv[t], t, cd, parts[0]);
+    if (t < n_fwd)
+        for (int i = 0; i < SKRULL_UNIT_LISTS; ++i) uc.fwd(fwd[t], 4 * (i + 1), cf, parts[1 + i]);
+    cost_f[t] = cf;
+    cost_d[t] = cd;
+    {
+        const int64_t load = wave_sum(t < n_fwd ? (int64_t)parts[3] * (cf + 16) : 0);
+        const int32_t longest = wave_max(t < n_fwd ? cf + 16 : 0);
+        if ((t & 63) == 0) {
+            atomicAdd(&load_s, (unsigned long long)load);
+            atomicMax(&tot.fwd_longest, longest);
+        }
+    }
+    int32_t ex[4], sum[4];
+    scan_all<4>(parts, ex, sum, scans);  // (its barriers also make the costs visible)
+    const bool list_order = (int64_t)sum[0] * j.kv_heads * (BN == 256 ? 2 : 1) <= j.compute_units;
+    if (sub == 0) {
+        order[0][a] = a;
+        order[1][a] = a;
+    }
+    const int32_t by_rounds = rank_in(cost_d, n_dkv, a, sub, log_t), by_keys = rank_in(cost_f, n_fwd, a, sub, log_t);
+    if (sub == 0 && a < n_dkv && !list_order) order[0][a] = by_rounds;
+    if (sub == 0 && a < n_fwd && j.head_dim == 64) order[1][a] = by_keys;
+    if (log_t > 0 && t >= kSmallThreads >> log_t) order[0][t] = order[1][t] = t;
+    __syncthreads();
+    const int32_t rd = order[0][t], rf = order[1][t];
+    at[0][rd] = parts[0];
+    for (int i = 1; i < 4; ++i) at[i][rf] = parts[i];
+    __syncthreads();
+    for (int i = 0; i < 4; ++i) parts[i] = at[i][t];
+    scan_all<4>(parts, ex, sum, scans);
+    for (int i = 0; i < 4; ++i) at[i][t] = ex[i];
+    __syncthreads();
+    if (t < n_dkv && j.dkv_units) {
+        int32_t c, n;
+        uc.dkv(dkv[t], t, c, n);
+        for (int32_t p = 0; p < n; ++p) j.dkv_units[at[0][rd] + p] = t | p << SKRULL_UNIT_SHIFT;
+    }
+    if (t < n_fwd)
+        for (int i = 0; i < SKRULL_UNIT_LISTS; ++i) {
+            int32_t c, n;
+            uc.fwd(fwd[t], 4 * (i + 1), c, n);
+            if (j.units[i])
+                for (int32_t p = 0; p < n; ++p) j.units[i][at[1 + i][rf] + p] = t | p << SKRULL_UNIT_SHIFT;
+        }
+    if (t == 0) {
+        tot.n_dkv_units = j.dkv_units ? sum[0] : 0;
+        for (int i = 0; i < SKRULL_UNIT_LISTS; ++i) tot.n_units[i] = j.units[i] ? sum[1 + i] : 0;
+        tot.fwd_load = j.units[2] ? (int64_t)load_s : 0;
+        if (!j.units[2]) tot.fwd_longest = 0;
+    }
+    __syncthreads();
+    for (int i = t; i < (int)(sizeof tot / 4); i += kSmallThreads) ((int32_t *)j.totals)[i] = ((const int32_t *)&tot)[i];
 }
 
 // ---------------------------------------------------------------------------
@@ -775,5 +1095,11 @@ hipError_t launch_plan_units(const skrull_attn_plan_t *p, int32_t asked, int32_t
         UnitsJob{(const int4 *)p->fwd_items, (const int4 *)p->dkv_items, p->q_begin, p->q_len, p->kv_len, p->shares_kv, p->BM, p->Hq,
                  p->Hkv, p->d, asked, longest_seq, compute_units, {p->units[0], p->units[1], p->units[2]}, p->dkv_units},
         totals);
+    return hipGetLastError();
+}
+
+hipError_t launch_plan_small(const SmallPlan &job, hipStream_t st)
+{
+    plan_small_kernel<<<1, kSmallThreads, 0, st>>>(job);
     return hipGetLastError();
 }

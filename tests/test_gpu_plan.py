@@ -134,3 +134,37 @@ def test_items_are_shared_out_only_where_that_pays(S, N, R, shared):
     base = (4 * plan.info.total_q * 8 + 255) // 256 * 256 + 256
     assert (plan.bwd_workspace_bytes > base) == shared
     plan.destroy()
+
+
+@pytest.mark.parametrize("S,bm,bn", [([64 * 511 + 1], 64, 64), ([64 * 512 + 1], 64, 64), ([64] * 512, 64, 64), ([64] * 513, 64, 64),
+                                     ([100] * 256 + [64] * 256, 64, 128), ([200] * 128, 64, 256), ([130] * 129, 64, 256)])
+def test_plan_on_both_sides_of_one_workgroup(oracle, S, bm, bn):
+    """Up to 512 sequences, segments and items of a list one workgroup makes the whole plan (with 4, 2 or 1 threads to
+    an item: lists of 128, 129, 256 and more items), above that several kernels do."""
+    _check(oracle, S, [1] * len(S), [0] * len(S), 4, 2, 64, bm, bn)
+
+
+def test_plans_made_by_many_threads_at_once():
+    """Plans in 24 threads, more than there are slots of pinned memory: each thread's plans are its own."""
+    import threading
+    from paper_2505_19609_amd import binding as B
+    failed = []
+
+    def work(i):
+        try:
+            for k in range(6):
+                S = [37 * i + 11 * k + 5, 300 + i, 64 * (k + 1)]
+                plan = B.skrull_attn_plan(S, [1] * 3, [0] * 3, 14, 2, 64, 0.125, 64, 64)
+                cu = B.skrull_attn_plan_export(plan, B.ARRAY_CU_Q)
+                items = B.skrull_attn_plan_export(plan, B.ARRAY_FWD_ITEMS)
+                assert cu.tolist() == [0, S[0], S[0] + S[1], sum(S)] and len(items) == sum(-(-s // 64) for s in S)
+                plan.destroy()
+        except Exception as e:  # reported by the main thread
+            failed.append((i, repr(e)))
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(24)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not failed, failed
