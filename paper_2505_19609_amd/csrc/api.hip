@@ -344,16 +344,28 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
                                                    : (longest_seq <= 8192 && blocks_per_cu >= 16.0);
         plan->wg_query_rows = small_shape ? 128 : 256;
     }
-    // The forward at head_dim 64 also has a shape of 12 wavefronts to a workgroup, three per SIMD, which share the tiles of
-    // keys that two per SIMD would wait for.  Each wavefront runs slower, so the longest unit must not be what
-    // the launch waits for, and its row blocks must fill 12 about as well as 8 (they do not with one head per group).
-    // Against 8 wavefronts, by r = the longest unit / an even share per compute unit, on 28 micro-batches of 14/2 heads:
-    // 2 to 8 % less time up to r = 0.89, 6 % more at 0.91, 8 % less at 0.95, 15 to 30 % more from 1.1 on; on 54
-    // more of 9 to 48 heads, by what 12 leave empty beside 8: 5 to 15 % less up to 16 % (24/8 heads, 8,192 tokens
-    // of 8 to 511: 33.5 -> 28.4 us), between 6 % less and 1 % more at 30 % (two heads per group).
-    plan->fwd_wide = p->wg_query_rows == 0 && plan->wg_query_rows == 256 && plan->units[2] && group > 1 &&
-                     5 * 12 * (int64_t)plan->n_units[2] <= 6 * 8 * (int64_t)plan->n_units[1] &&
-                     10 * (int64_t)totals.fwd_longest * compute_units <= 9 * totals.fwd_load * plan->Hkv;
+    // At head_dim 64, where the library chooses and has not taken the small shape:
+    //  Both kernels also have a shape of 12 wavefronts to a workgroup, three per SIMD, which share the tiles of
+    //    keys that two per SIMD would wait for.  Each wavefront runs slower, so the longest unit must not be what
+    //    the launch waits for, and its row blocks must fill 12 about as well as 8 (they do not with one head per group).
+    //    Against 8 wavefronts, by r = the longest unit / an even share per compute unit, on 28 micro-batches of 14/2 heads
+    //    (forward) and 40 more (backward): forward 2 to 8 % less time up to r = 0.89, 6 % more at 0.91, 8 % less at 0.95, 15
+    //    to 30 % more from 1.1 on; backward 1 to 5 % less up to 0.95, 4 to 10 % more from 1.08 on.  On 54 forwards of 9 to 48
+    //    heads, by what 12 leave empty beside 8: 5 to 15 % less up to 16 % (24/8 heads, 8,192 tokens
+    //    of 8 to 511: 33.5 -> 28.4 us), between 6 % less and 1 % more at 30 % (two heads per group).
+    //  A launch whose workgroups of 4 wavefronts, one per 128 rows and head, all run at once has those: half as
+    //    many wavefronts share a unit, where most of the chip would stay idle beside them.  Measured on 40 micro-batches of 16
+    //    to 6,000 tokens, 4 to 16 heads: forward up to 20 % less time (7 to 10 % in the middle, 2 % more at worst), backward 4
+    //    to 7 % less; a third more than fits, and dQ lost 11 to 43 %.
+    plan->fwd_waves = plan->wg_query_rows / 32;
+    plan->dq_waves = plan->d == 64 ? plan->wg_query_rows / 32 : 8;
+    if (p->wg_query_rows == 0 && plan->wg_query_rows == 256 && plan->d == 64) {
+        if (plan->units[2] && group > 1 && 5 * 12 * (int64_t)plan->n_units[2] <= 6 * 8 * (int64_t)plan->n_units[1] &&
+            10 * (int64_t)totals.fwd_longest * compute_units <= 9 * totals.fwd_load * plan->Hkv)
+            plan->fwd_waves = plan->dq_waves = 12;
+        else if (2 * totals.n_fwd * plan->Hq <= 3 * (int64_t)compute_units)
+            plan->dq_waves = plan->fwd_waves = 4;
+    }
     plan->head_split = totals.split.head_split;
     plan->n_split = totals.split.n_split;
     plan->n_whole_first = totals.split.n_whole_first;

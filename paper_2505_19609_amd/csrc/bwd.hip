@@ -72,11 +72,18 @@ struct BwdParams {
 // ---------------------------------------------------------------------------
 // dQ
 // ---------------------------------------------------------------------------
-// The dQ kernel comes in two shapes, like the forward: 8 wavefronts (256 query rows) with a
-// five-slot K ring and a four-slot V ring, one workgroup per compute unit; and, where two of
-// them fit the LDS together (head_dim 64), 4 wavefronts (128 rows) with three K slots and two
-// V slots, fetching one tile ahead with a barrier per tile.
-constexpr int NWQ_LARGE = 8, NWQ_SMALL = 4;
+// The dQ kernel comes in three shapes, like the forward.  Large: 8 wavefronts (256 query rows), two per SIMD, with a
+// five-slot K ring and a four-slot V ring, and a software pipeline from one half tile of keys to the next,
+// which takes 191 registers at head_dim 64 and 254 at 128.  At head_dim 64 also two that do one half tile
+// after another: with nothing kept from one to the next 168 registers do, so that three wavefronts per SIMD overlap
+// with each other instead.  Wide: 12 wavefronts, K and V rings of four slots; small: workgroups of 4
+// wavefronts, rings of two slots, a barrier per tile.  A wavefront alone on its SIMD is slower this way and
+// eight are as fast (23,053 tokens, 16/16 heads: backward 785 us pipelined, 792 with 8 of 12 at work), so the
+// large shape stays where a long unit is what a launch waits for and where 12 cannot be filled.
+// 26,624 tokens in 64 sequences, 14/2 heads: dQ 94 us large, 86 wide; 32,768 of 16 to 1,024: 88 and 75; slices of
+// three long sequences, 1.5e9 triples and more: forward and backward 6,240 with small workgroups that were pipelined (two
+// per unit), 6,200 this way (three).
+constexpr int NWQ_LARGE = 8, NWQ_SMALL = 4, NWQ_WIDE = 12;
 
 // Two scores and two (dP - D) values -> one packed bf16 pair of dS, in two parts so
 // that each part can sit behind one MFMA of a pipelined step (plain arithmetic would
@@ -105,7 +112,7 @@ __device__ __forceinline__ uint32_t ds_mul_pack(float t0, float t1, float g0, fl
 }
 
 // One workgroup = part of a forward work item (at most 256 query rows) x one KV head (tiles.h:
-// row_blocks); each of the 8 waves owns 32 query rows of one head, two waves per SIMD.  K and V stream in
+// row_blocks); each wave owns 32 query rows of one head.  In the large shape K and V stream in
 // 64-row tiles through LDS rings (K: five slots, V: four), fetched two tiles ahead by
 // buffer loads that write LDS directly; fetches are issued, and the workgroup meets
 // at a barrier, every second tile.  Half-tile j (32 keys) goes through
@@ -123,8 +130,9 @@ template <int D, int NWQ>
 __device__ __forceinline__ int dq_work(const int bid, RowBlocks &rb, BwdFeed &feed)
 {
     const kernarg_t<BwdParams> prm = kernarg<BwdParams>();
-    constexpr bool SMALL = NWQ == NWQ_SMALL;
-    constexpr int KSL = SMALL ? 3 : 5, VSL = SMALL ? 2 : 4;  // ring slots
+    // small and wide shapes: three wavefronts per SIMD, one half tile after another; large: two, pipelined
+    constexpr bool SMALL = NWQ == NWQ_SMALL, WIDE = NWQ == NWQ_WIDE, SIMPLE = SMALL || WIDE;
+    constexpr int KSL = SMALL ? 2 : (WIDE ? 4 : 5), VSL = SMALL ? 2 : 4;  // ring slots
     constexpr int KS = D / 16, TT = D / 32, KT = TILE_ROWS;
     typedef TileGeom<D> G;
     constexpr int TB = G::BYTES;
@@ -166,14 +174,20 @@ __device__ __forceinline__ int dq_work(const int bid, RowBlocks &rb, BwdFeed &fe
     const i32x4 rk = ld.rsrc(prm->k + ((size_t)kbase * prm->Hkv + c) * D, kvl);
     const i32x4 rv = ld.rsrc(prm->v + ((size_t)kbase * prm->Hkv + c) * D, kvl);
 
-    // Large shape: the fetch group issued at the start of an even period t is K and V tiles
+    // Large and wide shapes: the fetch group issued at the start of an even period t is K and V tiles
     // t+2, t+3 (tiles past the end read as zero).  Small shape: every period t fetches K
     // and V tile t+1.
     int kslot = 0;  // slot of K tile t (t mod KSL), advanced at the end of every period
     auto fetch = [&](int t) __attribute__((always_inline)) {
         if (SMALL) {
-            ld.load(rk, ring_k + (uint32_t)(kslot == 2 ? 0 : kslot + 1) * TB, (t + 1) * KT, wave);
+            ld.load(rk, ring_k + (uint32_t)((t + 1) & 1) * TB, (t + 1) * KT, wave);
             ld.load(rv, ring_v + (uint32_t)((t + 1) & 1) * TB, (t + 1) * KT, wave);
+        } else if (WIDE) {
+#pragma unroll
+            for (int x = 2; x < 4; ++x) {
+                ld.load(rk, ring_k + (uint32_t)((t + x) & 3) * TB, (t + x) * KT, wave);
+                ld.load(rv, ring_v + (uint32_t)((t + x) & 3) * TB, (t + x) * KT, wave);
+            }
         } else {
             const int k2 = kslot >= 3 ? kslot - 3 : kslot + 2, k3 = kslot >= 2 ? kslot - 2 : kslot + 3;
             ld.load(rk, ring_k + (uint32_t)k2 * TB, (t + 2) * KT, wave);
@@ -191,10 +205,15 @@ __device__ __forceinline__ int dq_work(const int bid, RowBlocks &rb, BwdFeed &fe
         ld.load(rv, ring_v + TB, KT, wave);
     }
     // this wave's staging region: half a ring slot that holds no tile yet (large shape: K slots
-    // 2-4 for waves 0-5 and V slots 2-3 for waves 6-7; small shape: K slots 1-2)
+    // 2-4 for waves 0-5 and V slots 2-3 for waves 6-7; wide shape: K slots 2-3, V slots 2-3 and a
+    // little more; small shape: K slot 1 and V slot 1)
     typedef WaveStage<D> Stage;
     static_assert(2 * Stage::BYTES == TB, "two staging regions per ring slot");
-    const uint32_t stage = SMALL ? ring_k + TB + (uint32_t)wave * Stage::BYTES
+    __shared__ __align__(16) unsigned char lds_more[WIDE ? 4 * Stage::BYTES : 16];
+    const uint32_t stage = SMALL ? (wave < 2 ? ring_k + TB + (uint32_t)wave * Stage::BYTES : ring_v + TB + (uint32_t)(wave - 2) * Stage::BYTES)
+                         : WIDE  ? (wave < 4   ? ring_k + 2 * TB + (uint32_t)wave * Stage::BYTES
+                                    : wave < 8 ? ring_v + 2 * TB + (uint32_t)(wave - 4) * Stage::BYTES
+                                               : lds_addr(lds_more) + (uint32_t)(wave - 8) * Stage::BYTES)
                                  : (wave < 6 ? ring_k + 2 * TB + (uint32_t)wave * Stage::BYTES
                                              : ring_v + 2 * TB + (uint32_t)(wave - 6) * Stage::BYTES);
 
@@ -352,6 +371,74 @@ __device__ __forceinline__ int dq_work(const int bid, RowBlocks &rb, BwdFeed &fe
         }
     };
 
+    if constexpr (SIMPLE) {
+        // Half tile j: A(j), V(j), B(j), nothing kept from one to the next
+        auto half = [&](int j, const unsigned char *kp, const unsigned char *vp) __attribute__((always_inline)) {
+            bf16x8 fk[KS], fv[KS], ct[2 * TT];
+#pragma unroll
+            for (int i = 0; i < KS; ++i) {
+                fk[i] = fa.rows(kp, 0, i);
+                fv[i] = fa.rows(vp, 0, i);
+            }
+            SB();
+            f32x16 s, g;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) { s[v] = 0.0f; g[v] = nd; }
+#pragma unroll
+            for (int i = 0; i < KS; ++i) {
+                s = mfma32(fk[i], qf[i], s);
+                ct[i] = fa.cols(kp, i % TT, i / TT);
+                SB();
+            }
+            asm volatile("" : "+v"(s));  // (the MFMAs of S are not moved behind those of dP)
+#pragma unroll
+            for (int i = 0; i < KS; ++i) {
+                g = mfma32(fv[i], dof[i], g);
+                SB();
+            }
+            // The arithmetic below is written out, and the compiler counts no wait states between an MFMA and
+            // such a reader of its result (11 for these): they are here.  (Without them the first scores were
+            // read before they were written where a wavefront had its SIMD to itself.)
+            asm volatile("s_nop 10" : "+v"(s), "+v"(g));
+            if (__builtin_expect(j >= n_full, 0)) {  // half tile touches the diagonal for this wave
+                int li = lane;
+                asm volatile("" : "+v"(li));
+                const int rel = p0 + wrow0 + (li & 31) - 32 * j - 4 * (li >> 5);  // my_pos - 32j - 4h
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const bool late = 8 * (v >> 2) + (v & 3) > rel;
+                    s[v] = late ? -INFINITY : s[v];
+                    g[v] = late ? 0.0f : g[v];
+                }
+            }
+            uint32_t pw[8];
+            float e[16];
+#pragma unroll
+            for (int v = 0; v < 16; v += 2) ds_exp2(s[v], s[v + 1], cs, lse2, e[v], e[v + 1]);
+#pragma unroll
+            for (int v = 0; v < 16; v += 2) pw[v >> 1] = ds_mul_pack(e[v], e[v + 1], g[v], g[v + 1]);
+            const bf16x8 ds0 = as_bf16x8(make_uint4(pw[0], pw[1], pw[2], pw[3]));
+            const bf16x8 ds1 = as_bf16x8(make_uint4(pw[4], pw[5], pw[6], pw[7]));
+            SB();
+#pragma unroll
+            for (int y = 0; y < 2 * TT; ++y) {
+                acc[y % TT] = mfma32(ct[y], y < TT ? ds0 : ds1, acc[y % TT]);
+                SB();
+            }
+        };
+#pragma unroll 1
+        for (int t = 0; t < n_tiles; ++t) {
+            if (t > 0 && (SMALL ? t + 1 < n_tiles : (t & 1) == 0 && t + 2 < n_tiles)) fetch(t);
+            if (t == n_tiles - 1) feed.ask();
+            const unsigned char *tk = lds_k[t & (KSL - 1)], *tv = lds_v[t & (VSL - 1)];
+            if (2 * t <= L) half(2 * t, tk, tv);
+            if (2 * t + 1 <= L) half(2 * t + 1, tk + HALF, tv + HALF);
+            if (SMALL || (t & 1)) {
+                wait_vmem();
+                __syncthreads();
+            }
+        }
+    } else {
     f32x16 sx, sy, gx, gy;  // S and dP - D of the current / next half tile, ping-pong
 #pragma unroll
     for (int v = 0; v < 16; ++v) { sx[v] = 0.0f; sy[v] = 0.0f; gx[v] = 0.0f; gy[v] = 0.0f; }
@@ -408,6 +495,7 @@ __device__ __forceinline__ int dq_work(const int bid, RowBlocks &rb, BwdFeed &fe
 #pragma unroll 1
     for (; t <= n_tiles; ++t) plain_period(t);
 
+    }
     feed.post();
     // Nobody reads a tile any more: the staging regions are free.  (The next item needs no barrier
     // of its own before its first tiles: they go to slots that stage nothing.)
@@ -437,7 +525,7 @@ __device__ __forceinline__ int dq_work(const int bid, RowBlocks &rb, BwdFeed &fe
 }
 
 template <int D, int NWQ>
-__global__ __launch_bounds__(64 * NWQ, 2) void dq_kernel(const BwdParams prm)
+__global__ __launch_bounds__(64 * NWQ, NWQ == NWQ_LARGE ? 2 : 3) void dq_kernel(const BwdParams prm)
 {
     __shared__ int work_slot[2];
     BwdFeed feed{prm.queue_dq, prm.n_work_dq, 0, 0, work_slot};
@@ -1084,8 +1172,6 @@ __global__ __launch_bounds__(256) void dkv_reduce_kernel(const BwdParams prm)
     out[((size_t)(krow + r) * prm.Hkv + c) * (D / 4) + q] = w;
 }
 
-// true when the dQ kernel runs in its 4-wavefront shape (it fits the LDS twice only at head_dim 64)
-bool small_dq_shape(const skrull_attn_plan_t *p) { return p->d == 64 && p->wg_query_rows == 32 * NWQ_SMALL; }
 int dkv_pairs(const skrull_attn_plan_t *p) { return (p->d == 64 && p->BN == 32 * PAIRS_12W) ? PAIRS_12W : PAIRS_8W; }
 
 template <int D, auto KernelQ, auto KernelKV>
@@ -1122,14 +1208,14 @@ hipError_t launch_pair(const skrull_attn_plan_t *p, BwdParams prm, int threads_q
 template <int D>
 hipError_t launch_d(const skrull_attn_plan_t *p, const BwdParams &prm, hipStream_t st, hipEvent_t *ev)
 {
-    if constexpr (D == 64) {  // the small dQ shape fits the LDS twice, and dK/dV has its 12-wavefront shape, only here
-        const bool small_q = small_dq_shape(p), wide_kv = dkv_pairs(p) == PAIRS_12W;
-        if (small_q && wide_kv)
-            return launch_pair<D, dq_kernel<D, NWQ_SMALL>, dkv_kernel<D, PAIRS_12W>>(p, prm, 64 * NWQ_SMALL, 128 * PAIRS_12W, st, ev);
-        if (small_q)
-            return launch_pair<D, dq_kernel<D, NWQ_SMALL>, dkv_kernel<D, PAIRS_8W>>(p, prm, 64 * NWQ_SMALL, 128 * PAIRS_8W, st, ev);
-        if (wide_kv)
+    if constexpr (D == 64) {  // dQ has its other shapes, and dK/dV its 12-wavefront one, only here
+        if (dkv_pairs(p) == PAIRS_12W) {
+            if (p->dq_waves == NWQ_SMALL) return launch_pair<D, dq_kernel<D, NWQ_SMALL>, dkv_kernel<D, PAIRS_12W>>(p, prm, 64 * NWQ_SMALL, 128 * PAIRS_12W, st, ev);
+            if (p->dq_waves == NWQ_WIDE) return launch_pair<D, dq_kernel<D, NWQ_WIDE>, dkv_kernel<D, PAIRS_12W>>(p, prm, 64 * NWQ_WIDE, 128 * PAIRS_12W, st, ev);
             return launch_pair<D, dq_kernel<D, NWQ_LARGE>, dkv_kernel<D, PAIRS_12W>>(p, prm, 64 * NWQ_LARGE, 128 * PAIRS_12W, st, ev);
+        }
+        if (p->dq_waves == NWQ_SMALL) return launch_pair<D, dq_kernel<D, NWQ_SMALL>, dkv_kernel<D, PAIRS_8W>>(p, prm, 64 * NWQ_SMALL, 128 * PAIRS_8W, st, ev);
+        if (p->dq_waves == NWQ_WIDE) return launch_pair<D, dq_kernel<D, NWQ_WIDE>, dkv_kernel<D, PAIRS_8W>>(p, prm, 64 * NWQ_WIDE, 128 * PAIRS_8W, st, ev);
     }
     return launch_pair<D, dq_kernel<D, NWQ_LARGE>, dkv_kernel<D, PAIRS_8W>>(p, prm, 64 * NWQ_LARGE, 128 * PAIRS_8W, st, ev);
 }
@@ -1139,7 +1225,9 @@ hipError_t launch_d(const skrull_attn_plan_t *p, const BwdParams &prm, hipStream
 static RowLaunch rows_dq(const skrull_attn_plan_t *p)
 {
     if (p->d == 128) return row_launch<dq_kernel<128, NWQ_LARGE>>(p, NWQ_LARGE);
-    return small_dq_shape(p) ? row_launch<dq_kernel<64, NWQ_SMALL>>(p, NWQ_SMALL) : row_launch<dq_kernel<64, NWQ_LARGE>>(p, NWQ_LARGE);
+    if (p->dq_waves == NWQ_SMALL) return row_launch<dq_kernel<64, NWQ_SMALL>>(p, NWQ_SMALL);
+    if (p->dq_waves == NWQ_WIDE) return row_launch<dq_kernel<64, NWQ_WIDE>>(p, NWQ_WIDE);
+    return row_launch<dq_kernel<64, NWQ_LARGE>>(p, NWQ_LARGE);
 }
 
 int grid_dq(const skrull_attn_plan_t *p) { return rows_dq(p).n_work; }

@@ -63,7 +63,7 @@ struct FwdParams {
 // barrier waits of one (most of the run time of a short sequence) hide behind the other.
 // The plan chooses per micro-batch.  At head_dim 64, where 152 registers allow three wavefronts per SIMD, there is
 // also a wide shape: the large one's rings (83 KB) with 12 wavefronts.  In a list of short sequences its third
-// wavefront per SIMD fills the starts, ends and latencies of the two others.
+// wavefront per SIMD fills the starts, ends and latencies of the two others (dQ has the same three shapes).
 constexpr int NW_LARGE = 8, NSLOT_LARGE = 4;
 constexpr int NW_SMALL = 4, NSLOT_SMALL = 2;
 constexpr int NW_WIDE = 12;
@@ -533,9 +533,9 @@ hipError_t launch_one(const FwdParams &prm, hipStream_t st)
 template <int D>
 RowLaunch rows_fwd(const skrull_attn_plan_t *p)
 {
-    if (p->wg_query_rows == 32 * NW_SMALL) return row_launch<fwd_kernel<D, NW_SMALL, NSLOT_SMALL>>(p, NW_SMALL);
+    if (p->fwd_waves == NW_SMALL) return row_launch<fwd_kernel<D, NW_SMALL, NSLOT_SMALL>>(p, NW_SMALL);
     if constexpr (D == 64)
-        if (p->fwd_wide) return row_launch<fwd_kernel<D, NW_WIDE, NSLOT_LARGE>>(p, NW_WIDE);
+        if (p->fwd_waves == NW_WIDE) return row_launch<fwd_kernel<D, NW_WIDE, NSLOT_LARGE>>(p, NW_WIDE);
     return row_launch<fwd_kernel<D, NW_LARGE, NSLOT_LARGE>>(p, NW_LARGE);
 }
 
@@ -558,7 +558,7 @@ hipError_t launch_fwd(const skrull_attn_plan_t *p, const void *q, const void *k,
     prm.rows = rows.rows;
     prm.scale_log2 = p->scale * 1.4426950408889634f;
     prm.trace = trace;
-    prm.variant = p->wg_query_rows == 32 * NW_SMALL ? 0 : (p->fwd_wide ? 2 : 1);
+    prm.variant = p->fwd_waves / 4 - 1;
     prm.n_work = rows.n_work;
     // One of the plan's queue slots per call, taken in turn, so that forward calls of one plan
     // that overlap on different streams do not share a queue.

@@ -1054,3 +1054,26 @@ def test_wide_forward_changes_no_bit(heads):
         assert np.array_equal(out[k], ref[k]), k
     out["plan"].destroy()
     ref["plan"].destroy()
+
+
+@pytest.mark.parametrize("heads,S,waves", [((14, 2), [1, 31, 32, 33, 255, 256, 257, 300, 511, 700, 97] * 8, 12),
+                                           ((9, 3), [64, 65, 127, 128, 129, 191, 192, 193, 1000] * 12, 12),
+                                           ((4, 4), [455, 283, 194, 1, 32], 4), ((14, 2), [600, 33, 129], 4),
+                                           ((6, 2), [1000, 65, 64, 63], 4)])
+def test_shapes_of_head_dim_64_change_no_bit(heads, S, waves):
+    """At head_dim 64 the plan gives forward and dQ workgroups of 12 wavefronts (many short units) or of 4 (a launch
+    that runs at once); asked for 256 rows they have 8, and dQ is pipelined.  Same bits, also with a slice and a cut."""
+    from paper_2505_19609_amd import binding as B
+    K = len(S)
+    N, R, Z = [1] * K + [3, 2], [0] * K + [1, 1], [0] * K + [0, 1]
+    w = W.Workload("shapes64", S + [800, 513], N, R, heads[0], heads[1], 64, 64 ** -0.5, 610, shard_cut=Z)
+    out = run_library(w, guard=True)
+    assert out["margins"] == [] and out["plan"].info.wg_query_rows == 256
+    ref = run_library(w, vals=out["vals"], wg_query_rows=256)
+    for i in (0, 1):
+        n, n8 = (B.skrull_attn_trace_layout(x["plan"])[1][i] for x in (out, ref))
+        assert n < n8 if waves == 12 else n == 2 * n8
+    for k in ("o", "lse", "dq", "dk", "dv"):
+        assert np.array_equal(out[k], ref[k]), k
+    out["plan"].destroy()
+    ref["plan"].destroy()
