@@ -497,10 +497,12 @@ __device__ inline int32_t parts_of_item(const SplitChoice &c, int32_t item, int3
 // What is not done, because units that read the same tiles find them in their die's L2 when they run together:
 //  the parts of a forward / dQ item apart from each other by their own half tiles (114 sequences of about 250
 //    tokens, 32/8 heads of 128: forward 215 -> 236, dQ 303 -> 328);
-//  key blocks with less work than a part (an eighth, or a quarter at head_dim 128 where no item is shared) of an
-//    even share per compute unit (`small`, in rounds; a cost counts for four) apart from the others of their sequence: they go
-//    out by their sequence's length (the same 114 sequences, backward: 653 us, by their own rounds 666, by the
-//    items' costs 663; 26,624 tokens above 237, 249 with a quarter);
+//  the key blocks of a short sequence apart from each other: they go out by the sequence's length, the rounds of its
+//    first block, where these are at most `small` (114 sequences of about 250 tokens, 32/8 heads of 128: dK/dV 359 us,
+//    by their own rounds 368, by the items' costs 371; 26,624 tokens above 134, 137, 146).  `small` is an eighth of an
+//    even share per compute unit, or a quarter at head_dim 128 where no item is shared, and 64 at most (128 is the same): these blocks
+//    are what fills the end of a launch, and 1,187 rounds, a quarter of the share of 24,576 + 8,192 tokens at
+//    32/8 heads of 128, brought them out before it (8,660 us, 8,540 this way, 8,522 by the items' costs);
 //  any order but the list's where all units run at once (4,923 tokens, 28/4 heads of 128: 111 us, else 114).
 struct UnitCosts {
     const int32_t *q_begin, *q_len, *kv_len, *shares_kv;
@@ -522,7 +524,8 @@ struct UnitCosts {
             if (it.y * BN < kv_len[it.x - 1]) c += tiles(it.x - 1, it.y * BN);
         }
         parts = parts_of_item(choice, i, it.w, group);
-        cost = max((min(c, 1 << 20) * group + parts - 1) / parts, min(min(whole, 1 << 20) * group, small));
+        whole = min(whole, 1 << 20) * group;
+        cost = whole <= small ? whole : (min(c, 1 << 20) * group + parts - 1) / parts;
     }
     // item of the forward / dQ list for workgroups of `waves` waves
     __device__ void fwd(const int4 &it, int32_t waves, int32_t &cost, int32_t &parts) const
@@ -535,7 +538,8 @@ struct UnitCosts {
 __device__ inline int32_t small_block(const PlanTotals &totals, const SplitChoice &choice, int32_t q_heads, int32_t head_dim, int32_t compute_units)
 {
     const int32_t fine = head_dim == 64 || choice.parts > 1 ? 2 : 1;
-    return (int32_t)min(totals.dkv_cost_sum * q_heads / (fine * (unsigned long long)compute_units), 1ull << 29);
+    // (a cost counts for four rounds)
+    return (int32_t)min(totals.dkv_cost_sum * q_heads / (fine * (unsigned long long)compute_units), 64ull);
 }
 struct UnitsJob {
     const int4 *fwd_items, *dkv_items;
