@@ -79,7 +79,8 @@ struct BwdParams {
 // with each other instead.  Wide: 12 wavefronts, K and V rings of four slots; small: workgroups of 4
 // wavefronts, rings of two slots, a barrier per tile.  A wavefront alone on its SIMD is slower this way and
 // eight are as fast (23,053 tokens, 16/16 heads: backward 785 us pipelined, 792 with 8 of 12 at work), so the
-// large shape stays where a long unit is what a launch waits for and where 12 cannot be filled.
+// large shape stays where a long unit is what a launch waits for and where 12 cannot be filled, and the small one is
+// pipelined too (three K slots, two workgroups per unit) where long units would leave the third place of a unit empty.
 // 26,624 tokens in 64 sequences, 14/2 heads: dQ 94 us large, 86 wide; 32,768 of 16 to 1,024: 88 and 75; slices of
 // three long sequences, 1.5e9 triples and more: forward and backward 6,240 with small workgroups that were pipelined (two
 // per unit), 6,200 this way (three).
@@ -126,13 +127,14 @@ __device__ __forceinline__ uint32_t ds_mul_pack(float t0, float t1, float g0, fl
 using BwdFeed = WorkFeed<kQueueStrideBwd, false>;
 
 // Does work item `bid`, whose rows are `rb`; returns the next one and leaves its rows in `rb`.
-template <int D, int NWQ>
+template <int D, int NWQ, bool PIPED>
 __device__ __forceinline__ int dq_work(const int bid, RowBlocks &rb, BwdFeed &feed)
 {
     const kernarg_t<BwdParams> prm = kernarg<BwdParams>();
-    // small and wide shapes: three wavefronts per SIMD, one half tile after another; large: two, pipelined
-    constexpr bool SMALL = NWQ == NWQ_SMALL, WIDE = NWQ == NWQ_WIDE, SIMPLE = SMALL || WIDE;
-    constexpr int KSL = SMALL ? 2 : (WIDE ? 4 : 5), VSL = SMALL ? 2 : 4;  // ring slots
+    // not PIPED: three wavefronts per SIMD, one half tile after another; PIPED: two
+    constexpr bool SMALL = NWQ == NWQ_SMALL, WIDE = NWQ == NWQ_WIDE;
+    constexpr int KSL = SMALL ? (PIPED ? 3 : 2) : (WIDE ? 4 : 5), VSL = SMALL ? 2 : 4;  // ring slots
+    static_assert(PIPED ? !WIDE : (KSL & (KSL - 1)) == 0, "K tile t in slot t mod KSL");
     constexpr int KS = D / 16, TT = D / 32, KT = TILE_ROWS;
     typedef TileGeom<D> G;
     constexpr int TB = G::BYTES;
@@ -180,7 +182,7 @@ __device__ __forceinline__ int dq_work(const int bid, RowBlocks &rb, BwdFeed &fe
     int kslot = 0;  // slot of K tile t (t mod KSL), advanced at the end of every period
     auto fetch = [&](int t) __attribute__((always_inline)) {
         if (SMALL) {
-            ld.load(rk, ring_k + (uint32_t)((t + 1) & 1) * TB, (t + 1) * KT, wave);
+            ld.load(rk, ring_k + (uint32_t)(PIPED ? (kslot == 2 ? 0 : kslot + 1) : (t + 1) & 1) * TB, (t + 1) * KT, wave);
             ld.load(rv, ring_v + (uint32_t)((t + 1) & 1) * TB, (t + 1) * KT, wave);
         } else if (WIDE) {
 #pragma unroll
@@ -206,11 +208,11 @@ __device__ __forceinline__ int dq_work(const int bid, RowBlocks &rb, BwdFeed &fe
     }
     // this wave's staging region: half a ring slot that holds no tile yet (large shape: K slots
     // 2-4 for waves 0-5 and V slots 2-3 for waves 6-7; wide shape: K slots 2-3, V slots 2-3 and a
-    // little more; small shape: K slot 1 and V slot 1)
+    // little more; small shape: K slot 1 and V slot 1, or K slots 1-2 of three)
     typedef WaveStage<D> Stage;
     static_assert(2 * Stage::BYTES == TB, "two staging regions per ring slot");
     __shared__ __align__(16) unsigned char lds_more[WIDE ? 4 * Stage::BYTES : 16];
-    const uint32_t stage = SMALL ? (wave < 2 ? ring_k + TB + (uint32_t)wave * Stage::BYTES : ring_v + TB + (uint32_t)(wave - 2) * Stage::BYTES)
+    const uint32_t stage = SMALL ? (PIPED || wave < 2 ? ring_k + TB + (uint32_t)wave * Stage::BYTES : ring_v + TB + (uint32_t)(wave - 2) * Stage::BYTES)
                          : WIDE  ? (wave < 4   ? ring_k + 2 * TB + (uint32_t)wave * Stage::BYTES
                                     : wave < 8 ? ring_v + 2 * TB + (uint32_t)(wave - 4) * Stage::BYTES
                                                : lds_addr(lds_more) + (uint32_t)(wave - 8) * Stage::BYTES)
@@ -371,7 +373,7 @@ __device__ __forceinline__ int dq_work(const int bid, RowBlocks &rb, BwdFeed &fe
         }
     };
 
-    if constexpr (SIMPLE) {
+    if constexpr (!PIPED) {
         // Half tile j: A(j), V(j), B(j), nothing kept from one to the next
         auto half = [&](int j, const unsigned char *kp, const unsigned char *vp) __attribute__((always_inline)) {
             bf16x8 fk[KS], fv[KS], ct[2 * TT];
@@ -524,8 +526,8 @@ __device__ __forceinline__ int dq_work(const int bid, RowBlocks &rb, BwdFeed &fe
     return next;
 }
 
-template <int D, int NWQ>
-__global__ __launch_bounds__(64 * NWQ, NWQ == NWQ_LARGE ? 2 : 3) void dq_kernel(const BwdParams prm)
+template <int D, int NWQ, bool PIPED = NWQ == NWQ_LARGE>
+__global__ __launch_bounds__(64 * NWQ, PIPED ? 2 : 3) void dq_kernel(const BwdParams prm)
 {
     __shared__ int work_slot[2];
     BwdFeed feed{prm.queue_dq, prm.n_work_dq, 0, 0, work_slot};
@@ -533,7 +535,7 @@ __global__ __launch_bounds__(64 * NWQ, NWQ == NWQ_LARGE ? 2 : 3) void dq_kernel(
     RowBlocks rb = row_blocks<NWQ>(kernarg<BwdParams>(), prm.fwd_items, max(w, 0));
     while (w >= 0) {
         if (rb.has(0)) {
-            w = dq_work<D, NWQ>(w, rb, feed);
+            w = dq_work<D, NWQ, PIPED>(w, rb, feed);
             if (w == kQueueEmpty) {
                 w = feed.other();
                 rb = row_blocks<NWQ>(kernarg<BwdParams>(), prm.fwd_items, max(w, 0));
@@ -1210,10 +1212,12 @@ hipError_t launch_d(const skrull_attn_plan_t *p, const BwdParams &prm, hipStream
 {
     if constexpr (D == 64) {  // dQ has its other shapes, and dK/dV its 12-wavefront one, only here
         if (dkv_pairs(p) == PAIRS_12W) {
+            if (p->dq_waves == NWQ_SMALL && p->dq_piped) return launch_pair<D, dq_kernel<D, NWQ_SMALL, true>, dkv_kernel<D, PAIRS_12W>>(p, prm, 64 * NWQ_SMALL, 128 * PAIRS_12W, st, ev);
             if (p->dq_waves == NWQ_SMALL) return launch_pair<D, dq_kernel<D, NWQ_SMALL>, dkv_kernel<D, PAIRS_12W>>(p, prm, 64 * NWQ_SMALL, 128 * PAIRS_12W, st, ev);
             if (p->dq_waves == NWQ_WIDE) return launch_pair<D, dq_kernel<D, NWQ_WIDE>, dkv_kernel<D, PAIRS_12W>>(p, prm, 64 * NWQ_WIDE, 128 * PAIRS_12W, st, ev);
             return launch_pair<D, dq_kernel<D, NWQ_LARGE>, dkv_kernel<D, PAIRS_12W>>(p, prm, 64 * NWQ_LARGE, 128 * PAIRS_12W, st, ev);
         }
+        if (p->dq_waves == NWQ_SMALL && p->dq_piped) return launch_pair<D, dq_kernel<D, NWQ_SMALL, true>, dkv_kernel<D, PAIRS_8W>>(p, prm, 64 * NWQ_SMALL, 128 * PAIRS_8W, st, ev);
         if (p->dq_waves == NWQ_SMALL) return launch_pair<D, dq_kernel<D, NWQ_SMALL>, dkv_kernel<D, PAIRS_8W>>(p, prm, 64 * NWQ_SMALL, 128 * PAIRS_8W, st, ev);
         if (p->dq_waves == NWQ_WIDE) return launch_pair<D, dq_kernel<D, NWQ_WIDE>, dkv_kernel<D, PAIRS_8W>>(p, prm, 64 * NWQ_WIDE, 128 * PAIRS_8W, st, ev);
     }
@@ -1225,6 +1229,7 @@ hipError_t launch_d(const skrull_attn_plan_t *p, const BwdParams &prm, hipStream
 static RowLaunch rows_dq(const skrull_attn_plan_t *p)
 {
     if (p->d == 128) return row_launch<dq_kernel<128, NWQ_LARGE>>(p, NWQ_LARGE);
+    if (p->dq_waves == NWQ_SMALL && p->dq_piped) return row_launch<dq_kernel<64, NWQ_SMALL, true>>(p, NWQ_SMALL);
     if (p->dq_waves == NWQ_SMALL) return row_launch<dq_kernel<64, NWQ_SMALL>>(p, NWQ_SMALL);
     if (p->dq_waves == NWQ_WIDE) return row_launch<dq_kernel<64, NWQ_WIDE>>(p, NWQ_WIDE);
     return row_launch<dq_kernel<64, NWQ_LARGE>>(p, NWQ_LARGE);

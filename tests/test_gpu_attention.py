@@ -1077,3 +1077,18 @@ def test_shapes_of_head_dim_64_change_no_bit(heads, S, waves):
         assert np.array_equal(out[k], ref[k]), k
     out["plan"].destroy()
     ref["plan"].destroy()
+
+
+@pytest.mark.parametrize("heads,S", [((16, 16), [9000, 1, 63, 130]), ((4, 4), [2100, 1, 64, 65, 127, 33])])
+def test_small_dq_shapes_change_no_bit(heads, S):
+    """dQ workgroups of 4 wavefronts are pipelined where long units are more than the chip has places for, or few end
+    alone; same bits as 8, with a slice and a cut beside them."""
+    w = W.Workload("dq_piped", S + [800, 513], [1] * len(S) + [3, 2], [0] * len(S) + [1, 1], heads[0], heads[1], 64,
+                   64 ** -0.5, 611, shard_cut=[0] * (len(S) + 1) + [1])
+    out = run_library(w, guard=True, wg_query_rows=128)
+    assert out["margins"] == [] and out["plan"].info.wg_query_rows == 128
+    ref = run_library(w, vals=out["vals"], wg_query_rows=256)
+    for k in ("o", "lse", "dq", "dk", "dv"):
+        assert np.array_equal(out[k], ref[k]), k
+    out["plan"].destroy()
+    ref["plan"].destroy()
