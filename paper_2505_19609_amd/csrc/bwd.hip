@@ -399,9 +399,9 @@ __device__ __forceinline__ int dq_work(const int bid, RowBlocks &rb, BwdFeed &fe
                 SB();
             }
             // The arithmetic below is written out, and the compiler counts no wait states between an MFMA and
-            // such a reader of its result (11 for these): they are here.  (Without them the first scores were
-            // read before they were written where a wavefront had its SIMD to itself.)
-            asm volatile("s_nop 10" : "+v"(s), "+v"(g));
+            // such a reader of its result (12 for these on gfx950; s_nop n is n + 1 of them): they are here.  (Without
+            // them the first scores were read before they were written where a wavefront had its SIMD to itself.)
+            asm volatile("s_nop 11" : "+v"(s), "+v"(g));
             if (__builtin_expect(j >= n_full, 0)) {  // half tile touches the diagonal for this wave
                 int li = lane;
                 asm volatile("" : "+v"(li));
