@@ -76,7 +76,8 @@ int resolve_scratch(int dev, void **out)
 }
 
 // Pinned host memory through which a plan's kernels get their input and give its totals back: a few
-// slots for the whole process, one for the time of a call; a call that finds none copies instead.
+// slots for the whole process, one for the time of a call; a call that finds none copies instead.  A call that
+// cannot wait for its kernels keeps its slot for good: they may still use it.
 struct PinnedSlots {
     static constexpr int kSlots = 16;
     static constexpr size_t kIn = 4 * (size_t)SKRULL_SMALL_PLAN * sizeof(int32_t), kBytes = (kIn + sizeof(PlanTotals) + 255) & ~(size_t)255;
@@ -126,6 +127,15 @@ int check_device(int *dev_out, int *compute_units)
     *dev_out = dev;
     *compute_units = prop.multiProcessorCount;
     return SKRULL_OK;
+}
+
+// Whether nothing that was queued on `st` so far can run any more.  (A wait ends a capture as invalid: what
+// was captured never runs.)
+bool is_idle(hipStream_t st)
+{
+    if (hipStreamSynchronize(st) == hipSuccess) return true;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(st, &capture) == hipSuccess && capture == hipStreamCaptureStatusInvalidated;
 }
 
 // A plan's arrays live on the device it was made on: the calls that use them must run there.
@@ -221,6 +231,7 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
     PlanTotals totals, *totals_h = nullptr;
     int64_t in_stride = 0;
     bool small = false;  // made by one workgroup
+    bool queued = false; // kernels have been launched that read and write the slot
     // tmp (released before return): S, N, R, cut [K each] | fwd_off, dkv_off [n_seg+1 each] |
     // totals | unsorted items; a small plan needs none
     const int64_t kin = align4(K), kpad = align4(n_seg + 1);
@@ -275,6 +286,7 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
         if (dkv_unit_ints > 0) plan->dkv_units = next;
     }
     if (pinned) totals_h = (PlanTotals *)((unsigned char *)pinned + PinnedSlots::kIn);
+    queued = true;
     if (small) {
         HIP_TRY(launch_plan_small(SmallPlan{pinned, totals_h, K, (int32_t)in_stride, BM, BN, bn_alt,
                                             INT32_MAX / (p->num_q_heads * p->head_dim), INT32_MAX / (p->num_kv_heads * p->head_dim),
@@ -305,6 +317,7 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
         HIP_TRY(hipMemcpyAsync(pinned ? totals_h : &totals, totals_d, sizeof totals, hipMemcpyDeviceToHost, st));
     }
     HIP_TRY(hipStreamSynchronize(st));
+    queued = false;
     if (pinned) memcpy(&totals, totals_h, sizeof totals);
     if (totals.bad_entry != 0 || totals.n_seg != plan->NS || totals.total_q > INT32_MAX ||
         totals.total_k > INT32_MAX || totals.n_fwd > kMaxItems || totals.n_dkv > kMaxItems ||
@@ -387,8 +400,8 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
     plan->n_dkv_units = totals.n_dkv_units;
     rc = SKRULL_OK;
 done:
-    if (pinned) g_pinned.give_back(pinned);
-    else free(host_in);
+    if (!pinned) free(host_in);
+    else if (!queued || is_idle(st)) g_pinned.give_back(pinned);  // (else nobody may have it any more)
     if (tmp) (void)hipFree(tmp);
     if (rc != SKRULL_OK) {
         if (plan) {
