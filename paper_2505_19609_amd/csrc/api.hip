@@ -77,7 +77,8 @@ int resolve_scratch(int dev, void **out)
 
 // Pinned host memory through which a plan's kernels get their input and give its totals back: a few
 // slots for the whole process, one for the time of a call; a call that finds none copies instead.  A call that
-// cannot wait for its kernels keeps its slot for good: they may still use it.
+// cannot wait for its kernels keeps its slot for good: they may still use it.  The memory is asked for as coherent:
+// without that the environment (HIP_HOST_COHERENT) decides.
 struct PinnedSlots {
     static constexpr int kSlots = 16;
     static constexpr size_t kIn = 4 * (size_t)SKRULL_SMALL_PLAN * sizeof(int32_t), kBytes = (kIn + sizeof(PlanTotals) + 255) & ~(size_t)255;
@@ -93,7 +94,7 @@ struct PinnedSlots {
             if (!tried) {
                 tried = true;
                 void *p = nullptr;
-                if (hipHostMalloc(&p, kSlots * kBytes, hipHostMallocPortable) == hipSuccess) base = (unsigned char *)p;
+                if (hipHostMalloc(&p, kSlots * kBytes, hipHostMallocPortable | hipHostMallocCoherent) == hipSuccess) base = (unsigned char *)p;
                 else (void)hipGetLastError();
             }
         }

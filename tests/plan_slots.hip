@@ -13,6 +13,7 @@ namespace {
 std::set<const void *> in_flight;  // slots that a kernel which may still run reads and writes
 const void *last_slot = nullptr;   // slot of the last launch
 int fail_units = 0;
+unsigned int host_flags = 0;         // of the last allocation of pinned memory
 bool waits_fail = false;
 bool other_thread_plans = false;   // a plan is made by another thread while this one frees memory
 
@@ -84,7 +85,12 @@ hipError_t hipFree(void *p)
     free(p);
     return hipSuccess;
 }
-hipError_t hipHostMalloc(void **p, size_t n, unsigned int) { *p = malloc(n); return hipSuccess; }
+hipError_t hipHostMalloc(void **p, size_t n, unsigned int flags)
+{
+    host_flags = flags;
+    *p = malloc(n);
+    return hipSuccess;
+}
 hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t) { memcpy(d, s, n); return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return wait(); }
 hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *s) { *s = hipStreamCaptureStatusNone; return hipSuccess; }
@@ -139,6 +145,10 @@ int main(int, char **argv)
             last_slot = nullptr;
             expect(plan(i % 2 ? kOneWorkgroup : kSeveralKernels) == SKRULL_OK && last_slot, "no slot left");
         }
+    } else if (what == "memory_is_coherent") {  // whatever the environment says about memory that does not ask
+        expect(plan(kOneWorkgroup) == SKRULL_OK && last_slot, "a plan failed");
+        expect(host_flags & hipHostMallocCoherent, "kernels and the host share memory that is not coherent");
+        expect(host_flags & hipHostMallocPortable, "the memory is one device's only");
     } else {
         fail("unknown case");
     }
