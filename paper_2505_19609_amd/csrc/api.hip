@@ -84,15 +84,13 @@ struct PinnedSlots {
     static constexpr size_t kIn = 4 * (size_t)SKRULL_SMALL_PLAN * sizeof(int32_t), kBytes = (kIn + sizeof(PlanTotals) + 255) & ~(size_t)255;
     std::mutex made;
     unsigned char *base = nullptr;  // held until the process ends
-    bool tried = false;
     std::atomic<uint32_t> used{0};
 
     int32_t *take()
     {
         {
             std::lock_guard<std::mutex> lock(made);
-            if (!tried) {
-                tried = true;
+            if (!base) {  // (a call that was refused it, for instance beside another thread's capture, leaves it to a later one)
                 void *p = nullptr;
                 if (hipHostMalloc(&p, kSlots * kBytes, hipHostMallocPortable | hipHostMallocCoherent) == hipSuccess) base = (unsigned char *)p;
                 else (void)hipGetLastError();

@@ -25,7 +25,7 @@ def program(tmp_path_factory):
     return str(d / "program")
 
 
-@pytest.mark.parametrize("case", ["wait_fails", "launch_fails", "failures_use_up_no_slots", "memory_is_coherent"])
+@pytest.mark.parametrize("case", ["wait_fails", "launch_fails", "failures_use_up_no_slots", "memory_is_coherent", "memory_comes_later"])
 def test_slots(program, case):
     r = subprocess.run([program, case], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout + r.stderr
