@@ -88,6 +88,7 @@ struct PinnedSlots {
 
     int32_t *take()
     {
+        unsigned char *memory;
         {
             std::lock_guard<std::mutex> lock(made);
             if (!base) {  // (a call that was refused it, for instance beside another thread's capture, leaves it to a later one)
@@ -95,12 +96,13 @@ struct PinnedSlots {
                 if (hipHostMalloc(&p, kSlots * kBytes, hipHostMallocPortable | hipHostMallocCoherent) == hipSuccess) base = (unsigned char *)p;
                 else (void)hipGetLastError();
             }
+            memory = base;
         }
         uint32_t u = used.load(std::memory_order_relaxed);
-        while (base) {
+        while (memory) {
             const int free_slot = __builtin_ffs(~u & ((1u << kSlots) - 1)) - 1;
             if (free_slot < 0) break;
-            if (used.compare_exchange_weak(u, u | 1u << free_slot, std::memory_order_acquire)) return (int32_t *)(base + free_slot * kBytes);
+            if (used.compare_exchange_weak(u, u | 1u << free_slot, std::memory_order_acquire)) return (int32_t *)(memory + free_slot * kBytes);
         }
         return nullptr;
     }
