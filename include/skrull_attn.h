@@ -28,7 +28,7 @@
  * Every function returns 0 (SKRULL_OK) or a negative code; nothing throws or
  * aborts.  State outside the plans: per calling thread, the text of its last error and
  * the opt-in profiling switch at the end of this header; per GPU, the static workspace
- * of skrull_attn_bwd_static; per process, 16 slots of pinned host memory (about 140 KB,
+ * of skrull_attn_bwd_static; per process, 16 slots of pinned host memory (about 530 KB,
  * held until the process ends) of which a skrull_attn_plan call uses one while it runs.  On failure output pointers written
  * through `out` arguments are left untouched.  Every step runs in HIP kernels;
  * there is no CPU fallback.

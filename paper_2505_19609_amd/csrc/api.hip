@@ -81,7 +81,10 @@ int resolve_scratch(int dev, void **out)
 // without that the environment (HIP_HOST_COHERENT) decides.
 struct PinnedSlots {
     static constexpr int kSlots = 16;
-    static constexpr size_t kIn = 4 * (size_t)SKRULL_SMALL_PLAN * sizeof(int32_t), kBytes = (kIn + sizeof(PlanTotals) + 255) & ~(size_t)255;
+    // Sequences whose description a slot has room for; a longer one is copied.  (600 sequences, 1,128 and 1,982 items:
+    // the call takes 147 us with its input and totals copied, 136 through a slot; 1,500 sequences: 390 and 359.)
+    static constexpr int32_t kSeqs = 2048;
+    static constexpr size_t kIn = 4 * (size_t)kSeqs * sizeof(int32_t), kBytes = (kIn + sizeof(PlanTotals) + 255) & ~(size_t)255;
     std::mutex made;
     unsigned char *base = nullptr;  // held until the process ends
     std::atomic<uint32_t> used{0};
@@ -254,10 +257,10 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
     plan->K = K; plan->NS = (int32_t)n_seg; plan->Hq = p->num_q_heads; plan->Hkv = p->num_kv_heads; plan->d = p->head_dim;
     plan->BM = BM; plan->BN = BN; plan->scale = p->softmax_scale; plan->device = dev;
 
-    if (K <= SKRULL_SMALL_PLAN) pinned = g_pinned.take();
-    small = pinned && n_seg <= SKRULL_SMALL_PLAN && cap_fwd <= SKRULL_SMALL_PLAN && cap_dkv <= SKRULL_SMALL_PLAN;
-    in_stride = pinned ? SKRULL_SMALL_PLAN : kin;
-    host_in = pinned ? pinned : (int32_t *)calloc((size_t)(4 * kin), sizeof(int32_t));
+    pinned = g_pinned.take();
+    small = pinned && K <= SKRULL_SMALL_PLAN && n_seg <= SKRULL_SMALL_PLAN && cap_fwd <= SKRULL_SMALL_PLAN && cap_dkv <= SKRULL_SMALL_PLAN;
+    in_stride = kin;
+    host_in = pinned && K <= PinnedSlots::kSeqs ? pinned : (int32_t *)calloc((size_t)(4 * kin), sizeof(int32_t));
     if (!host_in) { rc = SKRULL_ENOMEM; goto done; }
     memcpy(host_in, p->seq_len, (size_t)K * 4);
     memcpy(host_in + in_stride, p->shard_degree, (size_t)K * 4);
@@ -300,8 +303,8 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
         dkv_off = fwd_off + kpad;
         totals_d = (PlanTotals *)(dkv_off + kpad);
         scratch = dkv_off + kpad + totals_ints;
-        const int32_t *in = pinned;  // (the kernel reads pinned memory itself)
-        if (!pinned) {  // a pageable source is staged by the runtime before the call returns
+        const int32_t *in = host_in;  // (the kernel reads pinned memory itself)
+        if (host_in != pinned) {  // a pageable source is staged by the runtime before the call returns
             HIP_TRY(hipMemcpyAsync(tmp, host_in, (size_t)(4 * kin) * 4, hipMemcpyHostToDevice, st));
             in = tmp;
         }
@@ -401,8 +404,8 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
     plan->n_dkv_units = totals.n_dkv_units;
     rc = SKRULL_OK;
 done:
-    if (!pinned) free(host_in);
-    else if (!queued || is_idle(st)) g_pinned.give_back(pinned);  // (else nobody may have it any more)
+    if (host_in != pinned) free(host_in);
+    if (pinned && (!queued || is_idle(st))) g_pinned.give_back(pinned);  // (else nobody may have it any more)
     if (tmp) (void)hipFree(tmp);
     if (rc != SKRULL_OK) {
         if (plan) {

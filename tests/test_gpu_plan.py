@@ -144,6 +144,16 @@ def test_plan_on_both_sides_of_one_workgroup(oracle, S, bm, bn):
     _check(oracle, S, [1] * len(S), [0] * len(S), 4, 2, 64, bm, bn)
 
 
+@pytest.mark.parametrize("K", [513, 2048, 2049])
+def test_plan_on_both_sides_of_a_slot(oracle, K):
+    """Up to 2,048 sequences the kernels read a plan's input from pinned host memory, above that a copy of it; lengths
+    that differ, slices and two-chunk cuts."""
+    S = [2 + (37 * k) % 131 for k in range(K)]
+    cut = [int(k % 3 == 0) for k in range(K)]
+    N = [2 if s > 100 else 1 for s in S]
+    _check(oracle, S, N, [s % 2 if n == 2 else 0 for s, n in zip(S, N)], 4, 2, 64, 64, 64, cut=cut)
+
+
 def test_plans_made_by_many_threads_at_once():
     """Plans in 24 threads, more than there are slots of pinned memory: each thread's plans are its own."""
     import threading
