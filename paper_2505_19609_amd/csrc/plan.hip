@@ -307,24 +307,38 @@ __global__ __launch_bounds__(256) void plan_emit_kernel(
 // falls and the second grows with the length: sqrt(8 s), at least 2 blocks and, at head_dim 64, at
 // most 13.  On 82 micro-batches a quarter, half, twice and four times that change dK/dV on 22, by
 // +9, +4, +1 and +28 % on (geometric) average (profiles/chain_limit_sweep.txt).
-__device__ inline void count_chain(int32_t cost, int32_t group, int32_t q_heads, int32_t head_dim,
-                                   int32_t compute_units, PlanTotals *totals)
-{
-    const float share = (float)totals->dkv_cost_sum * (float)q_heads / (float)compute_units;
-    const float best = fminf(sqrtf(8.0f * share), head_dim == 64 ? 13.0f : 1e6f);
-    const int32_t base = max(2, (int32_t)best);
-    const int64_t chain = (int64_t)cost * group;
-    int above = 0;
-    while (above < SKRULL_CHAIN_LIMITS && chain > dkv_chain_limit(base, above)) ++above;
-    atomicAdd(&totals->chain_hist[above], 1);
-    totals->chain_base = base;  // (the same from every thread)
-}
+// A workgroup counts in LDS and adds its ten counts to the totals once: item by item into the totals, the atomics on
+// these few words were most of the sort (950 and 1,719 items: 39 us, 16 this way; the call 115 and 92).
+struct ChainCounts {
+    int32_t base, hist[SKRULL_CHAIN_LIMITS + 1];  // of a workgroup, in LDS
+    // by all threads; a barrier has to follow
+    __device__ void begin(const PlanTotals *totals, int32_t q_heads, int32_t head_dim, int32_t compute_units)
+    {
+        if (threadIdx.x <= SKRULL_CHAIN_LIMITS) hist[threadIdx.x] = 0;
+        const float share = (float)totals->dkv_cost_sum * (float)q_heads / (float)compute_units;
+        const float best = fminf(sqrtf(8.0f * share), head_dim == 64 ? 13.0f : 1e6f);
+        if (threadIdx.x == 0) base = max(2, (int32_t)best);
+    }
+    __device__ void count(int32_t cost, int32_t group)
+    {
+        const int64_t chain = (int64_t)cost * group;
+        int above = 0;
+        while (above < SKRULL_CHAIN_LIMITS && chain > dkv_chain_limit(base, above)) ++above;
+        atomicAdd(&hist[above], 1);
+    }
+    // by all threads, after a barrier
+    __device__ void end(PlanTotals *totals)
+    {
+        if (threadIdx.x <= SKRULL_CHAIN_LIMITS && hist[threadIdx.x] > 0) atomicAdd(&totals->chain_hist[threadIdx.x], hist[threadIdx.x]);
+        if (threadIdx.x == 0) totals->chain_base = base;  // (the same from every workgroup)
+    }
+};
 
 // Stable sort by descending .w: item a goes to slot
 //   #{b : cost_b > cost_a} + #{b < a : cost_b == cost_a}.
 // Costs are streamed through LDS in tiles; four threads walk a tile for one item, four costs to a
 // read.  (One thread per item and one cost to a read, each waited for, took 12 us for 180 items and
-// 25 us for 310; both lists together now take 6 to 10, 25 for 1,368.)  blockIdx.y: the list (0 forward / dQ, 1 dK/dV).
+// 25 us for 310; both lists together now take 14 for 1,054 and 1,318.)  blockIdx.y: the list (0 forward / dQ, 1 dK/dV).
 constexpr int32_t kSortItems = 64;  // items of a block
 struct SortJob {
     const int4 *in;
@@ -335,6 +349,7 @@ __global__ __launch_bounds__(256) void plan_sort_kernel(SortJob fwd, SortJob dkv
                                                         int32_t compute_units)
 {
     __shared__ __align__(16) int32_t tile[1024];
+    __shared__ ChainCounts chains;
     const int which = first_list + blockIdx.y;
     const int4 *__restrict__ in = which == 0 ? fwd.in : dkv.in;
     int4 *__restrict__ out = which == 0 ? fwd.out : dkv.out;
@@ -342,6 +357,7 @@ __global__ __launch_bounds__(256) void plan_sort_kernel(SortJob fwd, SortJob dkv
                                  : (int32_t)min((long long)totals->n_dkv, (long long)totals->cap_dkv);
     const int32_t first = blockIdx.x * kSortItems;
     if (first >= n) return;  // (the whole block)
+    if (which == 1) chains.begin(totals, q_heads, head_dim, compute_units);  // (barriers follow: n > 0)
     const int32_t a = first + threadIdx.x / 4, quarter = threadIdx.x % 4;
     const int4 me = (a < n) ? in[a] : make_int4(0, 0, 0, 0);
     int32_t rank = 0;
@@ -364,8 +380,11 @@ __global__ __launch_bounds__(256) void plan_sort_kernel(SortJob fwd, SortJob dkv
     rank += __shfl_xor(rank, 2, 64);
     if (a < n && quarter == 0) {
         out[rank] = me;
-        if (which == 1) count_chain(me.w, group, q_heads, head_dim, compute_units, totals);
+        if (which == 1) chains.count(me.w, group);
     }
+    if (which != 1) return;
+    __syncthreads();
+    chains.end(totals);
 }
 
 // ---------------------------------------------------------------------------
@@ -695,6 +714,7 @@ __global__ __launch_bounds__(kSmallThreads) void plan_small_kernel(SmallPlan j)
     __shared__ int32_t first_bad, longest_s, cost_max;
     __shared__ unsigned long long sum_s, pairs_s, load_s;
     __shared__ PlanTotals tot;
+    __shared__ ChainCounts chains;
     const int t = threadIdx.x;
     const int32_t group = j.q_heads / j.kv_heads, log_bm = __ffs(j.BM) - 1;  // (BM is a power of two)
     if (t == 0) {
@@ -820,6 +840,7 @@ __global__ __launch_bounds__(kSmallThreads) void plan_small_kernel(SmallPlan j)
         tot.block_n = BN;
     }
     __syncthreads();
+    chains.begin(&tot, j.q_heads, j.head_dim, j.compute_units);
     const int32_t log_t = max(n_fwd, n_dkv) <= kSmallThreads / 4 ? 2 : (max(n_fwd, n_dkv) <= kSmallThreads / 2 ? 1 : 0);
     const int32_t a = t >> log_t, sub = t & ((1 << log_t) - 1);  // threads of an item
     f = fwd[a];
@@ -833,8 +854,10 @@ __global__ __launch_bounds__(kSmallThreads) void plan_small_kernel(SmallPlan j)
     if (a < n_dkv && sub == (1 << log_t) - 1) {
         dkv[at_d] = d;
         ((int4 *)j.dkv_items)[at_d] = d;
-        count_chain(d.w, group, j.q_heads, j.head_dim, j.compute_units, &tot);
+        chains.count(d.w, group);
     }
+    __syncthreads();
+    chains.end(&tot);
     __syncthreads();
     // --- work units, as in plan_units_kernel
     if (t == 0) tot.split = choose_split(j.asked, tot, j.q_heads, j.kv_heads, j.head_dim, j.longest_seq, j.compute_units);
@@ -920,17 +943,21 @@ __global__ __launch_bounds__(256) void radix_hist_kernel(const int4 *__restrict_
                                                          int32_t *__restrict__ hist)
 {
     __shared__ int32_t h[256];
+    __shared__ ChainCounts chains;
     const int32_t n = list_length(totals, which);
+    const bool counts = which == 1 && shift == 0;
     h[threadIdx.x] = 0;
+    if (counts) chains.begin(totals, q_heads, head_dim, compute_units);
     __syncthreads();
     const int32_t base = blockIdx.x * kRadixBlock;
     for (int32_t i = threadIdx.x; i < kRadixBlock; i += 256)
         if (base + i < n) {
             const int32_t cost = in[base + i].w;
             atomicAdd(&h[((key_max - cost) >> shift) & 255], 1);
-            if (which == 1 && shift == 0) count_chain(cost, group, q_heads, head_dim, compute_units, totals);
+            if (counts) chains.count(cost, group);
         }
     __syncthreads();
+    if (counts) chains.end(totals);
     hist[threadIdx.x * nb + blockIdx.x] = h[threadIdx.x];
 }
 
@@ -999,9 +1026,9 @@ hipError_t launch_plan_ranges(const int32_t *S, const int32_t *N, const int32_t 
 }
 
 // Above this many items (the host's upper bound) a list is sorted by radix passes instead of
-// by rank counting, which is quadratic: both lists together take 5 us at 64 items of dK/dV, 9 at 256, 26 at
-// 1,024 and 47 at 2,000; one radix pass takes 95 us at 2,060 and 121 at 4,000.  (The line could lie a little
-// higher, but the lists of units hold an item's position in SKRULL_UNIT_SHIFT bits.)
+// by rank counting, which is quadratic: both lists together take 14 us at 1,318 items of dK/dV and 18 at 1,982; one
+// radix pass takes 73 us at 2,673.  (The line could lie higher, but the lists of units hold an item's
+// position in SKRULL_UNIT_SHIFT bits.)
 constexpr int32_t kRankSortMax = 1 << SKRULL_UNIT_SHIFT;
 
 int plan_radix_passes(int32_t cap, int32_t cost_bound)
