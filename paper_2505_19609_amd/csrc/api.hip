@@ -258,7 +258,12 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
     plan->BM = BM; plan->BN = BN; plan->scale = p->softmax_scale; plan->device = dev;
 
     pinned = g_pinned.take();
-    small = pinned && K <= SKRULL_SMALL_PLAN && n_seg <= SKRULL_SMALL_PLAN && cap_fwd <= SKRULL_SMALL_PLAN && cap_dkv <= SKRULL_SMALL_PLAN;
+    // One workgroup ranks lists of up to 256 items with two threads or more to an item; above that the several kernels
+    // are faster (203 and 354 items: the call takes 61 us by one workgroup, 53 by those; 239 and 420: 66 and 56; 152 and 263: 54
+    // and 52; below it 145 and 255: 45 and 50; 109 and 201: 41 and 47).  Where blocks of 192 keys may be taken, a list of
+    // such items is two thirds of cap_dkv (167 and 215 items: 46 and 53; 188 and 233: 50 and 55).
+    small = pinned && K <= SKRULL_SMALL_PLAN && n_seg <= SKRULL_SMALL_PLAN && cap_fwd <= 256 && cap_dkv <= (bn_alt ? 384 : 256);
+    static_assert(384 <= SKRULL_SMALL_PLAN, "a thread to an item");
     in_stride = kin;
     host_in = pinned && K <= PinnedSlots::kSeqs ? pinned : (int32_t *)calloc((size_t)(4 * kin), sizeof(int32_t));
     if (!host_in) { rc = SKRULL_ENOMEM; goto done; }

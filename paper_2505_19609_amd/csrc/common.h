@@ -131,7 +131,7 @@ __device__ __forceinline__ void trace_end(WgTrace *t, uint64_t t0, int work)
 #endif
 
 // plan.hip
-// A plan made by one workgroup: at most SKRULL_SMALL_PLAN sequences, segments and items of either list.
+// A plan made by one workgroup: at most SKRULL_SMALL_PLAN sequences, segments and items of either list (a thread each).
 #define SKRULL_SMALL_PLAN 512
 struct SmallPlan {
     const int32_t *in;      // pinned host memory: S, N, R, cut, `stride` ints apart

@@ -647,10 +647,9 @@ __global__ __launch_bounds__(256) void plan_units_kernel(UnitsJob j, PlanTotals 
 // The whole plan of a small micro-batch in one workgroup: what the four kernels above write, with everything
 // in between in LDS.  A plan is a chain of small dependent steps that nothing overlaps: four launches, a copy in, a
 // copy out and scratch memory around them took most of its time.  The input is read from pinned host memory
-// and the totals are written there.  The call (without destroying the plan), before and after: 3 sequences 49 ->
-// 37 us, 20 sequences with 76 and 95 items 62 -> 42, 64 with 135 and 173 items 67 -> 54, 114 with 181 and 310
-// items 73 -> 70 (the ranks are quadratic: 512 items of a list are the line, where it is as fast as the others);
-// the kernel itself takes 12, 16, 19 and 30 us.
+// and the totals are written there.  The call (without destroying the plan) by the several kernels and this
+// way: 3 sequences 44 and 34 us, 20 sequences with 91 and 115 items 51 and 39, 64 with 167 and 215 items 53 and 46 (the
+// ranks are quadratic: for the line see skrull_attn_plan).
 // ---------------------------------------------------------------------------
 constexpr int kSmallThreads = SKRULL_SMALL_PLAN, kSmallWaves = kSmallThreads / 64;
 

@@ -139,9 +139,18 @@ def test_items_are_shared_out_only_where_that_pays(S, N, R, shared):
 @pytest.mark.parametrize("S,bm,bn", [([64 * 511 + 1], 64, 64), ([64 * 512 + 1], 64, 64), ([64] * 512, 64, 64), ([64] * 513, 64, 64),
                                      ([100] * 256 + [64] * 256, 64, 128), ([200] * 128, 64, 256), ([130] * 129, 64, 256)])
 def test_plan_on_both_sides_of_one_workgroup(oracle, S, bm, bn):
-    """Up to 512 sequences, segments and items of a list one workgroup makes the whole plan (with 4, 2 or 1 threads to
-    an item: lists of 128, 129, 256 and more items), above that several kernels do."""
+    """Up to 512 sequences and 256 items of a list one workgroup makes the whole plan (with 4 or 2 threads to an item:
+    lists of 128, 129 and 256 items), above that several kernels do."""
     _check(oracle, S, [1] * len(S), [0] * len(S), 4, 2, 64, bm, bn)
+
+
+@pytest.mark.parametrize("S,bn", [([64 * 256], 64), ([64 * 256 + 1], 64), ([64] * 257, 64), ([64] * 255 + [65], 64), ([3000, 600] * 13 + [129], 0),
+                                  ([6000] * 8, 0), ([130] * 192, 0), ([130] * 192 + [1], 0), ([40] * 256, 0), ([40] * 257, 0)])
+@pytest.mark.parametrize("heads", [(4, 2, 64), (14, 2, 64), (32, 8, 64), (8, 2, 128)])
+def test_plan_at_the_last_lists_of_one_workgroup(oracle, S, bn, heads):
+    """256 items of a list and one more; with the key block left open at head_dim 64, 384 items of 128 keys that stay (a
+    thread to an item) or become fewer of 192."""
+    _check(oracle, S, [1] * len(S), [0] * len(S), *heads, bn and 64, bn)
 
 
 @pytest.mark.parametrize("K", [513, 2048, 2049])
