@@ -101,9 +101,12 @@ typedef struct {
     int32_t head_split;           /* most workgroups that share a dK/dV item by its heads (>= 1; see
                                      skrull_attn_plan); the workspace has room for so many partial
                                      sums of every row of K, also where fewer items are shared  */
-    int32_t wg_query_rows;        /* query rows per forward / dQ workgroup in effect (128 or 256;
-                                     dQ has the 128-row shape at head_dim 64 only)             */
-    int32_t reserved;             /* 0                                                         */
+    int32_t wg_query_rows;        /* query rows per forward / dQ workgroup asked for or chosen (128 or 256);
+                                     `shapes` says what runs: dQ has the 128-row shape at head_dim 64
+                                     only, and a choice of 256 there may run with 384 rows or 128 */
+    int32_t shapes;               /* workgroups that run: bits 0-7 wavefronts of a forward workgroup, bits
+                                     8-15 of a dQ workgroup (4, 8 or 12, of 32 query rows each), bit 16
+                                     set where dQ is the pipelined kernel                      */
 } skrull_attn_plan_info_t;
 
 /* Arrays a plan holds on the device, for skrull_attn_plan_export.  They are per
@@ -152,7 +155,10 @@ enum {
  * wg_query_rows 128 when the micro-batch holds enough work for the smaller
  * workgroups to pay (head_dim 64: at least 24 blocks of 256 query rows x heads
  * per compute unit or 1.5e9 attended (query, key, head) triples; head_dim 128:
- * at least 16 such blocks and no sequence above 8,192 tokens), else 256.  None
+ * at least 16 such blocks and no sequence above 8,192 tokens), else 256.  At head_dim 64 a
+ * choice of 256 (not a 256 that the caller gives) runs forward and dQ with workgroups of 12 wavefronts
+ * for lists of many short units and of 4 for launches that run at once, and dQ workgroups of 4 are
+ * pipelined or not by the length and number of their units (info.shapes).  None
  * of them changes a result beyond the
  * last bit of dK/dV (head_split and the sharing of items change the order of a sum).
  *

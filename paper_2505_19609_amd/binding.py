@@ -49,7 +49,21 @@ class PlanInfo(ctypes.Structure):
                 ("attended_pairs", ctypes.c_int64), ("useful_flops_fwd", ctypes.c_int64),
                 ("useful_flops_bwd", ctypes.c_int64), ("bwd_workspace_bytes", ctypes.c_int64),
                 ("num_segments", ctypes.c_int32), ("head_split", ctypes.c_int32),
-                ("wg_query_rows", ctypes.c_int32), ("reserved", ctypes.c_int32)]
+                ("wg_query_rows", ctypes.c_int32), ("shapes", ctypes.c_int32)]
+
+    @property
+    def fwd_waves(self):
+        """Wavefronts of a forward workgroup that runs."""
+        return self.shapes & 255
+
+    @property
+    def dq_waves(self):
+        """Wavefronts of a dQ workgroup that runs."""
+        return self.shapes >> 8 & 255
+
+    @property
+    def dq_pipelined(self):
+        return bool(self.shapes >> 16 & 1)
 
 
 class FlopsModel(ctypes.Structure):

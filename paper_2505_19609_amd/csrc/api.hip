@@ -448,7 +448,7 @@ int skrull_attn_plan_info(const skrull_attn_plan_t *plan, skrull_attn_plan_info_
     info->num_segments = plan->NS;
     info->head_split = plan->head_split;
     info->wg_query_rows = plan->wg_query_rows;
-    info->reserved = 0;
+    info->shapes = plan->fwd_waves | plan->dq_waves << 8 | (plan->dq_waves == 8 || plan->dq_piped ? 1 << 16 : 0);
     return SKRULL_OK;
 }
 

@@ -24,7 +24,7 @@ struct skrull_attn_plan {
     int32_t total_q, total_k, n_fwd, n_dkv;
     int64_t pairs;
     int32_t head_split;  // workgroups that share the query heads of one KV group in dK/dV
-    int32_t wg_query_rows;  // query rows per forward / dQ workgroup: 128 (4 wavefronts) or 256 (8)
+    int32_t wg_query_rows;  // query rows per forward / dQ workgroup, asked for or chosen: 128 or 256; what runs follows
     int32_t fwd_waves, dq_waves;  // wavefronts of a forward / dQ workgroup: 4, 8 or 12
     bool dq_piped;                // dQ of 4: pipelined, two workgroups per compute unit
     // dK/dV items that several workgroups share (the first n_split of the sorted list), and how:

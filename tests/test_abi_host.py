@@ -34,6 +34,12 @@ def test_struct_layouts_match_header(B):
     assert ctypes.sizeof(B.PlanInfo) == 10 * 4 + 4 * 8 + 4 * 4
 
 
+def test_shapes_word_of_the_plan_info(B):
+    info = B.PlanInfo(shapes=12 | 4 << 8 | 1 << 16)
+    assert (info.fwd_waves, info.dq_waves, info.dq_pipelined) == (12, 4, True)
+    assert not B.PlanInfo(shapes=8 | 4 << 8).dq_pipelined
+
+
 def test_strerror(B):
     assert B.skrull_attn_strerror(0) == "ok"
     assert "invalid" in B.skrull_attn_strerror(B.SKRULL_EINVAL)

@@ -1047,7 +1047,7 @@ def test_wide_forward_changes_no_bit(heads):
     w = W.Workload("wide", S, N, R, heads[0], heads[1], 64, 64 ** -0.5, 609, shard_cut=Z)
     out = run_library(w, backward=False)
     ref = run_library(w, backward=False, vals=out["vals"], wg_query_rows=256)
-    assert out["plan"].info.wg_query_rows == 256
+    assert out["plan"].info.wg_query_rows == 256 and out["plan"].fwd_waves == 12 and ref["plan"].fwd_waves == 8
     n, n8 = (B.skrull_attn_trace_layout(x["plan"])[1][0] for x in (out, ref))
     assert n < n8 <= 3 * n // 2
     for k in ("o", "lse"):
@@ -1070,6 +1070,8 @@ def test_shapes_of_head_dim_64_change_no_bit(heads, S, waves):
     out = run_library(w, guard=True)
     assert out["margins"] == [] and out["plan"].info.wg_query_rows == 256
     ref = run_library(w, vals=out["vals"], wg_query_rows=256)
+    for p, n in ((out["plan"], waves), (ref["plan"], 8)):
+        assert (p.fwd_waves, p.dq_waves, p.dq_pipelined) == (n, n, n == 8)
     for i in (0, 1):
         n, n8 = (B.skrull_attn_trace_layout(x["plan"])[1][i] for x in (out, ref))
         assert n < n8 if waves == 12 else n == 2 * n8
@@ -1087,6 +1089,7 @@ def test_small_dq_shapes_change_no_bit(heads, S):
                    64 ** -0.5, 611, shard_cut=[0] * (len(S) + 1) + [1])
     out = run_library(w, guard=True, wg_query_rows=128)
     assert out["margins"] == [] and out["plan"].info.wg_query_rows == 128
+    assert out["plan"].dq_waves == 4 and out["plan"].dq_pipelined
     ref = run_library(w, vals=out["vals"], wg_query_rows=256)
     for k in ("o", "lse", "dq", "dk", "dv"):
         assert np.array_equal(out[k], ref[k]), k
