@@ -13,7 +13,8 @@ the compute unit it ran on, and per kernel it reports
     tail          1 - busy measured from the moment the first compute unit has run dry, i.e.
                   the share of CU-time lost at the end of the launch
     lpt_bound     the same list scheduled greedily (each item to the unit that is free
-                  first) with the MEASURED workgroup durations: what ideal dispatch would give
+                  first) with the MEASURED workgroup durations: what ideal dispatch would give;
+                  a compute unit counts for as many places as workgroups were seen on one at once
 
     python -m paper_2505_19609_amd.balance --config 3
 """
@@ -30,7 +31,7 @@ REC = np.dtype([("t0", "<u8"), ("t1", "<u8"), ("hw_id", "<u4"), ("xcc_id", "<u4"
 TICK_US = 0.01   # s_memrealtime runs at 100 MHz
 
 
-def analyse(rec, slots_per_cu):
+def analyse(rec):
     """rec: structured records of one launch (written ones only)."""
     t0 = rec["t0"].astype(np.int64)
     t1 = rec["t1"].astype(np.int64)
@@ -39,7 +40,7 @@ def analyse(rec, slots_per_cu):
     # a compute unit: die, shader engine, shader array, CU
     cu = (rec["xcc_id"].astype(np.int64) & 0xF) << 16 | (rec["hw_id"].astype(np.int64) & 0xFF00)
     units = np.unique(cu)
-    covered, last_end = [], []
+    covered, last_end, places = [], [], 1
     for u in units:
         sel = np.nonzero(cu == u)[0]
         order = sel[np.argsort(t0[sel])]
@@ -53,28 +54,32 @@ def analyse(rec, slots_per_cu):
                 cur_e = max(cur_e, t1[i])
         tot += cur_e - cur_s
         covered.append(tot)
+        # workgroups that shared the unit at some moment (one that ends as another starts does not count)
+        step = np.repeat([1, -1], len(sel))
+        places = max(places, int(np.cumsum(step[np.lexsort((step, np.concatenate([t0[sel], t1[sel]])))]).max()))
         last_end.append(t1[sel].max())
     covered, last_end = np.array(covered, float), np.array(last_end, float)
     first_dry = last_end.min()
     tail_lost = float((end - last_end).sum()) / (len(units) * span)
     dur = (t1 - t0).astype(float)
     # greedy list scheduling of the same durations in grid order over the same number of slots
-    slots = [0.0] * (len(units) * slots_per_cu)
+    slots = [0.0] * (len(units) * places)
     heapq.heapify(slots)
     for b in np.argsort(rec["block"]):
         heapq.heappush(slots, heapq.heappop(slots) + dur[b])
     lpt_span = max(slots)
     return {"workgroups": int(len(rec)), "compute_units": int(len(units)),
+            "places_per_unit": places,
             "dies": int(len(np.unique(rec["xcc_id"] & 0xF))),
             "span_us": round(span * TICK_US, 2),
             "busy": round(float(covered.mean()) / span, 4),
             "tail_lost": round(tail_lost, 4),
             "first_unit_dry_at": round(float(first_dry - start) / span, 4),
             "wg_us_min_med_max": [round(float(x) * TICK_US, 2) for x in (dur.min(), np.median(dur), dur.max())],
-            "sum_wg_time_over_units_x_span": round(float(dur.sum()) / (len(units) * slots_per_cu * span), 4),
+            "sum_wg_time_over_units_x_span": round(float(dur.sum()) / (len(units) * places * span), 4),
             "greedy_span_us": round(lpt_span * TICK_US, 2),
             "span_over_greedy": round(span / lpt_span, 4),
-            "ideal_span_us": round(float(dur.sum()) / (len(units) * slots_per_cu) * TICK_US, 2)}
+            "ideal_span_us": round(float(dur.sum()) / (len(units) * places) * TICK_US, 2)}
 
 
 def main(argv=None):
@@ -117,16 +122,13 @@ def main(argv=None):
     B.skrull_attn_trace(None)
     rec = records.cpu().numpy().view(REC).reshape(-1)
     info = plan.info
-    # workgroups of one compute unit at a time: the 8-wavefront forward / dQ shapes and dK/dV fill one alone
-    slots = {"fwd": 2 if info.wg_query_rows == 128 else 1,
-             "dq": 2 if (info.wg_query_rows == 128 and d == 64) else 1,
-             "dkv": 1}
     out = {"workload": w.name, "block_m": int(info.block_m), "block_n": int(info.block_n),
-           "head_split": int(info.head_split), "wg_query_rows": int(info.wg_query_rows), "kernels": {}}
+           "head_split": int(info.head_split), "wg_query_rows": int(info.wg_query_rows),
+           "fwd_waves": info.fwd_waves, "dq_waves": info.dq_waves, "dq_pipelined": info.dq_pipelined, "kernels": {}}
     for name, f, n in zip(("fwd", "dq", "dkv"), first, num):
         r = rec[f:f + n]
         r = r[r["one"] == 1]
-        out["kernels"][name] = analyse(r, slots[name])
+        out["kernels"][name] = analyse(r)
         out["kernels"][name]["grid"] = n
     if args.dump:
         np.savez_compressed(args.dump, **{name: rec[f:f + n] for name, f, n in zip(("fwd", "dq", "dkv"), first, num)})
