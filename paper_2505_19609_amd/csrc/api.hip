@@ -388,17 +388,20 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
         else if (2 * totals.n_fwd * plan->Hq <= 3 * (int64_t)compute_units)
             plan->dq_waves = plan->fwd_waves = 4;
     }
-    // In the small shape three dQ workgroups share a compute unit, each slower than one of the two that the pipelined
-    // kernel has there.  By r = the longest unit / an even share per place: up to r = 1 the three take 1 to 6 % less time (61 of
-    // 67 micro-batches, 4 % more at worst), above it one more unit than places is a whole round more: 17 to 24 % more on
-    // 6 of 14 and 3 % less at best.  Where all units run at once there is no such round, and three take 4 to 14 % less, until
-    // few long ones end alone on their SIMDs (r = 3.5: 12 % more).
+    // Of dQ workgroups of 4 three share a compute unit, each slower than one of the two that the pipelined kernel has
+    // there.  Measured on 173 micro-batches, of 4 to 16 heads and 8 to 7,516 units, pipelined against not:
+    //  up to two units per compute unit all run at once either way, and a unit is faster pipelined once it is long
+    //    enough: from 24 half tiles of keys on (fwd_longest counts 16 for a unit's start and end) 1 to 12 % less time (all
+    //    of 63; 2 % at 24 to 31, 10 % from 130 on), at 20 to 23 from 5 % less to 1 % more, below that 1 % more on average, 8 at worst;
+    //  up to three per compute unit the pipelined kernel has a second round: 2 to 21 % more (all of 11);
+    //  above that by r = the longest unit / an even share per place: up to r = 1 it takes as much or up to 6 % more
+    //    (40 of 41, the other 1 % less), from 1.3 on, where a round of long units is what the launch waits for, 7 to 16 % less.
     plan->dq_piped = false;
-    if (plan->wg_query_rows == 128 && plan->d == 64 && plan->units[2]) {
+    if (plan->dq_waves == 4 && plan->units[2]) {
         const double places = 3.0 * (double)compute_units, units = (double)plan->n_units[0] * (double)plan->Hkv;
         const double share = (double)totals.fwd_load * (double)plan->n_units[0] / (double)(plan->n_units[2] > 0 ? plan->n_units[2] : 1) * (double)plan->Hkv / places;
-        const double r = share > 0.0 ? (double)totals.fwd_longest / share : 0.0;
-        plan->dq_piped = r >= 3.0 || (r >= 1.0 && units > places);
+        if (units <= 2.0 * (double)compute_units) plan->dq_piped = totals.fwd_longest >= 40;
+        else if (units > places) plan->dq_piped = (double)totals.fwd_longest >= share;
     }
     plan->head_split = totals.split.head_split;
     plan->n_split = totals.split.n_split;

@@ -1056,13 +1056,14 @@ def test_wide_forward_changes_no_bit(heads):
     ref["plan"].destroy()
 
 
-@pytest.mark.parametrize("heads,S,waves", [((14, 2), [1, 31, 32, 33, 255, 256, 257, 300, 511, 700, 97] * 8, 12),
-                                           ((9, 3), [64, 65, 127, 128, 129, 191, 192, 193, 1000] * 12, 12),
-                                           ((4, 4), [455, 283, 194, 1, 32], 4), ((14, 2), [600, 33, 129], 4),
-                                           ((6, 2), [1000, 65, 64, 63], 4)])
-def test_shapes_of_head_dim_64_change_no_bit(heads, S, waves):
+@pytest.mark.parametrize("heads,S,waves,piped", [((14, 2), [1, 31, 32, 33, 255, 256, 257, 300, 511, 700, 97] * 8, 12, False),
+                                                 ((9, 3), [64, 65, 127, 128, 129, 191, 192, 193, 1000] * 12, 12, False),
+                                                 ((4, 4), [455, 283, 194, 1, 32], 4, False), ((14, 2), [600, 33, 129], 4, False),
+                                                 ((6, 2), [1000, 65, 64, 63], 4, True)])
+def test_shapes_of_head_dim_64_change_no_bit(heads, S, waves, piped):
     """At head_dim 64 the plan gives forward and dQ workgroups of 12 wavefronts (many short units) or of 4 (a launch
-    that runs at once); asked for 256 rows they have 8, and dQ is pipelined.  Same bits, also with a slice and a cut."""
+    that runs at once), pipelined where one is long; asked for 256 rows they have 8, and dQ is pipelined.  Same bits, also
+    with a slice and a cut."""
     from paper_2505_19609_amd import binding as B
     K = len(S)
     N, R, Z = [1] * K + [3, 2], [0] * K + [1, 1], [0] * K + [0, 1]
@@ -1070,8 +1071,8 @@ def test_shapes_of_head_dim_64_change_no_bit(heads, S, waves):
     out = run_library(w, guard=True)
     assert out["margins"] == [] and out["plan"].info.wg_query_rows == 256
     ref = run_library(w, vals=out["vals"], wg_query_rows=256)
-    for p, n in ((out["plan"], waves), (ref["plan"], 8)):
-        assert (p.fwd_waves, p.dq_waves, p.dq_pipelined) == (n, n, n == 8)
+    for p, n, x in ((out["plan"], waves, piped), (ref["plan"], 8, True)):
+        assert (p.fwd_waves, p.dq_waves, p.dq_pipelined) == (n, n, x)
     for i in (0, 1):
         n, n8 = (B.skrull_attn_trace_layout(x["plan"])[1][i] for x in (out, ref))
         assert n < n8 if waves == 12 else n == 2 * n8
@@ -1079,6 +1080,24 @@ def test_shapes_of_head_dim_64_change_no_bit(heads, S, waves):
         assert np.array_equal(out[k], ref[k]), k
     out["plan"].destroy()
     ref["plan"].destroy()
+
+
+@pytest.mark.parametrize("rows", [0, 128])
+@pytest.mark.parametrize("heads,S,piped", [
+    ((4, 4), [736], False), ((4, 4), [737], True),               # all at once two to a unit: from 24 half tiles on
+    ((16, 16), [4096], True), ((16, 16), [4097], False),         # 512 units, and 16 more
+    ((16, 16), [6144], False), ((4, 4), [18000], False),         # up to three to a unit
+    ((16, 16), [6145], True), ((16, 16), [6145] * 3, False)])    # above that: r = 1.9 and 0.6
+def test_which_dq_of_four_waves_runs(heads, S, piped, rows):
+    """Both sides of the lines between the pipelined dQ kernel of 4 wavefronts and the other, however 4 came about."""
+    from paper_2505_19609_amd import binding as B
+    plan = B.skrull_attn_plan(S, [1] * len(S), [0] * len(S), *heads, 64, 0.125, wg_query_rows=rows)
+    at_once = 2 * sum(-(-s // 256) for s in S) * heads[0] <= 768
+    if rows == 128 or at_once:
+        assert (plan.dq_waves, plan.dq_pipelined) == (4, piped)
+    else:
+        assert plan.dq_waves != 4
+    plan.destroy()
 
 
 @pytest.mark.parametrize("heads,S", [((16, 16), [9000, 1, 63, 130]), ((4, 4), [2100, 1, 64, 65, 127, 33])])
