@@ -288,11 +288,12 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
     plan->dkv_items = plan->fwd_items + 4 * cap_fwd;
     {
         int32_t *next = plan->dkv_items + 4 * cap_dkv;
+        if (dkv_unit_ints > 0) plan->dkv_units = (int4 *)next;  // (16-byte aligned, as the items are)
+        next += dkv_unit_ints;
         for (int i = 0; i < SKRULL_UNIT_LISTS; ++i) {
             if (unit_ints[i] > 0) plan->units[i] = next;
             next += unit_ints[i];
         }
-        if (dkv_unit_ints > 0) plan->dkv_units = next;
     }
     if (pinned) totals_h = (PlanTotals *)((unsigned char *)pinned + PinnedSlots::kIn);
     queued = true;

@@ -40,7 +40,7 @@ struct KeyMap {
     int32_t n_split, n_whole_first, parts, chain;  // see skrull_attn_plan
     int32_t part_rows;                          // rows of one part's partial sums; 0: the rows of K themselves
     uint64_t inv_passes, inv_hkv;
-    const int32_t *units;                       // null, or the work units: item | part << SKRULL_UNIT_SHIFT
+    const int4 *units;                          // null, or the work units (skrull_attn_plan::dkv_units)
     uint64_t inv_whole;
 };
 // workgroups that share an item of the first n_split
@@ -634,32 +634,41 @@ __device__ __forceinline__ KeyBlock key_block(const P prm, int SUB, int bid)
     KeyBlock r;
     const int BN = prm->keys.BN, Hkv = prm->keys.Hkv, passes = prm->keys.passes, n_split = prm->keys.n_split;
     const int whole = Hkv * passes;
-    const int32_t *units = prm->keys.units;
-    int item, y, sub;
-    bool is_split;
+    const int4 *units = prm->keys.units;
+    int seq, block, item, sub;
     if (units) {
-        const int unit = __builtin_amdgcn_readfirstlane(quotient(bid, prm->keys.inv_whole)), u = plan_value(units, unit);
+        const int unit = __builtin_amdgcn_readfirstlane(quotient(bid, prm->keys.inv_whole));
+        const i32x4 u = plan_value((const i32x4 *)units, unit);
         const int x = bid - unit * whole;
-        y = quotient(x, prm->keys.inv_passes);
-        sub = x - y * passes;
-        item = u & ((1 << SKRULL_UNIT_SHIFT) - 1);
-        r.part = u >> SKRULL_UNIT_SHIFT;
-        r.c = y;
-        is_split = item < n_split;
+        r.c = quotient(x, prm->keys.inv_passes);
+        sub = x - r.c * passes;
+        seq = u.x;
+        block = u.y;
+        item = u.z & ((1 << SKRULL_UNIT_SHIFT) - 1);
+        r.part = u.z >> SKRULL_UNIT_SHIFT;
+        r.parts = u.w;
     } else {
         const int first = prm->keys.n_whole_first * whole, split = n_split * prm->keys.parts * whole;
-        is_split = bid >= first && bid < first + split;
+        const bool is_split = bid >= first && bid < first + split;
         const int per_item = is_split ? whole * prm->keys.parts : whole;
         const int rel = bid < first ? bid : (is_split ? bid - first : bid - split);
         const int at = __builtin_amdgcn_readfirstlane(rel / per_item), x = rel - at * per_item;
         item = is_split ? at : at + n_split;
-        y = quotient(x, prm->keys.inv_passes);
+        const int y = quotient(x, prm->keys.inv_passes);
         sub = x - y * passes;
         r.part = quotient(y, prm->keys.inv_hkv);
         r.c = y - r.part * Hkv;
+        const i32x4 it = plan_value((const i32x4 *)prm->dkv_items, item);
+        seq = it.x;
+        block = it.y;
+        r.parts = 1;
+        if (is_split) {
+            const int chain = prm->keys.chain;
+            r.parts = chain == 0 ? prm->keys.parts
+                                 : min(prm->keys.parts, __builtin_amdgcn_readfirstlane((it.w * prm->keys.g + chain - 1) / max(chain, 1)));
+        }
     }
-    const i32x4 it = plan_value((const i32x4 *)prm->dkv_items, item);
-    const int seq = it.x, prev = max(seq - 1, 0);
+    const int prev = max(seq - 1, 0);
     const int shares = plan_value(prm->shares_kv, seq), kvl_e = plan_value(prm->kv_len, prev);
     r.qb = plan_value(prm->q_begin, seq);
     r.ql = plan_value(prm->q_len, seq);
@@ -669,12 +678,6 @@ __device__ __forceinline__ KeyBlock key_block(const P prm, int SUB, int bid)
     r.qb_e = plan_value(prm->q_begin, prev);
     r.qbase_e = plan_value(prm->cu_q, prev);
     r.ql_e = plan_value(prm->q_len, prev);
-    r.parts = 1;
-    if (is_split) {
-        const int chain = prm->keys.chain;
-        r.parts = chain == 0 ? prm->keys.parts
-                             : min(prm->keys.parts, __builtin_amdgcn_readfirstlane((it.w * prm->keys.g + chain - 1) / max(chain, 1)));
-    }
     // A part takes an equal share of the heads where there is one (the parts of neighbouring key
     // blocks then walk the same query tiles at the same time), else an equal piece of the walk over
     // all of them.
@@ -684,8 +687,8 @@ __device__ __forceinline__ KeyBlock key_block(const P prm, int SUB, int bid)
     r.head_lo = r.c * g + (by_heads ? r.part * share : 0);
     r.piece = by_heads ? 0 : r.part;
     r.pieces = by_heads ? 1 : r.parts;
-    r.kv0 = it.y * BN + sub * SUB;
-    r.item_rows = r.part < r.parts ? min(BN, r.kvl - it.y * BN) - sub * SUB : 0;
+    r.kv0 = block * BN + sub * SUB;
+    r.item_rows = r.part < r.parts ? min(BN, r.kvl - block * BN) - sub * SUB : 0;
     r.part_row = prm->keys.part_rows ? item * BN + sub * SUB : r.kbase + r.kv0;
     if (!shares || r.kv0 >= kvl_e) r.ql_e = 0;
     return r;

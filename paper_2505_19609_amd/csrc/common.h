@@ -41,7 +41,11 @@ struct skrull_attn_plan {
     // part << SKRULL_UNIT_SHIFT, in list order; null for lists too long
     // for the rank sort and for very many heads
     int32_t *units[SKRULL_UNIT_LISTS], n_units[SKRULL_UNIT_LISTS];
-    int32_t *dkv_units, n_dkv_units;  // the same of the dK/dV list (item | part << SKRULL_UNIT_SHIFT), or null
+    // The same of the dK/dV list, or null: {segment, key block, item | part << SKRULL_UNIT_SHIFT, parts of the item}.
+    // (With the item's position alone, each unit began with one more load that all its others waited for: dK/dV of 60
+    // small launches takes 1.5 % more that way, of 40 micro-batches of long chains at head_dim 64 0.5 %.)
+    int4 *dkv_units;
+    int32_t n_dkv_units;
     WorkQueue *fwd_queues;  // SKRULL_FWD_QUEUE_SLOTS times eight dies' queues, at the start of the pool: for forward launches
     uint32_t fwd_calls;     // forward calls made so far (atomic): call i uses slot i mod SKRULL_FWD_QUEUE_SLOTS
 };
@@ -139,7 +143,8 @@ struct SmallPlan {
     int32_t K, stride, BM, BN, bn_alt, max_q_rows, max_k_rows, cap_fwd, cap_dkv;
     int32_t q_heads, kv_heads, head_dim, asked, longest_seq, compute_units;
     int32_t *q_begin, *q_len, *kv_len, *cu_q, *cu_k, *shares_kv, *fwd_items, *dkv_items;
-    int32_t *units[SKRULL_UNIT_LISTS], *dkv_units;
+    int32_t *units[SKRULL_UNIT_LISTS];
+    int4 *dkv_units;
 };
 hipError_t launch_plan_small(const SmallPlan &job, hipStream_t st);
 hipError_t launch_plan_ranges(const int32_t *S, const int32_t *N, const int32_t *r,

@@ -564,7 +564,8 @@ struct UnitsJob {
     const int4 *fwd_items, *dkv_items;
     const int32_t *q_begin, *q_len, *kv_len, *shares_kv;
     int32_t BM, q_heads, kv_heads, head_dim, asked, longest_seq, compute_units;
-    int32_t *units[SKRULL_UNIT_LISTS], *dkv_units;  // null: no list
+    int32_t *units[SKRULL_UNIT_LISTS];  // null: no list
+    int4 *dkv_units;
 };
 __global__ __launch_bounds__(256) void plan_units_kernel(UnitsJob j, PlanTotals *totals)
 {
@@ -581,8 +582,8 @@ __global__ __launch_bounds__(256) void plan_units_kernel(UnitsJob j, PlanTotals 
     const int32_t n = dkv ? (int32_t)min((long long)totals->n_dkv, (long long)totals->cap_dkv)
                           : (int32_t)min((long long)totals->n_fwd, (long long)totals->cap_fwd);
     const int32_t NW = 4 * blockIdx.y;  // forward / dQ: waves of a workgroup
-    int32_t *units = dkv ? j.dkv_units : j.units[max((int)blockIdx.y - 1, 0)];
-    if (!units || first >= n) return;  // (the whole block)
+    int32_t *units = dkv ? nullptr : j.units[blockIdx.y - 1];
+    if ((dkv ? !j.dkv_units : !units) || first >= n) return;  // (the whole block)
     __syncthreads();
     const SplitChoice choice = shared_choice;
     const int32_t BN = totals->block_n;
@@ -622,8 +623,12 @@ __global__ __launch_bounds__(256) void plan_units_kernel(UnitsJob j, PlanTotals 
     sum += __shfl_xor(sum, 1, 64);
     sum += __shfl_xor(sum, 2, 64);
     if (dkv && (int64_t)sum * j.kv_heads * (BN == 256 ? 2 : 1) <= j.compute_units) rank = before;
-    if (a < n)
+    if (a < n && dkv) {
+        const int4 it = j.dkv_items[a];
+        for (int32_t p = quarter; p < my_parts; p += 4) j.dkv_units[rank + p] = make_int4(it.x, it.y, a | p << SKRULL_UNIT_SHIFT, my_parts);
+    } else if (a < n) {
         for (int32_t p = quarter; p < my_parts; p += 4) units[rank + p] = a | p << SKRULL_UNIT_SHIFT;
+    }
     if (NW == 12 && first == 0) {
         int64_t load = 0;
         int32_t longest = 0;
@@ -900,7 +905,7 @@ __global__ __launch_bounds__(kSmallThreads) void plan_small_kernel(SmallPlan j)
     if (t < n_dkv && j.dkv_units) {
         int32_t c, n;
         uc.dkv(dkv[t], t, c, n);
-        for (int32_t p = 0; p < n; ++p) j.dkv_units[at[0][rd] + p] = t | p << SKRULL_UNIT_SHIFT;
+        for (int32_t p = 0; p < n; ++p) j.dkv_units[at[0][rd] + p] = make_int4(dkv[t].x, dkv[t].y, t | p << SKRULL_UNIT_SHIFT, n);
     }
     if (t < n_fwd)
         for (int i = 0; i < SKRULL_UNIT_LISTS; ++i) {
@@ -1114,7 +1119,7 @@ int64_t plan_dkv_unit_ints(const skrull_attn_plan_t *p, int32_t asked, int32_t c
 {
     const int32_t group = p->Hq / p->Hkv, parts = asked ? asked : (group > kMaxParts ? group : kMaxParts);
     if (cap_dkv > kRankSortMax || p->Hq > SKRULL_UNIT_HEADS) return 0;
-    return (int64_t)cap_dkv * parts;
+    return 4 * (int64_t)cap_dkv * parts;
 }
 
 hipError_t launch_plan_units(const skrull_attn_plan_t *p, int32_t asked, int32_t longest_seq, int32_t cap_fwd, int32_t cap_dkv,
