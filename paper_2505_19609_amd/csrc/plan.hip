@@ -521,7 +521,13 @@ __device__ inline int32_t parts_of_item(const SplitChoice &c, int32_t item, int3
 //    by their own rounds 368, by the items' costs 371; 26,624 tokens above 134, 137, 146).  `small` is an eighth of an
 //    even share per compute unit, or a quarter at head_dim 128 where no item is shared, and 64 at most (128 is the same): these blocks
 //    are what fills the end of a launch, and 1,187 rounds, a quarter of the share of 24,576 + 8,192 tokens at
-//    32/8 heads of 128, brought them out before it (8,660 us, 8,540 this way, 8,522 by the items' costs);
+//    32/8 heads of 128, brought them out before it (8,660 us, 8,540 this way, 8,522 by the items' costs).  Where the KV
+//    heads are a multiple of the eight dies, neighbours in the list with the same head are on the same die, and `small` is half
+//    a share if no block takes longer than that, or than 24 rounds (8/8 heads of 128: 32 sequences of 256 34 us, 38 by their own rounds; 33 of 511
+//    71 and 79; 16/16 heads of 64: 16 of 512 46 and 48).  With half a share elsewhere launches end worse: neighbours are on
+//    different dies (28/4 heads of 128: 63 of 130 68 us, 92 that way; 14/2 heads of 64: 128 of 256 75 and 88), or the short
+//    blocks are what is left to fill the end (5,866 and 1,546 tokens, 16/16 heads of 64: 175 and 190; a cut of 18,174 over 8
+//    ranks beside 1,024 and 463 201 and 210);
 //  any order but the list's where all units run at once (4,923 tokens, 28/4 heads of 128: 111 us, else 114).
 struct UnitCosts {
     const int32_t *q_begin, *q_len, *kv_len, *shares_kv;
@@ -554,11 +560,13 @@ struct UnitCosts {
         parts = (((rows + 31) >> 5) * group + waves - 1) / waves;
     }
 };
-__device__ inline int32_t small_block(const PlanTotals &totals, const SplitChoice &choice, int32_t q_heads, int32_t head_dim, int32_t compute_units)
+__device__ inline int32_t small_block(const PlanTotals &totals, const SplitChoice &choice, int32_t q_heads, int32_t kv_heads, int32_t head_dim,
+                                      int32_t compute_units)
 {
-    const int32_t fine = head_dim == 64 || choice.parts > 1 ? 2 : 1;
     // (a cost counts for four rounds)
-    return (int32_t)min(totals.dkv_cost_sum * q_heads / (fine * (unsigned long long)compute_units), 64ull);
+    const unsigned long long half = 2 * totals.dkv_cost_sum * q_heads / (unsigned long long)compute_units;
+    const bool all_short = kv_heads % 8 == 0 && 4ull * totals.dkv_cost_max * (q_heads / kv_heads) <= min(half, 24ull);
+    return (int32_t)min(all_short ? half : half / (head_dim == 64 || choice.parts > 1 ? 4 : 2), 64ull);
 }
 struct UnitsJob {
     const int4 *fwd_items, *dkv_items;
@@ -588,7 +596,7 @@ __global__ __launch_bounds__(256) void plan_units_kernel(UnitsJob j, PlanTotals 
     const SplitChoice choice = shared_choice;
     const int32_t BN = totals->block_n;
     const UnitCosts uc{j.q_begin, j.q_len, j.kv_len, j.shares_kv, j.BM, BN, group, j.head_dim, choice,
-                       dkv ? small_block(*totals, choice, j.q_heads, j.head_dim, j.compute_units) : 0};
+                       dkv ? small_block(*totals, choice, j.q_heads, j.kv_heads, j.head_dim, j.compute_units) : 0};
     auto unit_of = [&](int32_t i, int32_t &cost, int32_t &parts) {
         if (dkv) uc.dkv(j.dkv_items[i], i, cost, parts);
         else uc.fwd(j.fwd_items[i], NW, cost, parts);
@@ -867,7 +875,7 @@ __global__ __launch_bounds__(kSmallThreads) void plan_small_kernel(SmallPlan j)
     if (t == 0) tot.split = choose_split(j.asked, tot, j.q_heads, j.kv_heads, j.head_dim, j.longest_seq, j.compute_units);
     __syncthreads();
     const UnitCosts uc{q_begin, q_len, kv_len, shares, j.BM, BN, group, j.head_dim, tot.split,
-                       small_block(tot, tot.split, j.q_heads, j.head_dim, j.compute_units)};
+                       small_block(tot, tot.split, j.q_heads, j.kv_heads, j.head_dim, j.compute_units)};
     int32_t parts[4] = {0, 0, 0, 0}, cf = -1, cd = -1;  // dK/dV, then 4, 8 and 12 waves
     if (t < n_dkv) uc.dkv(dkv[t], t, cd, parts[0]);
     if (t < n_fwd)
