@@ -31,8 +31,9 @@ REC = np.dtype([("t0", "<u8"), ("t1", "<u8"), ("hw_id", "<u4"), ("xcc_id", "<u4"
 TICK_US = 0.01   # s_memrealtime runs at 100 MHz
 
 
-def analyse(rec):
-    """rec: structured records of one launch (written ones only)."""
+def analyse(rec, slots_per_cu=None):
+    """rec: structured records of one launch (written ones only); slots_per_cu: workgroups that a compute unit holds at
+    once, by default as many as were seen on one."""
     t0 = rec["t0"].astype(np.int64)
     t1 = rec["t1"].astype(np.int64)
     start, end = t0.min(), t1.max()
@@ -60,6 +61,7 @@ def analyse(rec):
         last_end.append(t1[sel].max())
     covered, last_end = np.array(covered, float), np.array(last_end, float)
     first_dry = last_end.min()
+    places = slots_per_cu or places
     tail_lost = float((end - last_end).sum()) / (len(units) * span)
     dur = (t1 - t0).astype(float)
     # greedy list scheduling of the same durations in grid order over the same number of slots

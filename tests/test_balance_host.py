@@ -19,3 +19,4 @@ def test_places_of_a_unit_are_those_that_were_taken(per_unit):
     assert r["places_per_unit"] == per_unit
     assert r["span_over_greedy"] == 1.0 and r["busy"] == 1.0 and r["sum_wg_time_over_units_x_span"] == 1.0
     assert r["ideal_span_us"] == r["span_us"] == 8.0
+    assert balance.analyse(np.array(rows, dtype=balance.REC), per_unit) == r
