@@ -5,7 +5,8 @@ choice forced, next to the choice the plan makes by itself.
     python -m paper_2505_19609_amd.shape_sweep dkv    # dK/dV items of 128 or 192 key rows (head_dim 64), head split
 
 One line per (head shape, length mix): kernel times in ms (median of HIP events over the
-repetitions) for every forced choice, and what `skrull_attn_plan` picks when the field is left 0.
+repetitions) for every forced choice, and what `skrull_attn_plan` picks when the field is left 0, with
+its times: at head_dim 64 the workgroups it then runs need not be those of either forced choice.
 """
 from __future__ import annotations
 
@@ -29,8 +30,13 @@ def _mixes():
     return {"config2": list(W.config(2).seq_len), "config2x2": list(W.config(2).seq_len) * 2, "lognormal40": logn, **MIXES}
 
 
+def _runs(info):
+    """The workgroups a plan runs, in wavefronts."""
+    return f"{info.wg_query_rows}, wavefronts {info.fwd_waves} and {info.dq_waves}{' pipelined' if info.dq_pipelined else ''}"
+
+
 def _time(S, heads, d, reps, **plan_args):
-    """(fwd, dq, dkv) ms and the plan's info for one forced choice."""
+    """(fwd, dq, dkv) ms and the plan's choices for one forced choice."""
     import torch
     from . import binding as B
     hq, hkv = heads
@@ -57,7 +63,7 @@ def _time(S, heads, d, reps, **plan_args):
     B.skrull_attn_profile(False)
     m = np.median(ms, axis=0)
     info = plan.info
-    picked = (int(info.wg_query_rows), int(info.block_n), int(info.head_split))
+    picked = (_runs(info), int(info.block_n), int(info.head_split))
     plan.destroy()
     return (m[0], m[3], m[2]), picked
 
@@ -77,14 +83,14 @@ def main(argv=None):
         shapes = [((8, 2), 128), ((16, 4), 128), ((28, 4), 128), ((32, 8), 128), ((64, 8), 128),
                   ((8, 8), 64), ((14, 2), 64), ((16, 16), 64), ((32, 8), 64), ((64, 8), 64)]
         names = ["config2", "128x256", "32x1024", "16x2048", "8x4096", "4x8192", "2x16384", "1x32768", "6000+26x1024", "ragged"]
-        print("heads/head_dim mix: forward ms with 128 / 256 query rows per workgroup (128 against 256), dQ likewise; plan picks")
+        print("heads/head_dim mix: forward ms with 128 / 256 query rows per workgroup (128 against 256), dQ likewise; what the plan picks, and its forward and dQ")
         for heads, d in shapes:
             for n in names:
                 (f1, q1, _), _ = _time(mixes[n], heads, d, args.reps, wg_query_rows=128)
                 (f2, q2, _), _ = _time(mixes[n], heads, d, args.reps, wg_query_rows=256)
-                _, picked = _time(mixes[n], heads, d, 1)
+                (f, q, _), picked = _time(mixes[n], heads, d, args.reps)
                 print(f"{heads[0]}/{heads[1]}/{d} {n}: fwd {f1:.3f} / {f2:.3f} ({100 * (f1 / f2 - 1):+.1f} %)  "
-                      f"dQ {q1:.3f} / {q2:.3f} ({100 * (q1 / q2 - 1):+.1f} %)  plan picks {picked[0]}", flush=True)
+                      f"dQ {q1:.3f} / {q2:.3f} ({100 * (q1 / q2 - 1):+.1f} %)  plan picks {picked[0]}: {f:.3f}, {q:.3f}", flush=True)
     else:
         shapes = [((14, 2), 64), ((32, 4), 64), ((32, 8), 64), ((16, 16), 64), ((64, 8), 64),
                   ((16, 1), 128), ((32, 2), 128), ((28, 4), 128), ((32, 8), 128)]

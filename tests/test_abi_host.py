@@ -40,6 +40,13 @@ def test_shapes_word_of_the_plan_info(B):
     assert not B.PlanInfo(shapes=8 | 4 << 8).dq_pipelined
 
 
+def test_shape_sweep_names_the_workgroups_that_run(B):
+    """256 rows asked for run as 8 wavefronts, 256 chosen may run as 12 or 4: the sweep tells them apart."""
+    from paper_2505_19609_amd import shape_sweep
+    assert len({shape_sweep._runs(B.PlanInfo(wg_query_rows=256, shapes=x | x << 8 | p << 16))
+                for x, p in ((4, 0), (4, 1), (8, 1), (12, 0))}) == 4
+
+
 def test_strerror(B):
     assert B.skrull_attn_strerror(0) == "ok"
     assert "invalid" in B.skrull_attn_strerror(B.SKRULL_EINVAL)
