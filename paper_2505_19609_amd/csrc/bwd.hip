@@ -32,7 +32,8 @@ namespace {
 constexpr float kLog2e = 1.4426950408889634f;
 
 // How a dK/dV work index stands for an item, a part of its chain, a KV head and a pass over the item's
-// key rows; quotients as in RowMap.  Handed out first are `n_whole_first` items that one workgroup does
+// key rows; quotients as in RowMap.  With a list of units these go out in its order.  Without one (lists too
+// long for the rank sort, very many heads) handed out first are `n_whole_first` items that one workgroup does
 // whole, then the parts of the first `n_split` items of the list, then the rest: the units of all
 // three run from long to short, and the whole items of the middle are as long as the longest parts.
 struct KeyMap {
@@ -72,7 +73,7 @@ struct BwdParams {
 // ---------------------------------------------------------------------------
 // dQ
 // ---------------------------------------------------------------------------
-// The dQ kernel comes in three shapes, like the forward.  Large: 8 wavefronts (256 query rows), two per SIMD, with a
+// The dQ kernel comes in three shapes, like the forward, and the small one in two kinds.  Large: 8 wavefronts (256 query rows), two per SIMD, with a
 // five-slot K ring and a four-slot V ring, and a software pipeline from one half tile of keys to the next,
 // which takes 191 registers at head_dim 64 and 254 at 128.  At head_dim 64 also two that do one half tile
 // after another: with nothing kept from one to the next 168 registers do, so that three wavefronts per SIMD overlap
@@ -80,7 +81,8 @@ struct BwdParams {
 // wavefronts, rings of two slots, a barrier per tile.  A wavefront alone on its SIMD is slower this way and
 // eight are as fast (23,053 tokens, 16/16 heads: backward 785 us pipelined, 792 with 8 of 12 at work), so the
 // large shape stays where a long unit is what a launch waits for and where 12 cannot be filled, and the small one is
-// pipelined too (three K slots, two workgroups per unit) where long units would leave the third place of a unit empty.
+// pipelined too (three K slots, two workgroups per unit) where long units would leave the third place of a unit empty
+// (the plan decides by their length and number).
 // 26,624 tokens in 64 sequences, 14/2 heads: dQ 94 us large, 86 wide; 32,768 of 16 to 1,024: 88 and 75; slices of
 // three long sequences, 1.5e9 triples and more: forward and backward 6,240 with small workgroups that were pipelined (two
 // per unit), 6,200 this way (three).

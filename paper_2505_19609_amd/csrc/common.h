@@ -29,7 +29,7 @@ struct skrull_attn_plan {
     bool dq_piped;                // dQ of 4: pipelined, two workgroups per compute unit
     // dK/dV items that several workgroups share (the first n_split of the sorted list), and how:
     // an item of cost c takes min(split_parts, ceil(c * heads per group / split_chain)) of them
-    // (split_chain 0: split_parts).  n_whole_first more items are handed out before those.
+    // (split_chain 0: split_parts).  Where there is no list of units, n_whole_first more items are handed out before those.
     int32_t n_split, n_whole_first, split_parts, split_chain;
     int32_t split_compact;  // 1: partial sums hold the rows of split items only; 0: every row of K
     int device;
@@ -38,7 +38,7 @@ struct skrull_attn_plan {
     int32_t *cu_q, *cu_k, *q_begin, *q_len, *kv_len, *shares_kv;  // per segment: [NS+1] x2, [NS] x4
     int32_t *fwd_items, *dkv_items;                   // [n][4], sorted
     // work units of the forward / dQ list for workgroups of 4, 8 and 12 wavefronts (see RowMap): item |
-    // part << SKRULL_UNIT_SHIFT, in list order; null for lists too long
+    // part << SKRULL_UNIT_SHIFT, longest first (UnitCosts in plan.hip); null for lists too long
     // for the rank sort and for very many heads
     int32_t *units[SKRULL_UNIT_LISTS], n_units[SKRULL_UNIT_LISTS];
     // The same of the dK/dV list, or null: {segment, key block, item | part << SKRULL_UNIT_SHIFT, parts of the item}.
