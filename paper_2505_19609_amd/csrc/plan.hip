@@ -528,12 +528,19 @@ __device__ inline int32_t parts_of_item(const SplitChoice &c, int32_t item, int3
 //    different dies (28/4 heads of 128: 63 of 130 68 us, 92 that way; 14/2 heads of 64: 128 of 256 75 and 88), or the short
 //    blocks are what is left to fill the end (5,866 and 1,546 tokens, 16/16 heads of 64: 175 and 190; a cut of 18,174 over 8
 //    ranks beside 1,024 and 463 201 and 210);
+//  at head_dim 128 with KV heads a multiple of the dies and no shared items, neighbouring key blocks of one length in blocks of
+//    256 rows apart from each other, where a launch has 3.5 workgroups and more per compute unit: those go out by the
+//    items' costs, and short sequences together up to 32 rounds.  (Of 252 micro-batches of six such head shapes 204 have so many: against the items'
+//    costs with nothing kept together their own rounds take from 7 % less to 7 % more time, this way from 7 % less to 2 % more; 2,500 and 30 of
+//    700 tokens, 32/8 heads: 410, 439, 402 us; 32 of 1,024, 64/8 heads: 1,203, 1,255, 1,192.  The other 48 take 4 % less on average by their
+//    own rounds; 16 of 512, 32/8 heads: 101 us by the items' costs, 91 by those);
 //  any order but the list's where all units run at once (4,923 tokens, 28/4 heads of 128: 111 us, else 114).
 struct UnitCosts {
     const int32_t *q_begin, *q_len, *kv_len, *shares_kv;
     int32_t BM, BN, group, head_dim;
     SplitChoice choice;
     int32_t small;
+    bool by_items;
     // query tiles of a segment that see key kv0 or later ones
     __device__ int32_t tiles(int32_t seq, int32_t kv0) const
     {
@@ -550,6 +557,7 @@ struct UnitCosts {
         }
         parts = parts_of_item(choice, i, it.w, group);
         whole = min(whole, 1 << 20) * group;
+        if (by_items) c = it.w * (BM >> 6);
         cost = whole <= small ? whole : (min(c, 1 << 20) * group + parts - 1) / parts;
     }
     // item of the forward / dQ list for workgroups of `waves` waves
@@ -560,13 +568,19 @@ struct UnitCosts {
         parts = (((rows + 31) >> 5) * group + waves - 1) / waves;
     }
 };
+__device__ inline bool by_item_costs(const PlanTotals &totals, const SplitChoice &choice, int32_t kv_heads, int32_t head_dim, int32_t compute_units)
+{
+    const int64_t workgroups = (int64_t)totals.n_dkv * ((totals.block_n + 127) / 128) * kv_heads;
+    return head_dim == 128 && kv_heads % 8 == 0 && choice.parts == 1 && 2 * workgroups >= 7 * (int64_t)compute_units;
+}
 __device__ inline int32_t small_block(const PlanTotals &totals, const SplitChoice &choice, int32_t q_heads, int32_t kv_heads, int32_t head_dim,
                                       int32_t compute_units)
 {
     // (a cost counts for four rounds)
     const unsigned long long half = 2 * totals.dkv_cost_sum * q_heads / (unsigned long long)compute_units;
     const bool all_short = kv_heads % 8 == 0 && 4ull * totals.dkv_cost_max * (q_heads / kv_heads) <= min(half, 24ull);
-    return (int32_t)min(all_short ? half : half / (head_dim == 64 || choice.parts > 1 ? 4 : 2), 64ull);
+    if (all_short) return (int32_t)min(half, 64ull);
+    return (int32_t)min(half / (head_dim == 64 || choice.parts > 1 ? 4 : 2), by_item_costs(totals, choice, kv_heads, head_dim, compute_units) ? 32ull : 64ull);
 }
 struct UnitsJob {
     const int4 *fwd_items, *dkv_items;
@@ -596,7 +610,8 @@ __global__ __launch_bounds__(256) void plan_units_kernel(UnitsJob j, PlanTotals 
     const SplitChoice choice = shared_choice;
     const int32_t BN = totals->block_n;
     const UnitCosts uc{j.q_begin, j.q_len, j.kv_len, j.shares_kv, j.BM, BN, group, j.head_dim, choice,
-                       dkv ? small_block(*totals, choice, j.q_heads, j.kv_heads, j.head_dim, j.compute_units) : 0};
+                       dkv ? small_block(*totals, choice, j.q_heads, j.kv_heads, j.head_dim, j.compute_units) : 0,
+                       dkv && by_item_costs(*totals, choice, j.kv_heads, j.head_dim, j.compute_units)};
     auto unit_of = [&](int32_t i, int32_t &cost, int32_t &parts) {
         if (dkv) uc.dkv(j.dkv_items[i], i, cost, parts);
         else uc.fwd(j.fwd_items[i], NW, cost, parts);
@@ -875,7 +890,8 @@ __global__ __launch_bounds__(kSmallThreads) void plan_small_kernel(SmallPlan j)
     if (t == 0) tot.split = choose_split(j.asked, tot, j.q_heads, j.kv_heads, j.head_dim, j.longest_seq, j.compute_units);
     __syncthreads();
     const UnitCosts uc{q_begin, q_len, kv_len, shares, j.BM, BN, group, j.head_dim, tot.split,
-                       small_block(tot, tot.split, j.q_heads, j.kv_heads, j.head_dim, j.compute_units)};
+                       small_block(tot, tot.split, j.q_heads, j.kv_heads, j.head_dim, j.compute_units),
+                       by_item_costs(tot, tot.split, j.kv_heads, j.head_dim, j.compute_units)};
     int32_t parts[4] = {0, 0, 0, 0}, cf = -1, cd = -1;  // dK/dV, then 4, 8 and 12 waves
     if (t < n_dkv) uc.dkv(dkv[t], t, cd, parts[0]);
     if (t < n_fwd)

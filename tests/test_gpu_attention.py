@@ -918,6 +918,24 @@ def test_units_of_lists_of_several_lengths(oracle, wg, rep):
     one["plan"].destroy()
 
 
+@pytest.mark.parametrize("bm,bn", [(0, 0), (64, 64), (128, 256)])
+@pytest.mark.parametrize("rep", [9, 40])
+def test_units_in_the_order_of_the_items(oracle, rep, bm, bn):
+    """With 8 KV heads of 128 and no shared items dK/dV goes out in the order of the items' costs but for short
+    sequences, in a plan by one workgroup and by several kernels: the sequences of a checked small micro-batch, a slice and
+    a cut among them, repeated, give the same bits."""
+    S, N, R, Z, heads, d = [300, 1, 64, 513, 129, 700, 610], [1] * 5 + [3, 2], [0] * 5 + [1, 1], [0] * 6 + [1], (16, 8), 128
+    w = W.Workload("items", S, N, R, heads[0], heads[1], d, d ** -0.5, 406, shard_cut=Z)
+    one = _exhaustive(oracle, w, block_m=bm, block_n=bn, rtol=2.0 ** -8, head_split=1, keep=True)
+    many = W.Workload(f"items_{rep}", S * rep, N * rep, R * rep, heads[0], heads[1], d, d ** -0.5, 406, shard_cut=Z * rep)
+    vals = {n: np.concatenate([a] * rep) for n, a in one["vals"].items()}
+    out = run_library(many, block_m=bm, block_n=bn, vals=vals, head_split=1)
+    for n in ("o", "dq", "dk", "dv"):
+        assert np.array_equal(out[n], np.concatenate([one[n]] * rep)), n
+    out["plan"].destroy()
+    one["plan"].destroy()
+
+
 SHARED = {  # lengths, degrees, indices, cuts, heads, head_dim, block_n, what the plan does
     "one head per group": ([2967], [1], [0], [0], (4, 4), 64, 0, "compact"),
     "short blocks": ([1100, 37, 700], [1] * 3, [0] * 3, [0] * 3, (3, 3), 128, 64, "compact"),
