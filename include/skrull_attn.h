@@ -157,7 +157,7 @@ enum {
  * per compute unit or 1.5e9 attended (query, key, head) triples; head_dim 128:
  * at least 16 such blocks and no sequence above 8,192 tokens), else 256.  At head_dim 64 a
  * choice of 256 (not a 256 that the caller gives) runs forward and dQ with workgroups of 12 wavefronts
- * for lists of many short units and of 4 for launches that run at once, and dQ workgroups of 4 are
+ * for lists of many short units and of 4 for most launches that run at once, and dQ workgroups of 4 are
  * pipelined or not by the length and number of their units (info.shapes).  None
  * of them changes a result beyond the
  * last bit of dK/dV (head_split and the sharing of items change the order of a sum).

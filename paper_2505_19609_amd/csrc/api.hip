@@ -380,14 +380,23 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
     //    many wavefronts share a unit, where most of the chip would stay idle beside them.  Measured on 40 micro-batches of 16
     //    to 6,000 tokens, 4 to 16 heads: forward up to 20 % less time (7 to 10 % in the middle, 2 % more at worst), backward 4
     //    to 7 % less; a third more than fits, and dQ lost 11 to 43 %.
+    //    Not where those of 8 all run at once too and either end with units of up to 128 rows, that is, of four wavefronts in any case (384
+    //    tokens, 4/4 heads: forward and dQ 26.7 us with 8, 30.5 with 4), and the next longest ones are enough shorter, or are many and
+    //    short, where starts count (64 of 200, 4/4 heads: 31.8 and 34.3).  677 launches of eight head shapes against 8 wavefronts: forward and dQ
+    //    together 0.929 of the time, 1.146 at worst, with 4 throughout; 0.927 and 1.033 this way.
     plan->fwd_waves = plan->wg_query_rows / 32;
     plan->dq_waves = plan->d == 64 ? plan->wg_query_rows / 32 : 8;
     if (p->wg_query_rows == 0 && plan->wg_query_rows == 256 && plan->d == 64) {
         if (plan->units[2] && group > 1 && 5 * 12 * (int64_t)plan->n_units[2] <= 6 * 8 * (int64_t)plan->n_units[1] &&
             10 * (int64_t)totals.fwd_longest * compute_units <= 9 * totals.fwd_load * plan->Hkv)
             plan->fwd_waves = plan->dq_waves = 12;
-        else if (2 * totals.n_fwd * plan->Hq <= 3 * (int64_t)compute_units)
-            plan->dq_waves = plan->fwd_waves = 4;
+        else if (2 * totals.n_fwd * plan->Hq <= 3 * (int64_t)compute_units) {
+            const int64_t of_eight = (int64_t)plan->n_units[1] * plan->Hkv;
+            const int32_t longest = totals.fwd_longest - 16, full = totals.fwd_longest_full - 16;
+            const bool once = plan->units[2] && of_eight <= compute_units, many = 2 * of_eight >= compute_units;
+            const bool ends_small = full > 0 && (4 * full <= 3 * longest || (many && 5 * full <= 4 * longest + 4));
+            if (!(once && (ends_small || (longest <= 8 && many)))) plan->dq_waves = plan->fwd_waves = 4;
+        }
     }
     // Of dQ workgroups of 4 three share a compute unit, each slower than one of the two that the pipelined kernel has
     // there.  Measured on 173 micro-batches, of 4 to 16 heads and 8 to 7,516 units, pipelined against not:

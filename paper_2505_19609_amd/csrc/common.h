@@ -69,9 +69,9 @@ struct PlanTotals {
     int32_t n_units[SKRULL_UNIT_LISTS];  // work units of the forward / dQ list for 4, 8 and 12 wavefronts
     int32_t n_dkv_units;
     // forward work in workgroups of 12 wavefronts, in half tiles of keys: of all units of a KV head, of the longest one
-    // (16 half tiles for a unit's start and end included)
+    // (16 half tiles for a unit's start and end included), of the longest one of more than 128 rows of a head (0: none)
     int64_t fwd_load;
-    int32_t fwd_longest;
+    int32_t fwd_longest, fwd_longest_full;
     SplitChoice split;         // how dK/dV items are shared (the units kernel's choice)
     int32_t cap_fwd, cap_dkv;  // room in the item arrays (the host's upper bounds)
     int32_t block_n;           // key rows per dK/dV item in effect (the ranges kernel's choice where open)

@@ -225,7 +225,7 @@ __global__ __launch_bounds__(kScanThreads) void plan_ranges_kernel(
         totals->dkv_cost_max = 0;
         for (int i = 0; i <= SKRULL_CHAIN_LIMITS; ++i) totals->chain_hist[i] = 0;
         for (int i = 0; i < SKRULL_UNIT_LISTS; ++i) totals->n_units[i] = 0;
-        totals->n_dkv_units = totals->fwd_longest = 0;
+        totals->n_dkv_units = totals->fwd_longest = totals->fwd_longest_full = 0;
         totals->fwd_load = 0;
         totals->cap_fwd = cap_fwd;
         totals->cap_dkv = cap_dkv;
@@ -567,6 +567,7 @@ struct UnitCosts {
         cost = head_dim == 64 ? (int32_t)(((uint32_t)(q_begin[it.x] + row0 + rows) + 31u) >> 5) : 0;
         parts = (((rows + 31) >> 5) * group + waves - 1) / waves;
     }
+    __device__ bool more_than_four_blocks(const int4 &it) const { return min(BM, q_len[it.x] - it.y * BM) > 128; }
 };
 __device__ inline bool by_item_costs(const PlanTotals &totals, const SplitChoice &choice, int32_t kv_heads, int32_t head_dim, int32_t compute_units)
 {
@@ -654,18 +655,21 @@ __global__ __launch_bounds__(256) void plan_units_kernel(UnitsJob j, PlanTotals 
     }
     if (NW == 12 && first == 0) {
         int64_t load = 0;
-        int32_t longest = 0;
+        int32_t longest = 0, longest_full = 0;
         for (int32_t i = threadIdx.x; i < n; i += blockDim.x) {
             int32_t cost, parts;
             unit_of(i, cost, parts);
             load += (int64_t)parts * (cost + 16);
             longest = max(longest, cost + 16);
+            if (uc.more_than_four_blocks(j.fwd_items[i])) longest_full = max(longest_full, cost + 16);
         }
         load = wave_sum(load);
         longest = wave_max(longest);
+        longest_full = wave_max(longest_full);
         if ((threadIdx.x & 63) == 0) {  // (zeroed by the ranges kernel)
             atomicAdd((unsigned long long *)&totals->fwd_load, (unsigned long long)load);
             atomicMax(&totals->fwd_longest, longest);
+            atomicMax(&totals->fwd_longest_full, longest_full);
         }
     }
     if (first == 0 && threadIdx.x == 0) *(dkv ? &totals->n_dkv_units : &totals->n_units[blockIdx.y - 1]) = sum;
@@ -901,9 +905,11 @@ __global__ __launch_bounds__(kSmallThreads) void plan_small_kernel(SmallPlan j)
     {
         const int64_t load = wave_sum(t < n_fwd ? (int64_t)parts[3] * (cf + 16) : 0);
         const int32_t longest = wave_max(t < n_fwd ? cf + 16 : 0);
+        const int32_t longest_full = wave_max(t < n_fwd && uc.more_than_four_blocks(fwd[t]) ? cf + 16 : 0);
         if ((t & 63) == 0) {
             atomicAdd(&load_s, (unsigned long long)load);
             atomicMax(&tot.fwd_longest, longest);
+            atomicMax(&tot.fwd_longest_full, longest_full);
         }
     }
     int32_t ex[4], sum[4];
@@ -942,7 +948,7 @@ __global__ __launch_bounds__(kSmallThreads) void plan_small_kernel(SmallPlan j)
         tot.n_dkv_units = j.dkv_units ? sum[0] : 0;
         for (int i = 0; i < SKRULL_UNIT_LISTS; ++i) tot.n_units[i] = j.units[i] ? sum[1 + i] : 0;
         tot.fwd_load = j.units[2] ? (int64_t)load_s : 0;
-        if (!j.units[2]) tot.fwd_longest = 0;
+        if (!j.units[2]) tot.fwd_longest = tot.fwd_longest_full = 0;
     }
     __syncthreads();
     for (int i = t; i < (int)(sizeof tot / 4); i += kSmallThreads) ((int32_t *)j.totals)[i] = ((const int32_t *)&tot)[i];

@@ -1100,6 +1100,17 @@ def test_shapes_of_head_dim_64_change_no_bit(heads, S, waves, piped):
     ref["plan"].destroy()
 
 
+@pytest.mark.parametrize("S,waves", [([384] * 20, 8), ([385] * 20, 4), ([640] * 20, 8), ([641] * 20, 4), ([640] * 5, 4), ([896] * 10, 4),
+                                     ([256] * 32, 8), ([256] * 31, 4), ([257] * 20, 8), ([128] * 64, 8), ([128] * 31, 4), ([200] * 65, 4)])
+def test_which_launches_that_run_at_once_keep_8_waves(S, waves):
+    """Both sides of the lines: launches that run at once have workgroups of 4 wavefronts, but of 8 where these run at once
+    as well and end with units of four row blocks, or are many and short."""
+    from paper_2505_19609_amd import binding as B
+    plan = B.skrull_attn_plan(S, [1] * len(S), [0] * len(S), 4, 4, 64, 0.125)
+    assert (plan.fwd_waves, plan.dq_waves) == (waves, waves)
+    plan.destroy()
+
+
 @pytest.mark.parametrize("rows", [0, 128])
 @pytest.mark.parametrize("heads,S,piped", [
     ((4, 4), [736], False), ((4, 4), [737], True),               # all at once two to a unit: from 24 half tiles on
