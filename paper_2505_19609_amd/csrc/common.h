@@ -5,12 +5,48 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <mutex>
+
 #include "skrull_attn.h"
 
 struct WorkQueue;
 // forward calls of one plan that may be in flight at once (each takes one queue slot in turn)
 #define SKRULL_FWD_QUEUE_SLOTS 64
 #define SKRULL_FWD_QUEUE_INTS 256  // of a slot: eight dies' queues, a 128-byte line each
+
+// Queues that need no kernel to clear them before a launch.  The calls of one stream run one after another, so a
+// plan keeps two sets for each stream it is used on: a launch works with one and clears the other, which the
+// launch before it has left, for the next.  (With a kernel before each that clears its queue, forwards of 26,624 tokens in 64 sequences, 14/2 heads of 64, come 64.0 us
+// apart, the last item of one and the first of the next 6.4; 63.0 and 4.7 without.)  A plan has them for its first
+// SKRULL_STREAM_STATES streams; calls on further streams, calls that are being captured (a replay has no
+// turn in that order) and calls on a handle that stands for a different stream in each thread clear a queue first.
+#define SKRULL_STREAM_STATES 4
+#define SKRULL_STREAM_STATE_INTS (2 * SKRULL_FWD_QUEUE_INTS)
+struct StreamStates {
+    std::mutex lock;  // held from the choice of a set until the launch that uses it is queued
+    int used = 0;
+    struct {
+        hipStream_t stream;
+        uint32_t fwd;  // forward launches so far
+    } of[SKRULL_STREAM_STATES] = {};
+
+    // The place of stream `st`, or -1.  With the lock held.
+    int find(hipStream_t st)
+    {
+        if (st == hipStreamPerThread) return -1;
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(st, &capture) != hipSuccess) {
+            (void)hipGetLastError();
+            return -1;
+        }
+        if (capture != hipStreamCaptureStatusNone) return -1;
+        for (int i = 0; i < used; ++i)
+            if (of[i].stream == st) return i;
+        if (used == SKRULL_STREAM_STATES) return -1;
+        of[used].stream = st;
+        return used++;
+    }
+};
 
 #define SKRULL_CHAIN_LIMITS 9
 #define SKRULL_UNIT_SHIFT 11  // rank-sorted lists have at most 2,048 items
@@ -46,8 +82,10 @@ struct skrull_attn_plan {
     // small launches takes 1.5 % more that way, of 40 micro-batches of long chains at head_dim 64 0.5 %.)
     int4 *dkv_units;
     int32_t n_dkv_units;
-    WorkQueue *fwd_queues;  // SKRULL_FWD_QUEUE_SLOTS times eight dies' queues, at the start of the pool: for forward launches
-    uint32_t fwd_calls;     // forward calls made so far (atomic): call i uses slot i mod SKRULL_FWD_QUEUE_SLOTS
+    WorkQueue *fwd_queues;  // SKRULL_FWD_QUEUE_SLOTS times eight dies' queues, at the start of the pool: for forward launches that clear one first
+    int32_t *stream_states; // SKRULL_STREAM_STATES times SKRULL_STREAM_STATE_INTS, zero when the plan is made (see StreamStates)
+    StreamStates *streams;
+    uint32_t fwd_calls;     // such calls made so far (atomic): call i uses slot i mod SKRULL_FWD_QUEUE_SLOTS
 };
 
 // Which dK/dV items several workgroups share, and how; see skrull_attn_plan.
@@ -145,6 +183,7 @@ struct SmallPlan {
     int32_t *q_begin, *q_len, *kv_len, *cu_q, *cu_k, *shares_kv, *fwd_items, *dkv_items;
     int32_t *units[SKRULL_UNIT_LISTS];
     int4 *dkv_units;
+    int4 *stream_states;  // cleared
 };
 hipError_t launch_plan_small(const SmallPlan &job, hipStream_t st);
 hipError_t launch_plan_ranges(const int32_t *S, const int32_t *N, const int32_t *r,

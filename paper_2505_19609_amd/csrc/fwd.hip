@@ -51,7 +51,8 @@ struct FwdParams {
     int32_t variant;  // 0: 4 wavefronts, 128 rows per workgroup; 1: 8 wavefronts, 256 rows; 2: 12 wavefronts
     float scale_log2;  // softmax_scale * log2(e)
     WgTrace *trace;    // null, or one record per work item (measurement aid)
-    WorkQueue *queue;  // work queue of the persistent launch, zeroed before use
+    WorkQueue *queue;  // work queue of the persistent launch, zero when it starts
+    WorkQueue *clear;  // null, or the one that the stream's next launch will use: zeroed by this one
     int32_t n_work, n_first;  // work items: what a plain grid would have as workgroups; workgroups launched
 };
 
@@ -488,6 +489,7 @@ template <int D, int NW, int NSLOT>
 __global__ __launch_bounds__(64 * NW, NW == NW_WIDE ? 3 : 2) void fwd_kernel(const FwdParams prm)
 {
     __shared__ int work_slot[2];
+    if (prm.clear && blockIdx.x == 0) clear_queues(prm.clear, kQueueStrideFwd);
     FwdFeed feed{prm.queue, prm.n_work, prm.n_first, 0, work_slot};
     const uint32_t marks = feed.begin();
     RowBlocks rb = uniform(row_blocks<NW>(kernarg<FwdParams>(), prm.items, (int)blockIdx.x));
@@ -510,7 +512,7 @@ __global__ __launch_bounds__(64 * NW, NW == NW_WIDE ? 3 : 2) void fwd_kernel(con
 template <auto Kernel>
 hipError_t launch_shape(FwdParams prm, int threads, hipStream_t st)
 {
-    if (prm.queue) {
+    if (prm.queue && !prm.clear) {
         queue_reset_kernel<<<1, 64, 0, st>>>(prm.queue, 1, kQueueStrideFwd);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -560,12 +562,27 @@ hipError_t launch_fwd(const skrull_attn_plan_t *p, const void *q, const void *k,
     prm.trace = trace;
     prm.variant = p->fwd_waves / 4 - 1;
     prm.n_work = rows.n_work;
-    // One of the plan's queue slots per call, taken in turn, so that forward calls of one plan
-    // that overlap on different streams do not share a queue.
+    prm.queue = prm.clear = nullptr;
     static_assert(8 * kQueueStrideFwd * sizeof(WorkQueue) == 4 * SKRULL_FWD_QUEUE_INTS, "a slot holds eight queues");
-    prm.queue = p->fwd_queues + 8 * kQueueStrideFwd * (__atomic_fetch_add(&const_cast<skrull_attn_plan_t *>(p)->fwd_calls, 1u, __ATOMIC_RELAXED) % SKRULL_FWD_QUEUE_SLOTS);
-    if (!rows.queued) prm.queue = nullptr;
-    if (p->d == 128) return launch_one<128>(prm, st);
-    if (p->d == 64) return launch_one<64>(prm, st);
-    return hipErrorInvalidValue;
+    constexpr int one = 8 * kQueueStrideFwd;
+    std::unique_lock<std::mutex> held(p->streams->lock, std::defer_lock);
+    uint32_t *turn = nullptr;
+    if (rows.queued) {
+        held.lock();
+        const int at = p->streams->find(st);
+        if (at >= 0) {
+            turn = &p->streams->of[at].fwd;
+            WorkQueue *sets = (WorkQueue *)(p->stream_states + at * SKRULL_STREAM_STATE_INTS);
+            prm.queue = sets + (*turn & 1) * one;
+            prm.clear = sets + (~*turn & 1) * one;
+        } else {
+            held.unlock();
+            // One of the plan's queue slots per call, taken in turn, so that forward calls of one plan
+            // that overlap on different streams do not share a queue.
+            prm.queue = p->fwd_queues + one * (__atomic_fetch_add(&const_cast<skrull_attn_plan_t *>(p)->fwd_calls, 1u, __ATOMIC_RELAXED) % SKRULL_FWD_QUEUE_SLOTS);
+        }
+    }
+    const hipError_t e = p->d == 128 ? launch_one<128>(prm, st) : p->d == 64 ? launch_one<64>(prm, st) : hipErrorInvalidValue;
+    if (e == hipSuccess && turn) ++*turn;
+    return e;
 }

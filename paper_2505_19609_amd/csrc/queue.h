@@ -221,7 +221,13 @@ template <int STRIDE, bool FIRST> struct WorkFeed {
     }
 };
 
-// Zeroes `n` launches' work queues (they must be zero when their kernel starts).
+// Zeroes a launch's queues; by the threads of one workgroup.
+__device__ __forceinline__ void clear_queues(WorkQueue *q, int stride)
+{
+    if (threadIdx.x < 8) ((int4 *)q)[threadIdx.x * stride] = make_int4(0, 0, 0, 0);
+}
+
+// Zeroes `n` launches' work queues (they must be zero when their kernel starts), for launches whose queues no launch before them has cleared.
 static __global__ void queue_reset_kernel(WorkQueue *q, int n, int stride)
 {
     int4 *w = (int4 *)q;

@@ -96,3 +96,49 @@ def test_forward_calls_of_one_plan_overlap_on_two_streams():
                 assert torch.equal(lse, ref_lse), rep
     torch.cuda.synchronize()
     plan.destroy()
+
+
+@pytest.mark.parametrize("heads,d,S", [((16, 4), 128, [9000, 700, 4000]), ((14, 2), 64, [700] * 30 + [64])])
+def test_calls_of_one_plan_on_many_streams_and_in_graphs_by_turns(heads, d, S):
+    """A launch clears the queues that its stream's next launch uses; calls on further streams than a plan has such
+    queues for, and captured ones, clear a queue first.  All by turns, on one plan, overlapping: every result is the
+    same bits."""
+    from paper_2505_19609_amd import binding as B
+    w = W.Workload("many_streams", S, [1] * len(S), [0] * len(S), heads[0], heads[1], d, d ** -0.5, 98)
+    plan = B.skrull_attn_plan(S, [1] * len(S), [0] * len(S), heads[0], heads[1], d, w.softmax_scale)
+    assert all(n > 256 for n in B.skrull_attn_trace_layout(plan)[1])  # persistent launches
+    dev = {n: to_dev(a) for n, a in W.make_values(w, plan.total_q, plan.total_k).items()}
+
+    def outputs():
+        return {"o": torch.empty_like(dev["q"]), "lse": torch.empty((heads[0], plan.total_q), dtype=torch.float32, device="cuda"),
+                "dq": torch.empty_like(dev["q"]), "dk": torch.empty_like(dev["k"]), "dv": torch.empty_like(dev["v"]),
+                "ws": torch.empty(int(plan.bwd_workspace_bytes), dtype=torch.uint8, device="cuda")}
+
+    def step(t):
+        B.skrull_attn_fwd(plan, dev["q"], dev["k"], dev["v"], t["o"], t["lse"])
+        B.skrull_attn_bwd(plan, dev["q"], dev["k"], dev["v"], t["o"], t["lse"], dev["do"], t["dq"], t["dk"], t["dv"], t["ws"])
+
+    ref = outputs()
+    step(ref)
+    streams = [torch.cuda.Stream() for _ in range(6)]   # (a plan has queues for four)
+    outs = [outputs() for _ in streams]
+    captured, graph = outputs(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=streams[0]):
+        step(captured)
+    for rep in range(6):
+        for t in outs + [captured]:
+            for x in t.values():
+                x.view(torch.uint8).fill_(0xFF if rep % 2 else 0)
+        torch.cuda.synchronize()
+        for k in range(2):
+            for i, (st, t) in enumerate(zip(streams, outs)):
+                with torch.cuda.stream(st):
+                    step(t)
+                    if k == 0 and i == rep:
+                        graph.replay()
+        torch.cuda.synchronize()
+        for t in outs + [captured]:
+            for n in ("o", "lse", "dq", "dk", "dv"):
+                assert torch.equal(t[n].view(torch.uint8), ref[n].view(torch.uint8)), (rep, n)
+    plan.destroy()
