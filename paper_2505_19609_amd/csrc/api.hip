@@ -246,7 +246,7 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
     const int64_t radix_ints = plan_radix_ints((int32_t)cap_fwd, (int32_t)cap_dkv, cost_bound);
     const int64_t tmp_ints = 4 * kin + 2 * kpad + totals_ints + 4 * (cap_fwd + cap_dkv) + radix_ints;
     const int64_t desc_ints = 6 * kpad;
-    const int64_t queue_ints = SKRULL_FWD_QUEUE_INTS * SKRULL_FWD_QUEUE_SLOTS;  // work queues of the forward launches
+    const int64_t queue_ints = SKRULL_QUEUE_INTS * SKRULL_FWD_QUEUE_SLOTS;  // work queues of the forward launches
     const int64_t state_ints = SKRULL_STREAM_STATES * SKRULL_STREAM_STATE_INTS;
     int32_t *fwd_off = nullptr, *dkv_off = nullptr, *scratch = nullptr;
     PlanTotals *totals_d = nullptr;

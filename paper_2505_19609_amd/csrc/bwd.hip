@@ -66,8 +66,11 @@ struct BwdParams {
     int32_t total_k;
     float *dk_part, *dv_part;
     WgTrace *trace_dq, *trace_dkv;  // null, or one record per work item (measurement aid)
-    WorkQueue *queue_dq, *queue_dkv;  // work queues of the persistent launches (workspace), zeroed before use
+    WorkQueue *queue_dq, *queue_dkv;  // work queues of the persistent launches, zero when they start
+    int32_t queue_stride;             // their dies' distance
     int32_t n_work_dq, n_work_dkv;    // work items: what a plain grid would have as workgroups
+    int32_t *clear;                   // null, or what the stream's next call will use: zeroed by this one
+    int32_t *rows_ready;              // one launch for both: dQ work items whose -D and LSE dK/dV may read
 };
 
 // ---------------------------------------------------------------------------
@@ -126,16 +129,46 @@ __device__ __forceinline__ uint32_t ds_mul_pack(float t0, float t1, float g0, fl
 // B(j).  B(j) reads the transposed K of the half tile BEFORE the one A(j+1) reads,
 // which is why the K ring has one slot more than the V ring.  Steps at the start, the
 // end and the causal diagonal of a wave's range take a plain path with guards.
-using BwdFeed = WorkFeed<kQueueStrideBwd, false>;
+// Where the work of dQ (KV: of dK/dV) comes from, read anew each time: kept through the work loops, as the compiler
+// would where both are in one kernel, these few values cost it scalar registers (45 spilled instead of 14).
+template <bool KV> struct BwdSource {
+    __device__ __forceinline__ WorkQueue *queue() const { return KV ? kernarg<BwdParams>()->queue_dkv : kernarg<BwdParams>()->queue_dq; }
+    __device__ __forceinline__ int stride() const { return kernarg<BwdParams>()->queue_stride; }
+    __device__ __forceinline__ int items() const { return KV ? kernarg<BwdParams>()->n_work_dkv : kernarg<BwdParams>()->n_work_dq; }
+};
+using DqFeed = WorkFeed<false, BwdSource<false>>;
+using DkvFeed = WorkFeed<false, BwdSource<true>>;
+
+// LDS of a dQ workgroup
+template <int D, int NWQ, bool PIPED>
+struct DqLds {
+    static constexpr bool SMALL = NWQ == NWQ_SMALL, WIDE = NWQ == NWQ_WIDE;
+    static constexpr int KSL = SMALL ? (PIPED ? 3 : 2) : (WIDE ? 4 : 5), VSL = SMALL ? 2 : 4;  // ring slots
+    static constexpr int MORE = (KSL + VSL) * TileGeom<D>::BYTES;                              // what the staging of a wide workgroup takes beside the rings
+    static constexpr int BYTES = MORE + (WIDE ? 4 * WaveStage<D>::BYTES : 0);
+};
+
+// A word that other workgroups of the launch read.
+template <typename T> __device__ __forceinline__ void store_shared(T *p, T x)
+{
+    __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void count_one(int32_t *counter)
+{
+    (void)__hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 
 // Does work item `bid`, whose rows are `rb`; returns the next one and leaves its rows in `rb`.
-template <int D, int NWQ, bool PIPED>
-__device__ __forceinline__ int dq_work(const int bid, RowBlocks &rb, BwdFeed &feed)
+// ONE: dK/dV follows in the same launch, so -D and LSE are stored when they are known, and the item is counted
+// as ready once they are in memory.
+template <int D, int NWQ, bool PIPED, bool ONE>
+__device__ __forceinline__ int dq_work(const int bid, RowBlocks &rb, DqFeed &feed, unsigned char *lds)
 {
     const kernarg_t<BwdParams> prm = kernarg<BwdParams>();
     // not PIPED: three wavefronts per SIMD, one half tile after another; PIPED: two
-    constexpr bool SMALL = NWQ == NWQ_SMALL, WIDE = NWQ == NWQ_WIDE;
-    constexpr int KSL = SMALL ? (PIPED ? 3 : 2) : (WIDE ? 4 : 5), VSL = SMALL ? 2 : 4;  // ring slots
+    typedef DqLds<D, NWQ, PIPED> Lds;
+    constexpr bool SMALL = Lds::SMALL, WIDE = Lds::WIDE;
+    constexpr int KSL = Lds::KSL, VSL = Lds::VSL;
     static_assert(PIPED ? !WIDE : (KSL & (KSL - 1)) == 0, "K tile t in slot t mod KSL");
     constexpr int KS = D / 16, TT = D / 32, KT = TILE_ROWS;
     typedef TileGeom<D> G;
@@ -144,8 +177,7 @@ __device__ __forceinline__ int dq_work(const int bid, RowBlocks &rb, BwdFeed &fe
     typedef RingLoader<D, NWQ> Loader;
     static_assert(KS == 2 * TT, "B(j) has half as many MFMAs as A(j+1)");
 
-    __shared__ __align__(16) unsigned char lds_k[KSL][TB];
-    __shared__ __align__(16) unsigned char lds_v[VSL][TB];
+    unsigned char (*lds_k)[TB] = (unsigned char (*)[TB])lds, (*lds_v)[TB] = lds_k + KSL;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform, lives in an SGPR
@@ -213,11 +245,10 @@ __device__ __forceinline__ int dq_work(const int bid, RowBlocks &rb, BwdFeed &fe
     // little more; small shape: K slot 1 and V slot 1, or K slots 1-2 of three)
     typedef WaveStage<D> Stage;
     static_assert(2 * Stage::BYTES == TB, "two staging regions per ring slot");
-    __shared__ __align__(16) unsigned char lds_more[WIDE ? 4 * Stage::BYTES : 16];
     const uint32_t stage = SMALL ? (PIPED || wave < 2 ? ring_k + TB + (uint32_t)wave * Stage::BYTES : ring_v + TB + (uint32_t)(wave - 2) * Stage::BYTES)
                          : WIDE  ? (wave < 4   ? ring_k + 2 * TB + (uint32_t)wave * Stage::BYTES
                                     : wave < 8 ? ring_v + 2 * TB + (uint32_t)(wave - 4) * Stage::BYTES
-                                               : lds_addr(lds_more) + (uint32_t)(wave - 8) * Stage::BYTES)
+                                               : lds_addr(lds + Lds::MORE) + (uint32_t)(wave - 8) * Stage::BYTES)
                                  : (wave < 6 ? ring_k + 2 * TB + (uint32_t)wave * Stage::BYTES
                                              : ring_v + 2 * TB + (uint32_t)(wave - 6) * Stage::BYTES);
 
@@ -259,12 +290,30 @@ __device__ __forceinline__ int dq_work(const int bid, RowBlocks &rb, BwdFeed &fe
         }
         nd = -add_other_half(dsum);
     }
+    // ONE: -D and LSE go out now.  The wait for the stores costs an item's start a microsecond, so only the last items,
+    // for which others may already be waiting, count themselves here; the others do behind the next barrier.
+    const bool last_items = ONE && bid + (int)gridDim.x >= prm->n_work_dq;
+    auto share_rows = [&]() __attribute__((always_inline)) {
+        if (wave_active && h == 0 && my_i < rows) {
+            const kernarg_t<BwdParams> out = kernarg<BwdParams>();
+            const size_t at = (size_t)head * out->total_q + qrow0 + my_i;
+            store_shared(out->delta + at, nd);
+            store_shared(out->lse2 + at, lse2);
+        }
+    };
+    // (behind a barrier before which every wave has waited for its stores)
+    auto count_ready = [&]() __attribute__((always_inline)) {
+        if (tid == 0) count_one(kernarg<BwdParams>()->rows_ready);
+    };
+    if (ONE && last_items) share_rows();
     // Everything issued so far has to land here: the compiler's own count of
     // outstanding loads must be zero before the loops, or the waits it places
     // for these fragments would also wait for the tile fetches in flight.
     wait_vmem();
     __syncthreads();
+    if (ONE && last_items) count_ready();
     if ((SMALL ? 1 : 2) < n_tiles) fetch(0);  // the staging regions are free again
+    if (ONE && !last_items) share_rows();
 
     f32x16 acc[TT];
     zero_acc(acc);
@@ -440,7 +489,13 @@ __device__ __forceinline__ int dq_work(const int bid, RowBlocks &rb, BwdFeed &fe
             if (SMALL || (t & 1)) {
                 wait_vmem();
                 __syncthreads();
+                if (ONE && t == 1 && !last_items) count_ready();
             }
+        }
+        if (ONE && n_tiles == 1 && !last_items) {
+            wait_vmem();
+            __syncthreads();
+            count_ready();
         }
     } else {
     f32x16 sx, sy, gx, gy;  // S and dP - D of the current / next half tile, ping-pong
@@ -467,6 +522,7 @@ __device__ __forceinline__ int dq_work(const int bid, RowBlocks &rb, BwdFeed &fe
         if (SMALL || (t & 1)) {
             wait_vmem();      // my share of the tiles of the next period(s) has landed
             __syncthreads();  // ... and everyone's; everyone is done with the tiles they replace
+            if (ONE && t == 1 && !last_items) count_ready();  // (every item has a period 1)
         }
         kslot = kslot == KSL - 1 ? 0 : kslot + 1;
     };
@@ -515,10 +571,10 @@ __device__ __forceinline__ int dq_work(const int bid, RowBlocks &rb, BwdFeed &fe
     st.init(li);
     if (wave_active) st.put_acc(stage, acc, out->scale, on, oh);
     RowBlocks rb_next{};
-    if (next >= 0) rb_next = row_blocks<NWQ>(out, out->fwd_items, next);  // (its loads are under way during the stores)
+    if (next >= 0) rb_next = row_blocks<ONE ? 0 : NWQ>(out, out->fwd_items, next);  // (its loads are under way during the stores)
     if (wave_active) {
         st.store(stage, out->dq + ((size_t)qrow0 * out->Hq + head) * D, (uint32_t)out->Hq * D * 2, wrow0, rows);
-        if (oh == 0 && oi < rows) {
+        if (!ONE && oh == 0 && oi < rows) {
             out->delta[(size_t)head * out->total_q + qrow0 + oi] = nd;
             out->lse2[(size_t)head * out->total_q + qrow0 + oi] = lse2;
         }
@@ -528,25 +584,36 @@ __device__ __forceinline__ int dq_work(const int bid, RowBlocks &rb, BwdFeed &fe
     return next;
 }
 
+// Does dQ work items until none is left.
+template <int D, int NWQ, bool PIPED, bool ONE>
+__device__ __forceinline__ void dq_loop(DqFeed &feed, unsigned char *lds)
+{
+    constexpr int NW = ONE ? 0 : NWQ;
+    int w = feed.first(feed.begin());
+    RowBlocks rb = row_blocks<NW>(kernarg<BwdParams>(), kernarg<BwdParams>()->fwd_items, max(w, 0));
+    while (w >= 0) {
+        if (rb.has(0)) {
+            w = dq_work<D, NWQ, PIPED, ONE>(w, rb, feed, lds);
+            if (w == kQueueEmpty) {
+                w = feed.other();
+                rb = row_blocks<NW>(kernarg<BwdParams>(), kernarg<BwdParams>()->fwd_items, max(w, 0));
+            }
+        } else {  // the item is too short for this part (the whole workgroup agrees)
+            if (ONE && threadIdx.x == 0) count_one(kernarg<BwdParams>()->rows_ready);
+            w = feed.again();
+            rb = row_blocks<NW>(kernarg<BwdParams>(), kernarg<BwdParams>()->fwd_items, max(w, 0));
+        }
+    }
+}
+
 template <int D, int NWQ, bool PIPED = NWQ == NWQ_LARGE>
 __global__ __launch_bounds__(64 * NWQ, PIPED ? 2 : 3) void dq_kernel(const BwdParams prm)
 {
+    __shared__ __align__(16) unsigned char lds[DqLds<D, NWQ, PIPED>::BYTES];
     __shared__ int work_slot[2];
-    BwdFeed feed{prm.queue_dq, prm.n_work_dq, 0, 0, work_slot};
-    int w = feed.first(feed.begin());
-    RowBlocks rb = row_blocks<NWQ>(kernarg<BwdParams>(), prm.fwd_items, max(w, 0));
-    while (w >= 0) {
-        if (rb.has(0)) {
-            w = dq_work<D, NWQ, PIPED>(w, rb, feed);
-            if (w == kQueueEmpty) {
-                w = feed.other();
-                rb = row_blocks<NWQ>(kernarg<BwdParams>(), prm.fwd_items, max(w, 0));
-            }
-        } else {  // the item is too short for this part (the whole workgroup agrees)
-            w = feed.again();
-            rb = row_blocks<NWQ>(kernarg<BwdParams>(), prm.fwd_items, max(w, 0));
-        }
-    }
+    if (prm.clear && blockIdx.x == 0) clear_state(prm.clear, SKRULL_BWD_STATE_INTS);
+    DqFeed feed{{}, 0, 0, work_slot};
+    dq_loop<D, NWQ, PIPED, false>(feed, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -698,16 +765,24 @@ __device__ __forceinline__ KeyBlock key_block(const P prm, int SUB, int bid)
 
 // Does work item `bid`, whose keys are `kb`; returns the next one and leaves its keys in `kb`.
 template <int D, int PAIRS>
-__device__ __forceinline__ int dkv_work(const int bid, KeyBlock &kb, BwdFeed &feed)
+struct DkvLds {
+    static constexpr int SLOT = 2 * TileGeom<D>::BYTES + 2 * TILE_ROWS * 4;  // Q rows | dO rows | LSE*log2e | D
+    static constexpr int P = 3 * SLOT;                                       // P exchange [pair][round parity][16-row block][lane*16]
+    static constexpr int BYTES = P + PAIRS * 2 * 4 * 1024;
+};
+
+template <int D, int PAIRS, bool ONE>
+__device__ __forceinline__ int dkv_work(const int bid, KeyBlock &kb, DkvFeed &feed, unsigned char *lds, bool &rows_seen)
 {
     const kernarg_t<BwdParams> prm = kernarg<BwdParams>();
     constexpr int NWP = 2 * PAIRS;   // wavefronts: PAIRS S waves, then PAIRS dP waves
     constexpr int SUB = 32 * PAIRS;  // key rows per workgroup
     constexpr int KS = D / 16, TT = D / 32, QT = TILE_ROWS;
     constexpr int TB = TileGeom<D>::BYTES;
-    constexpr int SLOT = 2 * TB + 2 * QT * 4;  // Q rows | dO rows | LSE*log2e | D
-    __shared__ __align__(16) unsigned char lds_ring[3][SLOT];
-    __shared__ __align__(16) unsigned char lds_p[PAIRS][2][4][1024];  // [pair][round parity][16-row block][lane*16]
+    typedef DkvLds<D, PAIRS> Lds;
+    constexpr int SLOT = Lds::SLOT;
+    unsigned char (*lds_ring)[SLOT] = (unsigned char (*)[SLOT])lds;
+    unsigned char (*lds_p)[2][4][1024] = (unsigned char (*)[2][4][1024])(lds + Lds::P);
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -732,7 +807,7 @@ __device__ __forceinline__ int dkv_work(const int bid, KeyBlock &kb, BwdFeed &fe
     // this wave's staging region: ring slots 1 and 2 hold no tile at the start and the end of a
     // pass (eight regions); the waves beyond the eighth use the P exchange area
     typedef WaveStage<D> Stage;
-    static_assert(8 * Stage::BYTES <= 2 * SLOT && (NWP - 8) * Stage::BYTES <= (int)sizeof(lds_p),
+    static_assert(8 * Stage::BYTES <= 2 * SLOT && (NWP - 8) * Stage::BYTES <= Lds::BYTES - Lds::P,
                   "staging regions do not fit the idle part of the LDS");
     const uint32_t stage = wave < 8 ? ring0 + SLOT + (uint32_t)wave * Stage::BYTES
                                     : lds_addr(&lds_p[0][0][0][0]) + (uint32_t)(wave - 8) * Stage::BYTES;
@@ -791,11 +866,20 @@ __device__ __forceinline__ int dkv_work(const int bid, KeyBlock &kb, BwdFeed &fe
         // rows past the end of the segment read as zero (and are masked)
         ld.load(ld.rsrc(prm->q + hoff, rows), base, i0, wave);
         ld.load(ld.rsrc(prm->d_o + hoff, rows), base + TB, i0, wave);
-        if (row_scalars)
-            dma_b32(rsrc_words(scalars + (size_t)head * total_q + first_row, (uint32_t)rows * 4), base + scalars_at, lane * 4,
-                    i0 * 4);
+        if (row_scalars) {
+            const i32x4 r = rsrc_words(scalars + (size_t)head * total_q + first_row, (uint32_t)rows * 4);
+            if (ONE) dma_b32_shared(r, base + scalars_at, lane * 4, i0 * 4);
+            else dma_b32(r, base + scalars_at, lane * 4, i0 * 4);
+        }
     };
 
+    if (ONE && !rows_seen) {  // this workgroup's first item
+        const kernarg_t<BwdParams> wait = kernarg<BwdParams>();
+        if (tid == 0)
+            while (__hip_atomic_load(wait->rows_ready, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < wait->n_work_dq) __builtin_amdgcn_s_sleep(4);
+        __syncthreads();  // (-D and LSE are read past the L2: with a fence by each workgroup, which empties it, dK/dV began 30 us later)
+        rows_seen = true;
+    }
     fetch(head0, tile0, 0);
     wait_vmem();
     __syncthreads();
@@ -1122,16 +1206,16 @@ __device__ __forceinline__ int dkv_work(const int bid, KeyBlock &kb, BwdFeed &fe
     return next;
 }
 
-template <int D, int PAIRS>
-__global__ __launch_bounds__(128 * PAIRS, PAIRS == PAIRS_12W ? 3 : 2) void dkv_kernel(const BwdParams prm)
+// Does dK/dV work items until none is left.
+template <int D, int PAIRS, bool ONE>
+__device__ __forceinline__ void dkv_loop(DkvFeed &feed, unsigned char *lds)
 {
-    __shared__ int work_slot[2];
-    BwdFeed feed{prm.queue_dkv, prm.n_work_dkv, 0, 0, work_slot};
+    bool rows_seen = !ONE;
     int w = feed.first(feed.begin());
     KeyBlock kb = key_block(kernarg<BwdParams>(), 32 * PAIRS, max(w, 0));
     while (w >= 0) {
         if (kb.item_rows > 0) {
-            w = dkv_work<D, PAIRS>(w, kb, feed);
+            w = dkv_work<D, PAIRS, ONE>(w, kb, feed, lds, rows_seen);
             if (w == kQueueEmpty) {
                 w = feed.other();
                 kb = key_block(kernarg<BwdParams>(), 32 * PAIRS, max(w, 0));
@@ -1141,6 +1225,43 @@ __global__ __launch_bounds__(128 * PAIRS, PAIRS == PAIRS_12W ? 3 : 2) void dkv_k
             kb = key_block(kernarg<BwdParams>(), 32 * PAIRS, max(w, 0));
         }
     }
+}
+
+template <int D, int PAIRS>
+__global__ __launch_bounds__(128 * PAIRS, PAIRS == PAIRS_12W ? 3 : 2) void dkv_kernel(const BwdParams prm)
+{
+    __shared__ __align__(16) unsigned char lds[DkvLds<D, PAIRS>::BYTES];
+    __shared__ int work_slot[2];
+    DkvFeed feed{{}, 0, 0, work_slot};
+    dkv_loop<D, PAIRS, false>(feed, lds);
+}
+
+// dQ, then dK/dV, in one launch: a workgroup that finds no dQ item left goes on with dK/dV items, so that the chip has
+// work while the last dQ items end.  These need -D and LSE*log2(e) of rows that other workgroups may still be at, but
+// only from their start: a dQ item forms both before its first product, so where every item has been handed out all that is
+// needed follows within microseconds.  The wait for it ends: items are only handed out to workgroups that run, and none
+// of these waits before it has counted its items as ready.
+// As two launches, from a workgroup's last dQ item to the first dK/dV item on its compute unit 14 to 19 us pass (the longest item's
+// end, the end of one launch and the start of the next), 2.5 this way.  Backward, two launches and this: 26,624 tokens in 64 sequences, 14/2 heads of 64,
+// 212 and 198 us; 16,384 in 20 229 and 212; 13,312 in 10, 28/4 heads of 128, 845 and 833; 32,768 of 16 to 1,024, 32/8 heads of 128,
+// 639 and 629; long chains the same within 0.3 %.  dQ workgroups have as many wavefronts as those of dK/dV here, 8 or 12, and
+// leave some without work where the plan's units are smaller.  Launches of many units of 4 stay two: three such workgroups share a
+// compute unit there (slices of three long sequences, 14/2 heads of 64: 4.68 ms, in one launch 5.1).
+template <int D, int PAIRS>
+__global__ __launch_bounds__(128 * PAIRS, PAIRS == PAIRS_12W ? 3 : 2) void bwd_kernel(const BwdParams prm)
+{
+    constexpr int NW = 2 * PAIRS;
+    constexpr bool PIPED = NW == NWQ_LARGE;
+    constexpr int BYTES = DqLds<D, NW, PIPED>::BYTES > DkvLds<D, PAIRS>::BYTES ? DqLds<D, NW, PIPED>::BYTES : DkvLds<D, PAIRS>::BYTES;
+    __shared__ __align__(16) unsigned char lds[BYTES];
+    __shared__ int work_slot[2];
+    if (prm.clear && blockIdx.x == 0) clear_state(prm.clear, SKRULL_BWD_STATE_INTS);
+    {
+        DqFeed feed{{}, 0, 0, work_slot};
+        dq_loop<D, NW, PIPED, true>(feed, lds);
+    }
+    DkvFeed feed{{}, 0, 0, work_slot};
+    dkv_loop<D, PAIRS, true>(feed, lds);
 }
 
 // Sum of the partial gradients of the items that several workgroups shared, rounded once:
@@ -1179,7 +1300,31 @@ __global__ __launch_bounds__(256) void dkv_reduce_kernel(const BwdParams prm)
     out[((size_t)(krow + r) * prm.Hkv + c) * (D / 4) + q] = w;
 }
 
+hipError_t clear_queues_first(const BwdParams &prm, hipStream_t st)
+{
+    queue_reset_kernel<<<1, 64, 0, st>>>(prm.queue_dq, 2, prm.queue_stride);
+    return hipGetLastError();
+}
+
 int dkv_pairs(const skrull_attn_plan_t *p) { return (p->d == 64 && p->BN == 32 * PAIRS_12W) ? PAIRS_12W : PAIRS_8W; }
+
+RowLaunch rows_dq(const skrull_attn_plan_t *p)
+{
+    if (p->d == 128) return row_launch<dq_kernel<128, NWQ_LARGE>>(p, NWQ_LARGE);
+    if (p->dq_waves == NWQ_SMALL && p->dq_piped) return row_launch<dq_kernel<64, NWQ_SMALL, true>>(p, NWQ_SMALL);
+    if (p->dq_waves == NWQ_SMALL) return row_launch<dq_kernel<64, NWQ_SMALL>>(p, NWQ_SMALL);
+    if (p->dq_waves == NWQ_WIDE) return row_launch<dq_kernel<64, NWQ_WIDE>>(p, NWQ_WIDE);
+    return row_launch<dq_kernel<64, NWQ_LARGE>>(p, NWQ_LARGE);
+}
+
+template <int D>
+hipError_t launch_sums(const skrull_attn_plan_t *p, const BwdParams &prm, hipStream_t st)
+{
+    if (p->n_split <= 0) return hipSuccess;
+    const dim3 grid((unsigned)p->n_split * p->Hkv, (unsigned)(p->BN + REDUCE_ROWS<D> - 1) / REDUCE_ROWS<D>, 2);
+    dkv_reduce_kernel<D><<<grid, 256, 0, st>>>(prm);
+    return hipGetLastError();
+}
 
 template <int D, auto KernelQ, auto KernelKV>
 hipError_t launch_pair(const skrull_attn_plan_t *p, BwdParams prm, int threads_q, int threads_kv, hipStream_t st,
@@ -1188,12 +1333,12 @@ hipError_t launch_pair(const skrull_attn_plan_t *p, BwdParams prm, int threads_q
     // dQ first: it also leaves -D and LSE*log2(e) of every (head, row) in the workspace,
     // which dK/dV reads.  Events: ev[0] start, ev[1] after dQ, ev[2] after dK/dV.
     if (ev) (void)hipEventRecord(ev[0], st);
-    const bool queued_q = prm.queue_dq != nullptr, queued_kv = wants_queue<KernelKV>(threads_kv, prm.n_work_dkv);
-    if (queued_q || queued_kv) {
-        queue_reset_kernel<<<1, 64, 0, st>>>(prm.queue_dkv - 8 * kQueueStrideBwd, 2, kQueueStrideBwd);
-        hipError_t e = hipGetLastError();
+    const bool queued_q = wants_queue<KernelQ>(threads_q, prm.n_work_dq), queued_kv = wants_queue<KernelKV>(threads_kv, prm.n_work_dkv);
+    if ((queued_q || queued_kv) && !prm.clear) {
+        hipError_t e = clear_queues_first(prm, st);
         if (e != hipSuccess) return e;
     }
+    if (!queued_q) prm.queue_dq = nullptr;
     if (!queued_kv) prm.queue_dkv = nullptr;
     KernelQ<<<launch_size<KernelQ>(threads_q, prm.n_work_dq, queued_q), threads_q, 0, st>>>(prm);
     hipError_t e = hipGetLastError();
@@ -1201,20 +1346,43 @@ hipError_t launch_pair(const skrull_attn_plan_t *p, BwdParams prm, int threads_q
     if (ev) (void)hipEventRecord(ev[1], st);
     KernelKV<<<launch_size<KernelKV>(threads_kv, prm.n_work_dkv, queued_kv), threads_kv, 0, st>>>(prm);
     e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if (p->n_split > 0) {
-        const dim3 grid((unsigned)p->n_split * p->Hkv, (unsigned)(p->BN + REDUCE_ROWS<D> - 1) / REDUCE_ROWS<D>, 2);
-        dkv_reduce_kernel<D><<<grid, 256, 0, st>>>(prm);
-        e = hipGetLastError();
+    if (e == hipSuccess) e = launch_sums<D>(p, prm, st);
+    if (e == hipSuccess && ev) (void)hipEventRecord(ev[2], st);
+    return e;
+}
+
+template <int D, int PAIRS>
+hipError_t launch_one(const skrull_attn_plan_t *p, const BwdParams &prm, hipStream_t st)
+{
+    if (!prm.clear) {
+        hipError_t e = clear_queues_first(prm, st);
         if (e != hipSuccess) return e;
     }
-    if (ev) (void)hipEventRecord(ev[2], st);
-    return hipGetLastError();
+    const int64_t work = (int64_t)prm.n_work_dq + prm.n_work_dkv;
+    const int resident = resident_of<bwd_kernel<D, PAIRS>>(128 * PAIRS);
+    bwd_kernel<D, PAIRS><<<(int)(work < resident ? work : resident), 128 * PAIRS, 0, st>>>(prm);
+    hipError_t e = hipGetLastError();
+    return e == hipSuccess ? launch_sums<D>(p, prm, st) : e;
+}
+template <int D, int PAIRS> bool chip_known() { return resident_of<bwd_kernel<D, PAIRS>>(128 * PAIRS) > 0; }
+
+// Whether a backward is one launch.
+bool is_one(const skrull_attn_plan_t *p)
+{
+    if (p->d == 128) return chip_known<128, PAIRS_8W>();
+    if (p->dq_waves == NWQ_SMALL && rows_dq(p).queued) return false;
+    if (dkv_pairs(p) == PAIRS_12W) return chip_known<64, PAIRS_12W>();
+    return p->dq_waves <= 8 && chip_known<64, PAIRS_8W>();
 }
 
 template <int D>
 hipError_t launch_d(const skrull_attn_plan_t *p, const BwdParams &prm, hipStream_t st, hipEvent_t *ev)
 {
+    if (!ev && is_one(p)) {  // (events are to time dQ and dK/dV by themselves)
+        if constexpr (D == 64)
+            if (dkv_pairs(p) == PAIRS_12W) return launch_one<D, PAIRS_12W>(p, prm, st);
+        return launch_one<D, PAIRS_8W>(p, prm, st);
+    }
     if constexpr (D == 64) {  // dQ has its other shapes, and dK/dV its 12-wavefront one, only here
         if (dkv_pairs(p) == PAIRS_12W) {
             if (p->dq_waves == NWQ_SMALL && p->dq_piped) return launch_pair<D, dq_kernel<D, NWQ_SMALL, true>, dkv_kernel<D, PAIRS_12W>>(p, prm, 64 * NWQ_SMALL, 128 * PAIRS_12W, st, ev);
@@ -1230,15 +1398,6 @@ hipError_t launch_d(const skrull_attn_plan_t *p, const BwdParams &prm, hipStream
 }
 
 }  // namespace
-
-static RowLaunch rows_dq(const skrull_attn_plan_t *p)
-{
-    if (p->d == 128) return row_launch<dq_kernel<128, NWQ_LARGE>>(p, NWQ_LARGE);
-    if (p->dq_waves == NWQ_SMALL && p->dq_piped) return row_launch<dq_kernel<64, NWQ_SMALL, true>>(p, NWQ_SMALL);
-    if (p->dq_waves == NWQ_SMALL) return row_launch<dq_kernel<64, NWQ_SMALL>>(p, NWQ_SMALL);
-    if (p->dq_waves == NWQ_WIDE) return row_launch<dq_kernel<64, NWQ_WIDE>>(p, NWQ_WIDE);
-    return row_launch<dq_kernel<64, NWQ_LARGE>>(p, NWQ_LARGE);
-}
 
 int grid_dq(const skrull_attn_plan_t *p) { return rows_dq(p).n_work; }
 
@@ -1279,17 +1438,37 @@ hipError_t launch_bwd(const skrull_attn_plan_t *p, const void *q, const void *k,
     prm.n_work_dq = rows_q.n_work;
     prm.n_work_dkv = grid_dkv(p);
     {
-        // workspace: -D | LSE*log2e | (256-byte aligned) work queues of two launches in 256 bytes | dK partials | dV partials
-        static_assert(2 * 8 * kQueueStrideBwd * sizeof(WorkQueue) == 256, "the queues' part of the workspace");
+        // workspace: -D | LSE*log2e | (256-byte aligned) 256 bytes, the state of calls that clear it first | dK partials | dV partials
+        static_assert(2 * 8 * kQueueStrideWorkspace * sizeof(WorkQueue) == 256, "the queues' part of the workspace");
+        static_assert(2 * 8 * kQueueStride * sizeof(WorkQueue) == 2 * 4 * SKRULL_QUEUE_INTS, "the queues' part of a plan's state");
         const size_t rows = (((size_t)p->Hq * p->total_q * 8) + 255) & ~(size_t)255;
-        prm.queue_dq = (WorkQueue *)((char *)delta + rows);
-        prm.queue_dkv = prm.queue_dq + 8 * kQueueStrideBwd;
-        if (!rows_q.queued) prm.queue_dq = nullptr;
         prm.dk_part = (float *)((char *)delta + rows + 256);
         const size_t part_rows = p->split_compact ? (size_t)p->n_split * p->BN : (size_t)p->total_k;
         prm.dv_part = prm.dk_part + (size_t)p->split_parts * part_rows * p->Hkv * p->d;
     }
-    if (p->d == 128) return launch_d<128>(p, prm, st, ev);
-    if (p->d == 64) return launch_d<64>(p, prm, st, ev);
-    return hipErrorInvalidValue;
+    std::unique_lock<std::mutex> held(p->streams->lock);
+    const int at = p->streams->find(st);
+    if (at >= 0) {
+        const uint32_t turn = p->streams->of[at].bwd;
+        int32_t *sets = p->stream_states + at * SKRULL_STREAM_STATE_INTS + 2 * SKRULL_QUEUE_INTS;
+        int32_t *mine = sets + (turn & 1) * SKRULL_BWD_STATE_INTS;
+        prm.queue_stride = kQueueStride;
+        prm.queue_dq = (WorkQueue *)mine;
+        prm.queue_dkv = (WorkQueue *)(mine + SKRULL_QUEUE_INTS);
+        prm.rows_ready = mine + 2 * SKRULL_QUEUE_INTS;
+        prm.clear = sets + (~turn & 1) * SKRULL_BWD_STATE_INTS;
+    } else {
+        held.unlock();
+        prm.queue_stride = kQueueStrideWorkspace;
+        prm.queue_dq = (WorkQueue *)((char *)prm.dk_part - 256);
+        prm.queue_dkv = prm.queue_dq + 8 * kQueueStrideWorkspace;
+        prm.rows_ready = (int32_t *)&prm.queue_dq->taken[0];  // (a word of the queues that the backward's do not use)
+        prm.clear = nullptr;
+    }
+    const hipError_t e = p->d == 128 ? launch_d<128>(p, prm, st, ev) : p->d == 64 ? launch_d<64>(p, prm, st, ev) : hipErrorInvalidValue;
+    if (at >= 0) {
+        if (e == hipSuccess) ++p->streams->of[at].bwd;
+        else p->streams->give_up(at);
+    }
+    return e;
 }

@@ -12,7 +12,9 @@
 struct WorkQueue;
 // forward calls of one plan that may be in flight at once (each takes one queue slot in turn)
 #define SKRULL_FWD_QUEUE_SLOTS 64
-#define SKRULL_FWD_QUEUE_INTS 256  // of a slot: eight dies' queues, a 128-byte line each
+#define SKRULL_QUEUE_INTS 256  // of a queue: eight dies' queues, a 128-byte line each
+// of what the workgroups of a backward share: the queues of dQ and of dK/dV, and counters, a line each
+#define SKRULL_BWD_STATE_INTS (2 * SKRULL_QUEUE_INTS + 128)
 
 // Queues that need no kernel to clear them before a launch.  The calls of one stream run one after another, so a
 // plan keeps two sets for each stream it is used on: a launch works with one and clears the other, which the
@@ -21,13 +23,13 @@ struct WorkQueue;
 // SKRULL_STREAM_STATES streams; calls on further streams, calls that are being captured (a replay has no
 // turn in that order) and calls on a handle that stands for a different stream in each thread clear a queue first.
 #define SKRULL_STREAM_STATES 4
-#define SKRULL_STREAM_STATE_INTS (2 * SKRULL_FWD_QUEUE_INTS)
+#define SKRULL_STREAM_STATE_INTS (2 * (SKRULL_QUEUE_INTS + SKRULL_BWD_STATE_INTS))
 struct StreamStates {
     std::mutex lock;  // held from the choice of a set until the launch that uses it is queued
     int used = 0;
     struct {
         hipStream_t stream;
-        uint32_t fwd;  // forward launches so far
+        uint32_t fwd, bwd;  // forward and backward calls so far that used a set
     } of[SKRULL_STREAM_STATES] = {};
 
     // The place of stream `st`, or -1.  With the lock held.
@@ -46,6 +48,8 @@ struct StreamStates {
         of[used].stream = st;
         return used++;
     }
+    // After a launch that failed nobody knows what its place's sets hold.
+    void give_up(int at) { of[at].stream = (hipStream_t)~(uintptr_t)0; }
 };
 
 #define SKRULL_CHAIN_LIMITS 9

@@ -120,7 +120,14 @@ __device__ __forceinline__ uint32_t softmax_sum_pack(float t0, float t1, float &
     return pk;
 }
 
-using FwdFeed = WorkFeed<kQueueStrideFwd, true>;
+struct FwdSource {
+    WorkQueue *q;
+    int n_work;
+    __device__ __forceinline__ WorkQueue *queue() const { return q; }
+    __device__ __forceinline__ int stride() const { return kQueueStride; }
+    __device__ __forceinline__ int items() const { return n_work; }
+};
+using FwdFeed = WorkFeed<true, FwdSource>;
 
 // Does work item `bid`, whose rows are `rb`; returns the next one and leaves its rows in `rb`.
 template <int D, int NW, int NSLOT>
@@ -489,8 +496,8 @@ template <int D, int NW, int NSLOT>
 __global__ __launch_bounds__(64 * NW, NW == NW_WIDE ? 3 : 2) void fwd_kernel(const FwdParams prm)
 {
     __shared__ int work_slot[2];
-    if (prm.clear && blockIdx.x == 0) clear_queues(prm.clear, kQueueStrideFwd);
-    FwdFeed feed{prm.queue, prm.n_work, prm.n_first, 0, work_slot};
+    if (prm.clear && blockIdx.x == 0) clear_state((int32_t *)prm.clear, SKRULL_QUEUE_INTS);
+    FwdFeed feed{{prm.queue, prm.n_work}, prm.n_first, 0, work_slot};
     const uint32_t marks = feed.begin();
     RowBlocks rb = uniform(row_blocks<NW>(kernarg<FwdParams>(), prm.items, (int)blockIdx.x));
     int w = feed.first(marks);
@@ -513,7 +520,7 @@ template <auto Kernel>
 hipError_t launch_shape(FwdParams prm, int threads, hipStream_t st)
 {
     if (prm.queue && !prm.clear) {
-        queue_reset_kernel<<<1, 64, 0, st>>>(prm.queue, 1, kQueueStrideFwd);
+        queue_reset_kernel<<<1, 64, 0, st>>>(prm.queue, 1, kQueueStride);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -563,26 +570,28 @@ hipError_t launch_fwd(const skrull_attn_plan_t *p, const void *q, const void *k,
     prm.variant = p->fwd_waves / 4 - 1;
     prm.n_work = rows.n_work;
     prm.queue = prm.clear = nullptr;
-    static_assert(8 * kQueueStrideFwd * sizeof(WorkQueue) == 4 * SKRULL_FWD_QUEUE_INTS, "a slot holds eight queues");
-    constexpr int one = 8 * kQueueStrideFwd;
+    static_assert(8 * kQueueStride * sizeof(WorkQueue) == 4 * SKRULL_QUEUE_INTS, "a slot holds eight queues");
     std::unique_lock<std::mutex> held(p->streams->lock, std::defer_lock);
-    uint32_t *turn = nullptr;
+    int at = -1;
     if (rows.queued) {
         held.lock();
-        const int at = p->streams->find(st);
+        at = p->streams->find(st);
         if (at >= 0) {
-            turn = &p->streams->of[at].fwd;
-            WorkQueue *sets = (WorkQueue *)(p->stream_states + at * SKRULL_STREAM_STATE_INTS);
-            prm.queue = sets + (*turn & 1) * one;
-            prm.clear = sets + (~*turn & 1) * one;
+            const uint32_t turn = p->streams->of[at].fwd;
+            int32_t *sets = p->stream_states + at * SKRULL_STREAM_STATE_INTS;
+            prm.queue = (WorkQueue *)(sets + (turn & 1) * SKRULL_QUEUE_INTS);
+            prm.clear = (WorkQueue *)(sets + (~turn & 1) * SKRULL_QUEUE_INTS);
         } else {
             held.unlock();
             // One of the plan's queue slots per call, taken in turn, so that forward calls of one plan
             // that overlap on different streams do not share a queue.
-            prm.queue = p->fwd_queues + one * (__atomic_fetch_add(&const_cast<skrull_attn_plan_t *>(p)->fwd_calls, 1u, __ATOMIC_RELAXED) % SKRULL_FWD_QUEUE_SLOTS);
+            prm.queue = p->fwd_queues + 8 * kQueueStride * (__atomic_fetch_add(&const_cast<skrull_attn_plan_t *>(p)->fwd_calls, 1u, __ATOMIC_RELAXED) % SKRULL_FWD_QUEUE_SLOTS);
         }
     }
     const hipError_t e = p->d == 128 ? launch_one<128>(prm, st) : p->d == 64 ? launch_one<64>(prm, st) : hipErrorInvalidValue;
-    if (e == hipSuccess && turn) ++*turn;
+    if (at >= 0) {
+        if (e == hipSuccess) ++p->streams->of[at].fwd;
+        else p->streams->give_up(at);
+    }
     return e;
 }

@@ -33,8 +33,8 @@ struct WorkQueue {                // of one die
 // A launch has eight of them, this many apart.  Atomics on one 128-byte line wait for each other, and all
 // workgroups of a launch send their first ones together: with the eight queues in one line the forward of 64
 // sequences, 26,624 tokens, 14/2 heads of 64, takes 83 us, with a line each 75, and one of 10,573 tokens 45
-// and 38.  (The workspace of a backward has room for one line per launch.)
-constexpr int kQueueStrideFwd = 8, kQueueStrideBwd = 1;
+// and 38.  (The workspace of a backward has room for one line per launch: what calls use that clear their queues first.)
+constexpr int kQueueStride = 8, kQueueStrideWorkspace = 1;
 
 // The kernel's one argument (a struct of parameters), read anew through an opaque pointer: in a
 // persistent kernel every parameter is an invariant of the work loop, and kept from one work
@@ -73,30 +73,30 @@ __device__ __forceinline__ int opaque(int x)
     asm volatile("" : "+v"(x));
     return x;
 }
-template <int STRIDE> __device__ __forceinline__ int next_count(WorkQueue *q, int xcd)
+__device__ __forceinline__ int next_count(WorkQueue *q, int stride, int xcd)
 {
-    return __hip_atomic_fetch_add(&q[(uint32_t)opaque(STRIDE * xcd)].next, opaque(1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return __hip_atomic_fetch_add(&q[(uint32_t)opaque(stride * xcd)].next, opaque(1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 // Marks first item 32 * word + bit of a die; the word's marks before that.
-template <int STRIDE> __device__ __forceinline__ uint32_t mark_first(WorkQueue *q, int xcd, int word, int bit)
+__device__ __forceinline__ uint32_t mark_first(WorkQueue *q, int stride, int xcd, int word, int bit)
 {
-    return __hip_atomic_fetch_or(&q[(uint32_t)opaque(STRIDE * xcd)].taken[word], (uint32_t)opaque(1 << bit), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return __hip_atomic_fetch_or(&q[(uint32_t)opaque(stride * xcd)].taken[word], (uint32_t)opaque(1 << bit), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // The work item that count `k` of die `xcd`'s queue stands for, or kQueueEmpty.
 constexpr int kNoWork = -1, kQueueEmpty = -2;
-template <int STRIDE, bool FIRST> __device__ __forceinline__ int counted_work(WorkQueue *q, int n_work, int n_first, int xcd, int k)
+template <bool FIRST> __device__ __forceinline__ int counted_work(WorkQueue *q, int stride, int n_work, int n_first, int xcd, int k)
 {
     const int mine = (n_first - xcd + 7) / 8;  // this die's first items
     while (FIRST && __builtin_expect(k < mine, 0)) {
         for (int i = 0; 32 * i < mine;) {
-            const uint32_t seen = __hip_atomic_load(&q[STRIDE * xcd].taken[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const uint32_t seen = __hip_atomic_load(&q[stride * xcd].taken[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             const int bit = __ffs(~seen) - 1;
             if (~seen == 0 || 32 * i + bit >= mine) { ++i; continue; }
-            if (!(mark_first<STRIDE>(q, xcd, i, bit) >> bit & 1)) return 8 * (32 * i + bit) + xcd;
+            if (!(mark_first(q, stride, xcd, i, bit) >> bit & 1)) return 8 * (32 * i + bit) + xcd;
         }
         // all marked, one by a late workgroup whose own count was past them: that one has two items
-        k = next_count<STRIDE>(q, xcd);
+        k = next_count(q, stride, xcd);
     }
     const int w = 8 * k + xcd;
     return w < n_work ? w : kQueueEmpty;
@@ -105,17 +105,17 @@ template <int STRIDE, bool FIRST> __device__ __forceinline__ int counted_work(Wo
 // The next item of the queue with the most items left; kNoWork when every queue is empty.  Called by
 // one lane.  Counters are device-scope atomics (the dies' L2 caches are not coherent with
 // each other for plain accesses).
-template <int STRIDE, bool FIRST> __device__ __forceinline__ int stolen_work(WorkQueue *q, int n_work, int n_first)
+template <bool FIRST> __device__ __forceinline__ int stolen_work(WorkQueue *q, int stride, int n_work, int n_first)
 {
     for (;;) {
         int best = -1, best_left = 0;
         for (int y = 0; y < 8; ++y) {
-            const int ky = __hip_atomic_load(&q[STRIDE * y].next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const int ky = __hip_atomic_load(&q[stride * y].next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             const int left = (n_work - y + 7) / 8 - ky;  // items of queue y: ceil((n_work - y) / 8)
             if (left > best_left) { best_left = left; best = y; }
         }
         if (best < 0) return kNoWork;
-        const int w = counted_work<STRIDE, FIRST>(q, n_work, n_first, best, next_count<STRIDE>(q, best));
+        const int w = counted_work<FIRST>(q, stride, n_work, n_first, best, next_count(q, stride, best));
         if (w >= 0) return w;
         // someone else took its last item in between: look again (every failed attempt
         // means a queue has run empty, so this ends after at most eight rounds)
@@ -146,9 +146,10 @@ __device__ __forceinline__ int my_xcd() { return __builtin_amdgcn_readfirstlane(
 // too: by index it was as fast at head_dim 128 without marks, but with them 1 to 3 % slower on short lists,
 // because the backward's counts share a line.
 // `slot` is two ints of LDS; the caller has a barrier between a `take` and the next `post`.
-template <int STRIDE, bool FIRST> struct WorkFeed {
-    WorkQueue *q;
-    int n_work, n_first, pending;  // items; how many of them are first items; the count asked for, or ~ an item
+// `Source` says where the queue is (queue(), or null; stride(), its dies' distance) and how many items there are (items()).
+template <bool FIRST, typename Source> struct WorkFeed {
+    Source src;
+    int n_first, pending;  // how many items are first items; the count asked for, or ~ an item
     int *slot;                     // the next item; with FIRST also one more that this workgroup has taken, or -1
 
     // The first item.  `begin` sends the atomics, so that the loads of its descriptor are under way with
@@ -157,16 +158,16 @@ template <int STRIDE, bool FIRST> struct WorkFeed {
     {
         const int b = (int)blockIdx.x;
         uint32_t marks = ~0u;
-        if (FIRST && q && b < n_first && threadIdx.x == 0) {
-            pending = next_count<STRIDE>(q, b & 7);
-            marks = mark_first<STRIDE>(q, b & 7, b >> 8, b >> 3 & 31);
+        if (FIRST && src.queue() && b < n_first && threadIdx.x == 0) {
+            pending = next_count(src.queue(), src.stride(), b & 7);
+            marks = mark_first(src.queue(), src.stride(), b & 7, b >> 8, b >> 3 & 31);
         }
         return marks;
     }
     __device__ __forceinline__ int first(uint32_t marks)
     {
         const int b = (int)blockIdx.x;
-        if (!q) return b;
+        if (!src.queue()) return b;
         if (FIRST && threadIdx.x == 0) slot[1] = -1;
         if (!FIRST || b >= n_first) return again();
         if (threadIdx.x == 0) {
@@ -175,7 +176,7 @@ template <int STRIDE, bool FIRST> struct WorkFeed {
             if (__builtin_expect(!own || pending >= (n_first - (b & 7) + 7) / 8, 0)) {
                 // late: another item instead, or, where others had the rights to all first items but had
                 // not marked this one, another item as well
-                const int w = counted_work<STRIDE, FIRST>(q, n_work, n_first, b & 7, pending);
+                const int w = counted_work<FIRST>(src.queue(), src.stride(), src.items(), n_first, b & 7, pending);
                 slot[own ? 1 : 0] = w;
             }
         }
@@ -185,33 +186,33 @@ template <int STRIDE, bool FIRST> struct WorkFeed {
     }
     __device__ __forceinline__ void ask()
     {
-        if (q && threadIdx.x == 0) {
+        if (src.queue() && threadIdx.x == 0) {
             const int more = FIRST ? slot[1] : -1;
             if (__builtin_expect(more >= 0, 0)) {
                 pending = ~more;
                 slot[1] = -1;
             } else {
-                pending = next_count<STRIDE>(q, my_xcd());
+                pending = next_count(src.queue(), src.stride(), my_xcd());
             }
         }
     }
     __device__ __forceinline__ void post()
     {
-        if (q && threadIdx.x == 0) *slot = FIRST && pending < 0 ? ~pending : counted_work<STRIDE, FIRST>(q, n_work, n_first, my_xcd(), pending);
+        if (src.queue() && threadIdx.x == 0) *slot = FIRST && pending < 0 ? ~pending : counted_work<FIRST>(src.queue(), src.stride(), src.items(), n_first, my_xcd(), pending);
     }
-    __device__ __forceinline__ int take() const { return q ? __builtin_amdgcn_readfirstlane(*slot) : kNoWork; }
+    __device__ __forceinline__ int take() const { return src.queue() ? __builtin_amdgcn_readfirstlane(*slot) : kNoWork; }
     // after kQueueEmpty: an item of another die's queue
     __device__ __forceinline__ int other()
     {
         __syncthreads();  // everyone has read the slot
-        if (threadIdx.x == 0) *slot = stolen_work<STRIDE, FIRST>(q, n_work, n_first);
+        if (threadIdx.x == 0) *slot = stolen_work<FIRST>(src.queue(), src.stride(), src.items(), n_first);
         __syncthreads();
         return take();
     }
     // all of it at once, for a workgroup that has no work to hide it behind
     __device__ __forceinline__ int again()
     {
-        if (!q) return kNoWork;
+        if (!src.queue()) return kNoWork;
         __syncthreads();  // everyone has read the slot
         ask();
         post();
@@ -221,10 +222,10 @@ template <int STRIDE, bool FIRST> struct WorkFeed {
     }
 };
 
-// Zeroes a launch's queues; by the threads of one workgroup.
-__device__ __forceinline__ void clear_queues(WorkQueue *q, int stride)
+// Zeroes what a later launch's workgroups will share; by the threads of one workgroup.
+__device__ __forceinline__ void clear_state(int32_t *state, int ints)
 {
-    if (threadIdx.x < 8) ((int4 *)q)[threadIdx.x * stride] = make_int4(0, 0, 0, 0);
+    for (int i = threadIdx.x; i < ints / 4; i += blockDim.x) ((int4 *)state)[i] = make_int4(0, 0, 0, 0);
 }
 
 // Zeroes `n` launches' work queues (they must be zero when their kernel starts), for launches whose queues no launch before them has cleared.

@@ -111,16 +111,17 @@ struct FragAddr {
 // (2 g + 1) * d and there are at most SKRULL_UNIT_HEADS query heads.
 struct RowMap {
     int32_t BM, g, Hkv;           // rows of an item; query heads per KV head; KV heads
+    int32_t waves;                // row blocks of a work unit: wavefronts of a workgroup, or fewer
     int32_t parts, spread;        // most workgroups per (item, KV head); 1: see RowLaunch
     const int32_t *units;         // null, or the work units: item | part << SKRULL_UNIT_SHIFT
-    uint64_t inv_g, inv_hkv;
+    uint64_t inv_g, inv_hkv, inv_waves;
 };
 // ceil(2^40 / d)
 static inline uint64_t inverse_of(int d) { return ((1ull << 40) + d - 1) / d; }
 static inline RowMap row_map(const skrull_attn_plan_t *p, int NW)
 {
     const int g = p->Hq / p->Hkv;
-    return RowMap{p->BM, g, p->Hkv, (p->BM / 32 * g + NW - 1) / NW, 0, p->units[NW / 4 - 1], inverse_of(g), inverse_of(p->Hkv)};
+    return RowMap{p->BM, g, p->Hkv, NW, (p->BM / 32 * g + NW - 1) / NW, 0, p->units[NW / 4 - 1], inverse_of(g), inverse_of(p->Hkv), inverse_of(NW)};
 }
 // How a forward / dQ launch is laid out.
 //  `spread`, for launches whose workgroups all run at once: neighbouring row blocks go to
@@ -161,9 +162,9 @@ struct RowBlocks {
     int c;                          // KV head
     int kvl, kbase;                 // the segment: its keys, their first packed row
     int p0, qrow0, rows;            // the item: position and packed row of its first query, its rows
-    int g, first, step, nblk;       // heads per KV head; row blocks of this part: first + wave * step
+    int g, first, step, end, nblk;  // heads per KV head; row blocks of this part: first + wave * step, below end
     uint64_t inv_g;
-    __device__ __forceinline__ bool has(int wave) const { return first + wave * step < nblk * g; }
+    __device__ __forceinline__ bool has(int wave) const { return first + wave * step < end; }
     __device__ __forceinline__ int block(int wave) const { return nblk - 1 - quotient(first + wave * step, inv_g); }
     __device__ __forceinline__ int head(int wave) const  // query head of the wave's row block
     {
@@ -174,11 +175,12 @@ struct RowBlocks {
 
 // work index -> (item, part, KV head).  Consecutive work items go to consecutive XCDs; the parts of
 // one (item, KV head) are Hkv apart so that they share an XCD (and its L2 copy of the K/V tiles)
-// whenever Hkv divides 8 or is a multiple of it.
+// whenever Hkv divides 8 or is a multiple of it.  A unit has NW row blocks; 0: as many as the launch says.
 template <int NW, typename P>
 __device__ __forceinline__ RowBlocks row_blocks(const P prm, const int4 *items, int bid)
 {
     RowBlocks r;
+    const int nw = NW ? NW : prm->rows.waves;
     const int BM = prm->rows.BM, Hkv = prm->rows.Hkv;
     const int32_t *units = prm->rows.units;
     int item, part;
@@ -206,9 +208,17 @@ __device__ __forceinline__ RowBlocks row_blocks(const P prm, const int4 *items, 
     r.inv_g = prm->rows.inv_g;
     r.nblk = (r.rows + 31) / 32;
     const bool spread = prm->rows.spread != 0;
-    const int parts = spread && !units ? min(prm->rows.parts, r.nblk * r.g) : (r.nblk * r.g + NW - 1) / NW;  // of this item
-    r.first = part >= parts ? r.nblk * r.g : (spread ? part : part * NW);  // (past the end: the item has no such part)
-    r.step = spread ? parts : 1;
+    const int blocks = r.nblk * r.g;
+    if (spread) {
+        const int parts = !units ? min(prm->rows.parts, blocks) : NW ? (blocks + nw - 1) / nw : quotient(blocks + nw - 1, prm->rows.inv_waves);  // of this item
+        r.first = part >= parts ? blocks : part;  // (past the end: the item has no such part)
+        r.step = parts;
+        r.end = blocks;
+    } else {
+        r.first = part * nw;
+        r.step = 1;
+        r.end = NW ? blocks : min(blocks, r.first + nw);
+    }
     return r;
 }
 
@@ -250,6 +260,13 @@ __device__ __forceinline__ void dma_b128(i32x4 rsrc, uint32_t lds, int voff, int
 __device__ __forceinline__ void dma_b32(i32x4 rsrc, uint32_t lds, int voff, int soff)
 {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds"
+                 :: "s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory", "m0");
+}
+
+// The same of words that other workgroups of this launch have written (store_shared): past this die's L2
+__device__ __forceinline__ void dma_b32_shared(i32x4 rsrc, uint32_t lds, int voff, int soff)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen sc1 lds"
                  :: "s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory", "m0");
 }
 

@@ -1143,3 +1143,41 @@ def test_small_dq_shapes_change_no_bit(heads, S):
         assert np.array_equal(out[k], ref[k]), k
     out["plan"].destroy()
     ref["plan"].destroy()
+
+
+@pytest.mark.parametrize("heads,d,S,kw,dq_waves", [
+    ((14, 2), 64, [1, 31, 32, 33, 255, 256, 257, 300, 511, 700, 97] * 8, {"block_n": 192}, 12), ((14, 2), 64, [2500, 33, 129, 1], {"wg_query_rows": 256}, 8),
+    ((4, 4), 64, [455, 283, 194, 1, 32], {}, 4), ((4, 4), 64, [64, 1], {}, 4), ((16, 16), 64, [1000, 65, 700] * 9, {"block_n": 128}, 8),
+    ((4, 2), 64, [1, 65, 63] * 700, {"block_n": 64, "wg_query_rows": 256}, 8),   # (too many items for lists of units)
+    ((8, 2), 128, [700, 1, 64, 65, 900], {}, 8), ((28, 4), 128, [1700] + [300] * 30, {}, 8), ((3, 3), 128, [1500, 129, 64], {"block_n": 256}, 8)])
+def test_dq_and_dkv_in_one_launch_and_in_two_give_the_same_bits(heads, d, S, kw, dq_waves):
+    """dK/dV begins while the last dQ items are under way; with the kernels' times asked for it is a launch of its own.
+    Fewer work items than the chip has places and more, shared dK/dV items, a slice and a cut beside them, and a workspace of
+    other contents each time."""
+    from paper_2505_19609_amd import binding as B
+    import torch
+    K = len(S)
+    w = W.Workload("one_launch", S + [800, 513], [1] * K + [3, 2], [0] * K + [1, 1], heads[0], heads[1], d, d ** -0.5, 612,
+                   shard_cut=[0] * (K + 1) + [1])
+    run = run_library(w, keep_device=True, **kw)
+    plan, t, i = run["plan"], run["dev"], run["dev_in"]
+    assert plan.dq_waves == dq_waves
+    ws = torch.empty(max(int(plan.bwd_workspace_bytes), 16), dtype=torch.uint8, device="cuda")
+
+    def backward():
+        return B.skrull_attn_bwd(plan, i["q"], i["k"], i["v"], t["o"], t["lse"], i["do"], t["dq"], t["dk"], t["dv"], ws)
+
+    B.skrull_attn_profile(True)
+    backward()
+    torch.cuda.synchronize()
+    B.skrull_attn_profile(False)
+    two = {n: t[n].clone() for n in ("dq", "dk", "dv")}
+    for fill in (0, 0xFF, 0x7F, 1):
+        for x in (ws, *(t[n] for n in two)):
+            x.view(torch.uint8).fill_(fill)
+        for _ in range(3):
+            backward()
+        torch.cuda.synchronize()
+        for n in two:
+            assert torch.equal(t[n].view(torch.int16), two[n].view(torch.int16)), (fill, n)
+    plan.destroy()
