@@ -106,7 +106,9 @@ typedef struct {
                                      only, and a choice of 256 there may run with 384 rows or 128 */
     int32_t shapes;               /* workgroups that run: bits 0-7 wavefronts of a forward workgroup, bits
                                      8-15 of a dQ workgroup (4, 8 or 12, of 32 query rows each), bit 16
-                                     set where dQ is the pipelined kernel                      */
+                                     set where dQ is the pipelined kernel; of dQ, where it is a launch of
+                                     its own (profiling: always).  In one launch with dK/dV its workgroups
+                                     are as large as those of dK/dV                            */
 } skrull_attn_plan_info_t;
 
 /* Arrays a plan holds on the device, for skrull_attn_plan_export.  They are per
@@ -210,9 +212,10 @@ int skrull_attn_plan_export(const skrull_attn_plan_t *plan, int which, void *dst
  * empty and then the largest remaining item of the fullest other list (the dies of one chip
  * differ in speed by several percent, which a fixed deal of workgroups to dies cannot even
  * out).  Results do not depend on which workgroup took which item.
- * Only enqueues on `hip_stream` (the attention kernel and, when there are more work items than
- * the chip holds workgroups at once, a small kernel that clears the queue before it); never
- * synchronises.
+ * Only enqueues on `hip_stream` (the attention kernel; when there are more work items than
+ * the chip holds workgroups at once, also a small kernel that clears the queue before it, in calls
+ * that are being captured, on hipStreamPerThread and on further streams than the first four that a plan is
+ * used on; on those a plan's calls clear each other's queues); never synchronises.
  * SKRULL_EINVAL on a null or misaligned pointer, or when the current device is
  * not the one the plan was made on.
  */
@@ -235,7 +238,9 @@ int skrull_attn_fwd(const skrull_attn_plan_t *plan, const void *q, const void *k
  * out differently may differ in the last bit of dK/dV).
  * `workspace` is DEVICE scratch of at least info.bwd_workspace_bytes, 16-byte
  * aligned; contents on entry are ignored and on exit unspecified.
- * Only enqueues on `hip_stream`; never synchronises.
+ * Only enqueues on `hip_stream`; never synchronises.  One kernel does it all (dQ, then dK/dV, then
+ * the sums of shared items), but for micro-batches of many long sequences at head_dim 64, where they are
+ * two or three, and while profiling; the forward's small kernel before it in the same cases.
  * SKRULL_EINVAL on a null or misaligned pointer, a workspace that is too small,
  * or when the current device is not the one the plan was made on.
  */
@@ -254,7 +259,7 @@ int skrull_attn_bwd(const skrull_attn_plan_t *plan, const void *q, const void *k
  * ends; its address on a device is looked up when the first plan is made on that device.
  * The call allocates and frees nothing, does not synchronise, and only enqueues kernels
  * on `hip_stream`.  Nothing in the array has to start at zero (every word read was
- * written by an earlier kernel of the same call).
+ * written earlier in the same call).
  * SKRULL_EINVAL, besides skrull_attn_bwd's cases, when info.bwd_workspace_bytes exceeds
  * SKRULL_STATIC_SCRATCH_BYTES (strerror names both sizes).
  * Every call on one GPU uses the same array: calls that may overlap on one GPU (two
@@ -275,7 +280,8 @@ const char *skrull_attn_strerror(int code);
 /*
  * Measurement aid (not part of the method).  While enabled, skrull_attn_fwd and
  * skrull_attn_bwd bracket each of their kernels with HIP events recorded on
- * the caller's stream.  skrull_attn_profile_read waits for the events of the
+ * the caller's stream; a backward then makes dQ and dK/dV two launches, which are slower together than
+ * the one it makes otherwise.  skrull_attn_profile_read waits for the events of the
  * most recent forward and backward calls and returns the kernel durations in
  * milliseconds: ms[0] forward, ms[1] always 0 (D = rowsum(dO*O) is formed inside
  * the dQ kernel), ms[2] dK/dV with its reduction, ms[3] dQ
@@ -300,7 +306,8 @@ int skrull_attn_profile_read(float ms[4]);
  *   uint32 one      1
  * Records of the forward kernel come first, then the dQ kernel's, then the dK/dV kernel's;
  * skrull_attn_trace_layout gives, for a plan, the first record and the number of records
- * (= workgroups; those that leave at once write nothing) of the three.  A call whose records
+ * (= workgroups; those that leave at once write nothing) of the three.  (One launch for dQ and
+ * dK/dV writes the same records, where its dQ items are larger fewer of them.)  A call whose records
  * do not fit `bytes` returns SKRULL_EINVAL.  skrull_attn_trace(NULL, 0) switches it off.
  * Untraced calls pay one scalar branch per workgroup.  skrull_attn_bwd_static is never traced.
  */

@@ -58,7 +58,7 @@ class PlanInfo(ctypes.Structure):
 
     @property
     def dq_waves(self):
-        """Wavefronts of a dQ workgroup that runs."""
+        """Wavefronts of a dQ workgroup where dQ is a launch of its own."""
         return self.shapes >> 8 & 255
 
     @property

@@ -70,7 +70,10 @@ struct BwdParams {
     int32_t queue_stride;             // their dies' distance
     int32_t n_work_dq, n_work_dkv;    // work items: what a plain grid would have as workgroups
     int32_t *clear;                   // null, or what the stream's next call will use: zeroed by this one
-    int32_t *rows_ready;              // one launch for both: dQ work items whose -D and LSE dK/dV may read
+    // one launch for all: dQ work items whose -D and LSE dK/dV may read; parts of shared dK/dV items whose sums are
+    // stored, of each (item, KV head) or, for very many of these, of all of them; pieces of the sums of these that have been handed out
+    int32_t *rows_ready, *parts_stored, *next_sum;
+    int32_t n_parts;                  // work items that are parts of shared dK/dV items; 0: they are counted for each item
 };
 
 // ---------------------------------------------------------------------------
@@ -690,6 +693,7 @@ constexpr int PAIRS_8W = 4, PAIRS_12W = 6;
 // over the query heads and tiles that see them.
 struct KeyBlock {
     int c, part, parts;            // KV head; part of the work, and of how many
+    int shared;                    // 0, or 1 + which counter counts this work item: it stands for a part of a shared item
     int head_lo, g;                // the query heads this part walks over
     int piece, pieces;             // which piece of that walk, and of how many
     int kv0, item_rows;            // first key position; key rows from there on that belong to the item
@@ -716,6 +720,7 @@ __device__ __forceinline__ KeyBlock key_block(const P prm, int SUB, int bid)
         item = u.z & ((1 << SKRULL_UNIT_SHIFT) - 1);
         r.part = u.z >> SKRULL_UNIT_SHIFT;
         r.parts = u.w;
+        r.shared = item < n_split ? 1 + item * Hkv + r.c : 0;
     } else {
         const int first = prm->keys.n_whole_first * whole, split = n_split * prm->keys.parts * whole;
         const bool is_split = bid >= first && bid < first + split;
@@ -731,6 +736,7 @@ __device__ __forceinline__ KeyBlock key_block(const P prm, int SUB, int bid)
         seq = it.x;
         block = it.y;
         r.parts = 1;
+        r.shared = is_split ? 1 + item * Hkv + r.c : 0;
         if (is_split) {
             const int chain = prm->keys.chain;
             r.parts = chain == 0 ? prm->keys.parts
@@ -764,15 +770,21 @@ __device__ __forceinline__ KeyBlock key_block(const P prm, int SUB, int bid)
 }
 
 // Does work item `bid`, whose keys are `kb`; returns the next one and leaves its keys in `kb`.
+// A part of a shared item (KeyBlock::shared) is stored.
+__device__ __forceinline__ void count_part(int shared)
+{
+    const kernarg_t<BwdParams> prm = kernarg<BwdParams>();
+    count_one(prm->parts_stored + (prm->n_parts ? 0 : shared - 1));
+}
+
 template <int D, int PAIRS>
 struct DkvLds {
     static constexpr int SLOT = 2 * TileGeom<D>::BYTES + 2 * TILE_ROWS * 4;  // Q rows | dO rows | LSE*log2e | D
-    static constexpr int P = 3 * SLOT;                                       // P exchange [pair][round parity][16-row block][lane*16]
-    static constexpr int BYTES = P + PAIRS * 2 * 4 * 1024;
+    static constexpr int RING = 3 * SLOT, P = PAIRS * 2 * 4 * 1024;          // P: exchange [pair][round parity][16-row block][lane*16]
 };
 
 template <int D, int PAIRS, bool ONE>
-__device__ __forceinline__ int dkv_work(const int bid, KeyBlock &kb, DkvFeed &feed, unsigned char *lds, bool &rows_seen)
+__device__ __forceinline__ int dkv_work(const int bid, KeyBlock &kb, DkvFeed &feed, unsigned char *ring, unsigned char *exchange, bool &rows_seen, int &part_owed)
 {
     const kernarg_t<BwdParams> prm = kernarg<BwdParams>();
     constexpr int NWP = 2 * PAIRS;   // wavefronts: PAIRS S waves, then PAIRS dP waves
@@ -781,8 +793,8 @@ __device__ __forceinline__ int dkv_work(const int bid, KeyBlock &kb, DkvFeed &fe
     constexpr int TB = TileGeom<D>::BYTES;
     typedef DkvLds<D, PAIRS> Lds;
     constexpr int SLOT = Lds::SLOT;
-    unsigned char (*lds_ring)[SLOT] = (unsigned char (*)[SLOT])lds;
-    unsigned char (*lds_p)[2][4][1024] = (unsigned char (*)[2][4][1024])(lds + Lds::P);
+    unsigned char (*lds_ring)[SLOT] = (unsigned char (*)[SLOT])ring;
+    unsigned char (*lds_p)[2][4][1024] = (unsigned char (*)[2][4][1024])exchange;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -807,7 +819,7 @@ __device__ __forceinline__ int dkv_work(const int bid, KeyBlock &kb, DkvFeed &fe
     // this wave's staging region: ring slots 1 and 2 hold no tile at the start and the end of a
     // pass (eight regions); the waves beyond the eighth use the P exchange area
     typedef WaveStage<D> Stage;
-    static_assert(8 * Stage::BYTES <= 2 * SLOT && (NWP - 8) * Stage::BYTES <= Lds::BYTES - Lds::P,
+    static_assert(8 * Stage::BYTES <= 2 * SLOT && (NWP - 8) * Stage::BYTES <= Lds::P,
                   "staging regions do not fit the idle part of the LDS");
     const uint32_t stage = wave < 8 ? ring0 + SLOT + (uint32_t)wave * Stage::BYTES
                                     : lds_addr(&lds_p[0][0][0][0]) + (uint32_t)(wave - 8) * Stage::BYTES;
@@ -883,6 +895,7 @@ __device__ __forceinline__ int dkv_work(const int bid, KeyBlock &kb, DkvFeed &fe
     fetch(head0, tile0, 0);
     wait_vmem();
     __syncthreads();
+    if (ONE && part_owed && tid == 0) count_part(part_owed);  // (everyone's stores of the item before are done)
 
     // Round T: ring slot T % 3 holds (head t % g, query tile n_qt - 1 - t / g), t = r0 + T: heads
     // innermost, query tiles from the end of the sequence down to the block's
@@ -1197,54 +1210,153 @@ __device__ __forceinline__ int dkv_work(const int bid, KeyBlock &kb, DkvFeed &fe
                      (uint32_t)out->Hkv * D * 2, wj0, kvl);
         } else if (my_j < kvl) {
             const size_t rows = out->keys.part_rows ? out->keys.part_rows : out->total_k;
-            const size_t at = (part * rows + part_row + (my_j - kv0)) * out->Hkv + c;
-            store_rows_f32<TT>((role == 0 ? out->dv_part : out->dk_part) + at * D, acc, h);
+            float *sums = role == 0 ? out->dv_part : out->dk_part;
+            if (ONE) {
+                const int valid = min(32, kvl - wj0);
+                const size_t at = ((size_t)part * out->Hkv + c) * rows + part_row + (wj0 - kv0);
+                AccTile<D>::store(shared_buffer(sums + at * D, valid * D * 4), acc, n, h, valid);
+            } else {
+                const size_t at = (part * rows + part_row + (my_j - kv0)) * out->Hkv + c;
+                store_rows_f32<TT>(sums + at * D, acc, h);
+            }
         }
     }
     trace_end(out->trace_dkv, trace_t0, bid);
+    part_owed = kb.shared;
     kb = uniform(kb_next);
     return next;
 }
 
 // Does dK/dV work items until none is left.
 template <int D, int PAIRS, bool ONE>
-__device__ __forceinline__ void dkv_loop(DkvFeed &feed, unsigned char *lds)
+__device__ __forceinline__ void dkv_loop(DkvFeed &feed, unsigned char *ring, unsigned char *exchange)
 {
     bool rows_seen = !ONE;
+    int part_owed = 0;
     int w = feed.first(feed.begin());
     KeyBlock kb = key_block(kernarg<BwdParams>(), 32 * PAIRS, max(w, 0));
     while (w >= 0) {
         if (kb.item_rows > 0) {
-            w = dkv_work<D, PAIRS, ONE>(w, kb, feed, lds, rows_seen);
+            w = dkv_work<D, PAIRS, ONE>(w, kb, feed, ring, exchange, rows_seen, part_owed);
             if (w == kQueueEmpty) {
+                if (ONE && part_owed) {  // (the search takes microseconds)
+                    wait_vmem();
+                    __syncthreads();
+                    if (threadIdx.x == 0) count_part(part_owed);
+                    part_owed = 0;
+                }
                 w = feed.other();
                 kb = key_block(kernarg<BwdParams>(), 32 * PAIRS, max(w, 0));
             }
         } else {  // the item has no second pass (the whole workgroup agrees)
+            if (ONE && kb.shared && threadIdx.x == 0) count_part(kb.shared);
             w = feed.again();
             kb = key_block(kernarg<BwdParams>(), 32 * PAIRS, max(w, 0));
         }
+    }
+    if (ONE && part_owed) {
+        wait_vmem();
+        __syncthreads();
+        if (threadIdx.x == 0) count_part(part_owed);
     }
 }
 
 template <int D, int PAIRS>
 __global__ __launch_bounds__(128 * PAIRS, PAIRS == PAIRS_12W ? 3 : 2) void dkv_kernel(const BwdParams prm)
 {
-    __shared__ __align__(16) unsigned char lds[DkvLds<D, PAIRS>::BYTES];
+    // (two arrays: in one, the compiler took a store to the exchange for one to the ring, and dK/dV of long chains 0.5 % longer)
+    __shared__ __align__(16) unsigned char ring[DkvLds<D, PAIRS>::RING], exchange[DkvLds<D, PAIRS>::P];
     __shared__ int work_slot[2];
     DkvFeed feed{{}, 0, 0, work_slot};
-    dkv_loop<D, PAIRS, false>(feed, lds);
+    dkv_loop<D, PAIRS, false>(feed, ring, exchange);
 }
 
-// dQ, then dK/dV, in one launch: a workgroup that finds no dQ item left goes on with dK/dV items, so that the chip has
+// Sums of the partial gradients of the items that several workgroups shared, rounded once (the same as
+// dkv_reduce_kernel, in the launch that leaves them): a 32-row tile of an item, dK and dV, at a time, handed out
+// to workgroups that find no dK/dV item left; a few register quads of the tile (AccTile) to a wavefront, of all parts at once.  The items with the
+// longest chains come first, as their parts did, so most pieces wait for nothing.  A wait ends: the parts are all handed out by
+// then, to workgroups that wait for nothing before they have counted theirs.
+template <int D, int PAIRS>
+__device__ __forceinline__ void sums_loop(int *slot)
+{
+    constexpr int QUADS = AccTile<D>::QUADS, MINE = (2 * QUADS + 2 * PAIRS - 1) / (2 * PAIRS);  // quads of a wavefront
+    constexpr int AT_ONCE = kMaxParts;  // parts asked for at once
+    const kernarg_t<BwdParams> prm = kernarg<BwdParams>();
+    const int Hkv = prm->Hkv, BN = prm->keys.BN, per_item = (BN + 31) / 32;
+    const int n_sums = prm->keys.n_split * Hkv * per_item;
+    auto claim = [&]() __attribute__((always_inline)) {
+        return __hip_atomic_fetch_add(prm->next_sum + opaque(0), opaque(1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    int next = 0;
+    if (threadIdx.x == 0) next = claim();
+    const int lane = threadIdx.x & 63, n = lane & 31, h = lane >> 5, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const size_t part_rows = prm->keys.part_rows ? prm->keys.part_rows : prm->total_k;
+    for (;;) {
+        __syncthreads();  // (everyone has read the slot)
+        if (threadIdx.x == 0) *slot = next;
+        __syncthreads();
+        const int w = __builtin_amdgcn_readfirstlane(*slot);
+        if (w >= n_sums) break;
+        if (threadIdx.x == 0) next = claim();
+        const int x = w / per_item, item = x / Hkv, c = x - item * Hkv, row0 = (w - x * per_item) * 32;
+        const i32x4 it = plan_value((const i32x4 *)prm->dkv_items, item);
+        const int kv0 = it.y * BN;
+        const int rows = min(32, min(BN, plan_value(prm->kv_len, it.x) - kv0) - row0);
+        const int krow = plan_value(prm->cu_k, it.x) + kv0 + row0;
+        const int chain = prm->keys.chain;
+        const int parts = chain == 0 ? prm->keys.parts : min(prm->keys.parts, (it.w * prm->keys.g + chain - 1) / chain);
+        if (rows <= 0) continue;
+        if (threadIdx.x == 0) {
+            const int32_t *stored = prm->parts_stored + (prm->n_parts ? 0 : x);
+            const int all = prm->n_parts ? prm->n_parts : parts * prm->keys.passes;
+            while (__hip_atomic_load(stored, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < all) __builtin_amdgcn_s_sleep(4);
+        }
+        __syncthreads();
+        const size_t first = c * part_rows + (prm->keys.part_rows ? (size_t)item * BN + row0 : (size_t)krow);
+        const size_t step = part_rows * Hkv * D;
+        f32x4 a[MINE];
+        for (int p0 = 0; p0 < parts; p0 += AT_ONCE) {
+            u32x4 b[AT_ONCE][MINE];
+#pragma unroll
+            for (int k = 0; k < AT_ONCE; ++k)
+                if (p0 + k < parts) {
+#pragma unroll
+                    for (int j = 0; j < MINE; ++j) {
+                        const int i = wave * MINE + j;  // (past dV's last quad: reads as zero)
+                        const float *sums = (i < QUADS ? prm->dk_part : prm->dv_part) + first * D + (p0 + k) * step;
+                        b[k][j] = __builtin_amdgcn_raw_buffer_load_b128(shared_buffer(sums, i < 2 * QUADS ? rows * D * 4 : 0), AccTile<D>::offset(i % QUADS, n, h, rows), 0, kPastL2);
+                    }
+                }
+#pragma unroll
+            for (int k = 0; k < AT_ONCE; ++k)
+                if (p0 + k < parts) {
+#pragma unroll
+                    for (int j = 0; j < MINE; ++j) a[j] = p0 + k == 0 ? __builtin_bit_cast(f32x4, b[k][j]) : a[j] + __builtin_bit_cast(f32x4, b[k][j]);
+                }
+        }
+#pragma unroll
+        for (int j = 0; j < MINE; ++j) {
+            const int i = wave * MINE + j;
+            const float mul = i < QUADS ? prm->scale : 1.0f;
+            const float a0 = a[j][0] * mul, a1 = a[j][1] * mul, a2 = a[j][2] * mul, a3 = a[j][3] * mul;
+            if (i < 2 * QUADS && n < rows)
+                *(uint2 *)((i < QUADS ? prm->dk : prm->dv) + ((size_t)(krow + n) * Hkv + c) * D + 8 * (i % QUADS) + 4 * h) = make_uint2(pack_bf16(a0, a1), pack_bf16(a2, a3));
+        }
+    }
+}
+
+// dQ, then dK/dV, then sums, in one launch: a workgroup that finds no dQ item left goes on with dK/dV items, so that the chip has
 // work while the last dQ items end.  These need -D and LSE*log2(e) of rows that other workgroups may still be at, but
 // only from their start: a dQ item forms both before its first product, so where every item has been handed out all that is
 // needed follows within microseconds.  The wait for it ends: items are only handed out to workgroups that run, and none
 // of these waits before it has counted its items as ready.
 // As two launches, from a workgroup's last dQ item to the first dK/dV item on its compute unit 14 to 19 us pass (the longest item's
-// end, the end of one launch and the start of the next), 2.5 this way.  Backward, two launches and this: 26,624 tokens in 64 sequences, 14/2 heads of 64,
-// 212 and 198 us; 16,384 in 20 229 and 212; 13,312 in 10, 28/4 heads of 128, 845 and 833; 32,768 of 16 to 1,024, 32/8 heads of 128,
-// 639 and 629; long chains the same within 0.3 %.  dQ workgroups have as many wavefronts as those of dK/dV here, 8 or 12, and
+// end, the end of one launch and the start of the next), 2.5 this way.  Then the sums of shared dK/dV items, while the last of the
+// other items end; from dK/dV to the next call's dQ over a launch for them 17 us passed.  Backward in three launches, with
+// the sums in a second one, and this: 26,624 tokens in 64 sequences, 14/2 heads of 64, 214, 197 and 193 us; 16,384 in 20 232, 215 and 211;
+// 13,312 in 10, 28/4 heads of 128, 837, 828 and 822; 32,768 of 16 to 1,024, 32/8 heads of 128, which shares none, 634 and 629; long chains
+// the same within 0.5 %; 932 tokens, 4/4 heads of 64, 29 and 22.6.  (With one counter for the parts of all items, which the sums then wait
+// for at the end, the sums cost as much as in a launch of their own: 209 us where this takes 196.)  dQ workgroups have as many wavefronts as those of dK/dV here, 8 or 12, and
 // leave some without work where the plan's units are smaller.  Launches of many units of 4 stay two: three such workgroups share a
 // compute unit there (slices of three long sequences, 14/2 heads of 64: 4.68 ms, in one launch 5.1).
 template <int D, int PAIRS>
@@ -1252,16 +1364,22 @@ __global__ __launch_bounds__(128 * PAIRS, PAIRS == PAIRS_12W ? 3 : 2) void bwd_k
 {
     constexpr int NW = 2 * PAIRS;
     constexpr bool PIPED = NW == NWQ_LARGE;
-    constexpr int BYTES = DqLds<D, NW, PIPED>::BYTES > DkvLds<D, PAIRS>::BYTES ? DqLds<D, NW, PIPED>::BYTES : DkvLds<D, PAIRS>::BYTES;
-    __shared__ __align__(16) unsigned char lds[BYTES];
+    typedef DqLds<D, NW, PIPED> Dq;
+    typedef DkvLds<D, PAIRS> Dkv;
+    // (dK/dV's two arrays are one where there is no room for them beside each other)
+    constexpr int APART = D == 64 ? Dkv::P : 16, TOGETHER = D == 64 ? Dkv::RING : Dkv::RING + Dkv::P;
+    __shared__ __align__(16) unsigned char lds[Dq::BYTES > TOGETHER ? Dq::BYTES : TOGETHER], apart[APART];
     __shared__ int work_slot[2];
     if (prm.clear && blockIdx.x == 0) clear_state(prm.clear, SKRULL_BWD_STATE_INTS);
     {
         DqFeed feed{{}, 0, 0, work_slot};
         dq_loop<D, NW, PIPED, true>(feed, lds);
     }
-    DkvFeed feed{{}, 0, 0, work_slot};
-    dkv_loop<D, PAIRS, true>(feed, lds);
+    {
+        DkvFeed feed{{}, 0, 0, work_slot};
+        dkv_loop<D, PAIRS, true>(feed, lds, D == 64 ? apart : lds + Dkv::RING);
+    }
+    if (kernarg<BwdParams>()->keys.n_split > 0) sums_loop<D, PAIRS>(work_slot);
 }
 
 // Sum of the partial gradients of the items that several workgroups shared, rounded once:
@@ -1308,7 +1426,7 @@ hipError_t clear_queues_first(const BwdParams &prm, hipStream_t st)
 
 int dkv_pairs(const skrull_attn_plan_t *p) { return (p->d == 64 && p->BN == 32 * PAIRS_12W) ? PAIRS_12W : PAIRS_8W; }
 
-RowLaunch rows_dq(const skrull_attn_plan_t *p)
+RowLaunch rows_dq_alone(const skrull_attn_plan_t *p)
 {
     if (p->d == 128) return row_launch<dq_kernel<128, NWQ_LARGE>>(p, NWQ_LARGE);
     if (p->dq_waves == NWQ_SMALL && p->dq_piped) return row_launch<dq_kernel<64, NWQ_SMALL, true>>(p, NWQ_SMALL);
@@ -1317,13 +1435,32 @@ RowLaunch rows_dq(const skrull_attn_plan_t *p)
     return row_launch<dq_kernel<64, NWQ_LARGE>>(p, NWQ_LARGE);
 }
 
-template <int D>
-hipError_t launch_sums(const skrull_attn_plan_t *p, const BwdParams &prm, hipStream_t st)
+template <int D, int PAIRS> bool chip_known() { return resident_of<bwd_kernel<D, PAIRS>>(128 * PAIRS) > 0; }
+
+// Whether a backward is one launch.
+bool is_one(const skrull_attn_plan_t *p)
 {
-    if (p->n_split <= 0) return hipSuccess;
-    const dim3 grid((unsigned)p->n_split * p->Hkv, (unsigned)(p->BN + REDUCE_ROWS<D> - 1) / REDUCE_ROWS<D>, 2);
-    dkv_reduce_kernel<D><<<grid, 256, 0, st>>>(prm);
-    return hipGetLastError();
+    if (p->d == 128) return chip_known<128, PAIRS_8W>();
+    if (p->dq_waves == NWQ_SMALL && rows_dq_alone(p).queued) return false;
+    if (dkv_pairs(p) == PAIRS_12W) return chip_known<64, PAIRS_12W>();
+    return p->dq_waves <= 8 && chip_known<64, PAIRS_8W>();
+}
+
+// The work items of dQ in one launch with dK/dV, where dK/dV begins on the compute units that dQ leaves.  Few long units, which a
+// dQ launch of its own would wait for, are no longer what counts; at head_dim 64 the row blocks of a KV group are then
+// better put together, 12 to a workgroup, on fewer compute units (skrull_attn_plan::dq_packed), unless dQ leaves half of the chip
+// anyway.  Units for workgroups of 4, more than there are larger ones at once, are made as large as these: 560 such units
+// took two rounds (4,925 tokens in 10 sequences, 14/2 heads: backward 61 us, 58 as two launches, 43 with units of 12).
+RowLaunch rows_dq_first(const skrull_attn_plan_t *p)
+{
+    const RowLaunch alone = rows_dq_alone(p);
+    if (p->d == 128) return alone;
+    const bool wide = dkv_pairs(p) == PAIRS_12W;
+    const int at_once = wide ? resident_of<bwd_kernel<64, PAIRS_12W>>(128 * PAIRS_12W) : resident_of<bwd_kernel<64, PAIRS_8W>>(128 * PAIRS_8W);
+    if (wide && p->dq_packed && 2 * alone.n_work > at_once) return row_launch<dq_kernel<64, NWQ_WIDE>>(p, NWQ_WIDE, true);
+    if (p->dq_waves == NWQ_SMALL && !p->dq_piped && alone.n_work > at_once)
+        return wide ? row_launch<dq_kernel<64, NWQ_WIDE>>(p, NWQ_WIDE) : row_launch<dq_kernel<64, NWQ_LARGE>>(p, NWQ_LARGE);
+    return alone;
 }
 
 template <int D, auto KernelQ, auto KernelKV>
@@ -1346,7 +1483,12 @@ hipError_t launch_pair(const skrull_attn_plan_t *p, BwdParams prm, int threads_q
     if (ev) (void)hipEventRecord(ev[1], st);
     KernelKV<<<launch_size<KernelKV>(threads_kv, prm.n_work_dkv, queued_kv), threads_kv, 0, st>>>(prm);
     e = hipGetLastError();
-    if (e == hipSuccess) e = launch_sums<D>(p, prm, st);
+    if (e != hipSuccess) return e;
+    if (p->n_split > 0) {
+        const dim3 grid((unsigned)p->n_split * p->Hkv, (unsigned)(p->BN + REDUCE_ROWS<D> - 1) / REDUCE_ROWS<D>, 2);
+        dkv_reduce_kernel<D><<<grid, 256, 0, st>>>(prm);
+        e = hipGetLastError();
+    }
     if (e == hipSuccess && ev) (void)hipEventRecord(ev[2], st);
     return e;
 }
@@ -1361,24 +1503,12 @@ hipError_t launch_one(const skrull_attn_plan_t *p, const BwdParams &prm, hipStre
     const int64_t work = (int64_t)prm.n_work_dq + prm.n_work_dkv;
     const int resident = resident_of<bwd_kernel<D, PAIRS>>(128 * PAIRS);
     bwd_kernel<D, PAIRS><<<(int)(work < resident ? work : resident), 128 * PAIRS, 0, st>>>(prm);
-    hipError_t e = hipGetLastError();
-    return e == hipSuccess ? launch_sums<D>(p, prm, st) : e;
+    return hipGetLastError();
 }
-template <int D, int PAIRS> bool chip_known() { return resident_of<bwd_kernel<D, PAIRS>>(128 * PAIRS) > 0; }
-
-// Whether a backward is one launch.
-bool is_one(const skrull_attn_plan_t *p)
-{
-    if (p->d == 128) return chip_known<128, PAIRS_8W>();
-    if (p->dq_waves == NWQ_SMALL && rows_dq(p).queued) return false;
-    if (dkv_pairs(p) == PAIRS_12W) return chip_known<64, PAIRS_12W>();
-    return p->dq_waves <= 8 && chip_known<64, PAIRS_8W>();
-}
-
 template <int D>
-hipError_t launch_d(const skrull_attn_plan_t *p, const BwdParams &prm, hipStream_t st, hipEvent_t *ev)
+hipError_t launch_d(const skrull_attn_plan_t *p, const BwdParams &prm, bool one, hipStream_t st, hipEvent_t *ev)
 {
-    if (!ev && is_one(p)) {  // (events are to time dQ and dK/dV by themselves)
+    if (one) {
         if constexpr (D == 64)
             if (dkv_pairs(p) == PAIRS_12W) return launch_one<D, PAIRS_12W>(p, prm, st);
         return launch_one<D, PAIRS_8W>(p, prm, st);
@@ -1399,7 +1529,7 @@ hipError_t launch_d(const skrull_attn_plan_t *p, const BwdParams &prm, hipStream
 
 }  // namespace
 
-int grid_dq(const skrull_attn_plan_t *p) { return rows_dq(p).n_work; }
+int grid_dq(const skrull_attn_plan_t *p) { return rows_dq_alone(p).n_work; }
 
 static KeyMap map_dkv(const skrull_attn_plan_t *p)
 {
@@ -1421,8 +1551,9 @@ hipError_t launch_bwd(const skrull_attn_plan_t *p, const void *q, const void *k,
 {
     BwdParams prm;
     prm.trace_dq = trace;
-    const RowLaunch rows_q = rows_dq(p);
-    prm.trace_dkv = trace ? trace + rows_q.n_work : nullptr;
+    const bool one = is_one(p) && !ev;  // (events are to time dQ and dK/dV by themselves)
+    const RowLaunch rows_q = one ? rows_dq_first(p) : rows_dq_alone(p);
+    prm.trace_dkv = trace ? trace + grid_dq(p) : nullptr;  // (one launch has as many dQ items or fewer)
     prm.q = (const uint16_t *)q; prm.k = (const uint16_t *)k; prm.v = (const uint16_t *)v;
     prm.d_o = (const uint16_t *)d_o; prm.o = (const uint16_t *)o; prm.lse = lse; prm.delta = delta;
     prm.lse2 = delta + (size_t)p->Hq * p->total_q;
@@ -1448,6 +1579,9 @@ hipError_t launch_bwd(const skrull_attn_plan_t *p, const void *q, const void *k,
     }
     std::unique_lock<std::mutex> held(p->streams->lock);
     const int at = p->streams->find(st);
+    prm.n_parts = 0;
+    if (at < 0 || (int64_t)p->n_split * p->Hkv > SKRULL_ITEM_COUNTERS)
+        prm.n_parts = (p->dkv_units ? p->n_dkv_units - (p->n_dkv - p->n_split) : p->n_split * p->split_parts) * p->Hkv * prm.keys.passes;
     if (at >= 0) {
         const uint32_t turn = p->streams->of[at].bwd;
         int32_t *sets = p->stream_states + at * SKRULL_STREAM_STATE_INTS + 2 * SKRULL_QUEUE_INTS;
@@ -1456,16 +1590,20 @@ hipError_t launch_bwd(const skrull_attn_plan_t *p, const void *q, const void *k,
         prm.queue_dq = (WorkQueue *)mine;
         prm.queue_dkv = (WorkQueue *)(mine + SKRULL_QUEUE_INTS);
         prm.rows_ready = mine + 2 * SKRULL_QUEUE_INTS;
+        prm.next_sum = prm.rows_ready + 32;
+        prm.parts_stored = prm.rows_ready + (prm.n_parts ? 64 : 128);
         prm.clear = sets + (~turn & 1) * SKRULL_BWD_STATE_INTS;
     } else {
         held.unlock();
         prm.queue_stride = kQueueStrideWorkspace;
         prm.queue_dq = (WorkQueue *)((char *)prm.dk_part - 256);
         prm.queue_dkv = prm.queue_dq + 8 * kQueueStrideWorkspace;
-        prm.rows_ready = (int32_t *)&prm.queue_dq->taken[0];  // (a word of the queues that the backward's do not use)
+        prm.rows_ready = (int32_t *)&prm.queue_dq[0].taken[0];  // (words of the queues that the backward's do not use)
+        prm.parts_stored = (int32_t *)&prm.queue_dq[1].taken[0];
+        prm.next_sum = (int32_t *)&prm.queue_dq[2].taken[0];
         prm.clear = nullptr;
     }
-    const hipError_t e = p->d == 128 ? launch_d<128>(p, prm, st, ev) : p->d == 64 ? launch_d<64>(p, prm, st, ev) : hipErrorInvalidValue;
+    const hipError_t e = p->d == 128 ? launch_d<128>(p, prm, one, st, ev) : p->d == 64 ? launch_d<64>(p, prm, one, st, ev) : hipErrorInvalidValue;
     if (at >= 0) {
         if (e == hipSuccess) ++p->streams->of[at].bwd;
         else p->streams->give_up(at);

@@ -13,8 +13,10 @@ struct WorkQueue;
 // forward calls of one plan that may be in flight at once (each takes one queue slot in turn)
 #define SKRULL_FWD_QUEUE_SLOTS 64
 #define SKRULL_QUEUE_INTS 256  // of a queue: eight dies' queues, a 128-byte line each
-// of what the workgroups of a backward share: the queues of dQ and of dK/dV, and counters, a line each
-#define SKRULL_BWD_STATE_INTS (2 * SKRULL_QUEUE_INTS + 128)
+// of what the workgroups of a backward share: the queues of dQ and of dK/dV, counters, a line each, and one more for each
+// (shared dK/dV item, KV head), up to a limit
+#define SKRULL_ITEM_COUNTERS 1024
+#define SKRULL_BWD_STATE_INTS (2 * SKRULL_QUEUE_INTS + 128 + SKRULL_ITEM_COUNTERS)
 
 // Queues that need no kernel to clear them before a launch.  The calls of one stream run one after another, so a
 // plan keeps two sets for each stream it is used on: a launch works with one and clears the other, which the
@@ -67,6 +69,7 @@ struct skrull_attn_plan {
     int32_t wg_query_rows;  // query rows per forward / dQ workgroup, asked for or chosen: 128 or 256; what runs follows
     int32_t fwd_waves, dq_waves;  // wavefronts of a forward / dQ workgroup: 4, 8 or 12
     bool dq_piped;                // dQ of 4: pipelined, two workgroups per compute unit
+    bool dq_packed;               // in one launch with dK/dV of 12 wavefronts: dQ units of 12 row blocks whatever dq_waves is
     // dK/dV items that several workgroups share (the first n_split of the sorted list), and how:
     // an item of cost c takes min(split_parts, ceil(c * heads per group / split_chain)) of them
     // (split_chain 0: split_parts).  Where there is no list of units, n_whole_first more items are handed out before those.

@@ -141,19 +141,20 @@ struct RowLaunch {
     int n_work;   // what a plain grid has as workgroups
     bool queued;  // more than the chip holds at once
 };
+// `packed`: neighbouring row blocks to a workgroup also where all run at once.
 template <auto Kernel>
-static RowLaunch row_launch(const skrull_attn_plan_t *p, int NW)
+static RowLaunch row_launch(const skrull_attn_plan_t *p, int NW, bool packed = false)
 {
     RowLaunch r{row_map(p, NW), 0, false};
     const int resident = resident_of<Kernel>(64 * NW);
     const int per_head = (p->BM + 32 * NW - 1) / (32 * NW);  // workgroups of an item's rows of one head
-    if ((int64_t)p->n_fwd * p->Hq * per_head <= resident) {
+    if (!packed && (int64_t)p->n_fwd * p->Hq * per_head <= resident) {
         r.rows.units = nullptr;
         r.rows.parts = r.rows.g * per_head;
     }
     r.n_work = r.rows.units ? p->n_units[NW / 4 - 1] * p->Hkv : p->n_fwd * p->Hkv * r.rows.parts;
     r.queued = resident > 0 && r.n_work > resident;
-    r.rows.spread = !r.queued;
+    r.rows.spread = !r.queued && !packed;
     return r;
 }
 __device__ __forceinline__ int quotient(int x, uint64_t inv) { return (int)(((uint64_t)(uint32_t)x * inv) >> 40); }
@@ -320,6 +321,33 @@ __device__ __forceinline__ bf16x8 acc_to_b(const f32x16 &s, int kb)
     return as_bf16x8(pk);
 }
 
+// 16 bytes per lane that other workgroups of this launch read or have written, at byte offset `voff` of a buffer: past this die's L2
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+constexpr int kPastL2 = 16;  // sc1
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t shared_buffer(const void *base, uint32_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00020000);
+}
+// A 32-column (t) x 32-row accumulator tile set as unrounded fp32, `valid` rows of it, in the order in which the lanes hold it:
+// register quad after register quad, of each first the lanes of half 0, then those of half 1.  (As rows, an instruction
+// would write 16 bytes each to 32 of them, which the L2 puts together but memory does not: dK/dV items with shared sums took 10 % longer.)
+template <int D>
+struct AccTile {
+    static constexpr int QUADS = D / 8;  // register quads
+    __device__ static __forceinline__ int offset(int quad, int n, int h, int valid) { return (2 * quad * valid + h * valid + n) * 16; }
+    template <int TT>
+    __device__ static __forceinline__ void store(__amdgpu_buffer_rsrc_t dst, const f32x16 (&acc)[TT], int n, int h, int valid)
+    {
+#pragma unroll
+        for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+            for (int vb = 0; vb < 4; ++vb) {
+                const f32x4 w = {acc[tt][4 * vb + 0], acc[tt][4 * vb + 1], acc[tt][4 * vb + 2], acc[tt][4 * vb + 3]};
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, w), dst, offset(4 * tt + vb, n, h, valid), 0, kPastL2);
+            }
+    }
+};
+
 // Store a 32-column (t) x 32-row accumulator tile set as unrounded fp32 rows of a [rows, H, D] float
 // tensor: this lane's row pointer `dst` (column 0), its half h.
 template <int TT>
@@ -349,7 +377,6 @@ __device__ __forceinline__ void store_rows_f32(float *dst, const f32x16 (&acc)[T
 // write and read; the caller makes sure no other wave uses the same bytes as a tile
 // meanwhile.  Regions are given as 32-bit LDS addresses.
 // ---------------------------------------------------------------------------
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef u32x4 __attribute__((address_space(3))) * lds_u4_t;
 typedef u32x2 __attribute__((address_space(3))) * lds_u2_t;

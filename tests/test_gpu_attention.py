@@ -1149,7 +1149,9 @@ def test_small_dq_shapes_change_no_bit(heads, S):
     ((14, 2), 64, [1, 31, 32, 33, 255, 256, 257, 300, 511, 700, 97] * 8, {"block_n": 192}, 12), ((14, 2), 64, [2500, 33, 129, 1], {"wg_query_rows": 256}, 8),
     ((4, 4), 64, [455, 283, 194, 1, 32], {}, 4), ((4, 4), 64, [64, 1], {}, 4), ((16, 16), 64, [1000, 65, 700] * 9, {"block_n": 128}, 8),
     ((4, 2), 64, [1, 65, 63] * 700, {"block_n": 64, "wg_query_rows": 256}, 8),   # (too many items for lists of units)
-    ((8, 2), 128, [700, 1, 64, 65, 900], {}, 8), ((28, 4), 128, [1700] + [300] * 30, {}, 8), ((3, 3), 128, [1500, 129, 64], {"block_n": 256}, 8)])
+    ((8, 2), 128, [700, 1, 64, 65, 900], {}, 8), ((28, 4), 128, [1700] + [300] * 30, {}, 8), ((3, 3), 128, [1500, 129, 64], {"block_n": 256}, 8),
+    # (parts of more shared items than there are counters for, with a list of units and without)
+    ((28, 4), 128, [300] * 90 + [1, 127], {"head_split": 7}, 8), ((4, 2), 64, [1, 65, 63] * 700, {"block_n": 64, "wg_query_rows": 256, "head_split": 2}, 8)])
 def test_dq_and_dkv_in_one_launch_and_in_two_give_the_same_bits(heads, d, S, kw, dq_waves):
     """dK/dV begins while the last dQ items are under way; with the kernels' times asked for it is a launch of its own.
     Fewer work items than the chip has places and more, shared dK/dV items, a slice and a cut beside them, and a workspace of
