@@ -1,6 +1,7 @@
 """torch.autograd wrapper around the library's forward / backward, for callers that
 train with PyTorch: argument marshalling and bookkeeping only, every step of the
-attention runs in the HIP kernels behind the C ABI."""
+attention runs in the HIP kernels behind the C ABI.  The marshalling is native code where
+nothing watches the call from Python, else the Function below: the same checks, outputs and errors."""
 from __future__ import annotations
 
 import torch
@@ -35,7 +36,41 @@ class _SkrullAttention(torch.autograd.Function):
         return dq, dk, dv, None
 
 
+def _watched():
+    """Whether something follows torch's calls from Python (a trace, a functorch transform, forward-mode
+    gradients, a mode, a compiler), which has to see the Function above."""
+    try:
+        return (torch._C._get_tracing_state() is not None or torch._C._functorch.peek_interpreter_stack() is not None
+                or torch.autograd.forward_ad._current_level >= 0 or torch._C._len_torch_dispatch_stack() > 0
+                or torch._C._len_torch_function_stack() > 0 or torch.compiler.is_compiling())
+    except AttributeError:   # (most of these are private to torch)
+        return True
+
+
+_native = None
+
+
+def _load_native():
+    """The same in native code (csrc/autograd.cpp), built in-tree with the library; raises if it is missing."""
+    global _native
+    B.lib()
+    try:
+        from . import _autograd
+    except ImportError as e:
+        raise RuntimeError("paper_2505_19609_amd/_autograd.so cannot be loaded: run __graft_entry__.build() "
+                           "(python -m paper_2505_19609_amd.build)") from e
+    _autograd.set_check(B._check)
+    _native = _autograd.attention
+    return _native
+
+
+_TENSORS = (torch.Tensor, torch.nn.Parameter)
+
+
 def skrull_attention(q, k, v, plan):
     """O = packed varlen causal attention of the micro-batch `plan` describes
     (a binding.Plan); differentiable with respect to q, k, v."""
+    if type(q) in _TENSORS and type(k) in _TENSORS and type(v) in _TENSORS and type(plan) is B.Plan and not _watched():
+        i = plan.info
+        return (_native or _load_native())(q, k, v, plan, i.total_q, i.total_k, i.num_q_heads, i.num_kv_heads, i.head_dim)
     return _SkrullAttention.apply(q, k, v, plan)

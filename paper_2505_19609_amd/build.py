@@ -10,6 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libskrull_attn.so")
+AUTOGRAD = os.path.join(HERE, "_autograd.so")
 SOURCES = ["api.hip", "plan.hip", "fwd.hip", "bwd.hip", "probe.hip", "dacp.cpp", "gds.cpp"]
 # packed fp32 VALU ops are switched off for all device code
 FLAGS = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-I" + os.path.join(ROOT, "include"),
@@ -47,11 +48,35 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _compile_autograd() -> str:
+    """Compile the native side of autograd.py against torch's C++ interface (host code only)."""
+    import sysconfig
+    from importlib.util import find_spec
+    torch_dir = os.path.dirname(find_spec("torch").origin)
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    obj = os.path.join(CSRC, "autograd.o")
+    subprocess.run(["g++", "-std=c++17", "-O2", "-fPIC", "-w", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+                    "-I" + os.path.join(ROOT, "include"), "-I" + os.path.join(torch_dir, "include"),
+                    "-I" + os.path.join(torch_dir, "include", "torch", "csrc", "api", "include"),
+                    "-I" + sysconfig.get_paths()["include"], "-I" + os.path.join(rocm, "include"),
+                    "-c", os.path.join(CSRC, "autograd.cpp"), "-o", obj], check=True)
+    return obj
+
+
+def _link_autograd(obj: str) -> None:
+    from importlib.util import find_spec
+    libs = os.path.join(os.path.dirname(find_spec("torch").origin), "lib")
+    subprocess.run(["g++", "-shared", "-fPIC", "-o", AUTOGRAD, obj, "-L" + libs, "-ltorch_python", "-ltorch", "-ltorch_cpu",
+                    "-lc10", "-lc10_hip", "-L" + HERE, "-l:" + os.path.basename(LIB), "-Wl,-rpath,$ORIGIN"], check=True)
+
+
 def build_library(jobs: int = 4) -> str:
-    """Compile every HIP source and link the shared library; returns its path."""
+    """Compile every HIP source and link the shared library, and the extension module beside it; returns the library's path."""
     with ThreadPoolExecutor(max_workers=jobs) as ex:
+        autograd = ex.submit(_compile_autograd)
         objs = list(ex.map(_compile, SOURCES))
-    subprocess.run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs], check=True)
+        subprocess.run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs], check=True)
+        _link_autograd(autograd.result())
     return LIB
 
 
