@@ -1447,14 +1447,18 @@ bool is_one(const skrull_attn_plan_t *p)
 }
 
 // The work items of dQ in one launch with dK/dV, where dK/dV begins on the compute units that dQ leaves.  Few long units, which a
-// dQ launch of its own would wait for, are no longer what counts; at head_dim 64 the row blocks of a KV group are then
-// better put together, 12 to a workgroup, on fewer compute units (skrull_attn_plan::dq_packed), unless dQ leaves half of the chip
-// anyway.  Units for workgroups of 4, more than there are larger ones at once, are made as large as these: 560 such units
+// dQ launch of its own would wait for, are no longer what counts; the row blocks of a KV group are then
+// better put together, as many as a workgroup has wavefronts, on fewer compute units, unless dQ leaves half of the chip
+// anyway.  At head_dim 64 see skrull_attn_plan::dq_packed; at 128 this is for what runs at once (else they are put together in
+// any case): of 50 backwards of 500 to 4,400 tokens 16 take 2 to 13 % less time, the others within 1 % of the same.  Units for workgroups of 4, more than there are larger ones at once, are made as large as these: 560 such units
 // took two rounds (4,925 tokens in 10 sequences, 14/2 heads: backward 61 us, 58 as two launches, 43 with units of 12).
 RowLaunch rows_dq_first(const skrull_attn_plan_t *p)
 {
     const RowLaunch alone = rows_dq_alone(p);
-    if (p->d == 128) return alone;
+    if (p->d == 128) {
+        if (!p->units[1] || p->Hq == p->Hkv || 2 * alone.n_work <= resident_of<bwd_kernel<128, PAIRS_8W>>(128 * PAIRS_8W)) return alone;
+        return row_launch<dq_kernel<128, NWQ_LARGE>>(p, NWQ_LARGE, true);
+    }
     const bool wide = dkv_pairs(p) == PAIRS_12W;
     const int at_once = wide ? resident_of<bwd_kernel<64, PAIRS_12W>>(128 * PAIRS_12W) : resident_of<bwd_kernel<64, PAIRS_8W>>(128 * PAIRS_8W);
     if (wide && p->dq_packed && 2 * alone.n_work > at_once) return row_launch<dq_kernel<64, NWQ_WIDE>>(p, NWQ_WIDE, true);
