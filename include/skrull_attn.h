@@ -103,7 +103,8 @@ typedef struct {
                                      sums of every row of K, also where fewer items are shared  */
     int32_t wg_query_rows;        /* query rows per forward / dQ workgroup asked for or chosen (128 or 256);
                                      `shapes` says what runs: dQ has the 128-row shape at head_dim 64
-                                     only, and a choice of 256 there may run with 384 rows or 128 */
+                                     only, and a choice of 256 may run with 128 (at head_dim 128 the
+                                     forward alone), at head_dim 64 with 384 */
     int32_t shapes;               /* workgroups that run: bits 0-7 wavefronts of a forward workgroup, bits
                                      8-15 of a dQ workgroup (4, 8 or 12, of 32 query rows each), bit 16
                                      set where dQ is the pipelined kernel; of dQ, where it is a launch of

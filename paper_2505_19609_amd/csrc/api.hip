@@ -403,6 +403,18 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
             if (!(once && (ends_small || (longest <= 8 && many)))) plan->dq_waves = plan->fwd_waves = 4;
         }
     }
+    // At head_dim 128, where the library chooses and has not taken the small shape, the forward has it by itself
+    //  for lists without long sequences from 6 blocks of 256 query rows x heads per compute unit on, where starts and ends of
+    //    units are most of the time and the second workgroup of a unit hides them: against 8 wavefronts 0 to 8 % less time (65
+    //    forwards, 4 % on average); from 4 to 6 blocks 5 % less to 6 % more, with sequences of 2,049 to 4,096 tokens within 3 % from 8 blocks
+    //    on, with longer ones up to 3 % more;
+    //  where 8 wavefronts would run at once: 7 % less time on 128 forwards, 17 at best, 2 % more at worst; but not where the longest sequence
+    //    has 257 to 384 tokens, whose last block is four wavefronts in any case (8 % more to 2 % less).
+    if (p->wg_query_rows == 0 && plan->wg_query_rows == 256 && plan->d == 128) {
+        const double blocks_per_cu = (double)plan->Hq * (double)totals.total_q / (256.0 * (double)compute_units);
+        const bool at_once = (int64_t)totals.n_fwd * plan->Hq <= compute_units || (plan->units[1] && (int64_t)plan->n_units[1] * plan->Hkv <= compute_units);
+        if ((longest_seq <= 2048 && blocks_per_cu >= 6.0) || (at_once && (longest_seq <= 256 || longest_seq > 384))) plan->fwd_waves = 4;
+    }
     // Of dQ workgroups of 4 three share a compute unit, each slower than one of the two that the pipelined kernel has
     // there.  Measured on 173 micro-batches, of 4 to 16 heads and 8 to 7,516 units, pipelined against not:
     //  up to two units per compute unit all run at once either way, and a unit is faster pipelined once it is long

@@ -1183,3 +1183,21 @@ def test_dq_and_dkv_in_one_launch_and_in_two_give_the_same_bits(heads, d, S, kw,
         for n in two:
             assert torch.equal(t[n].view(torch.int16), two[n].view(torch.int16)), (fill, n)
     plan.destroy()
+
+
+@pytest.mark.parametrize("S,waves", [([256], 4), ([257], 8), ([384], 8), ([385], 4), ([600, 33, 129], 4), ([700, 300, 900, 33, 1], 8),
+                                     ([1024] * 12, 4), ([1024] * 11, 8), ([2048] * 6, 4), ([2049] + [1024] * 11, 8)])
+def test_which_forward_of_head_dim_128_runs(S, waves):
+    """Both sides of the lines: at head_dim 128 the forward has workgroups of 4 wavefronts where 8 would all run at once, but for a
+    longest sequence of 257 to 384 tokens, and for lists of six blocks of rows and more per compute unit without a sequence of
+    more than 2,048 tokens; asked for 256 rows it has 8.  Same bits."""
+    heads = (32, 8)
+    w = W.Workload("fwd128", S, [1] * len(S), [0] * len(S), heads[0], heads[1], 128, 128 ** -0.5, 613)
+    out = run_library(w, backward=False, guard=True)
+    assert out["margins"] == [] and out["plan"].fwd_waves == waves and out["plan"].info.wg_query_rows == 256
+    ref = run_library(w, backward=False, vals=out["vals"], wg_query_rows=256)
+    assert ref["plan"].fwd_waves == 8
+    for k in ("o", "lse"):
+        assert np.array_equal(out[k], ref[k]), k
+    out["plan"].destroy()
+    ref["plan"].destroy()
