@@ -389,6 +389,8 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
     //    tokens, 4/4 heads: forward and dQ 26.7 us with 8, 30.5 with 4), and the next longest ones are enough shorter, or are many and
     //    short, where starts count (64 of 200, 4/4 heads: 31.8 and 34.3).  677 launches of eight head shapes against 8 wavefronts: forward and dQ
     //    together 0.929 of the time, 1.146 at worst, with 4 throughout; 0.927 and 1.033 this way.
+    //  A forward of which workgroups of 4 all run at once only because short items leave some of them without rows has those too: 5 to
+    //    31 % less time than with 8 on 13 forwards of 498 to 768 of them; a few more than fit, and it takes up to 50 % more.
     plan->fwd_waves = plan->wg_query_rows / 32;
     plan->dq_waves = plan->d == 64 ? plan->wg_query_rows / 32 : 8;
     if (p->wg_query_rows == 0 && plan->wg_query_rows == 256 && plan->d == 64) {
@@ -401,6 +403,8 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
             const bool once = plan->units[2] && of_eight <= compute_units, many = 2 * of_eight >= compute_units;
             const bool ends_small = full > 0 && (4 * full <= 3 * longest || (many && 5 * full <= 4 * longest + 4));
             if (!(once && (ends_small || (longest <= 8 && many)))) plan->dq_waves = plan->fwd_waves = 4;
+        } else if (plan->units[0] && (int64_t)plan->n_units[0] * plan->Hkv <= 3 * (int64_t)compute_units) {
+            plan->fwd_waves = 4;
         }
     }
     // At head_dim 128, where the library chooses and has not taken the small shape, the forward has it by itself

@@ -1201,3 +1201,17 @@ def test_which_forward_of_head_dim_128_runs(S, waves):
         assert np.array_equal(out[k], ref[k]), k
     out["plan"].destroy()
     ref["plan"].destroy()
+
+
+@pytest.mark.parametrize("heads,S,waves", [((14, 2), [300] * 21, 4), ((14, 2), [300] * 22, 12), ((16, 16), [100] * 48, 4), ((16, 16), [100] * 49, 8)])
+def test_forward_of_four_waves_that_runs_at_once(heads, S, waves):
+    """Both sides of the line: at head_dim 64 a forward has workgroups of 4 wavefronts, where dQ has 8, if the units that
+    have rows (at most three to a compute unit) all run at once.  Same bits as with 8."""
+    w = W.Workload("fwd64", S, [1] * len(S), [0] * len(S), heads[0], heads[1], 64, 0.125, 614)
+    out = run_library(w, backward=False, guard=True)
+    assert out["margins"] == [] and (out["plan"].fwd_waves, out["plan"].info.wg_query_rows) == (waves, 256)
+    ref = run_library(w, backward=False, vals=out["vals"], wg_query_rows=256)
+    for k in ("o", "lse"):
+        assert np.array_equal(out[k], ref[k]), k
+    out["plan"].destroy()
+    ref["plan"].destroy()
