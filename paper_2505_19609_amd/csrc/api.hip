@@ -439,6 +439,7 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
     // worst), for 4 pipelined 5 to 20 % less with sequences of up to 2,500 tokens, within 2 % at 4,300 and 4,700, 5 to 18 % more
     // from 10,000 on (a slice's prefix counts).  One head per group does not fill 12 from a sequence's last blocks.
     plan->dq_packed = plan->d == 64 && group > 1 && plan->units[2] && (plan->dq_waves == 8 || (plan->dq_waves == 4 && (!plan->dq_piped || totals.fwd_longest <= 128 + 16)));
+    plan->short_units = plan->d == 64 && plan->units[2] && totals.fwd_longest <= 10 + 16;
     plan->head_split = totals.split.head_split;
     plan->n_split = totals.split.n_split;
     plan->n_whole_first = totals.split.n_whole_first;

@@ -69,6 +69,7 @@ struct skrull_attn_plan {
     int32_t wg_query_rows;  // query rows per forward / dQ workgroup, asked for or chosen: 128 or 256; what runs follows
     int32_t fwd_waves, dq_waves;  // wavefronts of a forward / dQ workgroup: 4, 8 or 12
     bool dq_piped;                // dQ of 4: pipelined, two workgroups per compute unit
+    bool short_units;             // no forward / dQ unit is longer than 10 half tiles of keys (head_dim 64)
     bool dq_packed;               // in one launch with dK/dV of 12 wavefronts: dQ units of 12 row blocks whatever dq_waves is
     // dK/dV items that several workgroups share (the first n_split of the sorted list), and how:
     // an item of cost c takes min(split_parts, ceil(c * heads per group / split_chain)) of them
