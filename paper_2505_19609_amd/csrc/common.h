@@ -24,6 +24,7 @@ struct WorkQueue;
 // apart, the last item of one and the first of the next 6.4; 63.0 and 4.7 without.)  A plan has them for its first
 // SKRULL_STREAM_STATES streams; calls on further streams, calls that are being captured (a replay has no
 // turn in that order) and calls on a handle that stands for a different stream in each thread clear a queue first.
+// (hipStreamDestroy waits for a stream's work, so a handle that comes back stands for a stream that has nothing left to run.)
 #define SKRULL_STREAM_STATES 4
 #define SKRULL_STREAM_STATE_INTS (2 * (SKRULL_QUEUE_INTS + SKRULL_BWD_STATE_INTS))
 struct StreamStates {
