@@ -1248,7 +1248,7 @@ __device__ __forceinline__ void dkv_loop(DkvFeed &feed, unsigned char *ring, uns
                 w = feed.other();
                 kb = key_block(kernarg<BwdParams>(), 32 * PAIRS, max(w, 0));
             }
-        } else {  // the item has no second pass (the whole workgroup agrees)
+        } else {  // the item has no second pass, or no such part (the whole workgroup agrees)
             if (ONE && kb.shared && threadIdx.x == 0) count_part(kb.shared);
             w = feed.again();
             kb = key_block(kernarg<BwdParams>(), 32 * PAIRS, max(w, 0));
@@ -1308,7 +1308,9 @@ __device__ __forceinline__ void sums_loop(int *slot)
         if (rows <= 0) continue;
         if (threadIdx.x == 0) {
             const int32_t *stored = prm->parts_stored + (prm->n_parts ? 0 : x);
-            const int all = prm->n_parts ? prm->n_parts : parts * prm->keys.passes;
+            // (without a list of units every shared item has as many work items as the one of the most parts: those past its own
+            // parts are empty, and are counted as soon as somebody takes them, before the parts under way are stored)
+            const int all = prm->n_parts ? prm->n_parts : (prm->keys.units ? parts : prm->keys.parts) * prm->keys.passes;
             while (__hip_atomic_load(stored, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < all) __builtin_amdgcn_s_sleep(4);
         }
         __syncthreads();

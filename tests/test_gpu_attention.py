@@ -1185,6 +1185,50 @@ def test_dq_and_dkv_in_one_launch_and_in_two_give_the_same_bits(heads, d, S, kw,
     plan.destroy()
 
 
+@pytest.mark.parametrize("heads,d,S", [((8, 1), 128, [16384] + [1] * 2000), ((8, 1), 128, [8192] + [1] * 2000), ((14, 2), 64, [8192] + [1] * 2010)])
+def test_sums_of_shared_items_wait_for_all_parts_without_a_list_of_units(heads, d, S):
+    """A dK/dV list too long for a list of units deals every shared item as many work items as the one of the most parts
+    has; here most shared items have fewer parts than that, so some of these are empty.  The sums, in the same launch
+    as the parts, are those of the parts: the same bits as by a launch of their own, whatever the workspace held."""
+    import torch
+    from paper_2505_19609_amd import binding as B
+    from paper_2505_19609_amd.balance import REC
+    w = W.Workload("no_list", S, [1] * len(S), [0] * len(S), heads[0], heads[1], d, d ** -0.5, 615)
+    run = run_library(w, keep_device=True)
+    plan, t, i = run["plan"], run["dev"], run["dev_in"]
+    ws = torch.empty(int(plan.bwd_workspace_bytes), dtype=torch.uint8, device="cuda")
+
+    def backward():
+        B.skrull_attn_bwd(plan, i["q"], i["k"], i["v"], t["o"], t["lse"], i["do"], t["dq"], t["dk"], t["dv"], ws)
+
+    B.skrull_attn_profile(True)   # (dQ, dK/dV and the sums as launches of their own)
+    backward()
+    torch.cuda.synchronize()
+    B.skrull_attn_profile(False)
+    two = {n: t[n].clone() for n in ("dq", "dk", "dv")}
+    for fill in (0xFF, 0x7F, 0xFF, 0, 0xFF):
+        for x in (ws, *(t[n] for n in two)):
+            x.view(torch.uint8).fill_(fill)
+        backward()
+        torch.cuda.synchronize()
+        for n in two:
+            assert torch.equal(t[n].view(torch.int16), two[n].view(torch.int16)), (fill, n)
+
+    first, num = B.skrull_attn_trace_layout(plan)
+    records = torch.zeros((sum(num), REC.itemsize), dtype=torch.uint8, device="cuda")
+    B.skrull_attn_trace(records)
+    backward()
+    torch.cuda.synchronize()
+    B.skrull_attn_trace(None)
+    rec = records.cpu().numpy().view(REC).reshape(-1)
+    dq, dkv = (r[r["one"] == 1] for r in (rec[first[1]:first[2]], rec[first[2]:]))
+    assert dkv["t0"].min() < dq["t1"].max()   # one launch: as two, none of dK/dV begins before the last of dQ has ended
+    assert plan.n_dkv_items > 2048 and plan.info.block_n == (192 if d == 64 else 128)   # no list of units, one pass
+    parts, empty = num[2] - plan.n_dkv_items * heads[1], num[2] - len(dkv)   # (parts after the first one of each shared item)
+    assert 0 < empty < parts <= 1024          # items of fewer parts than the most; a counter each
+    plan.destroy()
+
+
 @pytest.mark.parametrize("S,waves", [([256], 4), ([257], 8), ([384], 8), ([385], 4), ([600, 33, 129], 4), ([700, 300, 900, 33, 1], 8),
                                      ([1024] * 12, 4), ([1024] * 11, 8), ([2048] * 6, 4), ([2049] + [1024] * 11, 8)])
 def test_which_forward_of_head_dim_128_runs(S, waves):
