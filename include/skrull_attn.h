@@ -240,8 +240,9 @@ int skrull_attn_fwd(const skrull_attn_plan_t *plan, const void *q, const void *k
  * `workspace` is DEVICE scratch of at least info.bwd_workspace_bytes, 16-byte
  * aligned; contents on entry are ignored and on exit unspecified.
  * Only enqueues on `hip_stream`; never synchronises.  One kernel does it all (dQ, then dK/dV, then
- * the sums of shared items), but for micro-batches of many long sequences at head_dim 64, where they are
- * two or three, and while profiling; the forward's small kernel before it in the same cases.
+ * the sums of shared items), but for micro-batches of many long sequences at head_dim 64, while profiling,
+ * and in the calls before which the forward has its small kernel: there they are two or three, that
+ * small kernel before them.
  * SKRULL_EINVAL on a null or misaligned pointer, a workspace that is too small,
  * or when the current device is not the one the plan was made on.
  */

@@ -1420,12 +1420,6 @@ __global__ __launch_bounds__(256) void dkv_reduce_kernel(const BwdParams prm)
     out[((size_t)(krow + r) * prm.Hkv + c) * (D / 4) + q] = w;
 }
 
-hipError_t clear_queues_first(const BwdParams &prm, hipStream_t st)
-{
-    queue_reset_kernel<<<1, 64, 0, st>>>(prm.queue_dq, 2, prm.queue_stride);
-    return hipGetLastError();
-}
-
 int dkv_pairs(const skrull_attn_plan_t *p) { return (p->d == 64 && p->BN == 32 * PAIRS_12W) ? PAIRS_12W : PAIRS_8W; }
 
 RowLaunch rows_dq_alone(const skrull_attn_plan_t *p)
@@ -1485,7 +1479,8 @@ hipError_t launch_pair(const skrull_attn_plan_t *p, BwdParams prm, int threads_q
     if (ev) (void)hipEventRecord(ev[0], st);
     const bool queued_q = wants_queue<KernelQ>(threads_q, prm.n_work_dq), queued_kv = wants_queue<KernelKV>(threads_kv, prm.n_work_dkv);
     if ((queued_q || queued_kv) && !prm.clear) {
-        hipError_t e = clear_queues_first(prm, st);
+        queue_reset_kernel<<<1, 64, 0, st>>>(prm.queue_dq, 2, prm.queue_stride);
+        hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     if (!queued_q) prm.queue_dq = nullptr;
@@ -1509,10 +1504,6 @@ hipError_t launch_pair(const skrull_attn_plan_t *p, BwdParams prm, int threads_q
 template <int D, int PAIRS>
 hipError_t launch_one(const skrull_attn_plan_t *p, const BwdParams &prm, hipStream_t st)
 {
-    if (!prm.clear) {
-        hipError_t e = clear_queues_first(prm, st);
-        if (e != hipSuccess) return e;
-    }
     const int64_t work = (int64_t)prm.n_work_dq + prm.n_work_dkv;
     const int resident = resident_of<bwd_kernel<D, PAIRS>>(128 * PAIRS);
     bwd_kernel<D, PAIRS><<<(int)(work < resident ? work : resident), 128 * PAIRS, 0, st>>>(prm);
@@ -1564,7 +1555,13 @@ hipError_t launch_bwd(const skrull_attn_plan_t *p, const void *q, const void *k,
 {
     BwdParams prm;
     prm.trace_dq = trace;
-    const bool one = is_one(p) && !ev;  // (events are to time dQ and dK/dV by themselves)
+    std::unique_lock<std::mutex> held(p->streams->lock);
+    const int at = p->streams->find(st);
+    if (at < 0) held.unlock();
+    // Events are to time dQ and dK/dV by themselves.  Calls without a place of their stream have the 256 bytes in the workspace alone for what
+    // workgroups share, two lines, and workgroups that wait would poll the line of dQ's queues: replayed from a graph, 838 tokens in 10
+    // sequences, 32/8 heads of 128, 39 us as three launches, 74 in one; 17,205 in 62, 8/4 heads, 204 and 295.
+    const bool one = at >= 0 && !ev && is_one(p);
     const RowLaunch rows_q = one ? rows_dq_first(p) : rows_dq_alone(p);
     prm.trace_dkv = trace ? trace + grid_dq(p) : nullptr;  // (one launch has as many dQ items or fewer)
     prm.q = (const uint16_t *)q; prm.k = (const uint16_t *)k; prm.v = (const uint16_t *)v;
@@ -1582,7 +1579,7 @@ hipError_t launch_bwd(const skrull_attn_plan_t *p, const void *q, const void *k,
     prm.n_work_dq = rows_q.n_work;
     prm.n_work_dkv = grid_dkv(p);
     {
-        // workspace: -D | LSE*log2e | (256-byte aligned) 256 bytes, the state of calls that clear it first | dK partials | dV partials
+        // workspace: -D | LSE*log2e | (256-byte aligned) 256 bytes, the queues of calls that clear them first | dK partials | dV partials
         static_assert(2 * 8 * kQueueStrideWorkspace * sizeof(WorkQueue) == 256, "the queues' part of the workspace");
         static_assert(2 * 8 * kQueueStride * sizeof(WorkQueue) == 2 * 4 * SKRULL_QUEUE_INTS, "the queues' part of a plan's state");
         const size_t rows = (((size_t)p->Hq * p->total_q * 8) + 255) & ~(size_t)255;
@@ -1590,10 +1587,8 @@ hipError_t launch_bwd(const skrull_attn_plan_t *p, const void *q, const void *k,
         const size_t part_rows = p->split_compact ? (size_t)p->n_split * p->BN : (size_t)p->total_k;
         prm.dv_part = prm.dk_part + (size_t)p->split_parts * part_rows * p->Hkv * p->d;
     }
-    std::unique_lock<std::mutex> held(p->streams->lock);
-    const int at = p->streams->find(st);
     prm.n_parts = 0;
-    if (at < 0 || (int64_t)p->n_split * p->Hkv > SKRULL_ITEM_COUNTERS)
+    if ((int64_t)p->n_split * p->Hkv > SKRULL_ITEM_COUNTERS)
         prm.n_parts = (p->dkv_units ? p->n_dkv_units - (p->n_dkv - p->n_split) : p->n_split * p->split_parts) * p->Hkv * prm.keys.passes;
     if (at >= 0) {
         const uint32_t turn = p->streams->of[at].bwd;
@@ -1607,14 +1602,10 @@ hipError_t launch_bwd(const skrull_attn_plan_t *p, const void *q, const void *k,
         prm.parts_stored = prm.rows_ready + (prm.n_parts ? 64 : 128);
         prm.clear = sets + (~turn & 1) * SKRULL_BWD_STATE_INTS;
     } else {
-        held.unlock();
         prm.queue_stride = kQueueStrideWorkspace;
         prm.queue_dq = (WorkQueue *)((char *)prm.dk_part - 256);
         prm.queue_dkv = prm.queue_dq + 8 * kQueueStrideWorkspace;
-        prm.rows_ready = (int32_t *)&prm.queue_dq[0].taken[0];  // (words of the queues that the backward's do not use)
-        prm.parts_stored = (int32_t *)&prm.queue_dq[1].taken[0];
-        prm.next_sum = (int32_t *)&prm.queue_dq[2].taken[0];
-        prm.clear = nullptr;
+        prm.rows_ready = prm.parts_stored = prm.next_sum = prm.clear = nullptr;
     }
     const hipError_t e = p->d == 128 ? launch_d<128>(p, prm, one, st, ev) : p->d == 64 ? launch_d<64>(p, prm, one, st, ev) : hipErrorInvalidValue;
     if (at >= 0) {

@@ -142,3 +142,55 @@ def test_calls_of_one_plan_on_many_streams_and_in_graphs_by_turns(heads, d, S):
             for n in ("o", "lse", "dq", "dk", "dv"):
                 assert torch.equal(t[n].view(torch.uint8), ref[n].view(torch.uint8)), (rep, n)
     plan.destroy()
+
+
+@pytest.mark.parametrize("where", ["default", "graph", "further_stream"])
+def test_only_calls_with_queues_of_their_stream_are_one_launch(where):
+    """dK/dV begins while dQ is under way on the default stream; a captured backward, and one on a stream that the plan
+    has no queues for, makes them launches of their own (in one they took up to twice as long).  Same bits."""
+    from paper_2505_19609_amd import binding as B
+    from paper_2505_19609_amd.balance import REC
+    S, heads, d = [277] * 62, (8, 4), 128
+    w = W.Workload("launches", S, [1] * len(S), [0] * len(S), heads[0], heads[1], d, d ** -0.5, 97)
+    plan = B.skrull_attn_plan(S, [1] * len(S), [0] * len(S), heads[0], heads[1], d, w.softmax_scale)
+    dev = {n: to_dev(a) for n, a in W.make_values(w, plan.total_q, plan.total_k).items()}
+    o, lse = torch.empty_like(dev["q"]), torch.empty((heads[0], plan.total_q), device="cuda")
+    outs = [[torch.empty_like(dev[n]) for n in "qkv"] for _ in range(2)]
+    ws = torch.empty(max(int(plan.bwd_workspace_bytes), 16), dtype=torch.uint8, device="cuda")
+
+    def backward(out):
+        B.skrull_attn_bwd(plan, dev["q"], dev["k"], dev["v"], o, lse, dev["do"], *out, ws)
+
+    B.skrull_attn_fwd(plan, dev["q"], dev["k"], dev["v"], o, lse)
+    backward(outs[0])
+    streams = [torch.cuda.Stream() for _ in range(5)]
+    torch.cuda.synchronize()
+    for s in streams[:4]:
+        with torch.cuda.stream(s):
+            backward(outs[1])
+        s.synchronize()
+    first, num = B.skrull_attn_trace_layout(plan)
+    records = torch.zeros((sum(num), REC.itemsize), dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    B.skrull_attn_trace(records)
+    try:
+        if where == "graph":
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=streams[0]):
+                backward(outs[1])
+            graph.replay()
+        elif where == "further_stream":
+            with torch.cuda.stream(streams[4]):
+                backward(outs[1])
+        else:
+            backward(outs[1])
+        torch.cuda.synchronize()
+    finally:
+        B.skrull_attn_trace(None)
+    rec = records.cpu().numpy().view(REC).reshape(-1)
+    dq, dkv = (r[r["one"] == 1] for r in (rec[first[1]:first[2]], rec[first[2]:]))
+    assert len(dq) > 0 and len(dkv) > 0
+    assert (dkv["t0"].min() < dq["t1"].max()) == (where == "default")
+    for a, b in zip(*outs):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+    plan.destroy()
