@@ -172,10 +172,11 @@ enum {
  * skrull_attn_plan_destroy.  A plan's descriptor and work lists are immutable and it may
  * be reused by any number of fwd/bwd calls on any stream of the same device.  The kernels
  * are persistent (workgroups take work items from queues until none is left, see
- * skrull_attn_fwd); a backward call keeps its queues in its own workspace, a forward call
- * takes one of the plan's 64 queue slots in turn, so at most 64 forward calls of one plan
+ * skrull_attn_fwd).  The calls on the default stream, which run one after another, have queues in the plan.
+ * Of the others a backward call keeps its queues in its own workspace and a forward call
+ * takes one of 64 queue slots of the plan in turn, so at most 64 such forward calls of one plan
  * may be in flight at once, and a forward call captured in a HIP graph (which keeps the
- * slot it was captured with) must not overlap with other forward calls of the same plan.
+ * slot it was captured with) must not overlap with other such forward calls of the same plan.
  * SKRULL_EINVAL: null pointer, K < 1, S_k < 1, degree < 1, index outside
  * [0, degree), more chunks than tokens (degree > S_k, or 2*degree > S_k for a
  * two-chunk cut), a cut other than the two above, head_split outside [0, Hq/Hkv],
@@ -214,9 +215,8 @@ int skrull_attn_plan_export(const skrull_attn_plan_t *plan, int which, void *dst
  * differ in speed by several percent, which a fixed deal of workgroups to dies cannot even
  * out).  Results do not depend on which workgroup took which item.
  * Only enqueues on `hip_stream` (the attention kernel; when there are more work items than
- * the chip holds workgroups at once, also a small kernel that clears the queue before it, in calls
- * that are being captured, on hipStreamPerThread and on further streams than the first four that a plan is
- * used on; on those a plan's calls clear each other's queues); never synchronises.
+ * the chip holds workgroups at once, also a small kernel before it that clears the queue, save on the
+ * default stream, where each call of a plan clears the queues of its next one); never synchronises.
  * SKRULL_EINVAL on a null or misaligned pointer, or when the current device is
  * not the one the plan was made on.
  */
@@ -240,9 +240,9 @@ int skrull_attn_fwd(const skrull_attn_plan_t *plan, const void *q, const void *k
  * `workspace` is DEVICE scratch of at least info.bwd_workspace_bytes, 16-byte
  * aligned; contents on entry are ignored and on exit unspecified.
  * Only enqueues on `hip_stream`; never synchronises.  One kernel does it all (dQ, then dK/dV, then
- * the sums of shared items), but for micro-batches of many long sequences at head_dim 64, while profiling,
- * and in the calls before which the forward has its small kernel: there they are two or three, that
- * small kernel before them.
+ * the sums of shared items) on the default stream, but for micro-batches of many long sequences at
+ * head_dim 64 and while profiling.  Else they are two or three, on other streams with the forward's small
+ * kernel before them.
  * SKRULL_EINVAL on a null or misaligned pointer, a workspace that is too small,
  * or when the current device is not the one the plan was made on.
  */

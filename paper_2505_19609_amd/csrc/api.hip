@@ -247,7 +247,7 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
     const int64_t tmp_ints = 4 * kin + 2 * kpad + totals_ints + 4 * (cap_fwd + cap_dkv) + radix_ints;
     const int64_t desc_ints = 6 * kpad;
     const int64_t queue_ints = SKRULL_QUEUE_INTS * SKRULL_FWD_QUEUE_SLOTS;  // work queues of the forward launches
-    const int64_t state_ints = SKRULL_STREAM_STATES * SKRULL_STREAM_STATE_INTS;
+    const int64_t sets_ints = SKRULL_SETS_INTS;
     int32_t *fwd_off = nullptr, *dkv_off = nullptr, *scratch = nullptr;
     PlanTotals *totals_d = nullptr;
     int64_t unit_ints[SKRULL_UNIT_LISTS] = {}, all_unit_ints = 0, dkv_unit_ints = 0;
@@ -255,8 +255,8 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
     plan = new (std::nothrow) skrull_attn_plan_t();
     if (!plan) return SKRULL_ENOMEM;
     memset(plan, 0, sizeof *plan);
-    plan->streams = new (std::nothrow) StreamStates();
-    if (!plan->streams) { delete plan; return SKRULL_ENOMEM; }
+    plan->default_stream = new (std::nothrow) DefaultStream();
+    if (!plan->default_stream) { delete plan; return SKRULL_ENOMEM; }
     plan->K = K; plan->NS = (int32_t)n_seg; plan->Hq = p->num_q_heads; plan->Hkv = p->num_kv_heads; plan->d = p->head_dim;
     plan->BM = BM; plan->BN = BN; plan->scale = p->softmax_scale; plan->device = dev;
 
@@ -279,10 +279,10 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
     if (!small) HIP_TRY(hipMalloc((void **)&tmp, (size_t)tmp_ints * sizeof(int32_t)));
     for (int i = 0; i < SKRULL_UNIT_LISTS; ++i) all_unit_ints += unit_ints[i] = plan_unit_ints(plan, (int32_t)cap_fwd, i);
     dkv_unit_ints = plan_dkv_unit_ints(plan, p->head_split, (int32_t)cap_dkv);
-    HIP_TRY(hipMalloc((void **)&plan->pool, (size_t)(queue_ints + state_ints + desc_ints + 4 * (cap_fwd + cap_dkv) + all_unit_ints + dkv_unit_ints) * sizeof(int32_t)));
+    HIP_TRY(hipMalloc((void **)&plan->pool, (size_t)(queue_ints + sets_ints + desc_ints + 4 * (cap_fwd + cap_dkv) + all_unit_ints + dkv_unit_ints) * sizeof(int32_t)));
     plan->fwd_queues = (WorkQueue *)plan->pool;   // (zeroed by the forward calls that use them, before their launch)
-    plan->stream_states = plan->pool + queue_ints;
-    plan->cu_q = plan->stream_states + state_ints;
+    plan->sets = plan->pool + queue_ints;
+    plan->cu_q = plan->sets + sets_ints;
     plan->cu_k = plan->cu_q + kpad;
     plan->q_begin = plan->cu_q + 2 * kpad;
     plan->q_len = plan->cu_q + 3 * kpad;
@@ -308,7 +308,7 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
                                             longest_seq, compute_units, plan->q_begin, plan->q_len, plan->kv_len, plan->cu_q, plan->cu_k,
                                             plan->shares_kv, plan->fwd_items, plan->dkv_items,
                                             {plan->units[0], plan->units[1], plan->units[2]}, plan->dkv_units,
-                                            (int4 *)plan->stream_states}, st));
+                                            (int4 *)plan->sets}, st));
     } else {
         fwd_off = tmp + 4 * kin;
         dkv_off = fwd_off + kpad;
@@ -455,7 +455,7 @@ done:
     if (rc != SKRULL_OK) {
         if (plan) {
             if (plan->pool) (void)hipFree(plan->pool);
-            delete plan->streams;
+            delete plan->default_stream;
             delete plan;
         }
         return rc;
@@ -592,7 +592,7 @@ void skrull_attn_plan_destroy(skrull_attn_plan_t *plan)
 {
     if (!plan) return;
     if (plan->pool) (void)hipFree(plan->pool);
-    delete plan->streams;
+    delete plan->default_stream;
     delete plan;
 }
 

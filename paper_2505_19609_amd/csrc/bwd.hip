@@ -1555,13 +1555,14 @@ hipError_t launch_bwd(const skrull_attn_plan_t *p, const void *q, const void *k,
 {
     BwdParams prm;
     prm.trace_dq = trace;
-    std::unique_lock<std::mutex> held(p->streams->lock);
-    const int at = p->streams->find(st);
-    if (at < 0) held.unlock();
-    // Events are to time dQ and dK/dV by themselves.  Calls without a place of their stream have the 256 bytes in the workspace alone for what
+    DefaultStream &own = *p->default_stream;
+    std::unique_lock<std::mutex> held(own.lock);
+    const bool in_turn = own.has(st);
+    if (!in_turn) held.unlock();
+    // Events are to time dQ and dK/dV by themselves.  Calls without a set of the plan's have the 256 bytes in the workspace alone for what
     // workgroups share, two lines, and workgroups that wait would poll the line of dQ's queues: replayed from a graph, 838 tokens in 10
     // sequences, 32/8 heads of 128, 39 us as three launches, 74 in one; 17,205 in 62, 8/4 heads, 204 and 295.
-    const bool one = at >= 0 && !ev && is_one(p);
+    const bool one = in_turn && !ev && is_one(p);
     const RowLaunch rows_q = one ? rows_dq_first(p) : rows_dq_alone(p);
     prm.trace_dkv = trace ? trace + grid_dq(p) : nullptr;  // (one launch has as many dQ items or fewer)
     prm.q = (const uint16_t *)q; prm.k = (const uint16_t *)k; prm.v = (const uint16_t *)v;
@@ -1590,17 +1591,15 @@ hipError_t launch_bwd(const skrull_attn_plan_t *p, const void *q, const void *k,
     prm.n_parts = 0;
     if ((int64_t)p->n_split * p->Hkv > SKRULL_ITEM_COUNTERS)
         prm.n_parts = (p->dkv_units ? p->n_dkv_units - (p->n_dkv - p->n_split) : p->n_split * p->split_parts) * p->Hkv * prm.keys.passes;
-    if (at >= 0) {
-        const uint32_t turn = p->streams->of[at].bwd;
-        int32_t *sets = p->stream_states + at * SKRULL_STREAM_STATE_INTS + 2 * SKRULL_QUEUE_INTS;
-        int32_t *mine = sets + (turn & 1) * SKRULL_BWD_STATE_INTS;
+    if (in_turn) {
+        int32_t *sets = p->sets + 2 * SKRULL_QUEUE_INTS, *mine = sets + (own.bwd & 1) * SKRULL_BWD_STATE_INTS;
         prm.queue_stride = kQueueStride;
         prm.queue_dq = (WorkQueue *)mine;
         prm.queue_dkv = (WorkQueue *)(mine + SKRULL_QUEUE_INTS);
         prm.rows_ready = mine + 2 * SKRULL_QUEUE_INTS;
         prm.next_sum = prm.rows_ready + 32;
         prm.parts_stored = prm.rows_ready + (prm.n_parts ? 64 : 128);
-        prm.clear = sets + (~turn & 1) * SKRULL_BWD_STATE_INTS;
+        prm.clear = sets + (~own.bwd & 1) * SKRULL_BWD_STATE_INTS;
     } else {
         prm.queue_stride = kQueueStrideWorkspace;
         prm.queue_dq = (WorkQueue *)((char *)prm.dk_part - 256);
@@ -1608,9 +1607,9 @@ hipError_t launch_bwd(const skrull_attn_plan_t *p, const void *q, const void *k,
         prm.rows_ready = prm.parts_stored = prm.next_sum = prm.clear = nullptr;
     }
     const hipError_t e = p->d == 128 ? launch_d<128>(p, prm, one, st, ev) : p->d == 64 ? launch_d<64>(p, prm, one, st, ev) : hipErrorInvalidValue;
-    if (at >= 0) {
-        if (e == hipSuccess) ++p->streams->of[at].bwd;
-        else p->streams->give_up(at);
+    if (in_turn) {
+        if (e == hipSuccess) ++own.bwd;
+        else own.lost = true;
     }
     return e;
 }

@@ -19,40 +19,29 @@ struct WorkQueue;
 #define SKRULL_BWD_STATE_INTS (2 * SKRULL_QUEUE_INTS + 128 + SKRULL_ITEM_COUNTERS)
 
 // Queues that need no kernel to clear them before a launch.  The calls of one stream run one after another, so a
-// plan keeps two sets for each stream it is used on: a launch works with one and clears the other, which the
+// plan keeps two sets for its calls on the default stream: a launch works with one and clears the other, which the
 // launch before it has left, for the next.  (With a kernel before each that clears its queue, forwards of 26,624 tokens in 64 sequences, 14/2 heads of 64, come 64.0 us
-// apart, the last item of one and the first of the next 6.4; 63.0 and 4.7 without.)  A plan has them for its first
-// SKRULL_STREAM_STATES streams; calls on further streams, calls that are being captured (a replay has no
-// turn in that order) and calls on a handle that stands for a different stream in each thread clear a queue first.
-// (hipStreamDestroy waits for a stream's work, so a handle that comes back stands for a stream that has nothing left to run.)
-#define SKRULL_STREAM_STATES 4
-#define SKRULL_STREAM_STATE_INTS (2 * (SKRULL_QUEUE_INTS + SKRULL_BWD_STATE_INTS))
-struct StreamStates {
-    std::mutex lock;  // held from the choice of a set until the launch that uses it is queued
-    int used = 0;
-    struct {
-        hipStream_t stream;
-        uint32_t fwd, bwd;  // forward and backward calls so far that used a set
-    } of[SKRULL_STREAM_STATES] = {};
+// apart, the last item of one and the first of the next 6.4; 63.0 and 4.7 without.)  Calls on other streams and calls that are
+// being captured (a replay has no turn in that order) clear a queue first: a stream that a program has made it may destroy
+// while its work is under way (hipStreamDestroy need not wait), and a later stream may have the same handle, so that calls with one handle
+// are not always one after another.  The default stream cannot be destroyed.
+#define SKRULL_SETS_INTS (2 * (SKRULL_QUEUE_INTS + SKRULL_BWD_STATE_INTS))
+struct DefaultStream {
+    std::mutex lock;            // held from the choice of a set until the launch that uses it is queued
+    uint32_t fwd = 0, bwd = 0;  // forward and backward calls so far that used a set
+    bool lost = false;          // a launch failed: nobody knows what its sets hold
 
-    // The place of stream `st`, or -1.  With the lock held.
-    int find(hipStream_t st)
+    // Whether a call on `st` may use a set.  With the lock held.
+    bool has(hipStream_t st) const
     {
-        if (st == hipStreamPerThread) return -1;
+        if (st != nullptr || lost) return false;
         hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(st, &capture) != hipSuccess) {
             (void)hipGetLastError();
-            return -1;
+            return false;
         }
-        if (capture != hipStreamCaptureStatusNone) return -1;
-        for (int i = 0; i < used; ++i)
-            if (of[i].stream == st) return i;
-        if (used == SKRULL_STREAM_STATES) return -1;
-        of[used].stream = st;
-        return used++;
+        return capture == hipStreamCaptureStatusNone;
     }
-    // After a launch that failed nobody knows what its place's sets hold.
-    void give_up(int at) { of[at].stream = (hipStream_t)~(uintptr_t)0; }
 };
 
 #define SKRULL_CHAIN_LIMITS 9
@@ -92,8 +81,8 @@ struct skrull_attn_plan {
     int4 *dkv_units;
     int32_t n_dkv_units;
     WorkQueue *fwd_queues;  // SKRULL_FWD_QUEUE_SLOTS times eight dies' queues, at the start of the pool: for forward launches that clear one first
-    int32_t *stream_states; // SKRULL_STREAM_STATES times SKRULL_STREAM_STATE_INTS, zero when the plan is made (see StreamStates)
-    StreamStates *streams;
+    int32_t *sets;          // SKRULL_SETS_INTS: two sets of a forward, two of a backward, zero when the plan is made (see DefaultStream)
+    DefaultStream *default_stream;
     uint32_t fwd_calls;     // such calls made so far (atomic): call i uses slot i mod SKRULL_FWD_QUEUE_SLOTS
 };
 
@@ -192,7 +181,7 @@ struct SmallPlan {
     int32_t *q_begin, *q_len, *kv_len, *cu_q, *cu_k, *shares_kv, *fwd_items, *dkv_items;
     int32_t *units[SKRULL_UNIT_LISTS];
     int4 *dkv_units;
-    int4 *stream_states;  // cleared
+    int4 *sets;  // cleared
 };
 hipError_t launch_plan_small(const SmallPlan &job, hipStream_t st);
 hipError_t launch_plan_ranges(const int32_t *S, const int32_t *N, const int32_t *r,

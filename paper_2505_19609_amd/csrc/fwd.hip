@@ -571,16 +571,15 @@ hipError_t launch_fwd(const skrull_attn_plan_t *p, const void *q, const void *k,
     prm.n_work = rows.n_work;
     prm.queue = prm.clear = nullptr;
     static_assert(8 * kQueueStride * sizeof(WorkQueue) == 4 * SKRULL_QUEUE_INTS, "a slot holds eight queues");
-    std::unique_lock<std::mutex> held(p->streams->lock, std::defer_lock);
-    int at = -1;
+    DefaultStream &own = *p->default_stream;
+    std::unique_lock<std::mutex> held(own.lock, std::defer_lock);
+    bool in_turn = false;
     if (rows.queued) {
         held.lock();
-        at = p->streams->find(st);
-        if (at >= 0) {
-            const uint32_t turn = p->streams->of[at].fwd;
-            int32_t *sets = p->stream_states + at * SKRULL_STREAM_STATE_INTS;
-            prm.queue = (WorkQueue *)(sets + (turn & 1) * SKRULL_QUEUE_INTS);
-            prm.clear = (WorkQueue *)(sets + (~turn & 1) * SKRULL_QUEUE_INTS);
+        in_turn = own.has(st);
+        if (in_turn) {
+            prm.queue = (WorkQueue *)(p->sets + (own.fwd & 1) * SKRULL_QUEUE_INTS);
+            prm.clear = (WorkQueue *)(p->sets + (~own.fwd & 1) * SKRULL_QUEUE_INTS);
         } else {
             held.unlock();
             // One of the plan's queue slots per call, taken in turn, so that forward calls of one plan
@@ -589,9 +588,9 @@ hipError_t launch_fwd(const skrull_attn_plan_t *p, const void *q, const void *k,
         }
     }
     const hipError_t e = p->d == 128 ? launch_one<128>(prm, st) : p->d == 64 ? launch_one<64>(prm, st) : hipErrorInvalidValue;
-    if (at >= 0) {
-        if (e == hipSuccess) ++p->streams->of[at].fwd;
-        else p->streams->give_up(at);
+    if (in_turn) {
+        if (e == hipSuccess) ++own.fwd;
+        else own.lost = true;
     }
     return e;
 }

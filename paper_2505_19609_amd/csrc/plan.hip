@@ -249,10 +249,10 @@ __device__ inline int32_t owner_of(const int32_t *off, int32_t K, int32_t item)
 }
 
 // The plan's queues start empty (by all threads of one workgroup).
-__device__ inline void clear_stream_states(int4 *states)
+__device__ inline void clear_sets(int4 *sets)
 {
-    static_assert(SKRULL_STREAM_STATE_INTS % 4 == 0, "cleared in fours");
-    for (int i = threadIdx.x; i < SKRULL_STREAM_STATES * SKRULL_STREAM_STATE_INTS / 4; i += blockDim.x) states[i] = make_int4(0, 0, 0, 0);
+    static_assert(SKRULL_SETS_INTS % 4 == 0, "cleared in fours");
+    for (int i = threadIdx.x; i < SKRULL_SETS_INTS / 4; i += blockDim.x) sets[i] = make_int4(0, 0, 0, 0);
 }
 
 __global__ __launch_bounds__(256) void plan_emit_kernel(
@@ -261,9 +261,9 @@ __global__ __launch_bounds__(256) void plan_emit_kernel(
     const int32_t *__restrict__ cu_q, const int32_t *__restrict__ shares_kv,
     const int32_t *__restrict__ fwd_off,
     const int32_t *__restrict__ dkv_off, int4 *__restrict__ fwd_items,
-    int4 *__restrict__ dkv_items, PlanTotals *__restrict__ totals, int4 *__restrict__ stream_states)
+    int4 *__restrict__ dkv_items, PlanTotals *__restrict__ totals, int4 *__restrict__ sets)
 {
-    if (blockIdx.x == 0) clear_stream_states(stream_states);
+    if (blockIdx.x == 0) clear_sets(sets);
     // the grid covers an upper bound of the item counts; the counts themselves are the
     // ranges kernel's (clamped: a count past the limit is rejected by the host afterwards)
     const int32_t n_fwd = (int32_t)min((long long)totals->n_fwd, (long long)totals->cap_fwd);
@@ -755,7 +755,7 @@ __global__ __launch_bounds__(kSmallThreads) void plan_small_kernel(SmallPlan j)
     __shared__ PlanTotals tot;
     __shared__ ChainCounts chains;
     const int t = threadIdx.x;
-    clear_stream_states(j.stream_states);
+    clear_sets(j.sets);
     const int32_t group = j.q_heads / j.kv_heads, log_bm = __ffs(j.BM) - 1;  // (BM is a power of two)
     if (t == 0) {
         first_bad = 0x7fffffff;
@@ -1132,7 +1132,7 @@ hipError_t launch_plan_items(const skrull_attn_plan_t *p, const int32_t *fwd_off
     plan_emit_kernel<<<(n + 255) / 256, 256, 0, st>>>(
         p->NS, p->BM, p->q_begin, p->q_len, p->kv_len, p->cu_q, p->shares_kv, fwd_off, dkv_off,
         (int4 *)(fwd_even ? p->fwd_items : scratch_fwd), (int4 *)(dkv_even ? p->dkv_items : scratch_dkv), totals,
-        (int4 *)p->stream_states);
+        (int4 *)p->sets);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     // short lists by rank counting, both in one launch when both are short
