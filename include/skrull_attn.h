@@ -241,8 +241,8 @@ int skrull_attn_fwd(const skrull_attn_plan_t *plan, const void *q, const void *k
  * aligned; contents on entry are ignored and on exit unspecified.
  * Only enqueues on `hip_stream`; never synchronises.  One kernel does it all (dQ, then dK/dV, then
  * the sums of shared items) on the default stream, but for micro-batches of many long sequences at
- * head_dim 64 and while profiling.  Else they are two or three, on other streams with the forward's small
- * kernel before them.
+ * head_dim 64 or of short ones that run at once, and while profiling.  Else they are two or three, on other
+ * streams with the forward's small kernel before them.
  * SKRULL_EINVAL on a null or misaligned pointer, a workspace that is too small,
  * or when the current device is not the one the plan was made on.
  */

@@ -258,7 +258,7 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
     plan->default_stream = new (std::nothrow) DefaultStream();
     if (!plan->default_stream) { delete plan; return SKRULL_ENOMEM; }
     plan->K = K; plan->NS = (int32_t)n_seg; plan->Hq = p->num_q_heads; plan->Hkv = p->num_kv_heads; plan->d = p->head_dim;
-    plan->BM = BM; plan->BN = BN; plan->scale = p->softmax_scale; plan->device = dev;
+    plan->BM = BM; plan->BN = BN; plan->longest_seq = longest_seq; plan->scale = p->softmax_scale; plan->device = dev;
 
     pinned = g_pinned.take();
     // One workgroup ranks lists of up to 256 items with two threads or more to an item; above that the several kernels
@@ -439,7 +439,6 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
     // worst), for 4 pipelined 5 to 20 % less with sequences of up to 2,500 tokens, within 2 % at 4,300 and 4,700, 5 to 18 % more
     // from 10,000 on (a slice's prefix counts).  One head per group does not fill 12 from a sequence's last blocks.
     plan->dq_packed = plan->d == 64 && group > 1 && plan->units[2] && (plan->dq_waves == 8 || (plan->dq_waves == 4 && (!plan->dq_piped || totals.fwd_longest <= 128 + 16)));
-    plan->short_units = plan->d == 64 && plan->units[2] && totals.fwd_longest <= 10 + 16;
     plan->head_split = totals.split.head_split;
     plan->n_split = totals.split.n_split;
     plan->n_whole_first = totals.split.n_whole_first;

@@ -1431,22 +1431,32 @@ RowLaunch rows_dq_alone(const skrull_attn_plan_t *p)
     return row_launch<dq_kernel<64, NWQ_LARGE>>(p, NWQ_LARGE);
 }
 
-template <int D, int PAIRS> bool chip_known() { return resident_of<bwd_kernel<D, PAIRS>>(128 * PAIRS) > 0; }
-
-// Whether a backward is one launch.
-bool is_one(const skrull_attn_plan_t *p)
+// Whether a launch of dK/dV has more work items than the chip holds at once.
+bool dkv_queued(const skrull_attn_plan_t *p)
 {
-    if (p->d == 128) return chip_known<128, PAIRS_8W>();
+    const int n = grid_dkv(p);
+    if (p->d == 128) return wants_queue<dkv_kernel<128, PAIRS_8W>>(128 * PAIRS_8W, n);
+    return dkv_pairs(p) == PAIRS_12W ? wants_queue<dkv_kernel<64, PAIRS_12W>>(128 * PAIRS_12W, n) : wants_queue<dkv_kernel<64, PAIRS_8W>>(128 * PAIRS_8W, n);
+}
+
+// Whether a backward is one launch, of workgroups that take dQ items, then dK/dV items.
+template <int D, int PAIRS> bool is_one(const skrull_attn_plan_t *p)
+{
     const RowLaunch dq = rows_dq_alone(p);
     if (p->dq_waves == NWQ_SMALL && dq.queued) return false;
-    if (dkv_pairs(p) == PAIRS_12W) {
-        const int at_once = resident_of<bwd_kernel<64, PAIRS_12W>>(128 * PAIRS_12W), dkv = grid_dkv(p);
-        // Where dQ and dK/dV are each one round of short items on most of the chip nothing overlaps, and two plain grids have
-        // no queues to look into: 493 tokens in 7 sequences, 16/16 heads, 15.3 us, in one launch 19.4; up to 300 tokens long 23.6 and 24.2.
-        if (p->short_units && p->Hq == p->Hkv && p->n_split == 0 && dq.n_work <= at_once && dkv <= at_once && dq.n_work + dkv > at_once) return false;
-        return at_once > 0;
-    }
-    return p->dq_waves <= 8 && chip_known<64, PAIRS_8W>();
+    if (D == 64 && PAIRS == PAIRS_8W && p->dq_waves > 8) return false;
+    // Where dQ would be a plain grid, and dK/dV too or its items short, separate launches look into no queues, which costs
+    // each workgroup of the one launch an atomic or more on few lines; what it saves are gaps and, the longer the items, the wait for the last of dQ.
+    // Of 581 such backwards, 21 to 5,600 tokens, all kinds of heads: 277 in one launch 14 % less time than as separate ones (6 % more to 35 % less), 304 separately
+    // 5 % less than in one (28 % more to 36 % less; against a launch for each of dQ, dK/dV and sums, queues cleared by one before them, all
+    // 8 % less and 5 % more at worst, in one launch throughout 58 % more at worst).
+    if (!dq.queued && (!dkv_queued(p) || p->longest_seq <= 160) && dq.n_work + grid_dkv(p) > 80 + p->longest_seq / 2) return false;
+    return resident_of<bwd_kernel<D, PAIRS>>(128 * PAIRS) > 0;
+}
+bool is_one(const skrull_attn_plan_t *p)
+{
+    if (p->d == 128) return is_one<128, PAIRS_8W>(p);
+    return dkv_pairs(p) == PAIRS_12W ? is_one<64, PAIRS_12W>(p) : is_one<64, PAIRS_8W>(p);
 }
 
 // The work items of dQ in one launch with dK/dV, where dK/dV begins on the compute units that dQ leaves.  Few long units, which a
@@ -1557,13 +1567,14 @@ hipError_t launch_bwd(const skrull_attn_plan_t *p, const void *q, const void *k,
     prm.trace_dq = trace;
     DefaultStream &own = *p->default_stream;
     std::unique_lock<std::mutex> held(own.lock);
-    const bool in_turn = own.has(st);
-    if (!in_turn) held.unlock();
+    bool in_turn = own.has(st);
     // Events are to time dQ and dK/dV by themselves.  Calls without a set of the plan's have the 256 bytes in the workspace alone for what
     // workgroups share, two lines, and workgroups that wait would poll the line of dQ's queues: replayed from a graph, 838 tokens in 10
     // sequences, 32/8 heads of 128, 39 us as three launches, 74 in one; 17,205 in 62, 8/4 heads, 204 and 295.
     const bool one = in_turn && !ev && is_one(p);
     const RowLaunch rows_q = one ? rows_dq_first(p) : rows_dq_alone(p);
+    in_turn = in_turn && (one || rows_q.queued || dkv_queued(p));  // (two plain grids share nothing)
+    if (!in_turn) held.unlock();
     prm.trace_dkv = trace ? trace + grid_dq(p) : nullptr;  // (one launch has as many dQ items or fewer)
     prm.q = (const uint16_t *)q; prm.k = (const uint16_t *)k; prm.v = (const uint16_t *)v;
     prm.d_o = (const uint16_t *)d_o; prm.o = (const uint16_t *)o; prm.lse = lse; prm.delta = delta;

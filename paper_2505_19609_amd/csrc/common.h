@@ -54,12 +54,12 @@ struct skrull_attn_plan {
     int32_t K, NS, Hq, Hkv, d, BM, BN;  // K sequences, NS >= K query segments
     float scale;
     int32_t total_q, total_k, n_fwd, n_dkv;
+    int32_t longest_seq;  // tokens of the longest sequence, also where this rank has a slice of it
     int64_t pairs;
     int32_t head_split;  // workgroups that share the query heads of one KV group in dK/dV
     int32_t wg_query_rows;  // query rows per forward / dQ workgroup, asked for or chosen: 128 or 256; what runs follows
     int32_t fwd_waves, dq_waves;  // wavefronts of a forward / dQ workgroup: 4, 8 or 12
     bool dq_piped;                // dQ of 4: pipelined, two workgroups per compute unit
-    bool short_units;             // no forward / dQ unit is longer than 10 half tiles of keys (head_dim 64)
     bool dq_packed;               // in one launch with dK/dV of 12 wavefronts: dQ units of 12 row blocks whatever dq_waves is
     // dK/dV items that several workgroups share (the first n_split of the sorted list), and how:
     // an item of cost c takes min(split_parts, ceil(c * heads per group / split_chain)) of them

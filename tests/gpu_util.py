@@ -77,6 +77,31 @@ def run_library(w, block_m=0, block_n=0, vals=None, backward=True, keep_device=F
     return out
 
 
+def trace_of(plan, backward):
+    """The records of the work items of dQ and of dK/dV that `backward`, one call on `plan`, leaves in the trace."""
+    import torch
+    from paper_2505_19609_amd import binding as B
+    from paper_2505_19609_amd.balance import REC
+    first, num = B.skrull_attn_trace_layout(plan)
+    records = torch.zeros((sum(num), REC.itemsize), dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    B.skrull_attn_trace(records)
+    try:
+        backward()
+        torch.cuda.synchronize()
+    finally:
+        B.skrull_attn_trace(None)
+    rec = records.cpu().numpy().view(REC).reshape(-1)
+    return [r[r["one"] == 1] for r in (rec[first[1]:first[2]], rec[first[2]:])]
+
+
+def dkv_begins_during_dq(plan, backward):
+    """Whether a dK/dV item begins before the last dQ item has ended: so it does in one launch, and never in two."""
+    dq, dkv = trace_of(plan, backward)
+    assert len(dq) > 0 and len(dkv) > 0
+    return bool(dkv["t0"].min() < dq["t1"].max())
+
+
 def widen(vals):
     from paper_2505_19609_amd import workloads as W
     return {n: W.bf16_bits_to_f32(a) for n, a in vals.items()}

@@ -12,7 +12,7 @@ import numpy as np
 import pytest
 
 from paper_2505_19609_amd import workloads as W
-from gpu_util import run_library, widen, bf16_ulp
+from gpu_util import run_library, widen, bf16_ulp, trace_of, dkv_begins_during_dq
 
 pytestmark = pytest.mark.gpu
 
@@ -1182,6 +1182,7 @@ def test_dq_and_dkv_in_one_launch_and_in_two_give_the_same_bits(heads, d, S, kw,
         torch.cuda.synchronize()
         for n in two:
             assert torch.equal(t[n].view(torch.int16), two[n].view(torch.int16)), (fill, n)
+    assert dkv_begins_during_dq(plan, backward)   # (what was compared with two launches was one)
     plan.destroy()
 
 
@@ -1192,7 +1193,6 @@ def test_sums_of_shared_items_wait_for_all_parts_without_a_list_of_units(heads, 
     as the parts, are those of the parts: the same bits as by a launch of their own, whatever the workspace held."""
     import torch
     from paper_2505_19609_amd import binding as B
-    from paper_2505_19609_amd.balance import REC
     w = W.Workload("no_list", S, [1] * len(S), [0] * len(S), heads[0], heads[1], d, d ** -0.5, 615)
     run = run_library(w, keep_device=True)
     plan, t, i = run["plan"], run["dev"], run["dev_in"]
@@ -1214,18 +1214,41 @@ def test_sums_of_shared_items_wait_for_all_parts_without_a_list_of_units(heads, 
         for n in two:
             assert torch.equal(t[n].view(torch.int16), two[n].view(torch.int16)), (fill, n)
 
-    first, num = B.skrull_attn_trace_layout(plan)
-    records = torch.zeros((sum(num), REC.itemsize), dtype=torch.uint8, device="cuda")
-    B.skrull_attn_trace(records)
-    backward()
-    torch.cuda.synchronize()
-    B.skrull_attn_trace(None)
-    rec = records.cpu().numpy().view(REC).reshape(-1)
-    dq, dkv = (r[r["one"] == 1] for r in (rec[first[1]:first[2]], rec[first[2]:]))
-    assert dkv["t0"].min() < dq["t1"].max()   # one launch: as two, none of dK/dV begins before the last of dQ has ended
+    dkv = trace_of(plan, backward)[1]
+    assert dkv_begins_during_dq(plan, backward)
+    num = B.skrull_attn_trace_layout(plan)[1]
     assert plan.n_dkv_items > 2048 and plan.info.block_n == (192 if d == 64 else 128)   # no list of units, one pass
     parts, empty = num[2] - plan.n_dkv_items * heads[1], num[2] - len(dkv)   # (parts after the first one of each shared item)
     assert 0 < empty < parts <= 1024          # items of fewer parts than the most; a counter each
+    plan.destroy()
+
+
+@pytest.mark.parametrize("heads,d,S,one", [
+    ((4, 4), 64, [60] * 9, True), ((4, 4), 64, [60] * 10, False), ((4, 4), 64, [1], True),   # 108 and 120 work items of dQ and dK/dV, 110
+    ((8, 8), 128, [60] * 6, True), ((8, 8), 128, [60] * 7, False),                           # 96 and 112, 110
+    ((8, 8), 128, [200] * 7, True), ((8, 8), 128, [200] * 8, False),                         # 168 and 192, 180
+    ((28, 4), 128, [64] * 8, False), ((28, 4), 128, [64], True),                             # shared dK/dV items
+    ((20, 20), 64, [40] * 19, False), ((20, 20), 64, [161] + [40] * 18, True)])              # more dK/dV items than run at once
+def test_which_backward_runs(heads, d, S, one):
+    """Both sides of the line between one launch and separate ones, where dQ would be a plain grid.  Same bits."""
+    import torch
+    from paper_2505_19609_amd import binding as B
+    w = W.Workload("launches", S, [1] * len(S), [0] * len(S), heads[0], heads[1], d, d ** -0.5, 616)
+    run = run_library(w, keep_device=True)
+    plan, t, i = run["plan"], run["dev"], run["dev_in"]
+    ws = torch.empty(max(int(plan.bwd_workspace_bytes), 16), dtype=torch.uint8, device="cuda")
+    outs = [[torch.empty_like(i[n]) for n in "qkv"] for _ in range(2)]
+
+    def backward(out):
+        B.skrull_attn_bwd(plan, i["q"], i["k"], i["v"], t["o"], t["lse"], i["do"], *out, ws)
+
+    B.skrull_attn_profile(True)   # (separate launches)
+    backward(outs[0])
+    torch.cuda.synchronize()
+    B.skrull_attn_profile(False)
+    assert dkv_begins_during_dq(plan, lambda: backward(outs[1])) == one
+    for a, b in zip(*outs):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
     plan.destroy()
 
 

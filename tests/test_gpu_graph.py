@@ -8,7 +8,7 @@ import pytest
 import torch
 
 from paper_2505_19609_amd import workloads as W
-from gpu_util import to_dev
+from gpu_util import to_dev, dkv_begins_during_dq
 
 pytestmark = pytest.mark.gpu
 
@@ -150,7 +150,6 @@ def test_only_calls_on_the_default_stream_are_one_launch(where):
     stream that the program made: its handle may stand for another stream later, with the first one's work still
     under way, so the plan keeps nothing for it.  Same bits."""
     from paper_2505_19609_amd import binding as B
-    from paper_2505_19609_amd.balance import REC
     S, heads, d = [277] * 62, (8, 4), 128
     w = W.Workload("launches", S, [1] * len(S), [0] * len(S), heads[0], heads[1], d, d ** -0.5, 97)
     plan = B.skrull_attn_plan(S, [1] * len(S), [0] * len(S), heads[0], heads[1], d, w.softmax_scale)
@@ -165,11 +164,8 @@ def test_only_calls_on_the_default_stream_are_one_launch(where):
     B.skrull_attn_fwd(plan, dev["q"], dev["k"], dev["v"], o, lse)
     backward(outs[0])
     stream = torch.cuda.Stream()
-    first, num = B.skrull_attn_trace_layout(plan)
-    records = torch.zeros((sum(num), REC.itemsize), dtype=torch.uint8, device="cuda")
-    torch.cuda.synchronize()
-    B.skrull_attn_trace(records)
-    try:
+
+    def call():
         if where == "graph":
             graph = torch.cuda.CUDAGraph()
             with torch.cuda.graph(graph, stream=stream):
@@ -180,13 +176,8 @@ def test_only_calls_on_the_default_stream_are_one_launch(where):
                 backward(outs[1])
         else:
             backward(outs[1])
-        torch.cuda.synchronize()
-    finally:
-        B.skrull_attn_trace(None)
-    rec = records.cpu().numpy().view(REC).reshape(-1)
-    dq, dkv = (r[r["one"] == 1] for r in (rec[first[1]:first[2]], rec[first[2]:]))
-    assert len(dq) > 0 and len(dkv) > 0
-    assert (dkv["t0"].min() < dq["t1"].max()) == (where == "default")
+
+    assert dkv_begins_during_dq(plan, call) == (where == "default")
     for a, b in zip(*outs):
         assert torch.equal(a.view(torch.int16), b.view(torch.int16))
     plan.destroy()
