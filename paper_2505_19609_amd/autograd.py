@@ -4,6 +4,8 @@ attention runs in the HIP kernels behind the C ABI.  The marshalling is native c
 nothing watches the call from Python, else the Function below: the same checks, outputs and errors."""
 from __future__ import annotations
 
+import warnings
+
 import torch
 
 from . import binding as B
@@ -47,20 +49,23 @@ def _watched():
         return True
 
 
-_native = None
+_native = None   # the same in native code; False where that cannot be loaded
 
 
 def _load_native():
-    """The same in native code (csrc/autograd.cpp), built in-tree with the library; raises if it is missing."""
+    """csrc/autograd.cpp, built in-tree with the library against the torch of that build.  The library's kernels are called either
+    way: without this module, or with one for another torch, by the Function above."""
     global _native
     B.lib()
     try:
         from . import _autograd
     except ImportError as e:
-        raise RuntimeError("paper_2505_19609_amd/_autograd.so cannot be loaded: run __graft_entry__.build() "
-                           "(python -m paper_2505_19609_amd.build)") from e
-    _autograd.set_check(B._check)
-    _native = _autograd.attention
+        warnings.warn(f"paper_2505_19609_amd/_autograd.so cannot be loaded ({e}): calls of skrull_attention take the host "
+                      "longer; build it with python -m paper_2505_19609_amd.build", RuntimeWarning, stacklevel=3)
+        _native = False
+    else:
+        _autograd.set_check(B._check)
+        _native = _autograd.attention
     return _native
 
 
@@ -71,6 +76,8 @@ def skrull_attention(q, k, v, plan):
     """O = packed varlen causal attention of the micro-batch `plan` describes
     (a binding.Plan); differentiable with respect to q, k, v."""
     if type(q) in _TENSORS and type(k) in _TENSORS and type(v) in _TENSORS and type(plan) is B.Plan and not _watched():
-        i = plan.info
-        return (_native or _load_native())(q, k, v, plan, i.total_q, i.total_k, i.num_q_heads, i.num_kv_heads, i.head_dim)
+        native = _load_native() if _native is None else _native
+        if native:
+            i = plan.info
+            return native(q, k, v, plan, i.total_q, i.total_k, i.num_q_heads, i.num_kv_heads, i.head_dim)
     return _SkrullAttention.apply(q, k, v, plan)

@@ -3,8 +3,11 @@ from __future__ import annotations
 
 import os
 import re
+import shutil
 import subprocess
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
+from importlib.util import find_spec
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -48,11 +51,14 @@ def _compile(src: str) -> str:
     return obj
 
 
-def _compile_autograd() -> str:
+def _torch_dir():
+    """Where torch is installed, or None where it, or the compiler for its interface, is not: the library needs neither."""
+    spec = find_spec("torch")
+    return os.path.dirname(spec.origin) if spec and shutil.which("g++") else None
+
+
+def _compile_autograd(torch_dir: str) -> str:
     """Compile the native side of autograd.py against torch's C++ interface (host code only)."""
-    import sysconfig
-    from importlib.util import find_spec
-    torch_dir = os.path.dirname(find_spec("torch").origin)
     rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
     obj = os.path.join(CSRC, "autograd.o")
     subprocess.run(["g++", "-std=c++17", "-O2", "-fPIC", "-w", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
@@ -63,20 +69,21 @@ def _compile_autograd() -> str:
     return obj
 
 
-def _link_autograd(obj: str) -> None:
-    from importlib.util import find_spec
-    libs = os.path.join(os.path.dirname(find_spec("torch").origin), "lib")
+def _link_autograd(torch_dir: str, obj: str) -> None:
+    libs = os.path.join(torch_dir, "lib")
     subprocess.run(["g++", "-shared", "-fPIC", "-o", AUTOGRAD, obj, "-L" + libs, "-ltorch_python", "-ltorch", "-ltorch_cpu",
                     "-lc10", "-lc10_hip", "-L" + HERE, "-l:" + os.path.basename(LIB), "-Wl,-rpath,$ORIGIN"], check=True)
 
 
 def build_library(jobs: int = 4) -> str:
-    """Compile every HIP source and link the shared library, and the extension module beside it; returns the library's path."""
+    """Compile every HIP source and link the shared library, and the extension module beside it where that can be built; returns the library's path."""
+    torch_dir = _torch_dir()
     with ThreadPoolExecutor(max_workers=jobs) as ex:
-        autograd = ex.submit(_compile_autograd)
+        autograd = ex.submit(_compile_autograd, torch_dir) if torch_dir else None
         objs = list(ex.map(_compile, SOURCES))
         subprocess.run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs], check=True)
-        _link_autograd(autograd.result())
+        if autograd:
+            _link_autograd(torch_dir, autograd.result())
     return LIB
 
 

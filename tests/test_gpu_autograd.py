@@ -23,6 +23,7 @@ def _both(monkeypatch, f):
     for watched in (True, False):
         monkeypatch.setattr(A, "_watched", lambda: watched)
         out.append(f(A.skrull_attention))
+    assert A._native   # (else both were the Function)
     return out
 
 
@@ -117,4 +118,16 @@ def test_traced_and_transformed_calls_take_the_function():
     with pytest.raises(RuntimeError):
         torch.func.grad(lambda q: skrull_attention(q, *qkv[1:], plan).float().sum())(qkv[0])
     assert want.requires_grad
+    plan.destroy()
+
+
+@pytest.mark.parametrize("backend", ["eager", "aot_eager"])
+def test_compiled_calls(backend):
+    from paper_2505_19609_amd.autograd import skrull_attention
+    plan, qkv, do = _case()
+    want = torch.autograd.grad(skrull_attention(*qkv, plan) * 2, qkv, do)
+    torch._dynamo.reset()
+    got = torch.autograd.grad(torch.compile(lambda q, k, v: skrull_attention(q, k, v, plan) * 2, backend=backend)(*qkv), qkv, do)
+    for a, b in zip(got, want):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
     plan.destroy()
