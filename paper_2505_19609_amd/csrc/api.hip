@@ -390,7 +390,8 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
     //    short, where starts count (64 of 200, 4/4 heads: 31.8 and 34.3).  677 launches of eight head shapes against 8 wavefronts: forward and dQ
     //    together 0.929 of the time, 1.146 at worst, with 4 throughout; 0.927 and 1.033 this way.
     //  A forward of which workgroups of 4 all run at once only because short items leave some of them without rows has those too: 5 to
-    //    31 % less time than with 8 on 13 forwards of 498 to 768 of them; a few more than fit, and it takes up to 50 % more.
+    //    31 % less time than with 8 on 13 forwards of 498 to 768 of them, 0 to 56 % less on 24 of thirteen kinds of heads with 800 to 7,200 tokens; a few
+    //    more than fit (three to a compute unit), and it takes up to 50 % more.
     plan->fwd_waves = plan->wg_query_rows / 32;
     plan->dq_waves = plan->d == 64 ? plan->wg_query_rows / 32 : 8;
     if (p->wg_query_rows == 0 && plan->wg_query_rows == 256 && plan->d == 64) {
@@ -437,7 +438,8 @@ int skrull_attn_plan(const skrull_attn_problem_t *p, void *hip_stream, skrull_at
     // In one launch with dK/dV of 12 wavefronts, dQ in units of 12 row blocks against the units above, 66 backwards of 14/2
     // heads: where those are for 8 wavefronts 2 to 11 % less time (all of 14), for 4 that are not pipelined up to 13 % less (10 of 10; 2 % more at
     // worst), for 4 pipelined 5 to 20 % less with sequences of up to 2,500 tokens, within 2 % at 4,300 and 4,700, 5 to 18 % more
-    // from 10,000 on (a slice's prefix counts).  One head per group does not fill 12 from a sequence's last blocks.
+    // from 10,000 on (a slice's prefix counts).  With other groups, 80 backwards of 300 to 30,000 tokens: of 2 as long on average (8 % less to
+    // 5 % more), of 3 and 8 3 % less (14 % to 0), of 4, 5 and 7 1 to 2 % less (8 % to 1 % more), of 16 as long (within 2 %).  One head per group does not fill 12 from a sequence's last blocks.
     plan->dq_packed = plan->d == 64 && group > 1 && plan->units[2] && (plan->dq_waves == 8 || (plan->dq_waves == 4 && (!plan->dq_piped || totals.fwd_longest <= 128 + 16)));
     plan->head_split = totals.split.head_split;
     plan->n_split = totals.split.n_split;

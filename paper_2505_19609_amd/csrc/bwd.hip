@@ -69,7 +69,7 @@ struct BwdParams {
     WorkQueue *queue_dq, *queue_dkv;  // work queues of the persistent launches, zero when they start
     int32_t queue_stride;             // their dies' distance
     int32_t n_work_dq, n_work_dkv;    // work items: what a plain grid would have as workgroups
-    int32_t *clear;                   // null, or what the stream's next call will use: zeroed by this one
+    int32_t *clear;                   // null, or what the stream's next call will use: zeroed by this one (see DefaultStream)
     // one launch for all: dQ work items whose -D and LSE dK/dV may read; parts of shared dK/dV items whose sums are
     // stored, of each (item, KV head) or, for very many of these, of all of them; pieces of the sums of these that have been handed out
     int32_t *rows_ready, *parts_stored, *next_sum;
@@ -277,8 +277,8 @@ __device__ __forceinline__ int dq_work(const int bid, RowBlocks &rb, DqFeed &fee
         for (int ks = 0; ks < KS; ++ks) dof[ks] = fa.rows_at(stage, ks);
         st.put(stage, vo);
         // D = rowsum(dO * O) of this lane's row (each half of the wave holds half of the
-        // head dims) and LSE in the exp2 domain; both are stored at the end of the item for the
-        // dK/dV kernel, launched after this one (it takes -D as the start of its dP accumulator)
+        // head dims) and LSE in the exp2 domain; both are stored for dK/dV, which takes -D as the start of its dP
+        // accumulator: now where that follows in this launch (share_rows), else at the end of the item
         float dsum = 0.0f;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
@@ -769,8 +769,7 @@ __device__ __forceinline__ KeyBlock key_block(const P prm, int SUB, int bid)
     return r;
 }
 
-// Does work item `bid`, whose keys are `kb`; returns the next one and leaves its keys in `kb`.
-// A part of a shared item (KeyBlock::shared) is stored.
+// Counts a part of a shared item (KeyBlock::shared) as stored.
 __device__ __forceinline__ void count_part(int shared)
 {
     const kernarg_t<BwdParams> prm = kernarg<BwdParams>();
@@ -783,6 +782,9 @@ struct DkvLds {
     static constexpr int RING = 3 * SLOT, P = PAIRS * 2 * 4 * 1024;          // P: exchange [pair][round parity][16-row block][lane*16]
 };
 
+// Does work item `bid`, whose keys are `kb`; returns the next one and leaves its keys in `kb`.
+// ONE: in one launch with dQ.  `rows_seen`: this workgroup has waited for the rows of dQ's items.  `part_owed`: the part of a shared item
+// (KeyBlock::shared) that it did last, stored but not counted yet, or 0; on return this item's.
 template <int D, int PAIRS, bool ONE>
 __device__ __forceinline__ int dkv_work(const int bid, KeyBlock &kb, DkvFeed &feed, unsigned char *ring, unsigned char *exchange, bool &rows_seen, int &part_owed)
 {

@@ -116,7 +116,7 @@ struct PlanTotals {
 constexpr int32_t kMaxParts = 8;  // workgroups that may share one dK/dV item whose heads are not split
 
 // Bytes of backward scratch without partial sums: -D and LSE*log2(e) per (head, row), then 256
-// bytes for the work queues of the two kernels.
+// bytes for the work queues of the two kernels in calls that clear these first.
 __host__ __device__ inline int64_t base_workspace(int32_t q_heads, int64_t total_q)
 {
     return ((((int64_t)q_heads * total_q * 8) + 255) & ~(int64_t)255) + 256;

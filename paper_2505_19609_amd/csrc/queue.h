@@ -143,8 +143,8 @@ __device__ __forceinline__ int my_xcd() { return __builtin_amdgcn_readfirstlane(
 // (30,934 tokens in 3 sequences, 4/4 heads of 64: forward 547 us claimed, 503 by index).  Where a
 // unit holds one workgroup and the items are alike, the order of arrival staggers them a little, and
 // they run faster than in step (dK/dV, 27 sequences, 20,011 tokens, 32/8 heads of 128: 3 %).  dQ claims
-// too: by index it was as fast at head_dim 128 without marks, but with them 1 to 3 % slower on short lists,
-// because the backward's counts share a line.
+// too: by index it was as fast at head_dim 128 without marks, but with them 1 to 3 % slower on short lists
+// (measured with all counts of a backward in one line, as they are on streams other than the default one).
 // `slot` is two ints of LDS; the caller has a barrier between a `take` and the next `post`.
 // `Source` says where the queue is (queue(), or null; stride(), its dies' distance) and how many items there are (items()).
 template <bool FIRST, typename Source> struct WorkFeed {
